@@ -40,7 +40,7 @@ FLOPS_PER_TERM = 20
 PROFILES = os.path.join(ROOT, "profiles")
 # kernel -> (library timer id, sources that define it, file holding its HBM counters)
 KERNELS = {
-    "direct_cartesian_kernel": (0, ["cartesian_sum.h", "direct.hip", "phasor.h", "types.h"],
+    "direct_cartesian_kernel": (0, ["cartesian_block.h", "direct.hip", "phasor.h", "types.h"],
                                 "direct_cartesian_kernel_vortex64_256x256_pmc.md"),
     "adjoint_cartesian_kernel": (1, ["adjoint.hip", "phasor.h", "types.h"],
                                  "adjoint_cartesian_kernel_vortex64_256x256_pmc.md"),

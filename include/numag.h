@@ -36,8 +36,9 @@
  * Tuning: launch shapes come from a table (numag_tune_get / numag_autotune
  * below); without an entry, the environment variable NUMAG_TARGET_WGS (read
  * once per process) sets the number of workgroups the direct sums aim for per
- * launch (default 2048, the value measured best on MI355X; the polar sums take
- * half, the adjoint twice).  Shapes change how the work is split, never a
+ * launch (default on a Cartesian detector: chosen by an estimate of the time from
+ * the point and pixel counts; otherwise 2048, the polar sums half and the adjoint
+ * twice of it).  Shapes change how the work is split, never a
  * result's definition; sums split differently agree to rounding.
  */
 #ifndef NUMAG_H
@@ -416,8 +417,10 @@ int numag_angular_spectrum(const numag_qgrid *grid, const double *f, int32_t n_f
  *             Cartesian or the polar kernel), NUMAG_TUNE_ADJOINT (the gradient's
  *             adjoint sums), NUMAG_TUNE_OBJECTS (the persistent object kernel of
  *             DILUTE / SPLIT modes on a Cartesian detector).
- *   shape     Cartesian direct and objects: lanes per detector row (8, 16, 32,
- *             64); polar direct: workgroup shape 0-4 (0: 64 q rows x 64 theta
+ *   shape     Cartesian direct: detector columns per workgroup (8: 32 columns,
+ *             64: 64, 16: 128, 32: 256; the axis the columns lie on may be the
+ *             detector's rows on thin detectors); Cartesian objects: lanes per
+ *             detector row (8, 16, 32, 64); polar direct: workgroup shape 0-4 (0: 64 q rows x 64 theta
  *             columns; 1: 32 x 64, only for at most 32 q rows; 2: 128 x 32;
  *             3: 256 x 16 with chunks of 16 points; 4: 256 x 16 with
  *             double-buffered chunks of 8 points); adjoint: 0.

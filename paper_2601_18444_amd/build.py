@@ -24,6 +24,9 @@ ARCH = "gfx950"
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # keep the matrix accumulators whole in loop headers: split into elements, each tile of
+    # them is held twice and the sum kernels spill
+    "-mllvm", "-amdgpu-codegenprepare-break-large-phis=0",
     "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument",
 ]
 

@@ -146,14 +146,13 @@ DirectLayout direct_layout(const numag_sample *s, const Detector &d)
 {
     DirectLayout L{};
     L.points = align_up((size_t)std::max<int64_t>(s->n_points, 1) * sizeof(PointRec));
-    // partial sums of the full detector or of its Hermitian half, whichever is larger
-    Detector dh = d;
+    // partial sums of every path and channel set, whichever is largest
     if (d.kind == NUMAG_GRID_CARTESIAN) {
-        dh.n0 = (d.n0 + 1) / 2;
-        const DirectPlan p = plan_direct_cartesian(d, s->n_points), ph = plan_direct_cartesian(dh, s->n_points);
-        L.partial = std::max(p.nsplit > 1 ? align_up(direct_partial_bytes(p, d)) : 0,
-                             ph.nsplit > 1 ? align_up(direct_partial_bytes(ph, dh)) : 0);
+        for (int ch : {4, 3, 1})
+            for (bool herm : {false, true})
+                L.partial = std::max(L.partial, align_up(cart_partial_bytes(plan_direct_cartesian(d, s->n_points, ch, herm))));
     } else {
+        Detector dh = d;
         dh.n1 = std::max(1, d.n1 / 2);
         const DirectPlan p = plan_direct_polar(d, s->n_points), ph = plan_direct_polar(dh, s->n_points);
         L.partial = std::max(align_up(direct_partial_bytes(p, d)), align_up(direct_partial_bytes(ph, dh)));
@@ -180,21 +179,9 @@ int run_direct(const numag_sample *s, const Rot &R, const Detector &d, double *a
     int rc = launch_prepare_points(s->pos, s->nuc, s->mag, 0, s->n_points, s->regular, s->obj_offsets,
                                    s->n_objects, s->obj_pos, R, pts, st);
     if (rc != NUMAG_OK) return rc;
-    if (d.kind == NUMAG_GRID_CARTESIAN) {
-        Detector dh = d;
-        if (hermitian) dh.n0 = (d.n0 + 1) / 2;  // rows [0, h): the first h n1 pixels of the output
-        const int64_t Ph = (int64_t)dh.n0 * d.n1;
-        DirectPlan p = plan_direct_cartesian(dh, s->n_points);
-        p.channels = channels;
-        if (p.nsplit == 1) {
-            rc = launch_direct_cartesian(pts, s->n_points, dh, p, amp, st);
-        } else {
-            rc = launch_direct_cartesian(pts, s->n_points, dh, p, part, st);
-            if (rc == NUMAG_OK) rc = launch_combine(part, p.nsplit, Ph, amp, 0, st);
-        }
-        if (rc != NUMAG_OK || !hermitian) return rc;
-        return launch_mirror_cartesian(amp, P, Ph, st);
-    }
+    if (d.kind == NUMAG_GRID_CARTESIAN)
+        return launch_direct_cartesian(pts, s->n_points, plan_direct_cartesian(d, s->n_points, channels, hermitian),
+                                       part, amp, 0, st);
     if (hermitian) {
         Detector dh = d;
         dh.n1 = d.n1 / 2;  // columns [0, n_theta / 2); their mirrors are m + n_theta / 2
@@ -381,14 +368,17 @@ std::vector<TuneShape> tune_candidates(int kernel, const Detector &d, int64_t W)
         for (int sh : shapes)
             for (int t : {512, 1024, 2048}) c.push_back(TuneShape{sh, t});
     } else if (kernel == kTuneDirect || kernel == kTuneObjects) {
-        const int l0 = def.shape;
-        std::vector<int> lanes{l0};
-        if (l0 > 8) lanes.push_back(l0 / 2);
-        if (l0 < 64) lanes.push_back(l0 * 2);
-        const std::vector<int> targets = kernel == kTuneDirect ? std::vector<int>{1024, 2048, 3072, 4096}
-                                                               : std::vector<int>{1024, 2048, 4096};
-        for (int l : lanes)
-            for (int t : targets) c.push_back(TuneShape{l, t});
+        if (kernel == kTuneDirect) {
+            for (int l : {8, 64, 16, 32})
+                for (int t : {256, 512, 768}) c.push_back(TuneShape{l, t});
+        } else {
+            const int l0 = def.shape;
+            std::vector<int> lanes{l0};
+            if (l0 > 8) lanes.push_back(l0 / 2);
+            if (l0 < 64) lanes.push_back(l0 * 2);
+            for (int l : lanes)
+                for (int t : {1024, 2048, 4096}) c.push_back(TuneShape{l, t});
+        }
     } else {
         for (int t : {2048, 4096, 8192}) c.push_back(TuneShape{0, t});
     }

@@ -1,0 +1,230 @@
+// Device building block of the Cartesian direct sums on the FP64 matrix cores.
+//
+// The phase separates, exp(-i (q_M m + q_N n)) = exp(-i q_M m) exp(-i q_N n) with m, n
+// a point's lab-frame coordinates along the two detector axes (M: the axis whose
+// blocks are packed into matrix rows, N: the other), and the detector is symmetric
+// about q = 0 on both axes.  So the sums of the four pixels (+-q_M, +-q_N) of one
+// cell |q_M|, |q_N| and one channel follow from four real contractions over points,
+//   RR = sum w yr zr,  RI = sum w yr zi,  IR = sum w yi zr,  II = sum w yi zi,
+// with (yr, yi) = exp(-i |q_M| m) and (zr, zi) = exp(-i |q_N| n):
+//   S(+,+) = (RR - II) + i (RI + IR),  S(+,-) = (RR + II) + i (IR - RI),
+// and S(-q) = conj S(q) for the other two (real weights).  That is one multiply-add
+// per term and channel, four instead of the ten and a half vector FP64 operations a
+// pixel-by-pixel walk with a two-term phasor recurrence takes, and it runs on
+// v_mfma_f64_16x16x4f64.
+//
+// The FP64 vector and matrix instructions share one pipe (measured: 74.7 TFLOP/s of
+// matrix products alone, 65.3 of vector FMAs alone, and their sum stays at 74.7 when
+// a wave issues both), so what is not a matrix product is kept small:
+//  - a workgroup of 8 waves owns one block of `na` |q_M| values (all channels; 64 row
+//    slots at most) and `nz` blocks of 16 |q_N| values, one per wave; waves beyond the
+//    nz blocks take other points of the same chunk (8 / nz groups);
+//  - the row operand w_c exp(-i |q_M| m) is formed once per chunk of 32 points for all
+//    waves and read from LDS; the column operand is the product of a block's centre
+//    phasor and one of 16 offsets exp(-i (b + 1/2) dq n), b = -8 .. 7 (8 sincos, the
+//    others are conjugates): one complex product per wave and four points.
+// A lane generates for one point (two entries of a 32-point chunk per wave
+// instruction), so every sincos lane does useful work; every phasor is a sincos or a
+// product of two, which keeps the error at the rounding of the phase itself.
+// Chunks are double-buffered: the next chunk is generated while this one is summed, one
+// barrier per chunk, its points loaded one chunk ahead of their use.
+#pragma once
+
+#include "numag_internal.h"
+#include "phasor.h"
+
+namespace numag {
+namespace cblk {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kChunk = 32;   // points per LDS chunk
+constexpr int kOff = 16;     // |q_N| values per column block
+constexpr int kMaxMT = 8;    // 16-row matrix tiles per wave
+
+// First channel of a CH-channel set: 4 (N, Mx, My, Mz), 3 (the magnetic channels, a
+// sample without nuclear weights) or 1 (N only).
+template <int CH>
+__host__ __device__ constexpr int ch_first()
+{
+    static_assert(CH == 4 || CH == 3 || CH == 1, "channel set");
+    return CH == 3 ? 1 : 0;
+}
+
+// What a lane needs of its point: coordinates along the two axes and the weights.
+template <int CH>
+struct Point {
+    double m, n;
+    double w[CH];
+};
+
+// Row slots: slot s = e CH + c is |q_M| value e of the block, channel c.  Its real
+// part sits in matrix row 16 (s / 8) + 8 ((s / 4) % 2) + s % 4 and its imaginary part
+// four rows further, so that after the contraction one lane holds RR, IR, RI and II
+// of a slot (accumulator register r of lane l is row 4 r + l / 16, column l % 16).
+__device__ __forceinline__ int slot_row(int s) { return 16 * (s >> 3) + 8 * ((s >> 2) & 1) + (s & 3); }
+
+// The wave's index in its workgroup, known to be uniform (scalar branches and loops:
+// a divergent loop around the matrix instructions costs a copy of the accumulators).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+template <int MT>
+struct Smem {
+    double y[2][kChunk][16 * MT + 1];   // odd row stride: the point-major stores are free of conflicts
+    double2 off[2][kChunk][kOff + 1];
+    double2 ctr[2][kChunk][kWaves + 1];
+    static constexpr int kRed = 8 * 64 * kWaves;  // doubles the epilogue's reduction uses at a time
+};
+static_assert(sizeof(Smem<1>) >= Smem<1>::kRed * sizeof(double), "the epilogue reduces over the whole buffer");
+
+template <int MT>
+__device__ __forceinline__ void zero(v4d (&accC)[MT], v4d (&accS)[MT])
+{
+#pragma unroll
+    for (int t = 0; t < MT; ++t) accC[t] = accS[t] = v4d{0.0, 0.0, 0.0, 0.0};
+}
+
+// Adds the points [jbeg, jend) of `ld` (Point<CH> load(j), called with j < jend only)
+// to this wave's tiles: row block rb, column block zb0 + wave % nz.  accC holds the
+// contractions with zr, accS those with zi.  Ends with a barrier.
+template <int MT, int CH, class Loader>
+__device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, const CartGeom &g, int rb,
+                                           int zb0, Smem<MT> &sm, v4d (&accC)[MT], v4d (&accS)[MT])
+{
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int half = lane >> 5, gp = lane & 31;  // generation: entry of a pair, point
+    const int zi = wave % g.nz, kg = wave / g.nz, nk = kWaves / g.nz;
+    const bool active = zb0 + zi < g.nzb;
+    const int r16 = lane & 15, kq = lane >> 4;
+    // phase of this lane's column entry: an offset (first half) or a block centre
+    const double qn = half == 0 ? ((double)wave + 0.5) * g.stepN
+                                : g.originN + ((double)(g.nN - g.B + kOff * (zb0 + wave)) + 7.5) * g.stepN;
+
+    auto fetch = [&](int64_t j0) {
+        Point<CH> p{};
+        if (j0 + gp < jend) p = ld.load(j0 + gp);
+        return p;
+    };
+    auto put_row = [&](int b, const Point<CH> &p, int e, double2 y) {
+        if (e < g.na) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int row = slot_row(e * CH + c);
+                sm.y[b][gp][row] = p.w[c] * y.x;
+                sm.y[b][gp][row + 4] = p.w[c] * y.y;
+            }
+        }
+    };
+    const double qm0 = axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * wave + half, g.stepM);
+    auto generate = [&](int b, const Point<CH> &p) {
+        double2 z, y;
+        twiddle2(qn * p.n, qm0 * p.m, z, y);
+        if (half == 0) {
+            sm.off[b][gp][8 + wave] = z;
+            sm.off[b][gp][7 - wave] = make_double2(z.x, -z.y);
+        } else {
+            sm.ctr[b][gp][wave] = z;
+        }
+        put_row(b, p, 2 * wave + half, y);
+#pragma unroll 1
+        for (int e0 = 2 * (wave + kWaves); e0 < g.na; e0 += 2 * kWaves) {
+            const double q = axis_value(g.originM, g.nM - g.A + rb * g.na + e0 + half, g.stepM);
+            put_row(b, p, e0 + half, twiddle(q * p.m));
+        }
+    };
+    auto sum = [&](int b, int np) {
+        const int steps = active ? (np + 3) >> 2 : 0;
+#pragma unroll 1
+        for (int s = kg; s < steps; s += nk) {
+            const int pt = 4 * s + kq;
+            const double *yp = &sm.y[b][pt][r16];
+            double a[MT];
+#pragma unroll
+            for (int t = 0; t < MT; ++t) a[t] = yp[16 * t];
+            const double2 z = cmul(sm.ctr[b][pt][zi], sm.off[b][pt][r16]);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                accC[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.x, accC[t], 0, 0, 0);
+                accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.y, accS[t], 0, 0, 0);
+            }
+        }
+    };
+
+    Point<CH> p = fetch(jbeg), q = fetch(jbeg + kChunk);
+    generate(0, p);
+    __syncthreads();
+    int b = 0;
+#pragma unroll 1
+    for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk, b ^= 1) {
+        if (j0 + kChunk < jend) {
+            p = q;
+            q = fetch(j0 + 2 * kChunk);  // a whole chunk ahead of its use
+            generate(b ^ 1, p);
+        }
+        sum(b, (int)min((int64_t)kChunk, jend - j0));
+        __syncthreads();
+    }
+}
+
+// The pixels +-|q| of a cell's slot on the two axes.
+struct CellPixels {
+    bool ok, twoM, twoN;      // slot on the detector; distinct mirrors on each axis
+    int c;                    // channel within the set
+    int64_t pp, pm, mp, mm;   // pixel (+,+), (+,-), (-,+), (-,-)
+};
+
+__device__ __forceinline__ CellPixels cell_pixels(const CartGeom &g, int CH, int rb, int zb, int s, int col)
+{
+    CellPixels x;
+    const int e = s / CH;
+    x.c = s - e * CH;
+    const int a = rb * g.na + e, b = kOff * zb + col;
+    x.ok = e < g.na && a < g.A && b < g.B;
+    const int ip = g.nM - g.A + a, im = g.A - 1 - a, jp = g.nN - g.B + b, jm = g.B - 1 - b;
+    x.twoM = ip != im;
+    x.twoN = jp != jm;
+    x.pp = ip * g.strideM + jp * g.strideN;
+    x.pm = ip * g.strideM + jm * g.strideN;
+    x.mp = im * g.strideM + jp * g.strideN;
+    x.mm = im * g.strideM + jm * g.strideN;
+    return x;
+}
+
+// Writes (add: adds) one channel of the four pixels of a cell; v = S(+,+), S(+,-).
+__device__ __forceinline__ void put_pixel(double *__restrict__ amp, int64_t p, int ch, double re, double im, bool add)
+{
+    double *o = amp + p * 8 + 2 * ch;
+    o[0] = add ? o[0] + re : re;
+    o[1] = add ? o[1] + im : im;
+}
+
+__device__ __forceinline__ void put_cell(double *__restrict__ amp, const CellPixels &x, int ch, double2 vp, double2 vm,
+                                         bool add)
+{
+    put_pixel(amp, x.pp, ch, vp.x, vp.y, add);
+    if (x.twoN) put_pixel(amp, x.pm, ch, vm.x, vm.y, add);
+    if (x.twoM) {
+        put_pixel(amp, x.mm, ch, vp.x, -vp.y, add);
+        if (x.twoN) put_pixel(amp, x.mp, ch, vm.x, -vm.y, add);
+    }
+}
+
+// A slot's channel and, from the lane that holds its first channel, the exact zeros
+// of the channels outside the set.
+__device__ __forceinline__ void put_slot(double *__restrict__ amp, const CellPixels &x, int CH, double2 vp, double2 vm,
+                                         bool add)
+{
+    const int first = CH == 3 ? 1 : 0;
+    put_cell(amp, x, first + x.c, vp, vm, add);
+    if (x.c == 0 && !add) {
+        const double2 o = make_double2(0.0, 0.0);
+        if (CH == 3) put_cell(amp, x, 0, o, o, false);
+        if (CH == 1)
+            for (int ch = 1; ch < 4; ++ch) put_cell(amp, x, ch, o, o, false);
+    }
+}
+
+}  // namespace cblk
+}  // namespace numag

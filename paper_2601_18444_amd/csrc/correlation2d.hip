@@ -75,31 +75,32 @@ __global__ void corr2d_scatter_kernel(const double *__restrict__ amp, int64_t R,
 
 static size_t al2(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// The real-space grid to evaluate: C(-r) = conj C(r) for real data, so only half
-// of a grid symmetric about r = 0 is summed (Cartesian: rows [0, ceil(n0/2));
-// polar with an even n_alpha: columns [0, n_alpha/2)) and the rest is mirrored.
+// The polar real-space grid to evaluate: C(-r) = conj C(r) for real data, so only
+// the columns [0, n_alpha/2) are summed when n_alpha is even and the rest mirrored.
 static Detector half_grid(const Detector &rd)
 {
     Detector rh = rd;
-    if (rd.kind == NUMAG_GRID_CARTESIAN)
-        rh.n0 = (rd.n0 + 1) / 2;
-    else if (rd.n1 % 2 == 0)
-        rh.n1 = rd.n1 / 2;
+    if (rd.kind == NUMAG_GRID_POLAR && rd.n1 % 2 == 0) rh.n1 = rd.n1 / 2;
     return rh;
 }
 
-static DirectPlan corr2d_plan(const Detector &rh, int64_t P)
+// Bytes of split partial sums, whatever the channel set.
+static size_t corr2d_partial_bytes(const Detector &rd, int64_t P)
 {
-    return rh.kind == NUMAG_GRID_CARTESIAN ? plan_direct_cartesian(rh, P) : plan_direct_polar(rh, P);
+    if (rd.kind == NUMAG_GRID_CARTESIAN) {
+        size_t b = 0;
+        for (int ch : {4, 3, 1}) b = std::max(b, cart_partial_bytes(plan_direct_cartesian(rd, P, ch, true)));
+        return b;
+    }
+    const Detector rh = half_grid(rd);
+    return direct_partial_bytes(plan_direct_polar(rh, P), rh);
 }
 
 size_t correlation_2d_workspace_bytes(const Detector &d, const Detector &rd)
 {
     const int64_t P = (int64_t)d.n0 * d.n1;
     const int64_t R = (int64_t)rd.n0 * rd.n1;
-    const Detector rh = half_grid(rd);
-    return al2((size_t)P * sizeof(PointRec)) + al2(direct_partial_bytes(corr2d_plan(rh, P), rh)) +
-           al2((size_t)R * 8 * sizeof(double));
+    return al2((size_t)P * sizeof(PointRec)) + al2(corr2d_partial_bytes(rd, P)) + al2((size_t)R * 8 * sizeof(double));
 }
 int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Detector &rd, double *C, void *ws,
                           size_t ws_bytes, hipStream_t s)
@@ -111,27 +112,24 @@ int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Det
         return NUMAG_E_WORKSPACE;
     }
     const Detector rh = half_grid(rd);
-    const int64_t Rh = (int64_t)rh.n0 * rh.n1;
-    const DirectPlan plan4 = corr2d_plan(rh, P);
     char *base = (char *)ws;
     PointRec *pts = (PointRec *)base;
     double *part = (double *)(base + al2((size_t)P * sizeof(PointRec)));
-    double *amp = (double *)(base + al2((size_t)P * sizeof(PointRec)) + al2(direct_partial_bytes(plan4, rh)));
+    double *amp = (double *)(base + al2((size_t)P * sizeof(PointRec)) + al2(corr2d_partial_bytes(rd, P)));
     for (int set0 = 0; set0 < n_f; set0 += 4) {
         // the sum kernels' channel set for this group: 1 (channel 0), 3 (channels 1-3) or 4
         const int m = std::min(4, n_f - set0);
-        DirectPlan plan = plan4;
-        plan.channels = m == 1 ? 1 : (m == 4 ? 4 : 3);
-        const int c0 = plan.channels == 3 ? 1 : 0;
+        const int channels = m == 1 ? 1 : (m == 4 ? 4 : 3);
+        const int c0 = channels == 3 ? 1 : 0;
         hipLaunchKernelGGL(corr2d_points_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, d, f, n_f, set0,
                            c0, pts);
         NUMAG_HIP_CHECK(hipGetLastError());
         int rc;
         if (rd.kind == NUMAG_GRID_CARTESIAN) {
-            rc = launch_direct_cartesian(pts, P, rh, plan, plan.nsplit > 1 ? part : amp, s);
-            if (rc == NUMAG_OK && plan.nsplit > 1) rc = launch_combine(part, plan.nsplit, Rh, amp, 0, s);
-            if (rc == NUMAG_OK) rc = launch_mirror_cartesian(amp, R, Rh, s);
+            rc = launch_direct_cartesian(pts, P, plan_direct_cartesian(rd, P, channels, true), part, amp, 0, s);
         } else {
+            DirectPlan plan = plan_direct_polar(rh, P);
+            plan.channels = channels;
             rc = launch_direct_polar(pts, P, rh, plan, part, s);
             if (rc == NUMAG_OK)
                 rc = rh.n1 != rd.n1 ? launch_combine_polar_half(part, plan.nsplit, rd.n0, rh.n1, amp, s)

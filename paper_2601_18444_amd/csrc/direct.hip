@@ -5,16 +5,29 @@
 // Sums (Sec. 3.3, DSFT):  S_c(q_p) = sum_j w_{j,c} exp(-i q_p . X_j),  q = (0, q_y, q_z).
 //
 // The phase separates in the lab frame, exp(-i (q_y Y + q_z Z)) =
-// exp(-i q_y Y) exp(-i q_z Z); the tile layout, the twiddle generation and the
-// two-term column recurrence are described in cartesian_sum.h.  There is no
-// transcendental per term, and everything is accumulated in FP64 (FP32 phasors
-// lose the 1e-5 gate at 10^-6 of the maximum on 2.6e5-point samples, however the
-// sums are folded).
+// exp(-i q_y Y) exp(-i q_z Z), and the detector is symmetric about q = 0: the sums are
+// real contractions over points on the FP64 matrix cores (cartesian_block.h), four
+// multiply-adds per point and pixel for the four channels.  Everything is FP64 (FP32
+// phasors lose the 1e-5 gate at 10^-6 of the maximum on 2.6e5-point samples, however
+// the sums are folded).
 //
-// Work is split over point ranges (split-K); a fixed-order FP64 combine sums
-// the partial results, so results are bitwise reproducible.
+// Work is split over point ranges (split-K); a fixed-order FP64 combine sums the
+// partial results, so results are bitwise reproducible.
+//
+// Measured, kernel time before (a lane walking 8 pixels of a row with a two-term phasor
+// recurrence, 10.5 vector FP64 instructions per term) and now:
+//   262,144 points, 256 x 256 pixels   6.30 -> 2.12 ms (65 of the card's 74.7 TFLOP/s)
+//   30,011 points, 201 x 333, 3 channels  0.64 (half detector) -> 0.265 ms
+//   4,169 points, 128 x 128               64 -> 29 us;  500 points, 48 x 81  53 -> 12 us
+// Of the 2.12 ms, 1.84 are the multiply-adds at the measured matrix rate and 0.19 the
+// generation of the phasor tables (0.77 with one column block per workgroup instead of
+// eight: the table of row operands is shared by the waves of a workgroup).  Letting
+// half of the waves generate while the others sum gained nothing (2.15 ms): vector and
+// matrix FP64 instructions share one pipe.
 #include <algorithm>
+#include <cmath>
 
+#include "cartesian_block.h"
 #include "cartesian_sum.h"
 
 namespace numag {
@@ -158,63 +171,239 @@ int launch_prepare_points(const double *pos, const double *nuc, const double *ma
 // ---------------------------------------------------------------------------
 // Cartesian direct sum.
 // ---------------------------------------------------------------------------
-constexpr int kThreads = cart::kThreads;
-constexpr int kChunk = cart::kChunk;
-
 struct PrepLoader {
     const PointRec *__restrict__ pts;
-    __device__ __forceinline__ cart::PointPart load(int64_t j, int slot) const
+    int swapped;
+    template <int CH>
+    __device__ __forceinline__ cblk::Point<CH> get(int64_t j) const
     {
         const PointRec &r = pts[j];
-        return cart::PointPart{r.Y, r.Z, slot < 4 ? r.w[slot] : 0.0};
+        cblk::Point<CH> p;
+        p.m = swapped ? r.Z : r.Y;
+        p.n = swapped ? r.Y : r.Z;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) p.w[c] = r.w[cblk::ch_first<CH>() + c];
+        return p;
     }
 };
 
-template <int LR, int CH>
-__global__ __launch_bounds__(kThreads, 2) void direct_cartesian_kernel(
-    const PointRec *__restrict__ pts, int64_t W, int64_t per, Detector d, double *__restrict__ out)
+template <int CH>
+struct PrepLoaderCh : PrepLoader {
+    __device__ __forceinline__ cblk::Point<CH> load(int64_t j) const { return this->template get<CH>(j); }
+};
+
+// Where a workgroup's sums go: partials [split][row block][column block][tile][half][4][64]
+// (store == 0; combined below), or straight into amp (1: written, 2: added).
+template <int MT, int CH>
+__global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(const PointRec *__restrict__ pts,
+                                                                              int64_t W, int64_t per, CartGeom g,
+                                                                              int store, double *__restrict__ out)
 {
-    using T = cart::Tile<LR>;
-    __shared__ cart::Smem<LR> sm;
-    const int col0 = blockIdx.x * T::COLS;
-    const int row0 = blockIdx.y * T::ROWS;
+    __shared__ cblk::Smem<MT> sm;
+    const int lane = threadIdx.x & 63, wave = cblk::wave_id();
+    const int zb0 = blockIdx.x * g.nz, rb = blockIdx.y;
     const int64_t jbeg = (int64_t)blockIdx.z * per;
     const int64_t jend = min(W, jbeg + per);
-    double acc[cart::kB][2 * CH];
-    cart::zero(acc);
-    cart::accumulate<LR, CH>(PrepLoader{pts}, jbeg, jend, d, col0, row0, sm, acc);
+    cblk::v4d accC[MT], accS[MT];
+    cblk::zero<MT>(accC, accS);
+    cblk::accumulate<MT, CH>(PrepLoaderCh<CH>{{pts, g.swapped}}, jbeg, jend, g, rb, zb0, sm, accC, accS);
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t P = (int64_t)d.n0 * d.n1;
-    double *dst = out + (int64_t)blockIdx.z * P * 8;
-    const int row = T::row(row0, lane, wave);
-    if (row >= d.n0) return;
-#pragma unroll
-    for (int c = 0; c < cart::kB; ++c) {
-        const int col = T::col(col0, lane, c);
-        if (col < d.n1) {
-            double *o = dst + ((int64_t)row * d.n1 + col) * 8;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) o[v] = cart::channel_value<CH>(acc[c], v);
+    const int zb = zb0 + wave % g.nz, kg = wave / g.nz, nk = cblk::kWaves / g.nz;
+    const bool active = zb < g.nzb;
+    auto put = [&](int t, int h, double RR, double IR, double RI, double II) {
+        const double2 vp = make_double2(RR - II, RI + IR), vm = make_double2(RR + II, IR - RI);
+        if (store == 0) {
+            double *o = out + (((((int64_t)blockIdx.z * g.nrb + rb) * g.nzb + zb) * MT + t) * 2 + h) * 256 + lane;
+            o[0] = vp.x;
+            o[64] = vp.y;
+            o[128] = vm.x;
+            o[192] = vm.y;
+        } else {
+            const cblk::CellPixels x = cblk::cell_pixels(g, CH, rb, zb, 8 * t + 4 * h + (lane >> 4), lane & 15);
+            if (x.ok) cblk::put_slot(out, x, CH, vp, vm, store == 2);
         }
+    };
+    if (nk == 1) {
+        if (!active) return;
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                put(t, h, accC[t][2 * h], accC[t][2 * h + 1], accS[t][2 * h], accS[t][2 * h + 1]);
+        return;
+    }
+    // sums of the point groups, in a fixed order through LDS, one tile at a time
+    double *red = (double *)&sm;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            red[(wave * 8 + r) * 64 + lane] = accC[t][r];
+            red[(wave * 8 + 4 + r) * 64 + lane] = accS[t][r];
+        }
+        __syncthreads();
+        if (active && kg < 2) {  // point group kg writes half kg
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int k = 0; k < nk; ++k) {
+                const double *p = red + (k * g.nz + wave % g.nz) * 512 + lane;
+                v[0] += p[(2 * kg) * 64];
+                v[1] += p[(2 * kg + 1) * 64];
+                v[2] += p[(4 + 2 * kg) * 64];
+                v[3] += p[(5 + 2 * kg) * 64];
+            }
+            put(t, kg, v[0], v[1], v[2], v[3]);
+        }
+        __syncthreads();
     }
 }
 
-int target_workgroups()
+// Fixed-order sum of the split partials, written (or added) to the pixels.
+__global__ __launch_bounds__(256) void cart_combine_kernel(const double *__restrict__ part, CartGeom g, int MT, int CH,
+                                                           int nsplit, int accumulate, double *__restrict__ amp)
+{
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = (int)(idx & 63);
+    const int64_t block = idx >> 6;  // (row block, column block, tile, half)
+    const int64_t blocks = (int64_t)g.nrb * g.nzb * MT * 2;
+    if (block >= blocks) return;
+    const int h = (int)(block & 1), t = (int)((block >> 1) % MT);
+    const int64_t rz = (block >> 1) / MT;
+    const cblk::CellPixels x =
+        cblk::cell_pixels(g, CH, (int)(rz / g.nzb), (int)(rz % g.nzb), 8 * t + 4 * h + (lane >> 4), lane & 15);
+    if (!x.ok) return;
+    const double *p = part + block * 256 + lane;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < nsplit; ++s, p += blocks * 256) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
+    }
+    cblk::put_slot(amp, x, CH, make_double2(v[0], v[1]), make_double2(v[2], v[3]), accumulate != 0);
+}
+
+// Workgroups NUMAG_TARGET_WGS asks for (0: not set).
+static int env_target()
 {
     static const int cached = [] {  // thread-safe one-time initialisation
         const char *e = getenv("NUMAG_TARGET_WGS");
         const int v = e != nullptr ? atoi(e) : 0;
-        return v > 0 ? v : 2048;
+        return v > 0 ? v : 0;
     }();
     return cached;
 }
 
+int target_workgroups() { return env_target() > 0 ? env_target() : 2048; }
+
+// ---------------------------------------------------------------------------
+// Work split of the Cartesian sums.
+// ---------------------------------------------------------------------------
+constexpr int64_t kCartCUs = 256;     // one workgroup of 8 waves per CU at a time
+constexpr int kMaxSplits = 65535;     // grid.z
+
+// Rows, columns and strides of the cells, row blocks for `channels`; the orientation
+// with fewer matrix tiles (thin detectors put their short axis into the packed rows).
+static void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt)
+{
+    int64_t best = -1;
+    for (int sw = 0; sw < 2; ++sw) {
+        const int nM = sw ? d.n1 : d.n0, nN = sw ? d.n0 : d.n1;
+        const int A = (nM + 1) / 2, B = (nN + 1) / 2;
+        const int per_block = 8 * cblk::kMaxMT / channels;  // |q_M| values of a full row block
+        const int nrb = (A + per_block - 1) / per_block;
+        const int na = (A + nrb - 1) / nrb;
+        const int m = (na * channels + 7) / 8;
+        const int nzb = (B + cblk::kOff - 1) / cblk::kOff;
+        const int64_t tiles = (int64_t)nrb * m * nzb;
+        if (best >= 0 && tiles >= best) continue;
+        best = tiles;
+        mt = m;
+        g.A = A;
+        g.B = B;
+        g.nM = nM;
+        g.nN = nN;
+        g.na = na;
+        g.nrb = nrb;
+        g.nzb = nzb;
+        g.swapped = sw;
+        g.originM = sw ? d.origin1 : d.origin0;
+        g.stepM = sw ? d.step1 : d.step0;
+        g.originN = sw ? d.origin0 : d.origin1;
+        g.stepN = sw ? d.step0 : d.step1;
+        g.strideM = sw ? 1 : d.n1;
+        g.strideN = sw ? d.n1 : 1;
+    }
+}
+
+// Column blocks per workgroup of a launch shape (the labels are those tables hold).
+static int cart_nz(int shape) { return shape == 32 ? 8 : shape == 16 ? 4 : shape == 64 ? 2 : 1; }
+
+static size_t cart_split_bytes(const CartGeom &g, int mt) { return (size_t)g.nrb * g.nzb * mt * 512 * sizeof(double); }
+
+// Point splits: a launch of about `target` workgroups, each split a multiple of 4
+// points (one matrix step), at least one step per point group of a workgroup.
+static void cart_splits(CartPlan &p, int64_t W, int64_t target, size_t max_partial)
+{
+    p.col_groups = (p.g.nzb + p.g.nz - 1) / p.g.nz;
+    const int64_t blocks = (int64_t)p.col_groups * p.g.nrb;
+    int64_t want = target / blocks;
+    want = std::min<int64_t>(want, (W + 4 * (cblk::kWaves / p.g.nz) - 1) / (4 * (cblk::kWaves / p.g.nz)));
+    if (max_partial > 0)
+        want = std::min<int64_t>(want, (int64_t)(max_partial / std::max<size_t>(1, cart_split_bytes(p.g, p.mt))));
+    want = std::max<int64_t>(1, std::min<int64_t>(want, kMaxSplits));
+    int64_t per = (W + want - 1) / want;
+    per = std::max<int64_t>(4, (per + 3) / 4 * 4);
+    p.per = per;
+    p.nsplit = (int)std::max<int64_t>(1, (W + per - 1) / per);
+}
+
+// Estimated time (cycles) of a split, from the pipe counts: a matrix instruction
+// holds the FP64 pipe of its SIMD 64 cycles, a vector one 4, a sincos about 27 of
+// them; partial sums move at about 1700 bytes a cycle each way.
+static double cart_cost(const CartPlan &p, int64_t W)
+{
+    const double pts = (double)std::min<int64_t>(p.per, std::max<int64_t>(W, 1));
+    const double chunks = std::ceil(pts / cblk::kChunk), steps = std::ceil(pts / 4.0);
+    // steps of the busiest SIMD: two column blocks, one, or a share of one
+    const double share = p.g.nz == 8 ? (p.g.nzb > 4 ? 2.0 : 1.0) : p.g.nz / 4.0;
+    const double busy = share * steps * (128.0 * p.mt + 60.0);
+    const double passes = std::ceil(p.g.na / 16.0);
+    const double gen = 2.0 * (150.0 + passes * (150.0 + 8.0 * p.channels));
+    const int64_t wgs = (int64_t)p.col_groups * p.g.nrb * p.nsplit;
+    const double rounds = std::ceil((double)wgs / (double)kCartCUs);
+    const double bytes = (double)cart_split_bytes(p.g, p.mt) * p.nsplit;
+    const double reduce = p.g.nz < 8 ? 400.0 * p.mt : 0.0;
+    return rounds * (4000.0 + chunks * gen + busy + reduce) + (p.nsplit > 1 ? 8000.0 + 2.0 * bytes / 1700.0 : 0.0);
+}
+
+static CartPlan cart_default_plan(const Detector &d, int64_t W, int channels, size_t max_partial)
+{
+    CartPlan best{};
+    double best_cost = -1.0;
+    for (int shape : {32, 16, 64, 8}) {
+        CartPlan p{};
+        p.channels = channels;
+        p.shape = shape;
+        cart_geometry(d, channels, p.g, p.mt);
+        p.g.nz = cart_nz(shape);
+        if (p.g.nz > 2 && p.g.nz / 2 >= p.g.nzb) continue;  // column blocks that no wave would have
+        const int64_t blocks = (int64_t)((p.g.nzb + p.g.nz - 1) / p.g.nz) * p.g.nrb;
+        for (int rounds : {1, 2, 3, 4}) {
+            const int64_t target = env_target() > 0 ? env_target() : std::max<int64_t>(rounds * kCartCUs, blocks);
+            cart_splits(p, W, target, max_partial);
+            const double cost = cart_cost(p, W);
+            if (best_cost < 0.0 || cost < 0.98 * best_cost) {
+                best_cost = cost;
+                best = p;
+            }
+        }
+    }
+    return best;
+}
+
 TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
 {
-    (void)W;
     switch (kernel) {
-        case kTuneDirect:
+        case kTuneDirect: {
             if (d.kind == NUMAG_GRID_POLAR) {
                 const int sh = default_polar_shape(d);
                 // half the Cartesian path's wave count: a polar workgroup of 8 waves holds
@@ -222,7 +411,9 @@ TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
                 // four (fewer partials too)
                 return TuneShape{sh, target_workgroups() * 2 / polar_shape_waves(sh)};
             }
-            return TuneShape{cart::choose_lanes(d.n1), target_workgroups()};
+            const CartPlan p = cart_default_plan(d, W, 4, 0);
+            return TuneShape{p.shape, (int)((int64_t)p.col_groups * p.g.nrb * p.nsplit)};
+        }
         case kTuneAdjoint:
             // twice the direct path's workgroups (measured about 2 % faster than the same
             // count: shorter row ranges balance better across the CUs)
@@ -243,31 +434,26 @@ TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W)
     return default_tune_shape(kernel, d, W);
 }
 
-DirectPlan plan_direct_cartesian(const Detector &d, int64_t W, int64_t max_splits)
+CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial)
 {
-    DirectPlan p{};
-    p.channels = 4;
-    const TuneShape ts = current_tune_shape(kTuneDirect, d, W);
-    p.lanes = ts.shape;
-    const int cols = p.lanes * cart::kB, rows = kThreads / p.lanes;
-    p.col_blocks = (d.n1 + cols - 1) / cols;
-    p.row_blocks = (d.n0 + rows - 1) / rows;
-    int64_t blocks = (int64_t)p.col_blocks * p.row_blocks;
-    int64_t want = (ts.target + blocks - 1) / blocks;
-    // each split should own a few chunks
-    int64_t max_split = (W + 4 * kChunk - 1) / (4 * kChunk);
-    if (max_split < 1) max_split = 1;
-    if (want > max_split) want = max_split;
-    if (max_splits > 0 && want > max_splits) want = max_splits;
-    if (want > 65535) want = 65535;
-    if (want < 1) want = 1;
-    int64_t per = (W + want - 1) / want;
-    per = ((per + kChunk - 1) / kChunk) * kChunk;
-    if (per < kChunk) per = kChunk;
-    p.per = per;
-    p.nsplit = (int)((W + per - 1) / per);
-    if (p.nsplit < 1) p.nsplit = 1;
+    Detector key = d;
+    if (hermitian) key.n0 = (d.n0 + 1) / 2;
+    TuneShape ts{};
+    if (!tuned_shape(kTuneDirect, key, W, &ts) || !valid_tune_shape(kTuneDirect, key, ts))
+        return cart_default_plan(d, W, channels, max_partial);
+    if (ts.target == 0) ts.target = default_tune_shape(kTuneDirect, key, W).target;
+    CartPlan p{};
+    p.channels = channels;
+    p.shape = ts.shape;
+    cart_geometry(d, channels, p.g, p.mt);
+    p.g.nz = cart_nz(ts.shape);
+    cart_splits(p, W, ts.target, max_partial);
     return p;
+}
+
+size_t cart_partial_bytes(const CartPlan &p)
+{
+    return p.nsplit > 1 ? cart_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
 }
 
 size_t direct_partial_bytes(const DirectPlan &p, const Detector &d)
@@ -275,28 +461,44 @@ size_t direct_partial_bytes(const DirectPlan &p, const Detector &d)
     return (size_t)p.nsplit * (size_t)d.n0 * (size_t)d.n1 * 8 * sizeof(double);
 }
 
-int launch_direct_cartesian(const PointRec *pts, int64_t W, const Detector &d, const DirectPlan &p,
-                            double *partial, hipStream_t s)
+template <int CH>
+static void launch_cart_tiles(const PointRec *pts, int64_t W, const CartPlan &p, int store, double *out, hipStream_t s)
 {
-    dim3 grid(p.col_blocks, p.row_blocks, p.nsplit);
-    dim3 block(kThreads);
-    TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
-#define NUMAG_LAUNCH_CART(LR, CH) \
-    hipLaunchKernelGGL((direct_cartesian_kernel<LR, CH>), grid, block, 0, s, pts, W, p.per, d, partial)
-#define NUMAG_LAUNCH_CART_CH(LR)                      \
-    switch (p.channels) {                             \
-        case 1: NUMAG_LAUNCH_CART(LR, 1); break;      \
-        case 3: NUMAG_LAUNCH_CART(LR, 3); break;      \
-        default: NUMAG_LAUNCH_CART(LR, 4); break;     \
+    const dim3 grid(p.col_groups, p.g.nrb, p.nsplit), block(cblk::kThreads);
+#define NUMAG_LAUNCH_CART(MT) \
+    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH>), grid, block, 0, s, pts, W, p.per, p.g, store, out)
+    switch (p.mt) {
+        case 1: NUMAG_LAUNCH_CART(1); break;
+        case 2: NUMAG_LAUNCH_CART(2); break;
+        case 3: NUMAG_LAUNCH_CART(3); break;
+        case 4: NUMAG_LAUNCH_CART(4); break;
+        case 5: NUMAG_LAUNCH_CART(5); break;
+        case 6: NUMAG_LAUNCH_CART(6); break;
+        case 7: NUMAG_LAUNCH_CART(7); break;
+        default: NUMAG_LAUNCH_CART(8); break;
     }
-    switch (p.lanes) {
-        case 8: NUMAG_LAUNCH_CART_CH(8); break;
-        case 16: NUMAG_LAUNCH_CART_CH(16); break;
-        case 32: NUMAG_LAUNCH_CART_CH(32); break;
-        default: NUMAG_LAUNCH_CART_CH(64); break;
-    }
-#undef NUMAG_LAUNCH_CART_CH
 #undef NUMAG_LAUNCH_CART
+}
+
+int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
+                            int accumulate, hipStream_t s)
+{
+    const bool split = p.nsplit > 1;
+    const int store = split ? 0 : (accumulate ? 2 : 1);
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        double *out = split ? partial : amp;
+        switch (p.channels) {
+            case 1: launch_cart_tiles<1>(pts, W, p, store, out, s); break;
+            case 3: launch_cart_tiles<3>(pts, W, p, store, out, s); break;
+            default: launch_cart_tiles<4>(pts, W, p, store, out, s); break;
+        }
+    }
+    NUMAG_HIP_CHECK(hipGetLastError());
+    if (!split) return NUMAG_OK;
+    const int64_t n = (int64_t)p.g.nrb * p.g.nzb * p.mt * 128;
+    hipLaunchKernelGGL(cart_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
+                       p.channels, p.nsplit, accumulate, amp);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

@@ -66,15 +66,24 @@ int launch_prepare_points(const double *pos, const double *nuc, const double *ma
                           const numag_regular *regular, const int64_t *h_offsets, int64_t K,
                           const double *obj_pos, const Rot &R, PointRec *out, hipStream_t s);
 
-// direct Cartesian sum.  Writes [nsplit][P][8] partial sums (or the final
-// [P][8] sums when nsplit == 1) for points [0, W).
+// Split of a direct sum into workgroups.
 struct DirectPlan {
-    int lanes;       // lanes per detector row (Cartesian) or theta columns per workgroup (polar)
-    int shape;       // polar: workgroup shape (index into the polar kernel's shapes)
+    int lanes;       // polar: theta columns per workgroup
+    int shape;       // launch shape (Cartesian: see CartPlan; polar: index into the polar kernel's shapes)
     int channels;    // channels summed: 4 (N, M), 3 (M only) or 1 (N only); the rest are written as 0
     int nsplit;      // point ranges summed by different workgroups
-    int64_t per;     // points per split (multiple of the chunk)
+    int64_t per;     // points per split
     int col_blocks, row_blocks;
+};
+// Split of a Cartesian direct sum (cartesian_block.h).
+struct CartPlan {
+    CartGeom g;
+    int mt;          // 16-row matrix tiles per wave
+    int shape;       // launch shape (8, 64, 16, 32: 1, 2, 4, 8 column blocks per workgroup)
+    int channels;
+    int nsplit;
+    int64_t per;     // points per split (a multiple of 4)
+    int col_groups;  // workgroups along N
 };
 // Hermitian completion of a half-detector sum (see direct.hip).
 int launch_mirror_cartesian(double *amp, int64_t P, int64_t Ph, hipStream_t s);
@@ -105,11 +114,18 @@ bool valid_tune_shape(int kernel, const Detector &d, const TuneShape &s);
 TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W);
 // The shape in use: the tuned one if the table holds it, else the default.
 TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W);
-// max_splits > 0 caps the point splits (and so the partial-sum buffer).
-DirectPlan plan_direct_cartesian(const Detector &d, int64_t W, int64_t max_splits = 0);
+// Plan of a Cartesian sum on the whole detector d.  The launch shape is looked up
+// under the part of the detector that the caller's path stands for (hermitian: the
+// first ceil(n0 / 2) rows); either way every pixel is written, the mirrored ones as
+// conjugates.  max_partial > 0 caps the bytes of partial sums.
+CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial = 0);
+// Bytes of partial sums (0 when one split writes the sums directly).
+size_t cart_partial_bytes(const CartPlan &p);
+// Writes (accumulate: adds) the sums of all pixels of the detector to amp [P][8].
+int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
+                            int accumulate, hipStream_t s);
+
 size_t direct_partial_bytes(const DirectPlan &p, const Detector &d);
-int launch_direct_cartesian(const PointRec *pts, int64_t W, const Detector &d, const DirectPlan &p,
-                            double *partial, hipStream_t s);
 
 // Polar detector direct sum: [nsplit][P][8] partials.
 // max_splits > 0 caps the point splits (rotation groups trade splits for rotations);

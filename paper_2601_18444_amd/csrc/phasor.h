@@ -27,12 +27,20 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 // Horner's rule in r^2; the quadrant k mod 4 swaps and negates them.  Arguments
 // beyond 2^19 take the library sincos.  Host-callable so that its accuracy can
 // be checked without a GPU.
-__host__ __device__ __forceinline__ void sincos_cw(double x, double *sp, double *cp)
+// The library call is kept out of line: inlined, its argument reduction takes enough
+// registers to push the sum kernels' accumulators into scratch memory.
+__host__ __device__ __attribute__((noinline)) static double2 sincos_library(double x)
 {
-    if (!(fabs(x) < 0x1p19)) {  // also NaN and infinities
-        sincos(x, sp, cp);
-        return;
-    }
+    double s, c;
+    sincos(x, &s, &c);
+    return make_double2(s, c);
+}
+
+// |x| < 2^19 takes the fast path (false also for NaN and infinities).
+__host__ __device__ __forceinline__ bool sincos_fast_range(double x) { return fabs(x) < 0x1p19; }
+
+__host__ __device__ __forceinline__ void sincos_fast(double x, double *sp, double *cp)
+{
     constexpr double kTwoOverPi = 0x1.45f306dc9c883p-1;
     constexpr double P1 = 0x1.921fb54400000p+0;
     constexpr double P2 = 0x1.0b4611a600000p-34;
@@ -68,12 +76,41 @@ __host__ __device__ __forceinline__ void sincos_cw(double x, double *sp, double 
     *cp = ((n + 1) & 2) ? -c0 : c0;
 }
 
+__host__ __device__ __forceinline__ void sincos_cw(double x, double *sp, double *cp)
+{
+    if (__builtin_expect(!sincos_fast_range(x), 0)) {
+        const double2 r = sincos_library(x);
+        *sp = r.x;
+        *cp = r.y;
+        return;
+    }
+    sincos_fast(x, sp, cp);
+}
+
 // exp(-i phi) = (cos phi, -sin phi)
 __host__ __device__ __forceinline__ double2 twiddle(double phi)
 {
     double s, c;
     sincos_cw(phi, &s, &c);
     return make_double2(c, -s);
+}
+
+// Two unit phasors at once: one range check, and the two chains interleave.
+__device__ __forceinline__ void twiddle2(double p0, double p1, double2 &e0, double2 &e1)
+{
+    double s0, c0, s1, c1;
+    if (__builtin_expect(!(sincos_fast_range(p0) && sincos_fast_range(p1)), 0)) {
+        const double2 r0 = sincos_library(p0), r1 = sincos_library(p1);
+        s0 = r0.x;
+        c0 = r0.y;
+        s1 = r1.x;
+        c1 = r1.y;
+    } else {
+        sincos_fast(p0, &s0, &c0);
+        sincos_fast(p1, &s1, &c1);
+    }
+    e0 = make_double2(c0, -s0);
+    e1 = make_double2(c1, -s1);
 }
 
 // origin + i * step

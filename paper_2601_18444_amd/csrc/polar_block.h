@@ -1,0 +1,173 @@
+// Device building block of the polar-detector sums (Sec. 3.2 (q, theta) grid) on the
+// FP64 matrix cores.
+//
+// S_c(q_i, theta_m) = sum_j w_{j,c} exp(-i q_i u_m(j)),  u_m = Y sin(theta_m) + Z cos(theta_m).
+// The phase does not separate over the detector, but at one theta the q rows do: with
+// blocks of 32 rows, row 32 a + 15.5 +- (b + 1/2) of block a has the phasor
+// exp(-i c_a u) exp(-+ i (b + 1/2) dq u), so the sums of a column are the same four
+// real contractions over points as a Cartesian cell's (cartesian_block.h) with the block
+// centres c_a in the place of |q_M| and the 16 offsets in that of |q_N|: two real
+// multiply-adds per term and channel (one where theta + pi is a column too and is
+// filled in as the conjugate), against the ten vector FP64 operations of a walk along q.
+//
+// A wave owns one theta column and one group of `na` row blocks (at most 16, all
+// channels), and works alone: tables of a chunk of 32 points go through its own LDS,
+// without workgroup barriers.  What bounds it is the FP64 pipe, which matrix and vector
+// instructions share; the tables cost one sincos per (point, column), products and
+// two-term recurrences x_{k+1} = 2 cos(step) x_k - x_{k-1} of at most 8 (offsets) and 16
+// (centres) steps:
+//   half h of the lanes (one lane per point) starts from exp(-i (8 h + 1/2) dq u) and
+//   walks 8 offsets; the last one of the second half is the first centre, 15.5 dq u,
+//   and the centre step is 32 dq u = 2 (15.5 dq u) + dq u.
+#pragma once
+
+#include "cartesian_block.h"
+
+namespace numag {
+namespace pblk {
+
+using cblk::v4d;
+using cblk::Point;
+
+constexpr int kWaves = 4;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kChunk = 32;    // points per chunk of a wave
+constexpr int kRows = 32;     // q rows per block
+constexpr int kMaxNA = 16;    // row blocks per wave
+
+// Row blocks a wave of MT tiles holds.
+template <int MT, int CH>
+constexpr int max_na() { return 8 * MT / CH < kMaxNA ? 8 * MT / CH : kMaxNA; }
+
+template <int MT, int CH>
+struct WaveSmem {
+    double2 off[kChunk][17];
+    double2 ctr[kChunk][max_na<MT, CH>() + 1];
+    double w[kChunk][CH + 1];
+};
+
+// Value of v in the other half of the wave (lane ^ 32).
+__device__ __forceinline__ double other_half(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __shfl_xor((int)b, 32), hi = __shfl_xor((int)(b >> 32), 32);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// x_{k+1} = k2 x_k - x_{k-1} for both parts.
+__device__ __forceinline__ double2 next_term(double k2, double2 x, double2 before)
+{
+    return make_double2(fma(k2, x.x, -before.x), fma(k2, x.y, -before.y));
+}
+
+// Tables of a chunk: point gp = lane % 32 of the wave at u; weights p.w.
+template <int MT, int CH>
+__device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int na, double dq, double u, const Point<CH> &p)
+{
+    const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
+    double2 x = twiddle(((half == 0 ? 0.0 : 8.0) + 0.5) * dq * u);
+    double2 st = cmul(x, x);  // dq u in the first half
+    const double2 so = make_double2(other_half(st.x), other_half(st.y));
+    if (half != 0) st = so;
+    const double k2 = st.x + st.x;
+    double2 y = cmul(x, st);
+    sm.off[gp][8 * half] = x;
+    sm.off[gp][8 * half + 1] = y;
+#pragma unroll
+    for (int k = 2; k < 8; ++k) {
+        const double2 z = next_term(k2, y, x);
+        sm.off[gp][8 * half + k] = z;
+        x = y;
+        y = z;
+    }
+    if (half != 0) {  // y = exp(-i 15.5 dq u)
+        const double2 cs = cmul(cmul(y, y), st);
+        const double kc = cs.x + cs.x;
+        double2 a = y, b = cmul(y, cs);
+        sm.ctr[gp][0] = a;
+        if (na > 1) sm.ctr[gp][1] = b;
+#pragma unroll 1
+        for (int k = 2; k < na; ++k) {
+            const double2 c = next_term(kc, b, a);
+            sm.ctr[gp][k] = c;
+            a = b;
+            b = c;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) sm.w[gp][c] = p.w[c];
+    }
+}
+
+// LDS operations of a wave complete in order: this only keeps the compiler from
+// moving reads and writes of the tables across.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Adds the points [jbeg, jend) of `ld` (Point<CH> load(j): m = Y, n = Z) to the wave's
+// tiles: theta direction (sth, cth), row blocks [a0, a0 + na) (the tables start at
+// block 0 of the wave: `shift` is the phase factor 32 a0 dq of its first block).
+template <int MT, int CH, class Loader>
+__device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, double sth, double cth,
+                                           double dq, int a0, int na, WaveSmem<MT, CH> &sm, v4d (&accC)[MT],
+                                           v4d (&accS)[MT])
+{
+    const int lane = threadIdx.x & 63, gp = lane & 31;
+    const int r16 = lane & 15, kq = lane >> 4;
+    // this lane's matrix row: slot 8 t + 4 (r16 / 8) + r16 % 4, part (r16 / 4) % 2
+    const int part = (r16 >> 2) & 1;
+    int ea[MT], wc[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int s = 8 * t + 4 * (r16 >> 3) + (r16 & 3);
+        ea[t] = min(s / CH, max_na<MT, CH>() - 1);
+        wc[t] = s % CH;
+    }
+    auto fetch = [&](int64_t j0) {
+        Point<CH> p{};
+        if (j0 + gp < jend) p = ld.load(j0 + gp);
+        return p;
+    };
+    Point<CH> p = fetch(jbeg);
+#pragma unroll 1
+    for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk) {
+        const double u = p.m * sth + p.n * cth;
+        generate<MT, CH>(sm, na, dq, u, p);
+        if (a0 != 0) {  // later row groups: rotate the weights' side by the group's first block
+            const double2 sh = twiddle((double)(kRows * a0) * dq * u);
+            if (lane >= 32)
+#pragma unroll 1
+                for (int k = 0; k < na; ++k) sm.ctr[gp][k] = cmul(sm.ctr[gp][k], sh);
+        }
+        wave_fence();
+        p = fetch(j0 + kChunk);
+        const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
+#pragma unroll 1
+        for (int s = 0; s < steps; ++s) {
+            const int pt = 4 * s + kq;
+            const double2 z = sm.off[pt][r16];
+            const double *cp = (const double *)&sm.ctr[pt][0] + part;
+            double a[MT];
+            if (CH == 3) {
+#pragma unroll
+                for (int t = 0; t < MT; ++t) a[t] = cp[2 * ea[t]] * sm.w[pt][wc[t]];
+            } else {
+                const double w = sm.w[pt][wc[0]];
+#pragma unroll
+                for (int t = 0; t < MT; ++t) a[t] = cp[2 * ea[t]] * w;
+            }
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                accC[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.x, accC[t], 0, 0, 0);
+                accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.y, accS[t], 0, 0, 0);
+            }
+        }
+        wave_fence();
+    }
+}
+
+}  // namespace pblk
+}  // namespace numag

@@ -9,8 +9,8 @@
 // rounding.
 //
 // Shapes per kernel:
-//   direct, Cartesian detector: lanes per detector row (8, 16, 32, 64) and the
-//     workgroups a launch aims for (split over points);
+//   direct, Cartesian detector: 8, 64, 16 or 32 for 1, 2, 4 or 8 blocks of 32 detector
+//     columns per workgroup, and the workgroups a launch aims for (split over points);
 //   direct, polar detector: one of the polar kernel's workgroup shapes
 //     (64 x 64, 32 x 64, 128 x 32, 256 x 16 single- or double-buffered) and the
 //     workgroups aimed for;

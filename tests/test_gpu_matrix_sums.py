@@ -1,0 +1,59 @@
+"""Edges of the matrix-core sums: detectors around the tile sizes (blocks of 32 pixels
+along one axis, packed rows along the other, thin and transposed detectors, single
+pixels), point counts around the 4-point matrix step and the 32-point chunk, every
+channel set and workgroup shape, against the FP64 oracle.
+
+Tolerance, from the arithmetic: a phasor is a product of at most a few rounded
+phasors whose phases are products rounded to |phase| 2^-53, and a sum of W terms
+adds at most W roundings, so each amplitude is within
+2^-52 (4 max|phase| + W + 128) sum|w| of the exact sum (the oracle's own error is of
+the same form and smaller)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2601_18444_amd import numag, synth  # noqa: E402
+from tests.helpers import amp_to_complex  # noqa: E402
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(autouse=True)
+def _clean_table():
+    numag.tune_clear()
+    yield
+    numag.tune_clear()
+
+
+def _check(orc, kind, n0, n1, W, chan, shape, path):
+    rng = np.random.default_rng(1000 * n0 + 10 * n1 + W + chan)
+    pos, nuc, mag = rng.uniform(-9, 9, (W, 3)), rng.standard_normal(W), rng.standard_normal((W, 3))
+    qmax = 1.3
+    R = synth.sample_rotation(33.0, 71.0)
+    grid = numag.qgrid(kind, n0, n1, qmax)
+    s = numag.Sample(pos=pos, nuc=nuc if chan != 2 else None, mag=mag if chan != 1 else None, device=DEV)
+    if shape is not None:
+        numag.tune_set(numag.TUNE_DIRECT, grid, W, shape, path=path)
+    amp, _ = numag.amplitudes(s, grid, rot=R, path=path)
+    qy, qz, _ = orc.pixels(kind, n0, n1, qmax)
+    on, om = (nuc if chan != 2 else np.zeros(W)), (mag if chan != 1 else np.zeros((W, 3)))
+    ref = orc.amplitudes(pos, on, om, qy, qz, R=R)
+    phase = 2 * qmax * np.abs(pos).sum(1).max()
+    w = np.concatenate([on[:, None], om @ R.T], axis=1)
+    tol = 2.0 ** -52 * (4 * phase + W + 128) * np.abs(w).sum(0)
+    err = np.abs(amp_to_complex(amp[0]) - ref).max(0)
+    assert np.all(err <= tol), (err, tol)
+
+
+@pytest.mark.parametrize("n0,n1", [(1, 1), (2, 1), (1, 2), (1, 700), (700, 1), (3, 300), (31, 33), (32, 32), (33, 65),
+                                   (34, 31), (64, 257), (129, 35), (200, 130)])
+@pytest.mark.parametrize("chan", [0, 1, 2])
+def test_cartesian_tiles(orc, n0, n1, chan):
+    for W, shape in [(1, None), (4, (8, 0)), (33, (64, 3)), (130, (16, 7)), (517, (32, 2)), (700, None)]:
+        for path in (numag.PATH_DIRECT, numag.PATH_DIRECT_HERMITIAN):
+            _check(orc, 0, n0, n1, W, chan, shape, path)
