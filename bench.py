@@ -47,7 +47,7 @@ KERNELS = {
 }
 # kernels measured outside the step (their counter summaries, same format)
 SIDE_KERNELS = {
-    "direct_polar_kernel": (0, ["cartesian_sum.h", "polar_sum.h", "polar.hip", "phasor.h", "types.h"],
+    "direct_polar_kernel": (0, ["cartesian_block.h", "polar_block.h", "polar.hip", "phasor.h", "types.h"],
                             "direct_polar_kernel_vortex64_polar256x256.md"),
 }
 

@@ -36,9 +36,8 @@
  * Tuning: launch shapes come from a table (numag_tune_get / numag_autotune
  * below); without an entry, the environment variable NUMAG_TARGET_WGS (read
  * once per process) sets the number of workgroups the direct sums aim for per
- * launch (default on a Cartesian detector: chosen by an estimate of the time from
- * the point and pixel counts; otherwise 2048, the polar sums half and the adjoint
- * twice of it).  Shapes change how the work is split, never a
+ * launch (default: chosen by an estimate of the time from the point and pixel
+ * counts; the adjoint 4096).  Shapes change how the work is split, never a
  * result's definition; sums split differently agree to rounding.
  */
 #ifndef NUMAG_H
@@ -420,10 +419,9 @@ int numag_angular_spectrum(const numag_qgrid *grid, const double *f, int32_t n_f
  *   shape     Cartesian direct: detector columns per workgroup (8: 32 columns,
  *             64: 64, 16: 128, 32: 256; the axis the columns lie on may be the
  *             detector's rows on thin detectors); Cartesian objects: lanes per
- *             detector row (8, 16, 32, 64); polar direct: workgroup shape 0-4 (0: 64 q rows x 64 theta
- *             columns; 1: 32 x 64, only for at most 32 q rows; 2: 128 x 32;
- *             3: 256 x 16 with chunks of 16 points; 4: 256 x 16 with
- *             double-buffered chunks of 8 points); adjoint: 0.
+ *             detector row (8, 16, 32, 64); polar direct: q rows per
+ *             wave (1: 32 rows, only for at most 32 q rows; 0: 64; 2: 128; 3: 256;
+ *             4: 512); adjoint: 0.
  *   target    workgroups a launch aims for (objects: work items); 0 = default.
  *   path      NUMAG_PATH_DIRECT or NUMAG_PATH_DIRECT_HERMITIAN (which part of
  *             the detector is evaluated).

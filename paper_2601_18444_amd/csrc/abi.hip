@@ -147,16 +147,12 @@ DirectLayout direct_layout(const numag_sample *s, const Detector &d)
     DirectLayout L{};
     L.points = align_up((size_t)std::max<int64_t>(s->n_points, 1) * sizeof(PointRec));
     // partial sums of every path and channel set, whichever is largest
-    if (d.kind == NUMAG_GRID_CARTESIAN) {
-        for (int ch : {4, 3, 1})
-            for (bool herm : {false, true})
-                L.partial = std::max(L.partial, align_up(cart_partial_bytes(plan_direct_cartesian(d, s->n_points, ch, herm))));
-    } else {
-        Detector dh = d;
-        dh.n1 = std::max(1, d.n1 / 2);
-        const DirectPlan p = plan_direct_polar(d, s->n_points), ph = plan_direct_polar(dh, s->n_points);
-        L.partial = std::max(align_up(direct_partial_bytes(p, d)), align_up(direct_partial_bytes(ph, dh)));
-    }
+    for (int ch : {4, 3, 1})
+        for (bool herm : {false, true})
+            L.partial = std::max(L.partial,
+                                 align_up(d.kind == NUMAG_GRID_CARTESIAN
+                                              ? cart_partial_bytes(plan_direct_cartesian(d, s->n_points, ch, herm))
+                                              : polar_partial_bytes(plan_direct_polar(d, s->n_points, ch, herm))));
     L.total = L.points + L.partial;
     return L;
 }
@@ -182,20 +178,8 @@ int run_direct(const numag_sample *s, const Rot &R, const Detector &d, double *a
     if (d.kind == NUMAG_GRID_CARTESIAN)
         return launch_direct_cartesian(pts, s->n_points, plan_direct_cartesian(d, s->n_points, channels, hermitian),
                                        part, amp, 0, st);
-    if (hermitian) {
-        Detector dh = d;
-        dh.n1 = d.n1 / 2;  // columns [0, n_theta / 2); their mirrors are m + n_theta / 2
-        DirectPlan p = plan_direct_polar(dh, s->n_points);
-        p.channels = channels;
-        rc = launch_direct_polar(pts, s->n_points, dh, p, part, st);
-        if (rc != NUMAG_OK) return rc;
-        return launch_combine_polar_half(part, p.nsplit, d.n0, dh.n1, amp, st);
-    }
-    DirectPlan p = plan_direct_polar(d, s->n_points);
-    p.channels = channels;
-    rc = launch_direct_polar(pts, s->n_points, d, p, part, st);
-    if (rc != NUMAG_OK) return rc;
-    return launch_combine(part, p.nsplit, P, amp, 0, st);
+    return launch_direct_polar(pts, s->n_points, plan_direct_polar(d, s->n_points, channels, hermitian), part, amp, 0,
+                               st);
 }
 
 unsigned long long next_plan_tag()
@@ -360,9 +344,11 @@ std::vector<TuneShape> tune_candidates(int kernel, const Detector &d, int64_t W)
     std::vector<TuneShape> c;
     const TuneShape def = default_tune_shape(kernel, d, W);
     if (kernel == kTuneDirect && d.kind == NUMAG_GRID_POLAR) {
-        const std::vector<int> shapes = d.n0 <= 32 ? std::vector<int>{1, 0} : std::vector<int>{0, 2, 3, 4};
-        for (int sh : shapes)
-            for (int t : {256, 512, 1024}) c.push_back(TuneShape{sh, t * 8 / polar_shape_waves(sh)});
+        // the smallest row group that covers the detector, and the one below
+        const std::vector<int> order{1, 0, 2, 3, 4};
+        const int at = (int)(std::find(order.begin(), order.end(), def.shape) - order.begin());
+        for (int k = at; k >= std::max(at - 1, d.n0 <= 32 ? 0 : 1); --k)
+            for (int t : {512, 1024, 2048}) c.push_back(TuneShape{order[(size_t)k], t});
     } else if (kernel == kTuneObjects && d.kind == NUMAG_GRID_POLAR) {
         const std::vector<int> shapes = d.n0 <= 32 ? std::vector<int>{1, 0} : std::vector<int>{0, 2, 4};
         for (int sh : shapes)

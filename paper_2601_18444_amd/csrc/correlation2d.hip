@@ -75,25 +75,14 @@ __global__ void corr2d_scatter_kernel(const double *__restrict__ amp, int64_t R,
 
 static size_t al2(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// The polar real-space grid to evaluate: C(-r) = conj C(r) for real data, so only
-// the columns [0, n_alpha/2) are summed when n_alpha is even and the rest mirrored.
-static Detector half_grid(const Detector &rd)
-{
-    Detector rh = rd;
-    if (rd.kind == NUMAG_GRID_POLAR && rd.n1 % 2 == 0) rh.n1 = rd.n1 / 2;
-    return rh;
-}
-
 // Bytes of split partial sums, whatever the channel set.
 static size_t corr2d_partial_bytes(const Detector &rd, int64_t P)
 {
-    if (rd.kind == NUMAG_GRID_CARTESIAN) {
-        size_t b = 0;
-        for (int ch : {4, 3, 1}) b = std::max(b, cart_partial_bytes(plan_direct_cartesian(rd, P, ch, true)));
-        return b;
-    }
-    const Detector rh = half_grid(rd);
-    return direct_partial_bytes(plan_direct_polar(rh, P), rh);
+    size_t b = 0;
+    for (int ch : {4, 3, 1})
+        b = std::max(b, rd.kind == NUMAG_GRID_CARTESIAN ? cart_partial_bytes(plan_direct_cartesian(rd, P, ch, true))
+                                                        : polar_partial_bytes(plan_direct_polar(rd, P, ch, true)));
+    return b;
 }
 
 size_t correlation_2d_workspace_bytes(const Detector &d, const Detector &rd)
@@ -111,7 +100,6 @@ int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Det
         set_error("numag_correlation_2d: workspace too small");
         return NUMAG_E_WORKSPACE;
     }
-    const Detector rh = half_grid(rd);
     char *base = (char *)ws;
     PointRec *pts = (PointRec *)base;
     double *part = (double *)(base + al2((size_t)P * sizeof(PointRec)));
@@ -124,17 +112,10 @@ int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Det
         hipLaunchKernelGGL(corr2d_points_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, d, f, n_f, set0,
                            c0, pts);
         NUMAG_HIP_CHECK(hipGetLastError());
-        int rc;
-        if (rd.kind == NUMAG_GRID_CARTESIAN) {
-            rc = launch_direct_cartesian(pts, P, plan_direct_cartesian(rd, P, channels, true), part, amp, 0, s);
-        } else {
-            DirectPlan plan = plan_direct_polar(rh, P);
-            plan.channels = channels;
-            rc = launch_direct_polar(pts, P, rh, plan, part, s);
-            if (rc == NUMAG_OK)
-                rc = rh.n1 != rd.n1 ? launch_combine_polar_half(part, plan.nsplit, rd.n0, rh.n1, amp, s)
-                                    : launch_combine(part, plan.nsplit, R, amp, 0, s);
-        }
+        const int rc =
+            rd.kind == NUMAG_GRID_CARTESIAN
+                ? launch_direct_cartesian(pts, P, plan_direct_cartesian(rd, P, channels, true), part, amp, 0, s)
+                : launch_direct_polar(pts, P, plan_direct_polar(rd, P, channels, true), part, amp, 0, s);
         if (rc != NUMAG_OK) return rc;
         hipLaunchKernelGGL(corr2d_scatter_kernel, dim3((unsigned)((R * 4 + 255) / 256)), dim3(256), 0, s, amp, R, n_f,
                            set0, c0, C);

@@ -281,8 +281,7 @@ __global__ __launch_bounds__(256) void cart_combine_kernel(const double *__restr
     cblk::put_slot(amp, x, CH, make_double2(v[0], v[1]), make_double2(v[2], v[3]), accumulate != 0);
 }
 
-// Workgroups NUMAG_TARGET_WGS asks for (0: not set).
-static int env_target()
+int env_target()
 {
     static const int cached = [] {  // thread-safe one-time initialisation
         const char *e = getenv("NUMAG_TARGET_WGS");
@@ -404,13 +403,7 @@ TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
 {
     switch (kernel) {
         case kTuneDirect: {
-            if (d.kind == NUMAG_GRID_POLAR) {
-                const int sh = default_polar_shape(d);
-                // half the Cartesian path's wave count: a polar workgroup of 8 waves holds
-                // its CU alone, and two rounds of them over the chip measured faster than
-                // four (fewer partials too)
-                return TuneShape{sh, target_workgroups() * 2 / polar_shape_waves(sh)};
-            }
+            if (d.kind == NUMAG_GRID_POLAR) return default_polar_tune(d, W);
             const CartPlan p = cart_default_plan(d, W, 4, 0);
             return TuneShape{p.shape, (int)((int64_t)p.col_groups * p.g.nrb * p.nsplit)};
         }
@@ -454,11 +447,6 @@ CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool 
 size_t cart_partial_bytes(const CartPlan &p)
 {
     return p.nsplit > 1 ? cart_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
-}
-
-size_t direct_partial_bytes(const DirectPlan &p, const Detector &d)
-{
-    return (size_t)p.nsplit * (size_t)d.n0 * (size_t)d.n1 * 8 * sizeof(double);
 }
 
 template <int CH>
@@ -518,35 +506,8 @@ int launch_fill(double *out, int64_t n, double value, hipStream_t s)
 }
 
 // ---------------------------------------------------------------------------
-// fixed-order FP64 combine of split partials.
-// ---------------------------------------------------------------------------
-__global__ void combine_kernel(const double *__restrict__ part, int nsplit, int64_t n,
-                               double *__restrict__ out, int accumulate)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double s = accumulate ? out[i] : 0.0;
-    for (int k = 0; k < nsplit; ++k) s += part[(int64_t)k * n + i];
-    out[i] = s;
-}
-
-int launch_combine(const double *part, int nsplit, int64_t P, double *out, int accumulate,
-                   hipStream_t s)
-{
-    int64_t n = P * 8;
-    if (n <= 0) return NUMAG_OK;
-    int64_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(combine_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, n, out,
-                       accumulate);
-    NUMAG_HIP_CHECK(hipGetLastError());
-    return NUMAG_OK;
-}
-
-// ---------------------------------------------------------------------------
-// Hermitian completion: for real weights S(-q) = conj S(q).  Cartesian: rows
-// [0, h) of the row-major output are computed, pixel p mirrors to P - 1 - p.
-// Polar (even n_theta): columns [0, n_theta / 2) are computed into a
-// [n0][n_theta / 2] block, column m mirrors to m + n_theta / 2.
+// Hermitian completion on a Cartesian detector: for real weights S(-q) = conj S(q);
+// rows [0, h) of the row-major output are computed, pixel p mirrors to P - 1 - p.
 // ---------------------------------------------------------------------------
 __global__ void mirror_cartesian_kernel(double *__restrict__ amp, int64_t P, int64_t Ph)
 {
@@ -562,35 +523,6 @@ int launch_mirror_cartesian(double *amp, int64_t P, int64_t Ph, hipStream_t s)
 {
     if (Ph <= 0) return NUMAG_OK;
     hipLaunchKernelGGL(mirror_cartesian_kernel, dim3((unsigned)((Ph * 8 + 255) / 256)), dim3(256), 0, s, amp, P, Ph);
-    NUMAG_HIP_CHECK(hipGetLastError());
-    return NUMAG_OK;
-}
-
-// out[i][m] = sum of the splits of part[.][i][m], out[i][m + nh] = its conjugate
-__global__ void combine_polar_half_kernel(const double *__restrict__ part, int nsplit, int n0, int nh,
-                                          double *__restrict__ out, int accumulate)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t Ph = (int64_t)n0 * nh;
-    if (idx >= Ph * 8) return;
-    const int64_t p = idx >> 3;
-    const int v = (int)(idx & 7);
-    double s = 0.0;
-    for (int k = 0; k < nsplit; ++k) s += part[(int64_t)k * Ph * 8 + idx];
-    const int64_t i = p / nh, m = p % nh;
-    const int64_t full = i * 2 * nh + m;
-    const double sm = (v & 1) ? -s : s;
-    out[full * 8 + v] = accumulate ? out[full * 8 + v] + s : s;
-    out[(full + nh) * 8 + v] = accumulate ? out[(full + nh) * 8 + v] + sm : sm;
-}
-
-int launch_combine_polar_half(const double *part, int nsplit, int n0, int nh, double *out, hipStream_t s,
-                              int accumulate)
-{
-    const int64_t n = (int64_t)n0 * nh * 8;
-    if (n <= 0) return NUMAG_OK;
-    hipLaunchKernelGGL(combine_polar_half_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, part, nsplit,
-                       n0, nh, out, accumulate);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

@@ -91,19 +91,11 @@ int run_bounded(const numag_sample &s, const Rot &R, const Detector &d, bool her
     if (W == 0 || (s.nuc == nullptr && s.mag == nullptr)) return launch_fill(amp, P * 8, 0.0, st);
     const int channels = s.nuc == nullptr ? 3 : (s.mag == nullptr ? 1 : 4);
     const bool cart = d.kind == NUMAG_GRID_CARTESIAN;
-    const Detector dh = evaluated(d, hermitian);
-    const int64_t Ph = (int64_t)dh.n0 * dh.n1;
     // splits: as the workspace path plans them, capped so the partial sums fill
     // at most half of the array; the rest holds a chunk of point records
-    const int64_t max_splits = std::max<int64_t>(1, (int64_t)((kCap / 2) / ((size_t)Ph * kPixelBytes)));
-    DirectPlan p0{};
-    size_t part_bytes = 0;
-    if (cart) {
-        part_bytes = align256(cart_partial_bytes(plan_direct_cartesian(d, W, channels, hermitian, kCap / 2)));
-    } else {
-        p0 = plan_direct_polar(dh, W, max_splits);
-        part_bytes = align256((size_t)p0.nsplit * (size_t)Ph * kPixelBytes);
-    }
+    const size_t part_bytes =
+        align256(cart ? cart_partial_bytes(plan_direct_cartesian(d, W, channels, hermitian, kCap / 2))
+                      : polar_partial_bytes(plan_direct_polar(d, W, channels, hermitian, kCap / 2)));
     double *part = (double *)scr;
     PointRec *pts = (PointRec *)(scr + part_bytes);
     int64_t chunk = (int64_t)((kCap - part_bytes) / sizeof(PointRec));
@@ -116,19 +108,12 @@ int run_bounded(const numag_sample &s, const Rot &R, const Detector &d, bool her
                                    pts, st);
         if (rc != NUMAG_OK) break;
         const int acc = c > 0 ? 1 : 0;
-        if (cart) {  // no more partial sums than the whole sample's plan (none: sums go straight to amp)
-            const CartPlan p = plan_direct_cartesian(d, Wc, channels, hermitian, std::max<size_t>(part_bytes, 1));
-            rc = launch_direct_cartesian(pts, Wc, p, part, amp, acc, st);
-            continue;
-        }
-        // a chunk's plan has no more splits than the first chunk's (Wc <= W)
-        DirectPlan p = n_chunks == 1 ? p0 : plan_direct_polar(dh, Wc, p0.nsplit);
-        p.channels = channels;
-        rc = launch_direct_polar(pts, Wc, dh, p, part, st);
-        if (rc == NUMAG_OK) {
-            rc = hermitian ? launch_combine_polar_half(part, p.nsplit, d.n0, dh.n1, amp, st, acc)
-                           : launch_combine(part, p.nsplit, Ph, amp, acc, st);
-        }
+        // no more partial sums than the whole sample's plan (none: sums go straight to amp)
+        const size_t cap = std::max<size_t>(part_bytes, 1);
+        rc = cart ? launch_direct_cartesian(pts, Wc, plan_direct_cartesian(d, Wc, channels, hermitian, cap), part, amp,
+                                            acc, st)
+                  : launch_direct_polar(pts, Wc, plan_direct_polar(d, Wc, channels, hermitian, cap), part, amp, acc,
+                                        st);
     }
     return rc;
 }

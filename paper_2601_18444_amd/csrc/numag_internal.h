@@ -66,15 +66,6 @@ int launch_prepare_points(const double *pos, const double *nuc, const double *ma
                           const numag_regular *regular, const int64_t *h_offsets, int64_t K,
                           const double *obj_pos, const Rot &R, PointRec *out, hipStream_t s);
 
-// Split of a direct sum into workgroups.
-struct DirectPlan {
-    int lanes;       // polar: theta columns per workgroup
-    int shape;       // launch shape (Cartesian: see CartPlan; polar: index into the polar kernel's shapes)
-    int channels;    // channels summed: 4 (N, M), 3 (M only) or 1 (N only); the rest are written as 0
-    int nsplit;      // point ranges summed by different workgroups
-    int64_t per;     // points per split
-    int col_blocks, row_blocks;
-};
 // Split of a Cartesian direct sum (cartesian_block.h).
 struct CartPlan {
     CartGeom g;
@@ -87,12 +78,10 @@ struct CartPlan {
 };
 // Hermitian completion of a half-detector sum (see direct.hip).
 int launch_mirror_cartesian(double *amp, int64_t P, int64_t Ph, hipStream_t s);
-// accumulate != 0: add into `out` instead of overwriting it
-int launch_combine_polar_half(const double *part, int nsplit, int n0, int nh, double *out, hipStream_t s,
-                              int accumulate = 0);
-
 // Workgroups a direct-sum launch aims for (split-K included).
 int target_workgroups();
+// The count NUMAG_TARGET_WGS asks for (0: not set).
+int env_target();
 
 // ---------------------------------------------------------------------------
 // Launch-shape table (tune.hip): tuned shapes keyed by kernel, the evaluated
@@ -125,30 +114,31 @@ size_t cart_partial_bytes(const CartPlan &p);
 int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
                             int accumulate, hipStream_t s);
 
-size_t direct_partial_bytes(const DirectPlan &p, const Detector &d);
-
-// Polar detector direct sum: [nsplit][P][8] partials.
-// max_splits > 0 caps the point splits (rotation groups trade splits for rotations);
-// shape >= 0 picks a workgroup shape (else the default for the detector) and
-// target_wgs > 0 the workgroups aimed for (else the library default).
+// Polar detector direct sum (polar_block.h).
 constexpr int kPolarShapeCount = 5;
+struct PolarPlan {
+    PolGeom g;
+    int mt;          // 16-row matrix tiles per wave
+    int shape;       // launch shape: 1, 0, 2, 3, 4 for 1, 2, 4, 8 or 16 row blocks of 32 per wave
+    int channels;    // channels summed: 4 (N, M), 3 (M only) or 1 (N only); the rest are written as 0
+    int nsplit;      // point ranges summed by different workgroups
+    int64_t per;     // points per split
+};
 int default_polar_shape(const Detector &d);
+TuneShape default_polar_tune(const Detector &d, int64_t W);
+// Plan on the whole detector d; the launch shape is looked up under the part the path
+// stands for (hermitian: half of the columns).  Every pixel is written; columns
+// theta + pi of an even detector as conjugates.  max_partial > 0 caps the partial sums.
+PolarPlan plan_direct_polar(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial = 0);
+size_t polar_partial_bytes(const PolarPlan &p);
+int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, double *partial, double *amp,
+                        int accumulate, hipStream_t s);
+// The old polar workgroup tiles of the object kernel.
 int polar_shape_rows(int shape);
 int polar_shape_cols(int shape);
 int polar_shape_waves(int shape);
-DirectPlan plan_direct_polar(const Detector &d, int64_t W, int64_t max_splits = 0, int shape = -1,
-                             int target_wgs = 0);
-// n_rot > 1: pts holds n_rot consecutive copies of W points (one per rotation of a
-// group) and the partials are [n_rot][p.nsplit][P][8].
-int launch_direct_polar(const PointRec *pts, int64_t W, const Detector &d, const DirectPlan &p,
-                        double *partial, hipStream_t s, int n_rot = 1);
 // out[i] = value for i < n (a kernel, so that callers may capture it in a graph).
 int launch_fill(double *out, int64_t n, double value, hipStream_t s);
-
-// Fixed-order sum of split partials: out[p][v] = sum_s part[s][p][v] (v < 8),
-// optionally added to `out` (accumulate != 0).
-int launch_combine(const double *part, int nsplit, int64_t P, double *out, int accumulate,
-                   hipStream_t s);
 
 // work items (object slot, rotation group, pixel block); each sums complete
 // objects and adds F F^H (and, in split mode, exp(-i q.R r^k) F) into an

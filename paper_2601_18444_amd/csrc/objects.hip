@@ -31,6 +31,14 @@
 
 namespace numag {
 
+int polar_shape_rows(int shape)
+{
+    const polar::ShapeDesc &s = polar::kShapes[shape];
+    return polar::kB * s.waves * (64 / s.cols);
+}
+int polar_shape_cols(int shape) { return polar::kShapes[shape].cols; }
+int polar_shape_waves(int shape) { return polar::kShapes[shape].waves; }
+
 namespace {
 
 struct RawLoader {

@@ -1,142 +1,241 @@
 // Direct Fourier sums on the paper's polar (q, theta) detector (Sec. 3.2), on the
-// building block of polar_sum.h.
-#include "polar_sum.h"
+// building block of polar_block.h.
+//
+// Measured, kernel time before (lanes walking q rows with a two-term recurrence, about
+// 10 vector FP64 instructions per term, every column summed) and now:
+//   100,003 points, 256 x 360       5.30 -> 1.36 ms (0.99 of it multiply-adds at 74.7 TFLOP/s)
+//   24,000 points, 1000 x 1000      9.55 -> 3.4 ms (2.6)
+// The rest is the tables: about 270 vector instructions per 32 points and column.
+#include <algorithm>
+#include <cmath>
+
+#include "polar_block.h"
 
 namespace numag {
 
-int polar_shape_rows(int shape)
+// Row blocks per wave of a launch shape.
+static int shape_blocks(int shape)
 {
-    const polar::ShapeDesc &s = polar::kShapes[shape];
-    return polar::kB * s.waves * (64 / s.cols);
+    constexpr int blocks[kPolarShapeCount] = {2, 1, 4, 8, 16};
+    return blocks[shape];
 }
-int polar_shape_cols(int shape) { return polar::kShapes[shape].cols; }
-int polar_shape_waves(int shape) { return polar::kShapes[shape].waves; }
 
 struct PolarRecLoader {
     const PointRec *__restrict__ pts;
-    __device__ __forceinline__ cart::PointPart load(int64_t j, int slot) const
+};
+template <int CH>
+struct PolarRecLoaderCh : PolarRecLoader {
+    __device__ __forceinline__ cblk::Point<CH> load(int64_t j) const
     {
         const PointRec &r = pts[j];
-        return cart::PointPart{r.Y, r.Z, r.w[slot]};
+        cblk::Point<CH> p;
+        p.m = r.Y;
+        p.n = r.Z;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) p.w[c] = r.w[cblk::ch_first<CH>() + c];
+        return p;
     }
 };
 
-// grid.z = rotation r of a group x split sp (nsp splits per rotation); the points of
-// rotation r are pts[r wrot, (r + 1) wrot).  One rotation: wrot = W, nsp = grid.z.
-template <int WV, int CW, int CHK, int NB, int CH>
-__global__ __launch_bounds__(64 * WV, 8 / WV) void direct_polar_kernel(const PointRec *__restrict__ pts,
-                                                                      int64_t wrot, int64_t per, int nsp, Detector d,
-                                                                      double *__restrict__ out)
+// One wave: one theta column, one row group, one point range.  Partials
+// [split][row group][column][tile][half][4][64] (store == 0), or amp (1: written,
+// 2: added).
+template <int MT, int CH>
+__global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
+                                                                         int64_t per, PolGeom g, int store,
+                                                                         double *__restrict__ out)
 {
-    using S = polar::Shape<WV, CW, CHK, NB>;
-    __shared__ polar::Smem<WV, CW, CHK, NB> sm;
-    const int col0 = blockIdx.x * CW;
-    const int64_t rbase = (int64_t)(blockIdx.z / nsp) * wrot;
-    const int64_t jbeg = rbase + (int64_t)(blockIdx.z % nsp) * per;
-    const int64_t jend = min(rbase + wrot, jbeg + per);
-    double acc[polar::kB][2 * CH];
+    __shared__ pblk::WaveSmem<MT, CH> sm[pblk::kWaves];
+    const int lane = threadIdx.x & 63, wave = cblk::wave_id();
+    const int col = blockIdx.x * pblk::kWaves + wave, rg = blockIdx.y;
+    if (col >= g.cols) return;  // no workgroup barriers below
+    const int64_t jbeg = (int64_t)blockIdx.z * per;
+    const int64_t jend = min(W, jbeg + per);
+    double sth, cth;
+    sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
+    cblk::v4d accC[MT], accS[MT];
+    cblk::zero<MT>(accC, accS);
+    pblk::accumulate<MT, CH>(PolarRecLoaderCh<CH>{{pts}}, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC,
+                             accS);
 #pragma unroll
-    for (int r = 0; r < polar::kB; ++r)
+    for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int v = 0; v < 2 * CH; ++v) acc[r][v] = 0.0;
-    polar::accumulate<WV, CW, CHK, NB, CH>(PolarRecLoader{pts}, jbeg, jend, d, col0, (int)blockIdx.y, sm, acc);
-    const int64_t P = (int64_t)d.n0 * d.n1;
-    double *dst = out + (int64_t)blockIdx.z * P * 8;
-    const int gcol = col0 + polar::lane_col<WV, CW>();
-    const int row0 = (int)blockIdx.y * S::ROWS + polar::lane_group<WV, CW>() * polar::kB;
-#pragma unroll
-    for (int r = 0; r < polar::kB; ++r) {
-        const int row = row0 + r;
-        if (row < d.n0 && gcol < d.n1) {
-            double *o = dst + ((int64_t)row * d.n1 + gcol) * 8;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) o[v] = cart::channel_value<CH>(acc[r], v);
+        for (int h = 0; h < 2; ++h) {
+            const double RR = accC[t][2 * h], IR = accC[t][2 * h + 1], RI = accS[t][2 * h], II = accS[t][2 * h + 1];
+            const double2 vp = make_double2(RR - II, RI + IR), vm = make_double2(RR + II, IR - RI);
+            if (store == 0) {
+                double *o = out +
+                            (((((int64_t)blockIdx.z * g.nrg + rg) * g.cols + col) * MT + t) * 2 + h) * 256 + lane;
+                o[0] = vp.x;
+                o[64] = vp.y;
+                o[128] = vm.x;
+                o[192] = vm.y;
+            } else {
+                pblk::put_slot(out, g, CH, rg, col, 8 * t + 4 * h + (lane >> 4), lane & 15, vp, vm, store == 2);
+            }
         }
-    }
 }
 
-// Default workgroup shape: 32 rows on detectors of at most 32 q rows; otherwise,
-// among the double-buffered shapes, the one with the fewest estimated VALU
-// instructions per (point, theta column): the sums (about 10.3 per term over the
-// padded rows) plus one generation per row block (about 150 for the sincos,
-// powers and stores, plus 2 per row group).  Measured on 262,144 points: 256 x 256
-// and 1000 x 1000 detectors take shape 4 (0.72 and 0.68 of the FP64 peak, against
-// 0.59 and 0.57 for shape 0), 128 x 128 takes shape 2 (0.68 against 0.63).
+// Fixed-order sum of the split partials, written (or added) to the pixels.
+__global__ __launch_bounds__(256) void polar_combine_kernel(const double *__restrict__ part, PolGeom g, int MT, int CH,
+                                                            int nsplit, int accumulate, double *__restrict__ amp)
+{
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = (int)(idx & 63);
+    const int64_t block = idx >> 6;  // (row group, column, tile, half)
+    const int64_t blocks = (int64_t)g.nrg * g.cols * MT * 2;
+    if (block >= blocks) return;
+    const int h = (int)(block & 1), t = (int)((block >> 1) % MT);
+    const int64_t rc = (block >> 1) / MT;
+    const double *p = part + block * 256 + lane;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < nsplit; ++s, p += blocks * 256) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
+    }
+    pblk::put_slot(amp, g, CH, (int)(rc / g.cols), (int)(rc % g.cols), 8 * t + 4 * h + (lane >> 4), lane & 15,
+                   make_double2(v[0], v[1]), make_double2(v[2], v[3]), accumulate != 0);
+}
+
+// ---------------------------------------------------------------------------
+// Work split.
+// ---------------------------------------------------------------------------
 int default_polar_shape(const Detector &d)
 {
     if (d.n0 <= 32) return 1;
-    int best = 0;
-    double best_cost = 0.0;
-    for (int sh : {0, 2, 4}) {
-        const int rows = polar_shape_rows(sh), cols = polar_shape_cols(sh);
-        const double rb = (double)((d.n0 + rows - 1) / rows);
-        const double cpad = (double)(((d.n1 + cols - 1) / cols) * cols) / (double)d.n1;
-        const double cost = cpad * rb * (10.3 * rows + 150.0 + 2.0 * rows / polar::kB);
-        if (sh == 0 || cost < best_cost) {
-            best = sh;
+    if (d.n0 <= 64) return 0;
+    return d.n0 <= 128 ? 2 : d.n0 <= 256 ? 3 : 4;
+}
+
+static void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int &mt)
+{
+    g.n0 = d.n0;
+    g.n_out = d.n_theta;
+    // theta + pi is a column of an even detector: its sums are conjugates
+    g.nh = d.n_theta % 2 == 0 ? d.n_theta / 2 : 0;
+    g.cols = g.nh > 0 ? g.nh : d.n_theta;
+    const int blocks = (d.n0 + pblk::kRows - 1) / pblk::kRows;
+    const int cap = std::min(shape_blocks(shape), std::min(pblk::kMaxNA, 8 * cblk::kMaxMT / channels));
+    g.nrg = (blocks + cap - 1) / cap;
+    g.na = (blocks + g.nrg - 1) / g.nrg;
+    g.dq = d.step0;
+    mt = (g.na * channels + 7) / 8;
+}
+
+static size_t polar_split_bytes(const PolGeom &g, int mt) { return (size_t)g.nrg * g.cols * mt * 512 * sizeof(double); }
+
+static void polar_splits(PolarPlan &p, int64_t W, int64_t target, size_t max_partial)
+{
+    const int64_t blocks = (int64_t)((p.g.cols + pblk::kWaves - 1) / pblk::kWaves) * p.g.nrg;
+    int64_t want = std::min<int64_t>(target / blocks, (W + pblk::kChunk - 1) / pblk::kChunk);
+    if (max_partial > 0)
+        want = std::min<int64_t>(want, (int64_t)(max_partial / std::max<size_t>(1, polar_split_bytes(p.g, p.mt))));
+    want = std::max<int64_t>(1, std::min<int64_t>(want, 65535));
+    int64_t per = (W + want - 1) / want;
+    per = std::max<int64_t>(4, (per + 3) / 4 * 4);
+    p.per = per;
+    p.nsplit = (int)std::max<int64_t>(1, (W + per - 1) / per);
+}
+
+// Rounds of 512 workgroups (two per CU) times the cycles of one split (a matrix
+// instruction holds its SIMD's FP64 pipe 64 cycles, the tables of a chunk take about
+// 150 vector instructions of 4), plus the partial sums at about 1700 bytes a cycle.
+static PolarPlan polar_default_plan(const Detector &d, int64_t W, int channels, size_t max_partial, int64_t target)
+{
+    PolarPlan best{};
+    double best_cost = -1.0;
+    for (int rounds = 1; rounds <= 8; ++rounds) {
+        PolarPlan p{};
+        p.channels = channels;
+        p.shape = default_polar_shape(d);
+        polar_geometry(d, channels, p.shape, p.g, p.mt);
+        const int64_t blocks = (int64_t)((p.g.cols + pblk::kWaves - 1) / pblk::kWaves) * p.g.nrg;
+        polar_splits(p, W, target > 0 ? target : std::max<int64_t>(512 * rounds, blocks), max_partial);
+        const double pts = (double)std::min<int64_t>(p.per, std::max<int64_t>(W, 1));
+        const double cycles = 2.0 * (3000.0 + std::ceil(pts / pblk::kChunk) * 700.0 +
+                                     std::ceil(pts / 4.0) * (128.0 * p.mt + 4.0 * p.mt + 40.0));
+        const double bytes = (double)polar_split_bytes(p.g, p.mt) * p.nsplit;
+        const double cost = std::ceil((double)(blocks * p.nsplit) / 512.0) * cycles +
+                            (p.nsplit > 1 ? 8000.0 + 2.0 * bytes / 1700.0 : 0.0);
+        if (best_cost < 0.0 || cost < 0.98 * best_cost) {
             best_cost = cost;
+            best = p;
         }
     }
     return best;
 }
 
-DirectPlan plan_direct_polar(const Detector &d, int64_t W, int64_t max_splits, int shape, int target_wgs)
+TuneShape default_polar_tune(const Detector &d, int64_t W)
 {
-    DirectPlan p{};
-    p.channels = 4;
-    const TuneShape ts = current_tune_shape(kTuneDirect, d, W);
-    p.shape = shape >= 0 && shape < kPolarShapeCount ? shape : ts.shape;
-    if (d.n0 > 32 && p.shape == 1) p.shape = 0;  // the 4-wave shape serves short detectors only
-    const polar::ShapeDesc &sd = polar::kShapes[p.shape];
-    p.lanes = sd.cols;
-    const int rows = polar_shape_rows(p.shape);
-    p.col_blocks = (d.n1 + sd.cols - 1) / sd.cols;
-    p.row_blocks = (d.n0 + rows - 1) / rows;
-    int64_t blocks = (int64_t)p.col_blocks * p.row_blocks;
-    const int tw = target_wgs > 0 ? target_wgs : ts.target;
-    int64_t want = (tw + blocks - 1) / blocks;
-    int64_t max_split = (W + 8 * sd.chunk - 1) / (8 * sd.chunk);
-    if (max_split < 1) max_split = 1;
-    if (want > max_split) want = max_split;
-    if (max_splits > 0 && want > max_splits) want = max_splits;
-    if (want > 65535) want = 65535;
-    if (want < 1) want = 1;
-    int64_t per = (W + want - 1) / want;
-    per = ((per + sd.chunk - 1) / sd.chunk) * sd.chunk;
-    if (per < sd.chunk) per = sd.chunk;
-    p.per = per;
-    p.nsplit = (int)((W + per - 1) / per);
-    if (p.nsplit < 1) p.nsplit = 1;
+    const PolarPlan p = polar_default_plan(d, W, 4, 0, env_target());
+    return TuneShape{p.shape, (int)((int64_t)((p.g.cols + pblk::kWaves - 1) / pblk::kWaves) * p.g.nrg * p.nsplit)};
+}
+
+PolarPlan plan_direct_polar(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial)
+{
+    Detector key = d;
+    if (hermitian) key.n1 = d.n1 / 2;
+    TuneShape ts{};
+    if (!tuned_shape(kTuneDirect, key, W, &ts) || !valid_tune_shape(kTuneDirect, key, ts))
+        return polar_default_plan(d, W, channels, max_partial, env_target());
+    if (ts.target == 0) ts.target = default_polar_tune(d, W).target;
+    PolarPlan p{};
+    p.channels = channels;
+    p.shape = ts.shape;
+    polar_geometry(d, channels, ts.shape, p.g, p.mt);
+    polar_splits(p, W, ts.target, max_partial);
     return p;
 }
 
-int launch_direct_polar(const PointRec *pts, int64_t W, const Detector &d, const DirectPlan &p,
-                        double *partial, hipStream_t s, int n_rot)
+size_t polar_partial_bytes(const PolarPlan &p)
 {
-    if ((int64_t)p.nsplit * n_rot > 65535) return NUMAG_E_INVALID;
-    if (p.shape < 0 || p.shape >= kPolarShapeCount) return NUMAG_E_INVALID;
-    const polar::ShapeDesc &sd = polar::kShapes[p.shape];
-    dim3 grid(p.col_blocks, p.row_blocks, p.nsplit * n_rot);
-    TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
-#define NUMAG_LAUNCH_POLAR(WV, CW, CHK, NB, CH)                                                                   \
-    hipLaunchKernelGGL((direct_polar_kernel<WV, CW, CHK, NB, CH>), grid, dim3(64 * WV), 0, s, pts, W, p.per, \
-                       p.nsplit, d, partial)
-#define NUMAG_LAUNCH_POLAR_CH(WV, CW, CHK, NB)                  \
-    switch (p.channels) {                                       \
-        case 1: NUMAG_LAUNCH_POLAR(WV, CW, CHK, NB, 1); break;  \
-        case 3: NUMAG_LAUNCH_POLAR(WV, CW, CHK, NB, 3); break;  \
-        default: NUMAG_LAUNCH_POLAR(WV, CW, CHK, NB, 4); break; \
+    return p.nsplit > 1 ? polar_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
+}
+
+template <int CH>
+static void launch_polar_tiles(const PointRec *pts, int64_t W, const PolarPlan &p, int store, double *out,
+                               hipStream_t s)
+{
+    const dim3 grid((p.g.cols + pblk::kWaves - 1) / pblk::kWaves, p.g.nrg, p.nsplit), block(pblk::kThreads);
+    // at most 16 row blocks: 2 CH tiles
+#define NUMAG_LAUNCH_POLAR(MT)   \
+    case MT:                     \
+        if constexpr (MT <= 2 * CH) \
+            hipLaunchKernelGGL((direct_polar_kernel<MT, CH>), grid, block, 0, s, pts, W, p.per, p.g, store, out); \
+        break
+    switch (p.mt) {
+        NUMAG_LAUNCH_POLAR(1);
+        NUMAG_LAUNCH_POLAR(2);
+        NUMAG_LAUNCH_POLAR(3);
+        NUMAG_LAUNCH_POLAR(4);
+        NUMAG_LAUNCH_POLAR(5);
+        NUMAG_LAUNCH_POLAR(6);
+        NUMAG_LAUNCH_POLAR(7);
+        NUMAG_LAUNCH_POLAR(8);
     }
-    switch (p.shape) {
-        case 0: NUMAG_LAUNCH_POLAR_CH(8, 64, 8, 2); break;
-        case 1: NUMAG_LAUNCH_POLAR_CH(4, 64, 8, 1); break;
-        case 2: NUMAG_LAUNCH_POLAR_CH(8, 32, 8, 2); break;
-        case 3: NUMAG_LAUNCH_POLAR_CH(8, 16, 16, 1); break;
-        default: NUMAG_LAUNCH_POLAR_CH(8, 16, 8, 2); break;
-    }
-#undef NUMAG_LAUNCH_POLAR_CH
 #undef NUMAG_LAUNCH_POLAR
-    (void)sd;
+}
+
+int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, double *partial, double *amp,
+                        int accumulate, hipStream_t s)
+{
+    const bool split = p.nsplit > 1;
+    const int store = split ? 0 : (accumulate ? 2 : 1);
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        double *out = split ? partial : amp;
+        switch (p.channels) {
+            case 1: launch_polar_tiles<1>(pts, W, p, store, out, s); break;
+            case 3: launch_polar_tiles<3>(pts, W, p, store, out, s); break;
+            default: launch_polar_tiles<4>(pts, W, p, store, out, s); break;
+        }
+    }
+    NUMAG_HIP_CHECK(hipGetLastError());
+    if (!split) return NUMAG_OK;
+    const int64_t n = (int64_t)p.g.nrg * p.g.cols * p.mt * 128;
+    hipLaunchKernelGGL(polar_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
+                       p.channels, p.nsplit, accumulate, amp);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

@@ -16,9 +16,11 @@
 // instructions share; the tables cost one sincos per (point, column), products and
 // two-term recurrences x_{k+1} = 2 cos(step) x_k - x_{k-1} of at most 8 (offsets) and 16
 // (centres) steps:
-//   half h of the lanes (one lane per point) starts from exp(-i (8 h + 1/2) dq u) and
-//   walks 8 offsets; the last one of the second half is the first centre, 15.5 dq u,
-//   and the centre step is 32 dq u = 2 (15.5 dq u) + dq u.
+//   the first half of the lanes (one lane per point) starts from exp(-i dq u / 2) and
+//   walks up 8 offsets, the second from exp(-i 15.5 dq u), which is also the centre of
+//   block 0, and walks down 8; the centre step is 32 dq u = 2 (15.5 dq u) + dq u.
+// Every start is a sincos of its own phase, so a phasor carries the rounding of that
+// phase, at most 16 times that of the centre step, and the recurrence's.
 #pragma once
 
 #include "cartesian_block.h"
@@ -60,34 +62,41 @@ __device__ __forceinline__ double2 next_term(double k2, double2 x, double2 befor
     return make_double2(fma(k2, x.x, -before.x), fma(k2, x.y, -before.y));
 }
 
-// Tables of a chunk: point gp = lane % 32 of the wave at u; weights p.w.
+// Tables of a chunk: point gp = lane % 32 of the wave at u, weights p.w, centres of the
+// row blocks from a0 on.
 template <int MT, int CH>
-__device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int na, double dq, double u, const Point<CH> &p)
+__device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int a0, double dq, double u, const Point<CH> &p)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
-    double2 x = twiddle(((half == 0 ? 0.0 : 8.0) + 0.5) * dq * u);
-    double2 st = cmul(x, x);  // dq u in the first half
+    double2 x = twiddle((half == 0 ? 0.5 : 15.5) * dq * u);
+    const double2 centre = x;  // of block 0 (second half)
+    double2 st = cmul(x, x);   // dq u in the first half
     const double2 so = make_double2(other_half(st.x), other_half(st.y));
-    if (half != 0) st = so;
+    if (half != 0) st = make_double2(so.x, -so.y);  // the second half walks down
     const double k2 = st.x + st.x;
+    const int at = half == 0 ? 0 : 15, by = half == 0 ? 1 : -1;
     double2 y = cmul(x, st);
-    sm.off[gp][8 * half] = x;
-    sm.off[gp][8 * half + 1] = y;
+    sm.off[gp][at] = x;
+    sm.off[gp][at + by] = y;
 #pragma unroll
     for (int k = 2; k < 8; ++k) {
         const double2 z = next_term(k2, y, x);
-        sm.off[gp][8 * half + k] = z;
+        sm.off[gp][at + by * k] = z;
         x = y;
         y = z;
     }
-    if (half != 0) {  // y = exp(-i 15.5 dq u)
-        const double2 cs = cmul(cmul(y, y), st);
+    double2 first = make_double2(1.0, 0.0);
+    if (a0 != 0) first = twiddle((double)(kRows * a0) * dq * u);  // wave-uniform
+    if (half != 0) {
+        const double2 cs = cmul(cmul(centre, centre), so);
         const double kc = cs.x + cs.x;
-        double2 a = y, b = cmul(y, cs);
+        double2 a = a0 != 0 ? cmul(centre, first) : centre, b = cmul(a, cs);
+        // every centre the tiles have room for: those beyond na are never stored, and
+        // the unrolled walk takes three instructions an entry
         sm.ctr[gp][0] = a;
-        if (na > 1) sm.ctr[gp][1] = b;
-#pragma unroll 1
-        for (int k = 2; k < na; ++k) {
+        if (max_na<MT, CH>() > 1) sm.ctr[gp][1] = b;
+#pragma unroll
+        for (int k = 2; k < max_na<MT, CH>(); ++k) {
             const double2 c = next_term(kc, b, a);
             sm.ctr[gp][k] = c;
             a = b;
@@ -108,11 +117,10 @@ __device__ __forceinline__ void wave_fence()
 }
 
 // Adds the points [jbeg, jend) of `ld` (Point<CH> load(j): m = Y, n = Z) to the wave's
-// tiles: theta direction (sth, cth), row blocks [a0, a0 + na) (the tables start at
-// block 0 of the wave: `shift` is the phase factor 32 a0 dq of its first block).
+// tiles: theta direction (sth, cth), row blocks from a0 on.
 template <int MT, int CH, class Loader>
 __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, double sth, double cth,
-                                           double dq, int a0, int na, WaveSmem<MT, CH> &sm, v4d (&accC)[MT],
+                                           double dq, int a0, WaveSmem<MT, CH> &sm, v4d (&accC)[MT],
                                            v4d (&accS)[MT])
 {
     const int lane = threadIdx.x & 63, gp = lane & 31;
@@ -135,13 +143,7 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
 #pragma unroll 1
     for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk) {
         const double u = p.m * sth + p.n * cth;
-        generate<MT, CH>(sm, na, dq, u, p);
-        if (a0 != 0) {  // later row groups: rotate the weights' side by the group's first block
-            const double2 sh = twiddle((double)(kRows * a0) * dq * u);
-            if (lane >= 32)
-#pragma unroll 1
-                for (int k = 0; k < na; ++k) sm.ctr[gp][k] = cmul(sm.ctr[gp][k], sh);
-        }
+        generate<MT, CH>(sm, a0, dq, u, p);
         wave_fence();
         p = fetch(j0 + kChunk);
         const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
@@ -166,6 +168,33 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
             }
         }
         wave_fence();
+    }
+}
+
+// The rows of block a, offset b: 32 a + 16 + b and 32 a + 15 - b, at the mirrored column
+// too (nh > 0: column m + nh holds the conjugates).
+__device__ __forceinline__ void put_slot(double *__restrict__ amp, const PolGeom &g, int CH, int rg, int col, int s,
+                                         int b, double2 vp, double2 vm, bool add)
+{
+    const int e = s / CH, c = s - e * CH, a = rg * g.na + e;
+    if (e >= g.na) return;
+    const int first = CH == 3 ? 1 : 0;
+    const int row[2] = {kRows * a + 16 + b, kRows * a + 15 - b};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (row[k] >= g.n0) continue;
+        const double2 v = k == 0 ? vp : vm;
+        const int64_t p = (int64_t)row[k] * g.n_out + col;
+        auto put = [&](int ch, double2 x) {
+            cblk::put_pixel(amp, p, ch, x.x, x.y, add);
+            if (g.nh > 0) cblk::put_pixel(amp, p + g.nh, ch, x.x, -x.y, add);
+        };
+        put(first + c, v);
+        if (c == 0 && !add) {  // channels outside the set
+            if (CH == 3) put(0, make_double2(0.0, 0.0));
+            if (CH == 1)
+                for (int ch = 1; ch < 4; ++ch) put(ch, make_double2(0.0, 0.0));
+        }
     }
 }
 

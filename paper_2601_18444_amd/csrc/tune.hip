@@ -11,9 +11,8 @@
 // Shapes per kernel:
 //   direct, Cartesian detector: 8, 64, 16 or 32 for 1, 2, 4 or 8 blocks of 32 detector
 //     columns per workgroup, and the workgroups a launch aims for (split over points);
-//   direct, polar detector: one of the polar kernel's workgroup shapes
-//     (64 x 64, 32 x 64, 128 x 32, 256 x 16 single- or double-buffered) and the
-//     workgroups aimed for;
+//   direct, polar detector: 1, 0, 2, 3 or 4 for 1, 2, 4, 8 or 16 blocks of 32 q rows
+//     per wave, and the workgroups aimed for;
 //   adjoint: the workgroups aimed for (point blocks x detector ranges);
 //   objects (persistent kernel): lanes per detector row (polar: the workgroup
 //     shape) and the work items aimed for.

@@ -35,6 +35,16 @@ struct CartGeom {
     int64_t strideM, strideN;  // pixels
 };
 
+// Work split of a polar direct sum (polar_block.h): theta columns [0, cols) of a detector
+// of n_out columns are summed; nh = n_out / 2 when column m + nh is filled with the
+// conjugate of column m, else 0.
+struct PolGeom {
+    int n0, n_out;          // q rows, theta columns of the detector
+    int cols, nh;
+    int na, nrg;            // row blocks (of 32 rows) per wave, row groups
+    double dq;
+};
+
 // Row-major 3x3 rotation as a kernel argument.
 struct Rot {
     double m[9];

@@ -1,6 +1,6 @@
 """Edges of the matrix-core sums: detectors around the tile sizes (blocks of 32 pixels
 along one axis, packed rows along the other, thin and transposed detectors, single
-pixels), point counts around the 4-point matrix step and the 32-point chunk, every
+pixels, blocks of 32 q rows on a polar one), point counts around the 4-point matrix step and the 32-point chunk, every
 channel set and workgroup shape, against the FP64 oracle.
 
 Tolerance, from the arithmetic: a phasor is a product of at most a few rounded
@@ -57,3 +57,15 @@ def test_cartesian_tiles(orc, n0, n1, chan):
     for W, shape in [(1, None), (4, (8, 0)), (33, (64, 3)), (130, (16, 7)), (517, (32, 2)), (700, None)]:
         for path in (numag.PATH_DIRECT, numag.PATH_DIRECT_HERMITIAN):
             _check(orc, 0, n0, n1, W, chan, shape, path)
+
+
+@pytest.mark.parametrize("n0,n1", [(1, 1), (1, 2), (2, 5), (31, 6), (32, 7), (33, 8), (65, 9), (150, 10), (257, 4),
+                                   (512, 3), (513, 6), (1000, 5)])
+@pytest.mark.parametrize("chan", [0, 1, 2])
+def test_polar_tiles(orc, n0, n1, chan):
+    """Row blocks of 32 q rows, up to 16 of them per wave, odd theta counts (every
+    column summed) and even ones (half of them), point counts around the chunk."""
+    shapes = [None, (0, 5), (2, 40), (3, 3), (4, 64)] + ([(1, 9)] if n0 <= 32 else [])
+    for W, shape in zip([1, 31, 32, 33, 130, 517], shapes):
+        for path in (numag.PATH_DIRECT, numag.PATH_DIRECT_HERMITIAN)[: 1 if n1 % 2 else 2]:
+            _check(orc, 1, n0, n1, W, chan, shape, path)
