@@ -42,7 +42,7 @@ PROFILES = os.path.join(ROOT, "profiles")
 KERNELS = {
     "direct_cartesian_kernel": (0, ["cartesian_block.h", "direct.hip", "phasor.h", "types.h"],
                                 "direct_cartesian_kernel_vortex64_256x256_pmc.md"),
-    "adjoint_cartesian_kernel": (1, ["adjoint.hip", "phasor.h", "types.h"],
+    "adjoint_cartesian_kernel": (1, ["adjoint.hip", "cartesian_block.h", "phasor.h", "types.h"],
                                  "adjoint_cartesian_kernel_vortex64_256x256_pmc.md"),
 }
 # kernels measured outside the step (their counter summaries, same format)

@@ -37,7 +37,7 @@
  * below); without an entry, the environment variable NUMAG_TARGET_WGS (read
  * once per process) sets the number of workgroups the direct sums aim for per
  * launch (default: chosen by an estimate of the time from the point and pixel
- * counts; the adjoint 4096).  Shapes change how the work is split, never a
+ * counts; the adjoint takes twice the given number).  Shapes change how the work is split, never a
  * result's definition; sums split differently agree to rounding.
  */
 #ifndef NUMAG_H

@@ -366,7 +366,7 @@ std::vector<TuneShape> tune_candidates(int kernel, const Detector &d, int64_t W)
                 for (int t : {1024, 2048, 4096}) c.push_back(TuneShape{l, t});
         }
     } else {
-        for (int t : {2048, 4096, 8192}) c.push_back(TuneShape{0, t});
+        for (int t : {256, 512, 1024, 2048}) c.push_back(TuneShape{0, t});
     }
     // the default first (it is kept unless another shape is clearly faster)
     std::vector<TuneShape> out{def};

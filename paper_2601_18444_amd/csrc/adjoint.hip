@@ -6,73 +6,157 @@
 //   dL/dm'_ja = Re sum_p a_a(p) exp(-i q_p . X_j),   a_a = 4 w r (scale/V) bH^2 conj((Pp S_M)_a)
 // with r = I_p - T_p and m' = R m (so dL/dm = R^T dL/dm').
 //
-// The adjoint sum swaps the roles of points and pixels: a lane owns a few
-// points and walks the detector, row by row.  The row-start phasor is the
-// previous row's times exp(-i dq_y Y) (one complex product), restarted from a
-// fresh FP64 sincos every kAdjRowRestart rows (at most 2^7 ulp of drift); along
-// the row the phasors follow the two-term recurrence
-//     p_{c+1} = 2 cos(dq_z Z) p_c - p_{c-1}
-// (two FMAs per column; an error made at column k reaches column c multiplied
-// by at most c - k + 1, so a 256-column row keeps about 38 of the 53 bits in
-// the worst case).  The residual weights of one row are staged in LDS and read
-// as wave-wide broadcasts.  Ten FP64 VALU operations per (point, pixel) term.
-#include "numag_internal.h"
-#include "phasor.h"
+// The adjoint sum is the transposed contraction of the forward sums
+// (cartesian_block.h, polar_block.h).  With the residual weights of the four pixels
+// (+-q_M, +-q_N) of a cell folded into four real coefficients (Re[a(p') exp(+i q.X)] =
+// Re[conj a(p') exp(-i q.X)] takes the pixels at -q onto those at q, for any target and
+// loss weights),
+//   G_c(j) = sum_a [ yr_a(j) T_{a,re,c}(j) + yi_a(j) T_{a,im,c}(j) ],
+//   T_{a,re,c}(j) = sum_b RR_{abc} zr_b(j) + RI_{abc} zi_b(j),  T_{a,im,c} likewise with IR, II,
+// so the work is real matrix products (coefficients) x (phasors of the points), one
+// multiply-add per point, pixel and channel, on v_mfma_f64_16x16x4f64, against ten
+// vector FP64 operations per point and pixel of a walk along the detector rows.
+//
+// The residual kernel writes the coefficients in the order the matrix instruction takes
+// its first operand, so a wave's operand load is one 16-byte read per lane and tile.
+//
+// Measured, kernel time before (a lane walking the detector rows of four points with a
+// two-term recurrence) and now: 262,144 points, 256 x 256: 6.14 -> 2.05 ms (67 of the
+// card's 74.7 TFLOP/s; 2.37 with the coefficients staged through registers, which
+// spilled); error of the gradient against 64 bits 8.2e-14 -> 6.6e-15, the walk of 256
+// columns being gone.  20,000 points, 150 x 181 polar: 228 -> 229 us: every column of an
+// odd detector is summed, so the multiply-adds fall only from 10 to 8 per term and the
+// column tables (about 200 vector instructions per 32 points and column) take the rest;
+// an even detector needs half of both.
+#include <algorithm>
+#include <cmath>
+
+#include "cartesian_block.h"
+#include "polar_block.h"
 
 namespace numag {
 
 constexpr int kResThreads = 256;
 
-// Residual weights a[p][4 complex] and per-block loss partials.
-__global__ __launch_bounds__(kResThreads) void residual_kernel(Detector d, numag_consts k,
+// Residual weights of one pixel (four complex numbers, a[8]) and its loss term.
+__device__ __forceinline__ double residual_pixel(const Detector &d, const numag_consts &k, int64_t p,
+                                                 const double *__restrict__ amp, const double *__restrict__ target,
+                                                 const double *__restrict__ weight, double (&a)[8])
+{
+    double s, c;
+    pixel_qhat(d, p, s, c);
+    const double *A = amp + p * 8;
+    // V = Pp S_M with Pp = I - qhat qhat^T, qhat = (0, s, c)
+    const double dot_r = s * A[4] + c * A[6], dot_i = s * A[5] + c * A[7];
+    const double Vr[3] = {A[2], A[4] - s * dot_r, A[6] - c * dot_r};
+    const double Vi[3] = {A[3], A[5] - s * dot_i, A[7] - c * dot_i};
+    const double cf = k.scale / k.V;
+    const double b2 = k.bH * k.bH;
+    const double absV2 =
+        Vr[0] * Vr[0] + Vi[0] * Vi[0] + Vr[1] * Vr[1] + Vi[1] * Vi[1] + Vr[2] * Vr[2] + Vi[2] * Vi[2];
+    const double I = cf * (A[0] * A[0] + A[1] * A[1] + b2 * absV2);
+    // dL/dI_p: 2 w (I - T) for the built-in loss, or the caller's upstream
+    // gradient (held in `weight`) when no target is given.
+    double dLdI, lp = 0.0;
+    if (target != nullptr) {
+        const double r = I - target[p];
+        const double w = weight[p];
+        lp = w * r * r;
+        dLdI = 2.0 * w * r;
+    } else {
+        dLdI = weight[p];
+    }
+    const double g = 2.0 * dLdI * cf;
+    a[0] = g * A[0];
+    a[1] = -g * A[1];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        a[2 + 2 * x] = g * b2 * Vr[x];
+        a[3 + 2 * x] = -g * b2 * Vi[x];
+    }
+    return lp;
+}
+
+// Coefficients [row block or (column, row group)][column block][step][tile][lane] of
+// (re, im) column parts: step s holds b = 16 v + 4 s + lane / 16, tile t and lane % 16 = 8 h
+// + 4 part + c the row a = 2 t + h, part (re, im), channel c.
+__device__ __forceinline__ int64_t coef_index(int64_t block, int MT, int e, int b16, int part, int c)
+{
+    return ((block * 4 + (b16 >> 2)) * MT + (e >> 1)) * 64 + 16 * (b16 & 3) + 8 * (e & 1) + 4 * part + c;
+}
+
+// One thread per cell of the padded grid: the residual weights of its pixels, folded,
+// as coefficients (zeros outside the detector), and per-block loss partials.
+// Cartesian cells (POLAR = 0): cell (a, b) of CartGeom; polar ones: offset b of row
+// block a of column col, with column col + nh as the mirror.
+template <int POLAR>
+__global__ __launch_bounds__(kResThreads) void residual_kernel(Detector d, numag_consts k, CartGeom cg, PolGeom pg,
+                                                               int MT, int64_t n_cells,
                                                                const double *__restrict__ amp,
                                                                const double *__restrict__ target,
                                                                const double *__restrict__ weight,
-                                                               double *__restrict__ a,
+                                                               double2 *__restrict__ coef,
                                                                double *__restrict__ loss_part)
 {
-    const int64_t P = (int64_t)d.n0 * d.n1;
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t idx = (int64_t)blockIdx.x * kResThreads + threadIdx.x;
     double lp = 0.0;
-    if (p < P) {
-        double s, c;
-        pixel_qhat(d, p, s, c);
-        const double qh[3] = {0.0, s, c};
-        const double *A = amp + p * 8;
-        double Vr[3], Vi[3];
-        for (int x = 0; x < 3; ++x) {
-            double dot_r = qh[0] * A[2] + qh[1] * A[4] + qh[2] * A[6];
-            double dot_i = qh[0] * A[3] + qh[1] * A[5] + qh[2] * A[7];
-            Vr[x] = A[2 + 2 * x] - qh[x] * dot_r;
-            Vi[x] = A[3 + 2 * x] - qh[x] * dot_i;
-        }
-        const double cf = k.scale / k.V;
-        const double b2 = k.bH * k.bH;
-        const double absV2 = Vr[0] * Vr[0] + Vi[0] * Vi[0] + Vr[1] * Vr[1] + Vi[1] * Vi[1] +
-                             Vr[2] * Vr[2] + Vi[2] * Vi[2];
-        const double I = cf * (A[0] * A[0] + A[1] * A[1] + b2 * absV2);
-        // dL/dI_p: 2 w (I - T) for the built-in loss, or the caller's upstream
-        // gradient (held in `weight`) when no target is given.
-        double dLdI;
-        if (target != nullptr) {
-            const double r = I - target[p];
-            const double w = weight[p];
-            lp = w * r * r;
-            dLdI = 2.0 * w * r;
+    if (idx < n_cells) {
+        // pixels (+,+), (+,-), (-,+), (-,-) of the cell; -1: none
+        int64_t px[4] = {-1, -1, -1, -1};
+        int64_t block;  // index of the 16-column coefficient block
+        int e, b16;
+        if (POLAR) {
+            const int ne = 2 * MT;
+            b16 = (int)(idx & 15);
+            const int64_t r = idx >> 4;
+            e = (int)(r % ne);
+            block = r / ne;  // col * nrg + rg
+            const int rg = (int)(block % pg.nrg), col = (int)(block / pg.nrg);
+            const int a = rg * pg.na + e;
+            if (e < pg.na) {
+                const int rp = pblk::kRows * a + 16 + b16, rm = pblk::kRows * a + 15 - b16;
+                if (rp < pg.n0) px[0] = (int64_t)rp * pg.n_out + col;
+                if (rm < pg.n0) px[1] = (int64_t)rm * pg.n_out + col;
+                if (pg.nh > 0) {
+                    if (px[1] >= 0) px[2] = px[1] + pg.nh;
+                    if (px[0] >= 0) px[3] = px[0] + pg.nh;
+                }
+            }
         } else {
-            dLdI = weight[p];
+            const int nb = 16 * cg.nzb, ne = 2 * MT;
+            const int b = (int)(idx % nb);
+            const int64_t r = idx / nb;
+            e = (int)(r % ne);
+            const int rb = (int)(r / ne);
+            b16 = b & 15;
+            block = (int64_t)rb * cg.nzb + (b >> 4);
+            const cblk::CellPixels x = cblk::cell_pixels(cg, 4, rb, b >> 4, 4 * e, b16);
+            if (x.ok) {
+                px[0] = x.pp;
+                if (x.twoN) px[1] = x.pm;
+                if (x.twoM) {
+                    px[3] = x.mm;
+                    if (x.twoN) px[2] = x.mp;
+                }
+            }
         }
-        const double g = 2.0 * dLdI * cf;
-        // polar: column-major [theta][q] so the adjoint stages a column contiguously
-        const int64_t po = d.kind == NUMAG_GRID_CARTESIAN ? p : (p % d.n1) * d.n0 + p / d.n1;
-        double *o = a + po * 8;
-        o[0] = g * A[0];
-        o[1] = -g * A[1];
-        for (int x = 0; x < 3; ++x) {
-            o[2 + 2 * x] = g * b2 * Vr[x];
-            o[3 + 2 * x] = -g * b2 * Vi[x];
+        double f[8] = {0.0}, g[8] = {0.0};  // folded weights of (+,+) and (+,-)
+        for (int q = 0; q < 4; ++q) {
+            if (px[q] < 0) continue;
+            double a[8];
+            lp += residual_pixel(d, k, px[q], amp, target, weight, a);
+            double(&t)[8] = (q == 0 || q == 3) ? f : g;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) t[v] += (q >= 2 && (v & 1)) ? -a[v] : a[v];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double fr = f[2 * c], fi = f[2 * c + 1], gr = g[2 * c], gi = g[2 * c + 1];
+            coef[coef_index(block, MT, e, b16, 0, c)] = make_double2(fr + gr, gi - fi);     // RR, RI
+            coef[coef_index(block, MT, e, b16, 1, c)] = make_double2(-fi - gi, gr - fr);    // IR, II
         }
     }
+    if (loss_part == nullptr) return;
     __shared__ double s_l[kResThreads];
     s_l[threadIdx.x] = lp;
     __syncthreads();
@@ -97,262 +181,236 @@ __global__ void loss_sum_kernel(const double *__restrict__ part, int n, double *
     if (threadIdx.x == 0) loss[0] = s_l[0];
 }
 
-constexpr int kAdjThreads = 256;
-constexpr int kAdjNPL = 4;      // points per lane
-constexpr int kAdjMaxCols = 256;  // columns staged per LDS pass
-constexpr int kAdjRowRestart = 64;  // rows between fresh row-start phasors
+// ---------------------------------------------------------------------------
+// Cartesian adjoint.  A wave owns 32 points (two matrix column tiles); lane l holds
+// point l % 16 of a tile and, of a step's four |q_N| values, number l / 16.  The 8 waves of
+// a workgroup share the coefficients of one 16-column block at a time through LDS
+// (double-buffered).  The column phasors live in registers: 16 offsets, four per lane,
+// times the block's centre, which advances by a product per block; the row phasors are
+// needed once per row block, when the tiles are folded into the point's four sums:
+// accumulator register r of lane l is row 4 r + l / 16, so lane l sums channel l / 16.
+// A split is a range of row blocks and one of column blocks.
+// ---------------------------------------------------------------------------
+constexpr int kAdjWaves = 8;
+constexpr int kAdjThreads = 64 * kAdjWaves;
+constexpr int kAdjNP = 2;
+constexpr int kAdjPoints = 16 * kAdjNP * kAdjWaves;  // points per workgroup
 
-// grid.x: point blocks of kAdjThreads * kAdjNPL; grid.y: row ranges.
-// Residual weights of one column as the adjoint reads them (from LDS).
-struct ColW {
-    double a0r, a0i, a1r, a1i, a2r, a2i, a3r, a3i;
+struct AdjSplit {
+    int nr, nv;        // ranges of row blocks and of column blocks
+    int per_r, per_v;  // blocks per range
 };
 
-__device__ __forceinline__ ColW load_col(const double *p)
-{
-    return ColW{p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]};
-}
-
-// One column for the lane's points: Re(a p) (two FMAs per channel), then the
-// recurrence step to the next column.
-__device__ __forceinline__ void adjoint_column(const ColW &w, double2 (&pc)[kAdjNPL], double2 (&pm)[kAdjNPL],
-                                               const double (&kz)[kAdjNPL], double (&acc)[kAdjNPL][4])
-{
-#pragma unroll
-    for (int u = 0; u < kAdjNPL; ++u) {
-        const double2 p = pc[u];
-        acc[u][0] = fma(-w.a0i, p.y, fma(w.a0r, p.x, acc[u][0]));
-        acc[u][1] = fma(-w.a1i, p.y, fma(w.a1r, p.x, acc[u][1]));
-        acc[u][2] = fma(-w.a2i, p.y, fma(w.a2r, p.x, acc[u][2]));
-        acc[u][3] = fma(-w.a3i, p.y, fma(w.a3r, p.x, acc[u][3]));
-        pc[u] = make_double2(fma(kz[u], p.x, -pm[u].x), fma(kz[u], p.y, -pm[u].y));
-        pm[u] = p;
-    }
-}
-
-// The detector rows of the split are walked as segments of at most kAdjMaxCols
-// columns.  While a segment is summed from one LDS buffer, each thread holds the
-// next segment's residual weights in registers (loaded at the segment's start)
-// and stores them into the other buffer afterwards: one barrier per segment and
-// the global-memory latency hidden behind the sums.  Within a segment the
-// weights of column k + 1 are read from LDS before column k is summed.
-constexpr int kAdjPer = kAdjMaxCols * 8 / kAdjThreads;  // doubles per thread per segment
-static_assert(kAdjPer * kAdjThreads == kAdjMaxCols * 8, "segment split over the threads");
-
+template <int MT>
 __global__ __launch_bounds__(kAdjThreads, 2) void adjoint_cartesian_kernel(
-    const PointRec *__restrict__ pts, int64_t W, Detector d, const double *__restrict__ a,
-    int rows_per_split, double *__restrict__ gpart)
-{
-    __shared__ double s_a[2][kAdjMaxCols * 8];
-    const int64_t jb = (int64_t)blockIdx.x * kAdjThreads * kAdjNPL + threadIdx.x;
-    const int r0 = blockIdx.y * rows_per_split;
-    const int r1 = min(d.n0, r0 + rows_per_split);
-    const int segs = (d.n1 + kAdjMaxCols - 1) / kAdjMaxCols;  // segments per row
-    const int nseg = (r1 - r0) * segs;
-
-    double Y[kAdjNPL], Z[kAdjNPL], kz[kAdjNPL];
-    double2 ez0[kAdjNPL], dzc[kAdjNPL], ey[kAdjNPL], dy[kAdjNPL];
-    double acc[kAdjNPL][4];
-    const double qz0 = axis_value(d.origin1, 0, d.step1);
-#pragma unroll
-    for (int u = 0; u < kAdjNPL; ++u) {
-        const int64_t j = jb + (int64_t)u * kAdjThreads;
-        const bool ok = j < W;
-        Y[u] = ok ? pts[j].Y : 0.0;
-        Z[u] = ok ? pts[j].Z : 0.0;
-        ez0[u] = twiddle(qz0 * Z[u]);
-        const double2 dz = twiddle(d.step1 * Z[u]);
-        dzc[u] = make_double2(dz.x, -dz.y);  // inverse column step
-        kz[u] = dz.x + dz.x;
-        dy[u] = twiddle(d.step0 * Y[u]);     // row step
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
-    }
-
-    // residual weights of segment g (row r0 + g / segs, columns from (g % segs) kAdjMaxCols)
-    auto fetch = [&](int g, double (&reg)[kAdjPer]) {
-        const int row = r0 + g / segs, c0 = (g % segs) * kAdjMaxCols;
-        const int nc = min(kAdjMaxCols, d.n1 - c0);
-        const double *src = a + ((int64_t)row * d.n1 + c0) * 8;
-#pragma unroll
-        for (int e = 0; e < kAdjPer; ++e) {
-            const int i = threadIdx.x + e * kAdjThreads;
-            reg[e] = i < nc * 8 ? src[i] : 0.0;
-        }
-    };
-    double reg[kAdjPer];
-    if (nseg > 0) {
-        fetch(0, reg);
-#pragma unroll
-        for (int e = 0; e < kAdjPer; ++e) s_a[0][threadIdx.x + e * kAdjThreads] = reg[e];
-    }
-    __syncthreads();
-
-    double2 pc[kAdjNPL], pm[kAdjNPL];  // phasors of the current column and of the one before
-    for (int g = 0; g < nseg; ++g) {
-        const int buf = g & 1;
-        if (g + 1 < nseg) fetch(g + 1, reg);
-        const int c0 = (g % segs) * kAdjMaxCols;
-        const int nc = min(kAdjMaxCols, d.n1 - c0);
-        if (c0 == 0) {  // row start: fresh column phasors
-            const int rr = g / segs;  // row within the split
-            if (rr % kAdjRowRestart == 0) {
-                const double qy = axis_value(d.origin0, r0 + rr, d.step0);
-#pragma unroll
-                for (int u = 0; u < kAdjNPL; ++u) ey[u] = twiddle(qy * Y[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < kAdjNPL; ++u) {
-                pc[u] = cmul(ey[u], ez0[u]);
-                pm[u] = cmul(pc[u], dzc[u]);
-                ey[u] = cmul(ey[u], dy[u]);  // next row
-            }
-        }
-        const double *sa = s_a[buf];
-        ColW wa = load_col(sa);
-        int k = 0;
-        for (; k + 1 < nc; k += 2) {
-            const ColW wb = load_col(sa + (k + 1) * 8);
-            __builtin_amdgcn_sched_barrier(0);
-            adjoint_column(wa, pc, pm, kz, acc);
-            __builtin_amdgcn_sched_barrier(0);
-            wa = load_col(sa + min(k + 2, nc - 1) * 8);
-            __builtin_amdgcn_sched_barrier(0);
-            adjoint_column(wb, pc, pm, kz, acc);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (k < nc) adjoint_column(wa, pc, pm, kz, acc);
-        if (g + 1 < nseg) {
-#pragma unroll
-            for (int e = 0; e < kAdjPer; ++e) s_a[buf ^ 1][threadIdx.x + e * kAdjThreads] = reg[e];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < kAdjNPL; ++u) {
-        const int64_t j = jb + (int64_t)u * kAdjThreads;
-        if (j < W) {
-            double *o = gpart + ((int64_t)blockIdx.y * W + j) * 4;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = acc[u][v];
-        }
-    }
-}
-
-// Polar detector: phase q_i u_m with u_m = Y sin(theta_m) + Z cos(theta_m).  A lane
-// owns kAdjNPL points; per theta column it forms u, the q step exp(-i dq u) (one
-// sincos) and walks the q rows with the two-term recurrence, restarted from a
-// fresh sincos every kPolRestart rows (the error growth of the recurrence stays
-// below kPolRestart^2 / 2 ulp, 2^15 ulp or 7e-12 relative; the first segment starts
-// at q = 0, whose phasor is 1 without a sincos).  The residual weights are column-major
-// [theta][q][8] and are walked as segments of kPolRestart rows of one column,
-// double-buffered in LDS like the Cartesian kernel's: the next segment is held
-// in registers while the current one is summed.
-// grid.x: point blocks of kAdjThreads * kAdjNPL; grid.y: theta-column ranges.
-constexpr int kPolRestart = 256;
-constexpr int kPolPer = kPolRestart * 8 / kAdjThreads;  // doubles per thread per segment
-static_assert(kPolPer * kAdjThreads == kPolRestart * 8, "segment split over the threads");
-
-__global__ __launch_bounds__(kAdjThreads, 2) void adjoint_polar_kernel(
-    const PointRec *__restrict__ pts, int64_t W, Detector d, const double *__restrict__ a, int cols_per_split,
+    const PointRec *__restrict__ pts, int64_t W, CartGeom g, AdjSplit sp, const double2 *__restrict__ coef,
     double *__restrict__ gpart)
 {
-    __shared__ double s_a[2][kPolRestart * 8];
-    const int64_t jb = (int64_t)blockIdx.x * kAdjThreads * kAdjNPL + threadIdx.x;
-    const int c0 = blockIdx.y * cols_per_split;
-    const int c1 = min(d.n1, c0 + cols_per_split);
-    const int rsegs = (d.n0 + kPolRestart - 1) / kPolRestart;  // segments per column
-    const int nseg = max(0, c1 - c0) * rsegs;
+    constexpr int kStage = 4 * MT * 64;  // coefficients of a 16-column block
+    __shared__ double2 s_c[2][kStage];
+    const int lane = threadIdx.x & 63, wave = cblk::wave_id();
+    const int pt = lane & 15, kq = lane >> 4;
+    const int64_t j0 = (int64_t)blockIdx.x * kAdjPoints + wave * (16 * kAdjNP) + pt;
+    const int rb0 = (int)(blockIdx.y / sp.nv) * sp.per_r, rb1 = min(g.nrb, rb0 + sp.per_r);
+    const int v0 = (int)(blockIdx.y % sp.nv) * sp.per_v, v1 = min(g.nzb, v0 + sp.per_v);
 
-    double Y[kAdjNPL], Z[kAdjNPL];
-    double acc[kAdjNPL][4];
+    double m[kAdjNP], n[kAdjNP], G[kAdjNP];
+    double2 off[kAdjNP][4], adv[kAdjNP];
+    // centre of the first column block of the split
+    const double qc = g.originN + ((double)(g.nN - g.B + 16 * v0) + 7.5) * g.stepN;
 #pragma unroll
-    for (int u = 0; u < kAdjNPL; ++u) {
-        const int64_t j = jb + (int64_t)u * kAdjThreads;
+    for (int u = 0; u < kAdjNP; ++u) {
+        const int64_t j = j0 + 16 * u;
         const bool ok = j < W;
-        Y[u] = ok ? pts[j].Y : 0.0;
-        Z[u] = ok ? pts[j].Z : 0.0;
+        const double y = ok ? pts[j].Y : 0.0, z = ok ? pts[j].Z : 0.0;
+        m[u] = g.swapped ? z : y;
+        n[u] = g.swapped ? y : z;
+        G[u] = 0.0;
+        adv[u] = twiddle(16.0 * g.stepN * n[u]);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
+        for (int s = 0; s < 4; ++s) off[u][s] = twiddle(((double)(4 * s + kq) - 7.5) * g.stepN * n[u]);
     }
 
-    // residual weights of segment g (column c0 + g / rsegs, rows from (g % rsegs) kPolRestart)
-    auto fetch = [&](int g, double (&reg)[kPolPer]) {
-        const int col = c0 + g / rsegs, r0 = (g % rsegs) * kPolRestart;
-        const int nr = min(kPolRestart, d.n0 - r0);
-        const double *src = a + ((int64_t)col * d.n0 + r0) * 8;
-#pragma unroll
-        for (int e = 0; e < kPolPer; ++e) {
-            const int i = threadIdx.x + e * kAdjThreads;
-            reg[e] = i < nr * 8 ? src[i] : 0.0;
-        }
+    // block i of the walk over (row block, column block)
+    const int nv = v1 - v0, total = max(0, rb1 - rb0) * max(0, nv);
+    auto stage = [&](int i) {
+        cblk::copy_to_lds(coef + ((int64_t)(rb0 + i / nv) * g.nzb + v0 + i % nv) * kStage, s_c[i & 1], kStage,
+                          kAdjWaves);
     };
-    double reg[kPolPer];
-    if (nseg > 0) {
-        fetch(0, reg);
-#pragma unroll
-        for (int e = 0; e < kPolPer; ++e) s_a[0][threadIdx.x + e * kAdjThreads] = reg[e];
-    }
+    cblk::v4d acc[MT][kAdjNP];
+    if (total > 0) stage(0);
+    cblk::wait_copies();
     __syncthreads();
-
-    double uu[kAdjNPL], kq[kAdjNPL];
-    double2 stc[kAdjNPL];  // inverse q step exp(+i dq u)
-    for (int g = 0; g < nseg; ++g) {
-        const int buf = g & 1;
-        if (g + 1 < nseg) fetch(g + 1, reg);
-        const int col = c0 + g / rsegs, r0 = (g % rsegs) * kPolRestart;
-        const int nr = min(kPolRestart, d.n0 - r0);
-        if (r0 == 0) {  // new column: u and the q step of every point
-            const double th = (2.0 * 3.141592653589793 * (double)col) / (double)d.n_theta;
-            double sth, cth;
-            sincos(th, &sth, &cth);
+    int i = 0;
+#pragma unroll 1
+    for (int rb = rb0; rb < rb1; ++rb) {
 #pragma unroll
-            for (int u = 0; u < kAdjNPL; ++u) {
-                uu[u] = Y[u] * sth + Z[u] * cth;
-                const double2 st = twiddle(d.step0 * uu[u]);
-                stc[u] = make_double2(st.x, -st.y);
-                kq[u] = st.x + st.x;
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int u = 0; u < kAdjNP; ++u) acc[t][u] = cblk::v4d{0.0, 0.0, 0.0, 0.0};
+        double2 ctr[kAdjNP];
+#pragma unroll
+        for (int u = 0; u < kAdjNP; ++u) ctr[u] = twiddle(qc * n[u]);
+#pragma unroll 1
+        for (int v = v0; v < v1; ++v, ++i) {
+            if (i + 1 < total) stage(i + 1);  // arrives under the products
+            const double2 *sc = &s_c[i & 1][lane];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double2 z[kAdjNP];
+#pragma unroll
+                for (int u = 0; u < kAdjNP; ++u) z[u] = cmul(ctr[u], off[u][s]);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const double2 a = sc[(s * MT + t) * 64];
+#pragma unroll
+                    for (int u = 0; u < kAdjNP; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, z[u].x, acc[t][u], 0, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < kAdjNP; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, z[u].y, acc[t][u], 0, 0, 0);
+                }
             }
-        }
-        // recurrence restart at row r0: phasors of rows r0 and r0 - 1
-        const double q0 = axis_value(0.0, r0, d.step0);
-        double2 pc[kAdjNPL], pm[kAdjNPL];
 #pragma unroll
-        for (int u = 0; u < kAdjNPL; ++u) {
-            pc[u] = r0 == 0 ? make_double2(1.0, 0.0) : twiddle(q0 * uu[u]);
-            pm[u] = cmul(pc[u], stc[u]);
+            for (int u = 0; u < kAdjNP; ++u) ctr[u] = cmul(ctr[u], adv[u]);
+            cblk::wait_copies();
+            __syncthreads();
         }
-        const double *sa = s_a[buf];
-#pragma unroll 2
-        for (int i = 0; i < nr; ++i) {
-            const double *ai = sa + i * 8;
-            const double a0r = ai[0], a0i = ai[1], a1r = ai[2], a1i = ai[3];
-            const double a2r = ai[4], a2i = ai[5], a3r = ai[6], a3i = ai[7];
+        // fold the tiles of this row block: rows a = 2 t + h
+        const double qm = axis_value(g.originM, g.nM - g.A + rb * g.na, g.stepM);
 #pragma unroll
-            for (int u = 0; u < kAdjNPL; ++u) {
-                const double2 p = pc[u];
-                acc[u][0] = fma(-a0i, p.y, fma(a0r, p.x, acc[u][0]));
-                acc[u][1] = fma(-a1i, p.y, fma(a1r, p.x, acc[u][1]));
-                acc[u][2] = fma(-a2i, p.y, fma(a2r, p.x, acc[u][2]));
-                acc[u][3] = fma(-a3i, p.y, fma(a3r, p.x, acc[u][3]));
-                pc[u] = make_double2(fma(kq[u], p.x, -pm[u].x), fma(kq[u], p.y, -pm[u].y));
-                pm[u] = p;
-            }
-        }
-        if (g + 1 < nseg) {
+        for (int u = 0; u < kAdjNP; ++u) {
+            double2 y, dm;
+            twiddle2(qm * m[u], g.stepM * m[u], y, dm);
 #pragma unroll
-            for (int e = 0; e < kPolPer; ++e) s_a[buf ^ 1][threadIdx.x + e * kAdjThreads] = reg[e];
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    G[u] = fma(y.x, acc[t][u][2 * h], fma(y.y, acc[t][u][2 * h + 1], G[u]));
+                    y = cmul(y, dm);
+                }
         }
-        __syncthreads();
     }
 #pragma unroll
-    for (int u = 0; u < kAdjNPL; ++u) {
-        const int64_t j = jb + (int64_t)u * kAdjThreads;
-        if (j < W) {
-            double *o = gpart + ((int64_t)blockIdx.y * W + j) * 4;
+    for (int u = 0; u < kAdjNP; ++u) {
+        const int64_t j = j0 + 16 * u;
+        if (j < W) gpart[((int64_t)blockIdx.y * W + j) * 4 + kq] = G[u];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Polar adjoint.  At one theta the q rows separate into block centres and offsets
+// (polar_block.h), so a column's residual weights are a coefficient block per 8 row
+// blocks: T = coefficients x offset phasors (16 columns deep), folded with the centres'.
+// A wave owns 32 points (two matrix column tiles), generates its column tables into its
+// own LDS with two lanes per point and loads a block's coefficients into registers before
+// it does, so that waves run free of workgroup barriers and one generates while another
+// of its SIMD multiplies.  A split is a range of theta columns.
+// ---------------------------------------------------------------------------
+constexpr int kPolWaves = 8;
+constexpr int kPolThreads = 64 * kPolWaves;
+constexpr int kPolNP = 2;
+constexpr int kPolPoints = 16 * kPolNP * kPolWaves;  // points per workgroup
+constexpr int kPolNA = 8;                            // row blocks per coefficient block
+
+// v of lane k (wave-uniform) as a uniform value.
+__device__ __forceinline__ double lane_value(double v, int k)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, k), hi = __builtin_amdgcn_readlane((int)(b >> 32), k);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+template <int MT>
+struct PolWaveTables {
+    double2 off[32][17];
+    double2 ctr[32][2 * MT + 1];
+};
+
+template <int MT>
+__global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
+                                                                       PolGeom g, int cols_per_split,
+                                                                       const double2 *__restrict__ coef,
+                                                                       double *__restrict__ gpart)
+{
+    constexpr int kStage = 4 * MT * 64;
+    __shared__ PolWaveTables<MT> s_t[kPolWaves];
+    const int lane = threadIdx.x & 63, wave = cblk::wave_id();
+    const int pt = lane & 15, kq = lane >> 4;
+    const int half = lane >> 5, gp = lane & 31;
+    const int64_t jw = (int64_t)blockIdx.x * kPolPoints + wave * 32;
+    const int c0 = blockIdx.y * cols_per_split, c1 = min(g.cols, c0 + cols_per_split);
+    PolWaveTables<MT> &tab = s_t[wave];
+    const bool ok = jw + gp < W;
+    const double Y = ok ? pts[jw + gp].Y : 0.0, Z = ok ? pts[jw + gp].Z : 0.0;
+    double G[kPolNP];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = acc[u][v];
+    for (int u = 0; u < kPolNP; ++u) G[u] = 0.0;
+
+    const double2 *src = coef + (int64_t)c0 * g.nrg * kStage + lane;
+    const double2 *last = coef + ((int64_t)c1 * g.nrg - 1) * kStage + lane;
+    double2 co[4][MT];  // coefficients of a block, loaded one block ahead of their use
+    auto load = [&](const double2 *from) {
+#pragma unroll
+        for (int k = 0; k < 4 * MT; ++k) co[k / MT][k % MT] = from[64 * k];
+    };
+    if (c0 < c1) load(src);
+    double2 dir = make_double2(0.0, 0.0);  // (sin, cos) of the angles of 64 columns, one per lane
+#pragma unroll 1
+    for (int col = c0; col < c1; ++col) {
+        const int cl = (col - c0) & 63;
+        if (cl == 0) sincos_cw((2.0 * 3.141592653589793 * (double)(col + lane)) / (double)g.n_out, &dir.x, &dir.y);
+        const double sth = lane_value(dir.x, cl), cth = lane_value(dir.y, cl);
+        const double u0 = Y * sth + Z * cth;
+        double2 first, step;  // centre of the group's first block, centre step (second half)
+        pblk::offsets(tab.off, g.dq, u0, first, step);
+        double2 adv = make_double2(1.0, 0.0);  // from one row group to the next
+        if (g.nrg > 1) adv = twiddle((double)(pblk::kRows * g.na) * g.dq * u0);
+#pragma unroll 1
+        for (int rg = 0; rg < g.nrg; ++rg) {
+            if (half != 0) pblk::centres<2 * MT>(tab.ctr[gp], first, step);
+            if (g.nrg > 1) first = cmul(first, adv);
+            pblk::wave_fence();
+            cblk::v4d acc[MT][kPolNP];
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int u = 0; u < kPolNP; ++u) acc[t][u] = cblk::v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double2 z[kPolNP];
+#pragma unroll
+                for (int u = 0; u < kPolNP; ++u) z[u] = tab.off[16 * u + pt][4 * s + kq];
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const double2 a = co[s][t];
+#pragma unroll
+                    for (int u = 0; u < kPolNP; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, z[u].x, acc[t][u], 0, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < kPolNP; ++u)
+                        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, z[u].y, acc[t][u], 0, 0, 0);
+                }
+            }
+            src += kStage;
+            load(src < last ? src : last);  // (the last block again at the end, unused)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < kPolNP; ++u)
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const double2 y = tab.ctr[16 * u + pt][2 * t + h];
+                        G[u] = fma(y.x, acc[t][u][2 * h], fma(y.y, acc[t][u][2 * h + 1], G[u]));
+                    }
+            pblk::wave_fence();
         }
+    }
+#pragma unroll
+    for (int u = 0; u < kPolNP; ++u) {
+        const int64_t j = jw + 16 * u + pt;
+        if (j < W) gpart[((int64_t)blockIdx.y * W + j) * 4 + kq] = G[u];
     }
 }
 
@@ -371,123 +429,188 @@ __global__ void grad_finalize_kernel(const double *__restrict__ gpart, int nspli
     }
 }
 
-// Ranges the detector is split into (rows on a Cartesian detector, theta
-// columns on a polar one), so that point blocks x ranges fill the chip.
-static int adjoint_row_splits(const Detector &d, int64_t W)
-{
-    int64_t pblocks = (W + kAdjThreads * kAdjNPL - 1) / (kAdjThreads * kAdjNPL);
-    if (pblocks < 1) pblocks = 1;
-    const int64_t target = current_tune_shape(kTuneAdjoint, d, W).target;
-    int64_t want = (target + pblocks - 1) / pblocks;
-    const int extent = d.kind == NUMAG_GRID_CARTESIAN ? d.n0 : d.n1;
-    if (want > extent) want = extent;
-    if (want < 1) want = 1;
-    return (int)want;
-}
+// ---------------------------------------------------------------------------
+// Work split.
+// ---------------------------------------------------------------------------
+// Everything launch_grad derives from the detector and the point count.
+struct GradPlan {
+    CartGeom cg;
+    PolGeom pg;
+    int mt;
+    int64_t n_cells;   // padded cells (residual threads)
+    int64_t n_blocks;  // coefficient blocks of 4 mt 64 double2
+    int64_t pblocks;   // point blocks
+    AdjSplit sp;       // Cartesian ranges
+    int cols_per, nsplit;
+};
 
-// The part of the detector the adjoint sums: the whole detector, or the half of the
-// Hermitian path (Cartesian rows [0, ceil(n0 / 2)), polar columns [0, n_theta / 2);
-// d.n_theta stays that of the whole detector).
-static Detector adjoint_detector(const Detector &d_full, bool hermitian)
+// Ranges the detector is split into, so that point blocks x ranges fill the chip (one
+// workgroup per CU at a time): of the counts up to four rounds of 256 workgroups, the one
+// with the fewest coefficient blocks on the busiest CU; a split costs the point's
+// phasors and partial gradients, about one block's time.  A table entry's target sets
+// the workgroups instead.
+static GradPlan grad_plan(const Detector &d, int64_t W, bool hermitian, bool use_table = true)
 {
-    Detector d = d_full;
-    if (hermitian) {
-        if (d.kind == NUMAG_GRID_CARTESIAN)
-            d.n0 = (d.n0 + 1) / 2;
-        else
-            d.n1 = d.n1 / 2;
+    GradPlan p{};
+    const bool cart = d.kind == NUMAG_GRID_CARTESIAN;
+    int64_t units;
+    if (cart) {
+        cart_geometry(d, 4, p.cg, p.mt);
+        p.cg.na = 2 * p.mt;
+        p.cg.nrb = (p.cg.A + p.cg.na - 1) / p.cg.na;
+        p.n_blocks = (int64_t)p.cg.nrb * p.cg.nzb;
+        units = p.n_blocks;
+    } else {
+        p.pg.n0 = d.n0;
+        p.pg.n_out = d.n_theta;
+        p.pg.nh = d.n_theta % 2 == 0 ? d.n_theta / 2 : 0;
+        p.pg.cols = p.pg.nh > 0 ? p.pg.nh : d.n_theta;
+        p.pg.dq = d.step0;
+        const int blocks = (d.n0 + pblk::kRows - 1) / pblk::kRows;
+        p.pg.nrg = (blocks + kPolNA - 1) / kPolNA;
+        p.pg.na = (blocks + p.pg.nrg - 1) / p.pg.nrg;
+        p.mt = (p.pg.na + 1) / 2;
+        p.pg.na = std::min(2 * p.mt, blocks);
+        p.pg.nrg = (blocks + p.pg.na - 1) / p.pg.na;
+        p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;
+        units = p.pg.cols;
     }
-    return d;
+    p.n_cells = p.n_blocks * 2 * p.mt * 16;
+    const int per_wg = cart ? kAdjPoints : kPolPoints;
+    p.pblocks = std::max<int64_t>(1, (W + per_wg - 1) / per_wg);
+    Detector key = d;
+    if (hermitian) {
+        if (cart) key.n0 = (d.n0 + 1) / 2;
+        else key.n1 = d.n1 / 2;
+    }
+    auto set = [&](int64_t want) {
+        want = std::max<int64_t>(1, std::min<int64_t>(want, std::min<int64_t>(units, 65535)));
+        if (cart) {  // ranges of row blocks first: a range of column blocks folds every row block again
+            int64_t nr = std::min<int64_t>(want, p.cg.nrb);
+            p.sp.per_r = (int)((p.cg.nrb + nr - 1) / nr);
+            p.sp.nr = (p.cg.nrb + p.sp.per_r - 1) / p.sp.per_r;
+            const int64_t nv = std::max<int64_t>(1, std::min<int64_t>(want / p.sp.nr, p.cg.nzb));
+            p.sp.per_v = (int)((p.cg.nzb + nv - 1) / nv);
+            p.sp.nv = (p.cg.nzb + p.sp.per_v - 1) / p.sp.per_v;
+            p.nsplit = p.sp.nr * p.sp.nv;
+        } else {
+            p.cols_per = (int)((p.pg.cols + want - 1) / want);
+            p.nsplit = (p.pg.cols + p.cols_per - 1) / p.cols_per;
+        }
+    };
+    TuneShape ts{};
+    int64_t target = env_target() > 0 ? 2 * (int64_t)env_target() : 0;
+    if (use_table && tuned_shape(kTuneAdjoint, key, W, &ts) && valid_tune_shape(kTuneAdjoint, key, ts) && ts.target > 0)
+        target = ts.target;
+    if (target > 0) {
+        set((target + p.pblocks - 1) / p.pblocks);
+        return p;
+    }
+    int64_t best = 1;
+    double best_cost = -1.0;
+    for (int r = 0; r <= 8; ++r) {  // half rounds
+        const int64_t want = std::max<int64_t>(1, 128 * r / p.pblocks);
+        set(want);
+        const double per = cart ? (double)p.sp.per_r * p.sp.per_v + 0.2 * p.sp.per_r : (double)p.cols_per * p.pg.nrg;
+        const double rounds = std::ceil((double)(p.pblocks * p.nsplit) / 256.0);
+        const double cost = rounds * (per + 0.5) + 2e-6 * (double)p.nsplit * (double)W;
+        if (best_cost < 0.0 || cost < 0.99 * best_cost) {
+            best_cost = cost;
+            best = want;
+        }
+    }
+    set(best);
+    return p;
 }
 
-// Scratch of launch_grad: the residual weights and loss partials of the whole
-// detector, and the gradient partials of the row splits of the part the adjoint
-// sums (its launch shape, hence its split count, is looked up for that part).
-size_t grad_workspace_bytes(const Detector &d_full, int64_t W, bool hermitian)
+int default_adjoint_target(const Detector &d, int64_t W)
 {
-    const int64_t P = (int64_t)d_full.n0 * d_full.n1;
-    const int64_t nres = (P + kResThreads - 1) / kResThreads;
-    const int splits = adjoint_row_splits(adjoint_detector(d_full, hermitian), W);
-    size_t b = 0;
-    b += (size_t)P * 8 * sizeof(double);          // residual weights
-    b += (size_t)(nres + 1) * sizeof(double);      // loss partials
-    b += (size_t)splits * (size_t)W * 4 * sizeof(double);
-    return b + 3 * 256;
+    // (the key detector of a half path stands for itself here: only the count is reported)
+    const GradPlan p = grad_plan(d, W, false, false);
+    return (int)std::min<int64_t>(p.pblocks * p.nsplit, 1 << 20);
 }
 
-// Residual weights folded onto half of a detector that is symmetric about q = 0:
-// the term of the mirror pixel p' (at -q_p within an ulp) is
-// Re[a(p') exp(+i q_p X)] = Re[conj a(p') exp(-i q_p X)], so the adjoint over the
-// half with a(p) + conj a(p') equals the full one, whatever the target and the
-// loss weights.  Cartesian: p' = P - 1 - p for p < Ph (pixels whose mirror lies
-// in the half, the middle row of an odd n0, keep their own weight); polar
-// (column-major [theta][q], even n_theta): p' = p + Ph.
-__global__ void fold_residual_kernel(double *__restrict__ a, int64_t P, int64_t Ph, int polar)
+static size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Scratch of launch_grad: coefficients, loss partials, gradient partials of the splits.
+size_t grad_workspace_bytes(const Detector &d, int64_t W, bool hermitian)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= Ph * 8) return;
-    const int64_t p = idx >> 3;
-    const int v = (int)(idx & 7);
-    const int64_t q = polar ? p + Ph : P - 1 - p;
-    if (q < Ph) return;
-    a[idx] += (v & 1) ? -a[q * 8 + v] : a[q * 8 + v];
+    const GradPlan p = grad_plan(d, W, hermitian);
+    const int64_t nres = (p.n_cells + kResThreads - 1) / kResThreads;
+    return al((size_t)p.n_blocks * 4 * p.mt * 64 * sizeof(double2)) + al((size_t)nres * sizeof(double)) +
+           al((size_t)p.nsplit * (size_t)std::max<int64_t>(W, 1) * 4 * sizeof(double));
 }
 
-int launch_grad(const PointRec *pts, int64_t W, const Detector &d_full, const numag_consts &c,
-                const double *amp, const double *target, const double *weight, double *loss,
-                double *dnuc, double *dmag, const Rot &R, void *ws, size_t ws_bytes, hipStream_t s,
-                bool hermitian)
+int launch_grad(const PointRec *pts, int64_t W, const Detector &d, const numag_consts &c, const double *amp,
+                const double *target, const double *weight, double *loss, double *dnuc, double *dmag, const Rot &R,
+                void *ws, size_t ws_bytes, hipStream_t s, bool hermitian)
 {
-    const Detector &dr = d_full;  // the residual and the loss cover the whole detector
-    const int64_t P = (int64_t)dr.n0 * dr.n1;
-    const int64_t nres = (P + kResThreads - 1) / kResThreads;
-    // the adjoint sums the whole detector, or half of it with folded weights; the
-    // split count is the one grad_workspace_bytes sized the scratch for
-    const Detector d = adjoint_detector(d_full, hermitian);
-    const int splits = adjoint_row_splits(d, W);
+    const GradPlan p = grad_plan(d, W, hermitian);
+    const bool cart = d.kind == NUMAG_GRID_CARTESIAN;
+    const int64_t nres = (p.n_cells + kResThreads - 1) / kResThreads;
     char *base = (char *)ws;
     auto take = [&](size_t bytes) {
         char *r = base;
-        base += (bytes + 255) & ~(size_t)255;
+        base += al(bytes);
         return r;
     };
-    double *a = (double *)take((size_t)P * 8 * sizeof(double));
-    double *lpart = (double *)take((size_t)(nres + 1) * sizeof(double));
-    double *gpart = (double *)take((size_t)splits * (size_t)W * 4 * sizeof(double));
+    double2 *coef = (double2 *)take((size_t)p.n_blocks * 4 * p.mt * 64 * sizeof(double2));
+    double *lpart = (double *)take((size_t)nres * sizeof(double));
+    double *gpart = (double *)take((size_t)p.nsplit * (size_t)std::max<int64_t>(W, 1) * 4 * sizeof(double));
     if ((size_t)(base - (char *)ws) > ws_bytes) {
         set_error("numag_grad: workspace too small");
         return NUMAG_E_WORKSPACE;
     }
-    hipLaunchKernelGGL(residual_kernel, dim3((unsigned)nres), dim3(kResThreads), 0, s, dr, c, amp, target,
-                       weight, a, lpart);
+    if (cart)
+        hipLaunchKernelGGL((residual_kernel<0>), dim3((unsigned)nres), dim3(kResThreads), 0, s, d, c, p.cg, p.pg, p.mt,
+                           p.n_cells, amp, target, weight, coef, loss != nullptr ? lpart : nullptr);
+    else
+        hipLaunchKernelGGL((residual_kernel<1>), dim3((unsigned)nres), dim3(kResThreads), 0, s, d, c, p.cg, p.pg, p.mt,
+                           p.n_cells, amp, target, weight, coef, loss != nullptr ? lpart : nullptr);
     NUMAG_HIP_CHECK(hipGetLastError());
     if (loss != nullptr) {
         hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, lpart, (int)nres, loss);
         NUMAG_HIP_CHECK(hipGetLastError());
     }
     if (W <= 0) return NUMAG_OK;
-    if (hermitian) {
-        const int64_t Ph = (int64_t)d.n0 * d.n1;
-        hipLaunchKernelGGL(fold_residual_kernel, dim3((unsigned)((Ph * 8 + 255) / 256)), dim3(256), 0, s, a, P, Ph,
-                           d.kind == NUMAG_GRID_POLAR ? 1 : 0);
-        NUMAG_HIP_CHECK(hipGetLastError());
-    }
-    const int extent = d.kind == NUMAG_GRID_CARTESIAN ? d.n0 : d.n1;
-    const int per = (extent + splits - 1) / splits;
-    const int nsplit = (extent + per - 1) / per;
-    const int64_t pblocks = (W + kAdjThreads * kAdjNPL - 1) / (kAdjThreads * kAdjNPL);
+    const dim3 grid((unsigned)p.pblocks, p.nsplit);
     {
         TimedLaunch timed(NUMAG_KERNEL_ADJOINT, s);
-        if (d.kind == NUMAG_GRID_CARTESIAN)
-            hipLaunchKernelGGL(adjoint_cartesian_kernel, dim3((unsigned)pblocks, nsplit), dim3(kAdjThreads), 0, s,
-                               pts, W, d, a, per, gpart);
-        else
-            hipLaunchKernelGGL(adjoint_polar_kernel, dim3((unsigned)pblocks, nsplit), dim3(kAdjThreads), 0, s, pts,
-                               W, d, a, per, gpart);
+#define NUMAG_LAUNCH_ADJ_C(MT)                                                                                     \
+    case MT:                                                                                                       \
+        hipLaunchKernelGGL((adjoint_cartesian_kernel<MT>), grid, dim3(kAdjThreads), 0, s, pts, W, p.cg, p.sp, coef, \
+                           gpart);                                                                                 \
+        break
+#define NUMAG_LAUNCH_ADJ_P(MT)                                                                                     \
+    case MT:                                                                                                       \
+        hipLaunchKernelGGL((adjoint_polar_kernel<MT>), grid, dim3(kPolThreads), 0, s, pts, W, p.pg, p.cols_per, coef, \
+                           gpart);                                                                                 \
+        break
+        if (cart) {
+            switch (p.mt) {
+                NUMAG_LAUNCH_ADJ_C(1);
+                NUMAG_LAUNCH_ADJ_C(2);
+                NUMAG_LAUNCH_ADJ_C(3);
+                NUMAG_LAUNCH_ADJ_C(4);
+                NUMAG_LAUNCH_ADJ_C(5);
+                NUMAG_LAUNCH_ADJ_C(6);
+                NUMAG_LAUNCH_ADJ_C(7);
+                NUMAG_LAUNCH_ADJ_C(8);
+            }
+        } else {
+            switch (p.mt) {
+                NUMAG_LAUNCH_ADJ_P(1);
+                NUMAG_LAUNCH_ADJ_P(2);
+                NUMAG_LAUNCH_ADJ_P(3);
+                NUMAG_LAUNCH_ADJ_P(4);
+            }
+        }
+#undef NUMAG_LAUNCH_ADJ_C
+#undef NUMAG_LAUNCH_ADJ_P
     }
     NUMAG_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(grad_finalize_kernel, dim3((unsigned)((W + 255) / 256)), dim3(256), 0, s, gpart,
-                       nsplit, W, R, dnuc, dmag);
+    hipLaunchKernelGGL(grad_finalize_kernel, dim3((unsigned)((W + 255) / 256)), dim3(256), 0, s, gpart, p.nsplit, W, R,
+                       dnuc, dmag);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

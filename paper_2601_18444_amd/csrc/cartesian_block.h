@@ -79,6 +79,18 @@ struct Smem {
 };
 static_assert(sizeof(Smem<1>) >= Smem<1>::kRed * sizeof(double), "the epilogue reduces over the whole buffer");
 
+// Copies the n double2 (a multiple of 64) at src to LDS at dst, 64 of them per wave
+// instruction, straight from memory without passing through registers; done for this
+// wave's share by wait_copies().
+__device__ __forceinline__ void copy_to_lds(const double2 *src, double2 *dst, int n, int waves)
+{
+    const int lane = threadIdx.x & 63;
+    for (int k = 64 * wave_id(); k < n; k += 64 * waves)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + k + lane),
+                                         (__attribute__((address_space(3))) void *)(dst + k), 16, 0, 0);
+}
+__device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 template <int MT>
 __device__ __forceinline__ void zero(v4d (&accC)[MT], v4d (&accS)[MT])
 {

@@ -301,7 +301,7 @@ constexpr int kMaxSplits = 65535;     // grid.z
 
 // Rows, columns and strides of the cells, row blocks for `channels`; the orientation
 // with fewer matrix tiles (thin detectors put their short axis into the packed rows).
-static void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt)
+void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt)
 {
     int64_t best = -1;
     for (int sw = 0; sw < 2; ++sw) {
@@ -408,9 +408,7 @@ TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
             return TuneShape{p.shape, (int)((int64_t)p.col_groups * p.g.nrb * p.nsplit)};
         }
         case kTuneAdjoint:
-            // twice the direct path's workgroups (measured about 2 % faster than the same
-            // count: shorter row ranges balance better across the CUs)
-            return TuneShape{0, 2 * target_workgroups()};
+            return TuneShape{0, default_adjoint_target(d, W)};
         default:  // the persistent object kernel: lanes per row (polar: workgroup shape), work items
             if (d.kind == NUMAG_GRID_POLAR) return TuneShape{default_polar_shape(d), 1024};
             return TuneShape{cart::choose_lanes(d.n1), 2048};

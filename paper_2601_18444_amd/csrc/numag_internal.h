@@ -108,6 +108,8 @@ TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W);
 // first ceil(n0 / 2) rows); either way every pixel is written, the mirrored ones as
 // conjugates.  max_partial > 0 caps the bytes of partial sums.
 CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial = 0);
+// Cells, row blocks and matrix tiles of detector d for `channels` (cartesian_block.h).
+void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt);
 // Bytes of partial sums (0 when one split writes the sums directly).
 size_t cart_partial_bytes(const CartPlan &p);
 // Writes (accumulate: adds) the sums of all pixels of the detector to amp [P][8].
@@ -198,14 +200,15 @@ int launch_azimuthal(const Detector &d, const double *f, int n_f, int n_bins, do
 int launch_correlation(const double *q, const double *I, int n_q, int n_f, const double *r, int n_r,
                        double scale, double *c, double *p, hipStream_t s);
 
-// residual weights, loss, adjoint sum (hermitian: over half of a detector that
-// is symmetric about q = 0, with the residual weights folded onto it).
+// residual weights, loss, adjoint sum (hermitian: which table entry sets the split; the
+// adjoint always runs on residual weights folded onto the independent pixels).
 int launch_grad(const PointRec *pts, int64_t W, const Detector &d, const numag_consts &c,
                 const double *amp, const double *target, const double *weight, double *loss,
                 double *dnuc, double *dmag, const Rot &R, void *ws, size_t ws_bytes, hipStream_t s,
                 bool hermitian = false);
 // Workspace bytes of launch_grad on detector d (whole), for the path it will run.
 size_t grad_workspace_bytes(const Detector &d, int64_t W, bool hermitian);
+int default_adjoint_target(const Detector &d, int64_t W);
 
 // 2D correlation function (eq. crav2d) from data on detector d onto real-space grid rd.
 size_t correlation_2d_workspace_bytes(const Detector &d, const Detector &rd);

@@ -62,46 +62,62 @@ __device__ __forceinline__ double2 next_term(double k2, double2 x, double2 befor
     return make_double2(fma(k2, x.x, -before.x), fma(k2, x.y, -before.y));
 }
 
+// Offset phasors of point gp = lane % 32 at u, written to off[gp]; returns, in the second
+// half of the lanes, the centre of block 0 (exp(-i 15.5 dq u)) and the centre step.
+__device__ __forceinline__ void offsets(double2 (*off)[17], double dq, double u, double2 &centre, double2 &step)
+{
+    const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
+    double2 x = twiddle((half == 0 ? 0.5 : 15.5) * dq * u);
+    centre = x;
+    double2 st = cmul(x, x);  // dq u in the first half
+    const double2 so = make_double2(other_half(st.x), other_half(st.y));
+    if (half != 0) st = make_double2(so.x, -so.y);  // the second half walks down
+    const double k2 = st.x + st.x;
+    const int at = half == 0 ? 0 : 15, by = half == 0 ? 1 : -1;
+    double2 y = cmul(x, st);
+    off[gp][at] = x;
+    off[gp][at + by] = y;
+#pragma unroll
+    for (int k = 2; k < 8; ++k) {
+        const double2 z = next_term(k2, y, x);
+        off[gp][at + by * k] = z;
+        x = y;
+        y = z;
+    }
+    step = cmul(cmul(centre, centre), so);
+}
+
+// N centres from a on, written to ctr[gp] by the second half of the lanes.  Every one the
+// tiles have room for: those beyond the row blocks are never used, and the unrolled
+// walk takes three instructions an entry.
+template <int N>
+__device__ __forceinline__ void centres(double2 *ctr, double2 a, double2 step)
+{
+    const double k2 = step.x + step.x;
+    double2 b = cmul(a, step);
+    ctr[0] = a;
+    if (N > 1) ctr[1] = b;
+#pragma unroll
+    for (int k = 2; k < N; ++k) {
+        const double2 c = next_term(k2, b, a);
+        ctr[k] = c;
+        a = b;
+        b = c;
+    }
+}
+
 // Tables of a chunk: point gp = lane % 32 of the wave at u, weights p.w, centres of the
 // row blocks from a0 on.
 template <int MT, int CH>
 __device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int a0, double dq, double u, const Point<CH> &p)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
-    double2 x = twiddle((half == 0 ? 0.5 : 15.5) * dq * u);
-    const double2 centre = x;  // of block 0 (second half)
-    double2 st = cmul(x, x);   // dq u in the first half
-    const double2 so = make_double2(other_half(st.x), other_half(st.y));
-    if (half != 0) st = make_double2(so.x, -so.y);  // the second half walks down
-    const double k2 = st.x + st.x;
-    const int at = half == 0 ? 0 : 15, by = half == 0 ? 1 : -1;
-    double2 y = cmul(x, st);
-    sm.off[gp][at] = x;
-    sm.off[gp][at + by] = y;
-#pragma unroll
-    for (int k = 2; k < 8; ++k) {
-        const double2 z = next_term(k2, y, x);
-        sm.off[gp][at + by * k] = z;
-        x = y;
-        y = z;
-    }
-    double2 first = make_double2(1.0, 0.0);
+    double2 centre, step, first = make_double2(1.0, 0.0);
+    offsets(sm.off, dq, u, centre, step);
     if (a0 != 0) first = twiddle((double)(kRows * a0) * dq * u);  // wave-uniform
     if (half != 0) {
-        const double2 cs = cmul(cmul(centre, centre), so);
-        const double kc = cs.x + cs.x;
-        double2 a = a0 != 0 ? cmul(centre, first) : centre, b = cmul(a, cs);
-        // every centre the tiles have room for: those beyond na are never stored, and
-        // the unrolled walk takes three instructions an entry
-        sm.ctr[gp][0] = a;
-        if (max_na<MT, CH>() > 1) sm.ctr[gp][1] = b;
-#pragma unroll
-        for (int k = 2; k < max_na<MT, CH>(); ++k) {
-            const double2 c = next_term(kc, b, a);
-            sm.ctr[gp][k] = c;
-            a = b;
-            b = c;
-        }
+        if (a0 != 0) centre = cmul(centre, first);
+        centres<max_na<MT, CH>()>(sm.ctr[gp], centre, step);
     } else {
 #pragma unroll
         for (int c = 0; c < CH; ++c) sm.w[gp][c] = p.w[c];
