@@ -416,12 +416,11 @@ int numag_angular_spectrum(const numag_qgrid *grid, const double *f, int32_t n_f
  *             Cartesian or the polar kernel), NUMAG_TUNE_ADJOINT (the gradient's
  *             adjoint sums), NUMAG_TUNE_OBJECTS (the persistent object kernel of
  *             DILUTE / SPLIT modes on a Cartesian detector).
- *   shape     Cartesian direct: detector columns per workgroup (8: 32 columns,
- *             64: 64, 16: 128, 32: 256; the axis the columns lie on may be the
- *             detector's rows on thin detectors); Cartesian objects: lanes per
- *             detector row (8, 16, 32, 64); polar direct: q rows per
- *             wave (1: 32 rows, only for at most 32 q rows; 0: 64; 2: 128; 3: 256;
- *             4: 512); adjoint: 0.
+ *   shape     Cartesian direct and objects: detector columns per workgroup (8: 32
+ *             columns, 64: 64, 16: 128, 32: 256; the axis the columns lie on may be
+ *             the detector's rows on thin detectors); polar direct and objects: q
+ *             rows per wave (1: 32 rows, only for at most 32 q rows; 0: 64; 2: 128;
+ *             3: 256; 4: 512); adjoint: 0.
  *   target    workgroups a launch aims for (objects: work items); 0 = default.
  *   path      NUMAG_PATH_DIRECT or NUMAG_PATH_DIRECT_HERMITIAN (which part of
  *             the detector is evaluated).

@@ -350,20 +350,13 @@ std::vector<TuneShape> tune_candidates(int kernel, const Detector &d, int64_t W)
         for (int k = at; k >= std::max(at - 1, d.n0 <= 32 ? 0 : 1); --k)
             for (int t : {512, 1024, 2048}) c.push_back(TuneShape{order[(size_t)k], t});
     } else if (kernel == kTuneObjects && d.kind == NUMAG_GRID_POLAR) {
-        const std::vector<int> shapes = d.n0 <= 32 ? std::vector<int>{1, 0} : std::vector<int>{0, 2, 4};
-        for (int sh : shapes)
-            for (int t : {512, 1024, 2048}) c.push_back(TuneShape{sh, t});
+        for (int t : {2048, 4096, 8192, 16384}) c.push_back(TuneShape{def.shape, t});
     } else if (kernel == kTuneDirect || kernel == kTuneObjects) {
         if (kernel == kTuneDirect) {
             for (int l : {8, 64, 16, 32})
                 for (int t : {256, 512, 768}) c.push_back(TuneShape{l, t});
         } else {
-            const int l0 = def.shape;
-            std::vector<int> lanes{l0};
-            if (l0 > 8) lanes.push_back(l0 / 2);
-            if (l0 < 64) lanes.push_back(l0 * 2);
-            for (int l : lanes)
-                for (int t : {1024, 2048, 4096}) c.push_back(TuneShape{l, t});
+            for (int t : {512, 1024, 2048}) c.push_back(TuneShape{def.shape, t});
         }
     } else {
         for (int t : {256, 512, 1024, 2048}) c.push_back(TuneShape{0, t});

@@ -98,12 +98,26 @@ __device__ __forceinline__ void zero(v4d (&accC)[MT], v4d (&accS)[MT])
     for (int t = 0; t < MT; ++t) accC[t] = accS[t] = v4d{0.0, 0.0, 0.0, 0.0};
 }
 
-// Adds the points [jbeg, jend) of `ld` (Point<CH> load(j), called with j < jend only)
-// to this wave's tiles: row block rb, column block zb0 + wave % nz.  accC holds the
-// contractions with zr, accS those with zi.  Ends with a barrier.
+// Loader concept: `Raw raw(int64_t j) const` loads what point j needs from memory, and
+// `Point<CH> point(const Raw &) const` makes the point of it, one chunk later.
+//
+// Adds the points [jbeg, jend) of `ld` to this wave's tiles: row block rb, column block
+// zb0 + wave % nz.  accC holds the contractions with zr, accS those with zi.  p and q
+// hold the raw points of the first two chunks (first_points).  Ends with a barrier.
+template <class Loader>
+__device__ __forceinline__ void first_points(const Loader &ld, int64_t jbeg, int64_t jend, typename Loader::Raw &p,
+                                             typename Loader::Raw &q)
+{
+    const int gp = threadIdx.x & 31;
+    p = q = typename Loader::Raw{};
+    if (jbeg + gp < jend) p = ld.raw(jbeg + gp);
+    if (jbeg + kChunk + gp < jend) q = ld.raw(jbeg + kChunk + gp);
+}
+
 template <int MT, int CH, class Loader>
 __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, const CartGeom &g, int rb,
-                                           int zb0, Smem<MT> &sm, v4d (&accC)[MT], v4d (&accS)[MT])
+                                           int zb0, Smem<MT> &sm, typename Loader::Raw p, typename Loader::Raw q,
+                                           v4d (&accC)[MT], v4d (&accS)[MT])
 {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int half = lane >> 5, gp = lane & 31;  // generation: entry of a pair, point
@@ -114,11 +128,6 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     const double qn = half == 0 ? ((double)wave + 0.5) * g.stepN
                                 : g.originN + ((double)(g.nN - g.B + kOff * (zb0 + wave)) + 7.5) * g.stepN;
 
-    auto fetch = [&](int64_t j0) {
-        Point<CH> p{};
-        if (j0 + gp < jend) p = ld.load(j0 + gp);
-        return p;
-    };
     auto put_row = [&](int b, const Point<CH> &p, int e, double2 y) {
         if (e < g.na) {
 #pragma unroll
@@ -130,7 +139,8 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         }
     };
     const double qm0 = axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * wave + half, g.stepM);
-    auto generate = [&](int b, const Point<CH> &p) {
+    auto generate = [&](int b, const typename Loader::Raw &raw) {
+        const Point<CH> p = ld.point(raw);
         double2 z, y;
         twiddle2(qn * p.n, qm0 * p.m, z, y);
         if (half == 0) {
@@ -164,7 +174,6 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         }
     };
 
-    Point<CH> p = fetch(jbeg), q = fetch(jbeg + kChunk);
     generate(0, p);
     __syncthreads();
     int b = 0;
@@ -172,10 +181,58 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk, b ^= 1) {
         if (j0 + kChunk < jend) {
             p = q;
-            q = fetch(j0 + 2 * kChunk);  // a whole chunk ahead of its use
+            if (j0 + 2 * kChunk + gp < jend) q = ld.raw(j0 + 2 * kChunk + gp);  // a whole chunk ahead of its use
+            else q = typename Loader::Raw{};
             generate(b ^ 1, p);
         }
         sum(b, (int)min((int64_t)kChunk, jend - j0));
+        __syncthreads();
+    }
+}
+
+// Hands the finished sums to put(t, h, S(+,+), S(+,-)): slot 8 t + 4 h + lane / 16, column
+// lane % 16 of the block.  With several point groups they are first added, in a fixed
+// order, through LDS (one tile at a time; group k < 2 then puts half k): every wave of
+// the workgroup has to call this.
+template <int MT, class Put>
+__device__ __forceinline__ void finish(const CartGeom &g, int zb0, Smem<MT> &sm, const v4d (&accC)[MT],
+                                       const v4d (&accS)[MT], const Put &put)
+{
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int zi = wave % g.nz, kg = wave / g.nz, nk = kWaves / g.nz;
+    const bool active = zb0 + zi < g.nzb;
+    auto out = [&](int t, int h, double RR, double IR, double RI, double II) {
+        put(t, h, make_double2(RR - II, RI + IR), make_double2(RR + II, IR - RI));
+    };
+    if (nk == 1) {
+        if (!active) return;
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                out(t, h, accC[t][2 * h], accC[t][2 * h + 1], accS[t][2 * h], accS[t][2 * h + 1]);
+        return;
+    }
+    double *red = (double *)&sm;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            red[(wave * 8 + r) * 64 + lane] = accC[t][r];
+            red[(wave * 8 + 4 + r) * 64 + lane] = accS[t][r];
+        }
+        __syncthreads();
+        if (active && kg < 2) {
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int k = 0; k < nk; ++k) {
+                const double *p = red + (k * g.nz + zi) * 512 + lane;
+                v[0] += p[(2 * kg) * 64];
+                v[1] += p[(2 * kg + 1) * 64];
+                v[2] += p[(4 + 2 * kg) * 64];
+                v[3] += p[(5 + 2 * kg) * 64];
+            }
+            out(t, kg, v[0], v[1], v[2], v[3]);
+        }
         __syncthreads();
     }
 }

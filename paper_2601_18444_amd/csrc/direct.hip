@@ -28,7 +28,6 @@
 #include <cmath>
 
 #include "cartesian_block.h"
-#include "cartesian_sum.h"
 
 namespace numag {
 
@@ -171,25 +170,22 @@ int launch_prepare_points(const double *pos, const double *nuc, const double *ma
 // ---------------------------------------------------------------------------
 // Cartesian direct sum.
 // ---------------------------------------------------------------------------
+template <int CH>
 struct PrepLoader {
+    using Raw = cblk::Point<CH>;
     const PointRec *__restrict__ pts;
     int swapped;
-    template <int CH>
-    __device__ __forceinline__ cblk::Point<CH> get(int64_t j) const
+    __device__ __forceinline__ Raw raw(int64_t j) const
     {
         const PointRec &r = pts[j];
-        cblk::Point<CH> p;
+        Raw p;
         p.m = swapped ? r.Z : r.Y;
         p.n = swapped ? r.Y : r.Z;
 #pragma unroll
         for (int c = 0; c < CH; ++c) p.w[c] = r.w[cblk::ch_first<CH>() + c];
         return p;
     }
-};
-
-template <int CH>
-struct PrepLoaderCh : PrepLoader {
-    __device__ __forceinline__ cblk::Point<CH> load(int64_t j) const { return this->template get<CH>(j); }
+    __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const { return r; }
 };
 
 // Where a workgroup's sums go: partials [split][row block][column block][tile][half][4][64]
@@ -200,18 +196,18 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(con
                                                                               int store, double *__restrict__ out)
 {
     __shared__ cblk::Smem<MT> sm;
-    const int lane = threadIdx.x & 63, wave = cblk::wave_id();
+    const int lane = threadIdx.x & 63;
     const int zb0 = blockIdx.x * g.nz, rb = blockIdx.y;
     const int64_t jbeg = (int64_t)blockIdx.z * per;
     const int64_t jend = min(W, jbeg + per);
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
-    cblk::accumulate<MT, CH>(PrepLoaderCh<CH>{{pts, g.swapped}}, jbeg, jend, g, rb, zb0, sm, accC, accS);
-
-    const int zb = zb0 + wave % g.nz, kg = wave / g.nz, nk = cblk::kWaves / g.nz;
-    const bool active = zb < g.nzb;
-    auto put = [&](int t, int h, double RR, double IR, double RI, double II) {
-        const double2 vp = make_double2(RR - II, RI + IR), vm = make_double2(RR + II, IR - RI);
+    const PrepLoader<CH> ld{pts, g.swapped};
+    typename PrepLoader<CH>::Raw p, q;
+    cblk::first_points(ld, jbeg, jend, p, q);
+    cblk::accumulate<MT, CH>(ld, jbeg, jend, g, rb, zb0, sm, p, q, accC, accS);
+    const int zb = zb0 + cblk::wave_id() % g.nz;
+    cblk::finish<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
         if (store == 0) {
             double *o = out + (((((int64_t)blockIdx.z * g.nrb + rb) * g.nzb + zb) * MT + t) * 2 + h) * 256 + lane;
             o[0] = vp.x;
@@ -222,39 +218,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(con
             const cblk::CellPixels x = cblk::cell_pixels(g, CH, rb, zb, 8 * t + 4 * h + (lane >> 4), lane & 15);
             if (x.ok) cblk::put_slot(out, x, CH, vp, vm, store == 2);
         }
-    };
-    if (nk == 1) {
-        if (!active) return;
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                put(t, h, accC[t][2 * h], accC[t][2 * h + 1], accS[t][2 * h], accS[t][2 * h + 1]);
-        return;
-    }
-    // sums of the point groups, in a fixed order through LDS, one tile at a time
-    double *red = (double *)&sm;
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            red[(wave * 8 + r) * 64 + lane] = accC[t][r];
-            red[(wave * 8 + 4 + r) * 64 + lane] = accS[t][r];
-        }
-        __syncthreads();
-        if (active && kg < 2) {  // point group kg writes half kg
-            double v[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int k = 0; k < nk; ++k) {
-                const double *p = red + (k * g.nz + wave % g.nz) * 512 + lane;
-                v[0] += p[(2 * kg) * 64];
-                v[1] += p[(2 * kg + 1) * 64];
-                v[2] += p[(4 + 2 * kg) * 64];
-                v[3] += p[(5 + 2 * kg) * 64];
-            }
-            put(t, kg, v[0], v[1], v[2], v[3]);
-        }
-        __syncthreads();
-    }
+    });
 }
 
 // Fixed-order sum of the split partials, written (or added) to the pixels.
@@ -290,8 +254,6 @@ int env_target()
     }();
     return cached;
 }
-
-int target_workgroups() { return env_target() > 0 ? env_target() : 2048; }
 
 // ---------------------------------------------------------------------------
 // Work split of the Cartesian sums.
@@ -334,7 +296,7 @@ void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt)
 }
 
 // Column blocks per workgroup of a launch shape (the labels are those tables hold).
-static int cart_nz(int shape) { return shape == 32 ? 8 : shape == 16 ? 4 : shape == 64 ? 2 : 1; }
+int cart_nz(int shape) { return shape == 32 ? 8 : shape == 16 ? 4 : shape == 64 ? 2 : 1; }
 
 static size_t cart_split_bytes(const CartGeom &g, int mt) { return (size_t)g.nrb * g.nzb * mt * 512 * sizeof(double); }
 
@@ -409,9 +371,16 @@ TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
         }
         case kTuneAdjoint:
             return TuneShape{0, default_adjoint_target(d, W)};
-        default:  // the persistent object kernel: lanes per row (polar: workgroup shape), work items
-            if (d.kind == NUMAG_GRID_POLAR) return TuneShape{default_polar_shape(d), 1024};
-            return TuneShape{cart::choose_lanes(d.n1), 2048};
+        default: {  // the persistent object kernel: shapes as for the direct sums, work items
+            // (eight per workgroup or wave that fits the chip: the largest go first, so the
+            // last ones even the load out; 16 particles x 24 rotations on 128 x 128 take
+            // 6.0 ms with half as many, 5.74 with these, 5.64 with twice as many)
+            if (d.kind == NUMAG_GRID_POLAR) return TuneShape{default_polar_shape(d), 16384};
+            CartGeom g{};
+            int mt = 0;
+            cart_geometry(d, 4, g, mt);
+            return TuneShape{g.nzb > 4 ? 32 : g.nzb > 2 ? 16 : g.nzb > 1 ? 64 : 8, 2048};
+        }
     }
 }
 
@@ -499,28 +468,6 @@ int launch_fill(double *out, int64_t n, double value, hipStream_t s)
 {
     if (n <= 0) return NUMAG_OK;
     hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, out, n, value);
-    NUMAG_HIP_CHECK(hipGetLastError());
-    return NUMAG_OK;
-}
-
-// ---------------------------------------------------------------------------
-// Hermitian completion on a Cartesian detector: for real weights S(-q) = conj S(q);
-// rows [0, h) of the row-major output are computed, pixel p mirrors to P - 1 - p.
-// ---------------------------------------------------------------------------
-__global__ void mirror_cartesian_kernel(double *__restrict__ amp, int64_t P, int64_t Ph)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Ph * 8) return;
-    const int64_t p = i >> 3;
-    const int v = (int)(i & 7);
-    const int64_t q = P - 1 - p;
-    if (q >= Ph) amp[q * 8 + v] = (v & 1) ? -amp[i] : amp[i];
-}
-
-int launch_mirror_cartesian(double *amp, int64_t P, int64_t Ph, hipStream_t s)
-{
-    if (Ph <= 0) return NUMAG_OK;
-    hipLaunchKernelGGL(mirror_cartesian_kernel, dim3((unsigned)((Ph * 8 + 255) / 256)), dim3(256), 0, s, amp, P, Ph);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

@@ -76,10 +76,6 @@ struct CartPlan {
     int64_t per;     // points per split (a multiple of 4)
     int col_groups;  // workgroups along N
 };
-// Hermitian completion of a half-detector sum (see direct.hip).
-int launch_mirror_cartesian(double *amp, int64_t P, int64_t Ph, hipStream_t s);
-// Workgroups a direct-sum launch aims for (split-K included).
-int target_workgroups();
 // The count NUMAG_TARGET_WGS asks for (0: not set).
 int env_target();
 
@@ -110,6 +106,8 @@ TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W);
 CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial = 0);
 // Cells, row blocks and matrix tiles of detector d for `channels` (cartesian_block.h).
 void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt);
+// Column blocks per workgroup of a launch shape.
+int cart_nz(int shape);
 // Bytes of partial sums (0 when one split writes the sums directly).
 size_t cart_partial_bytes(const CartPlan &p);
 // Writes (accumulate: adds) the sums of all pixels of the detector to amp [P][8].
@@ -127,6 +125,8 @@ struct PolarPlan {
     int64_t per;     // points per split
 };
 int default_polar_shape(const Detector &d);
+// Row groups, columns and tiles of detector d for `channels` under a launch shape.
+void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int &mt);
 TuneShape default_polar_tune(const Detector &d, int64_t W);
 // Plan on the whole detector d; the launch shape is looked up under the part the path
 // stands for (hermitian: half of the columns).  Every pixel is written; columns
@@ -135,21 +135,20 @@ PolarPlan plan_direct_polar(const Detector &d, int64_t W, int channels, bool her
 size_t polar_partial_bytes(const PolarPlan &p);
 int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, double *partial, double *amp,
                         int accumulate, hipStream_t s);
-// The old polar workgroup tiles of the object kernel.
-int polar_shape_rows(int shape);
-int polar_shape_cols(int shape);
-int polar_shape_waves(int shape);
 // out[i] = value for i < n (a kernel, so that callers may capture it in a graph).
 int launch_fill(double *out, int64_t n, double value, hipStream_t s);
 
-// work items (object slot, rotation group, pixel block); each sums complete
-// objects and adds F F^H (and, in split mode, exp(-i q.R r^k) F) into an
-// accumulator slot no other item touches; slots are reduced in a fixed order.
+// Work items (object slot, pixel block) of the object kernel; each sums complete objects
+// and adds F F^H (and, in split mode, exp(-i q.R r^k) F) into accumulators no other item
+// touches; slots are reduced in a fixed order.
 struct ObjectsPlan {
-    int lanes;      // lanes per detector row
-    int col_blocks, row_blocks;
-    int n_slots;    // accumulator slots (object set x rotation range)
-    int n_out;      // spectral matrices written (K per object, or 1)
+    CartGeom cg;     // Cartesian detector
+    PolGeom pg;      // polar detector
+    int mt;          // matrix tiles per wave
+    int64_t n_blocks;  // pixel blocks (items per slot)
+    int64_t n_th;    // tile halves of the detector (accumulator rows of a slot)
+    int n_slots;     // accumulator slots (object set x rotation range)
+    int n_out;       // spectral matrices written (K per object, or 1)
     int64_t n_items;
 };
 
@@ -171,16 +170,13 @@ struct ObjPlan {
     size_t ws_bytes = 0;        // workspace bytes the plan's calls need
     std::shared_ptr<ObjPlanTables> tables;  // the persistent kernel's tables
 };
-// Detector part the object kernel sums: all of d, or with `hermitian` the first
-// ceil(n0 / 2) rows of a Cartesian detector or the theta columns [0, n_theta / 2)
-// of a polar one (the rest follow by G(-q) = conj G(q)).
+// Detector part an object-mode path stands for (the key of its launch shape): all of d,
+// or with `hermitian` the first ceil(n0 / 2) rows of a Cartesian detector or the theta
+// columns [0, n_theta / 2) of a polar one.
 Detector objects_detector(const Detector &d, bool hermitian);
 // Fills pl.tables, pl.image (rotations excepted), pl.o_rot and pl.ws_bytes of a plan
 // whose other fields are set (either detector kind).
 void build_objects_plan(ObjPlan &pl);
-// out[i] = NaN (i < n) when the tag at tag_ptr is not `tag`.
-int launch_tag_guard(const unsigned long long *tag_ptr, unsigned long long tag, double *out, int64_t n,
-                     hipStream_t st);
 // Enqueues the sums of a plan whose image is in `ws` (kernels only).
 int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_out, double *amp_out, void *ws,
                         hipStream_t st);

@@ -7,56 +7,89 @@
 // (one object, or a contiguous group of roughly equal point count) and a range
 // of rotations, sized so that every slot costs about the same; a large particle
 // gets many rotation ranges, a small one a single range.  A work item is
-// (slot, pixel block): the workgroup sums every point of the slot's objects for
-// every rotation of its range with the Cartesian building block (FP64), then
-// adds F F^H (and, in split mode, exp(-i q.R r^k) F for the coherent total)
-// into the slot's FP64 accumulators, which no other item touches.  Items are
-// sorted by cost and handed out by a persistent kernel through an atomic
-// counter; slots are reduced in a fixed order, so results are reproducible
+// (slot, pixel block): every point of the slot's objects is summed for every rotation
+// of its range with the matrix building blocks of the direct sums, then F F^H (and,
+// in split mode, exp(-i q.R r^k) F for the coherent total) goes into the slot's FP64
+// accumulators, which no other item touches.  Items are sorted by cost and handed out by
+// a persistent kernel through an atomic counter -- to workgroups of 8 waves on a
+// Cartesian detector (cartesian_block.h), to single waves on a polar one
+// (polar_block.h); slots are reduced in a fixed order, so results are reproducible
 // bit for bit.
 //
 // Rotations are applied on the fly (X = R x, w' = (n, R m)) while a chunk's
-// twiddles are generated, so the point data is read once per chunk and never
-// rewritten per orientation.  On a polar detector the same work queue runs on the
-// polar building block (polar_sum.h): a pixel block is one of its workgroup
-// tiles (q rows x theta columns).
+// phasors are generated, so the point data is read once per chunk and never
+// rewritten per orientation; the first points of the next object are loaded before
+// the products of the current one.
+//
+// Accumulators hold only the independent half of the pixels (G(-q) = conj G(q) for
+// real weights), in the order the lanes hold them: lane l has channel g = l / 16 of
+// the pixels of one slot, takes the other channels from lanes l ^ 16, 32, 48 and
+// keeps four of the sixteen reals of G (kPacked), so that every access is a
+// coalesced wave-wide row; the reduction puts them into pixel order.
+//
+// Measured, kernel time before (10.5 vector FP64 instructions per term over every pixel)
+// and now: 16 particles (96,000 points) x 24 rotations, 128 x 128: 14.2 -> 5.74 ms (4.04 of
+// it multiply-adds at 74.7 TFLOP/s); 96 objects (240,000 points) split, 256 x 256: 6.19 -> 2.45 ms
+// (1.68; the largest object's items run alone at the end).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <memory>
 #include <vector>
 
-#include "cartesian_sum.h"
-#include "polar_sum.h"
+#include "cartesian_block.h"
+#include "polar_block.h"
 
 namespace numag {
 
-int polar_shape_rows(int shape)
-{
-    const polar::ShapeDesc &s = polar::kShapes[shape];
-    return polar::kB * s.waves * (64 / s.cols);
-}
-int polar_shape_cols(int shape) { return polar::kShapes[shape].cols; }
-int polar_shape_waves(int shape) { return polar::kShapes[shape].waves; }
-
 namespace {
 
-struct RawLoader {
-    const double *pos, *nuc, *mag;
-    const double *R;  // row-major 3x3, wave-uniform
-    __device__ __forceinline__ cart::PointPart load(int64_t j, int slot) const
+__device__ __forceinline__ double uniform(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+__device__ __forceinline__ Rot uniform_rot(const double *p)
+{
+    Rot R;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) R.m[i] = uniform(p[i]);
+    return R;
+}
+
+// Points of the sample rotated by R (the axes swapped for a transposed Cartesian grid).
+struct RotLoader {
+    struct Raw {
+        double x[3], n, m[3];
+    };
+    const double *__restrict__ pos, *__restrict__ nuc, *__restrict__ mag;
+    Rot R;
+    int swapped;
+    __device__ __forceinline__ Raw raw(int64_t j) const
     {
-        const double x0 = pos[3 * j], x1 = pos[3 * j + 1], x2 = pos[3 * j + 2];
-        cart::PointPart p;
-        p.Y = R[3] * x0 + R[4] * x1 + R[5] * x2;
-        p.Z = R[6] * x0 + R[7] * x1 + R[8] * x2;
-        p.w = 0.0;
-        if (slot == 0) {
-            p.w = nuc != nullptr ? nuc[j] : 0.0;
-        } else if (slot < 4 && mag != nullptr) {
-            const int a = slot - 1;
-            p.w = R[3 * a] * mag[3 * j] + R[3 * a + 1] * mag[3 * j + 1] + R[3 * a + 2] * mag[3 * j + 2];
+        Raw r{};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) r.x[i] = pos[3 * j + i];
+        if (nuc != nullptr) r.n = nuc[j];
+        if (mag != nullptr) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) r.m[i] = mag[3 * j + i];
         }
+        return r;
+    }
+    __device__ __forceinline__ cblk::Point<4> point(const Raw &r) const
+    {
+        cblk::Point<4> p;
+        const double Y = R.m[3] * r.x[0] + R.m[4] * r.x[1] + R.m[5] * r.x[2];
+        const double Z = R.m[6] * r.x[0] + R.m[7] * r.x[1] + R.m[8] * r.x[2];
+        p.m = swapped ? Z : Y;
+        p.n = swapped ? Y : Z;
+        p.w[0] = r.n;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            p.w[1 + i] = R.m[3 * i] * r.m[0] + R.m[3 * i + 1] * r.m[1] + R.m[3 * i + 2] * r.m[2];
         return p;
     }
 };
@@ -70,165 +103,165 @@ struct ObjArgs {
     const double *rot;       // [n_rot][9]
     const int2 *items;       // (slot, pixel block), sorted by cost
     const int4 *slots;       // (object lo, object hi, rotation lo, rotation hi)
-    int n_items, col_blocks;
+    int n_items;
     int *counter;
-    double *spec;            // [n_slots][P][16]
-    double *amp;             // [n_slots][P][8] or null (split mode)
+    double *spec;            // [n_slots][tiles][2 halves][2 signs][4][64]
+    double *amp;             // [n_slots][tiles][2 halves][4][64] or null (split mode)
 };
 
-template <int LR>
-__global__ __launch_bounds__(cart::kThreads, 2) void objects_kernel(ObjArgs a, Detector d)
+// Entry of the packed spectral matrix that lane group g keeps in row e: its own diagonal
+// entry, then one real of the pair (g, g ^ e): the real part in the group of the smaller
+// channel, the imaginary part in the other.
+__device__ constexpr int kPacked[4][4] = {{0, 4, 6, 8}, {1, 5, 12, 10}, {2, 14, 7, 11}, {3, 15, 13, 9}};
+
+// Adds (first: writes) F F^H of one sign to the lane's four accumulators o[64 e].
+__device__ __forceinline__ void add_spectral(double *__restrict__ o, bool first, double2 F)
 {
-    using T = cart::Tile<LR>;
-    __shared__ cart::Smem<LR> sm;
+    const int g = (threadIdx.x & 63) >> 4;
+    double v[4];
+    v[0] = F.x * F.x + F.y * F.y;
+#pragma unroll
+    for (int e = 1; e < 4; ++e) {
+        const double ox = __shfl_xor(F.x, 16 * e), oy = __shfl_xor(F.y, 16 * e);
+        // Re F_a conj(F_b) is symmetric; Im of the smaller channel a (the other lane's)
+        // with b (this one's) is a_i b_r - a_r b_i
+        v[e] = g < (g ^ e) ? F.x * ox + F.y * oy : oy * F.x - ox * F.y;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[64 * e] = first ? v[e] : o[64 * e] + v[e];
+}
+
+// Adds (first: writes) one channel of the pixel pair times the object's phasors y z, y conj z.
+__device__ __forceinline__ void add_amplitude(double *__restrict__ o, bool first, double2 vp, double2 vm, double2 y,
+                                              double2 z)
+{
+    const double2 a = cmul(cmul(y, z), vp), b = cmul(cmul(y, make_double2(z.x, -z.y)), vm);
+    o[0] = first ? a.x : o[0] + a.x;
+    o[64] = first ? a.y : o[64] + a.y;
+    o[128] = first ? b.x : o[128] + b.x;
+    o[192] = first ? b.y : o[192] + b.y;
+}
+
+// Lab position (Y, Z) of object k.
+__device__ __forceinline__ double2 object_yz(const ObjArgs &a, const Rot &R, int k)
+{
+    if (a.obj_pos == nullptr) return make_double2(0.0, 0.0);
+    const double *o = a.obj_pos + 3 * (int64_t)k;
+    return make_double2(R.m[3] * o[0] + R.m[4] * o[1] + R.m[5] * o[2],
+                        R.m[6] * o[0] + R.m[7] * o[1] + R.m[8] * o[2]);
+}
+
+template <int MT>
+__global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, CartGeom g)
+{
+    __shared__ cblk::Smem<MT> sm;
     __shared__ int s_item;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t P = (int64_t)d.n0 * d.n1;
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
+    const int lane = threadIdx.x & 63;
+    const int groups = (g.nzb + g.nz - 1) / g.nz;
+    const int64_t tiles = (int64_t)g.nrb * g.nzb * MT;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
         __syncthreads();
-        const int it = s_item;
+        const int it = __builtin_amdgcn_readfirstlane(s_item);
         __syncthreads();
         if (it >= a.n_items) break;
         const int2 item = a.items[it];
-        const int slot = item.x, blk = item.y;
-        const int col0 = (blk % a.col_blocks) * T::COLS;
-        const int row0 = (blk / a.col_blocks) * T::ROWS;
-        const int row = T::row(row0, lane, wave);
-        const int4 sr = a.slots[slot];
-        double *G = a.spec + (int64_t)slot * P * 16;
-        for (int r = sr.z; r < sr.w; ++r) {
-            const double *R = a.rot + 9 * (int64_t)r;
-            for (int k = sr.x; k < sr.y; ++k) {
-                double acc[cart::kB][8];
-                cart::zero(acc);
-                cart::accumulate<LR>(RawLoader{a.pos, a.nuc, a.mag, R}, a.off[k], a.off[k + 1], d, col0, row0, sm,
-                                     acc);
-                // lab position of the object (split mode)
-                double XY = 0.0, XZ = 0.0;
-                if (a.amp != nullptr && a.obj_pos != nullptr) {
-                    const double *o = a.obj_pos + 3 * k;
-                    XY = R[3] * o[0] + R[4] * o[1] + R[5] * o[2];
-                    XZ = R[6] * o[0] + R[7] * o[1] + R[8] * o[2];
+        const int slot = __builtin_amdgcn_readfirstlane(item.x), blk = __builtin_amdgcn_readfirstlane(item.y);
+        const int rb = blk / groups, zb0 = (blk % groups) * g.nz;
+        const int zb = zb0 + cblk::wave_id() % g.nz;
+        const int4 sv = a.slots[slot];
+        const int k0 = __builtin_amdgcn_readfirstlane(sv.x), k1 = __builtin_amdgcn_readfirstlane(sv.y);
+        const int r0 = __builtin_amdgcn_readfirstlane(sv.z), r1 = __builtin_amdgcn_readfirstlane(sv.w);
+        const int64_t tile0 = slot * tiles + ((int64_t)rb * g.nzb + zb) * MT;
+        RotLoader ld{a.pos, a.nuc, a.mag, uniform_rot(a.rot + 9 * (int64_t)r0), g.swapped};
+        RotLoader::Raw p, q;
+        cblk::first_points(ld, a.off[k0], a.off[k0 + 1], p, q);
+        for (int r = r0; r < r1; ++r) {
+            if (r != r0) ld.R = uniform_rot(a.rot + 9 * (int64_t)r);
+            for (int k = k0; k < k1; ++k) {
+                cblk::v4d accC[MT], accS[MT];
+                cblk::zero<MT>(accC, accS);
+                cblk::accumulate<MT, 4>(ld, a.off[k], a.off[k + 1], g, rb, zb0, sm, p, q, accC, accS);
+                const int kn = k + 1 < k1 ? k + 1 : k0;  // the next object (raw points do not depend on r)
+                cblk::first_points(ld, a.off[kn], a.off[kn + 1], p, q);
+                const bool first = r == r0 && k == k0;
+                double2 z = make_double2(1.0, 0.0);
+                double Xm = 0.0;
+                if (a.amp != nullptr) {
+                    const double2 X = object_yz(a, ld.R, k);
+                    Xm = g.swapped ? X.y : X.x;
+                    z = twiddle(axis_value(g.originN, g.nN - g.B + cblk::kOff * zb + (lane & 15), g.stepN) *
+                                (g.swapped ? X.x : X.y));
                 }
-                {
-#pragma unroll
-                    for (int c = 0; c < cart::kB; ++c) {
-                        const int col = T::col(col0, lane, c);
-                        if (row >= d.n0 || col >= d.n1) continue;
-                        const int64_t p = (int64_t)row * d.n1 + col;
-                        const double *F = acc[c];
-                        double *g = G + p * 16;
-                        // G_ab += F_a conj(F_b): diagonal, then the upper triangle
-                        g[0] += F[0] * F[0] + F[1] * F[1];
-                        g[1] += F[2] * F[2] + F[3] * F[3];
-                        g[2] += F[4] * F[4] + F[5] * F[5];
-                        g[3] += F[6] * F[6] + F[7] * F[7];
-                        const int pa[6] = {0, 0, 0, 1, 1, 2};
-                        const int pb[6] = {1, 2, 3, 2, 3, 3};
-#pragma unroll
-                        for (int t = 0; t < 6; ++t) {
-                            const double ar = F[2 * pa[t]], ai = F[2 * pa[t] + 1];
-                            const double br = F[2 * pb[t]], bi = F[2 * pb[t] + 1];
-                            g[4 + 2 * t] += ar * br + ai * bi;
-                            g[5 + 2 * t] += ai * br - ar * bi;
-                        }
-                        if (a.amp != nullptr) {
-                            const double qy = axis_value(d.origin0, row, d.step0);
-                            const double qz = axis_value(d.origin1, col, d.step1);
-                            const double2 ph = twiddle(qy * XY + qz * XZ);
-                            double *o = a.amp + ((int64_t)slot * P + p) * 8;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                o[2 * v] += ph.x * F[2 * v] - ph.y * F[2 * v + 1];
-                                o[2 * v + 1] += ph.x * F[2 * v + 1] + ph.y * F[2 * v];
-                            }
-                        }
+                cblk::finish<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
+                    const int64_t th = (tile0 + t) * 2 + h;
+                    double *o = a.spec + th * 512 + lane;
+                    add_spectral(o, first, vp);
+                    add_spectral(o + 256, first, vm);
+                    if (a.amp != nullptr) {
+                        const double qm = axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * t + h, g.stepM);
+                        add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(qm * Xm), z);
                     }
-                }
+                });
             }
         }
     }
 }
 
-// The same work queue on a polar detector: a pixel block is a polar workgroup
-// tile (col_blocks theta-column blocks of CW columns x row blocks of ROWS q rows);
-// the lane's pixels are its 8 q rows of one theta column.
-template <int WV, int CW, int CHK, int NB>
-__global__ __launch_bounds__(64 * WV, 8 / WV) void objects_polar_kernel(ObjArgs a, Detector d)
+// A work item belongs to one wave: (slot, theta column and row group).
+template <int MT>
+__global__ __launch_bounds__(pblk::kThreads, 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
 {
-    using S = polar::Shape<WV, CW, CHK, NB>;
-    __shared__ polar::Smem<WV, CW, CHK, NB> sm;
-    __shared__ int s_item;
-    const int64_t P = (int64_t)d.n0 * d.n1;
+    __shared__ pblk::WaveSmem<MT, 4> sm[pblk::kWaves];
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
-    const int lc = polar::lane_col<WV, CW>(), lg = polar::lane_group<WV, CW>();
+    const int lane = threadIdx.x & 63, wave = cblk::wave_id();
+    const int64_t tiles = (int64_t)g.nrg * g.cols * MT;
     for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
-        __syncthreads();
-        const int it = s_item;
-        __syncthreads();
+        int it = 0;
+        if (lane == 0) it = atomicAdd(a.counter, 1);
+        it = __builtin_amdgcn_readfirstlane(it);
         if (it >= a.n_items) break;
         const int2 item = a.items[it];
-        const int slot = item.x, blk = item.y;
-        const int col0 = (blk % a.col_blocks) * CW;
-        const int rb = blk / a.col_blocks;
-        const int col = col0 + lc;
-        const int row0 = rb * S::ROWS + lg * polar::kB;
-        const int4 sr = a.slots[slot];
-        double *G = a.spec + (int64_t)slot * P * 16;
-        for (int r = sr.z; r < sr.w; ++r) {
-            const double *R = a.rot + 9 * (int64_t)r;
-            for (int k = sr.x; k < sr.y; ++k) {
-                double acc[polar::kB][8];
-#pragma unroll
-                for (int q = 0; q < polar::kB; ++q)
-#pragma unroll
-                    for (int v = 0; v < 8; ++v) acc[q][v] = 0.0;
-                polar::accumulate<WV, CW, CHK, NB, 4>(RawLoader{a.pos, a.nuc, a.mag, R}, a.off[k], a.off[k + 1], d,
-                                                      col0, rb, sm, acc);
-                if (col >= d.n1) continue;
-                // lab position of the object projected on the column direction (split mode)
+        const int slot = __builtin_amdgcn_readfirstlane(item.x), blk = __builtin_amdgcn_readfirstlane(item.y);
+        const int rg = blk / g.cols, col = blk % g.cols;
+        const int4 sv = a.slots[slot];
+        const int k0 = __builtin_amdgcn_readfirstlane(sv.x), k1 = __builtin_amdgcn_readfirstlane(sv.y);
+        const int r0 = __builtin_amdgcn_readfirstlane(sv.z), r1 = __builtin_amdgcn_readfirstlane(sv.w);
+        const int64_t tile0 = slot * tiles + ((int64_t)rg * g.cols + col) * MT;
+        double sth, cth;
+        sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
+        RotLoader ld{a.pos, a.nuc, a.mag, Rot{}, 0};
+        for (int r = r0; r < r1; ++r) {
+            ld.R = uniform_rot(a.rot + 9 * (int64_t)r);
+            for (int k = k0; k < k1; ++k) {
+                cblk::v4d accC[MT], accS[MT];
+                cblk::zero<MT>(accC, accS);
+                pblk::accumulate<MT, 4>(ld, a.off[k], a.off[k + 1], sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
+                const bool first = r == r0 && k == k0;
                 double uk = 0.0;
-                if (a.amp != nullptr && a.obj_pos != nullptr) {
-                    const double *o = a.obj_pos + 3 * k;
-                    const double XY = R[3] * o[0] + R[4] * o[1] + R[5] * o[2];
-                    const double XZ = R[6] * o[0] + R[7] * o[1] + R[8] * o[2];
-                    const double2 tr = sm.trig[lc];  // valid until the next accumulate call
-                    uk = XY * tr.x + XZ * tr.y;
+                double2 z = make_double2(1.0, 0.0);
+                if (a.amp != nullptr) {
+                    const double2 X = object_yz(a, ld.R, k);
+                    uk = X.x * sth + X.y * cth;
+                    z = twiddle(((double)(lane & 15) + 0.5) * g.dq * uk);
                 }
 #pragma unroll
-                for (int q = 0; q < polar::kB; ++q) {
-                    const int row = row0 + q;
-                    if (row >= d.n0) break;
-                    const int64_t p = (int64_t)row * d.n1 + col;
-                    const double *F = acc[q];
-                    double *g = G + p * 16;
-                    // G_ab += F_a conj(F_b): diagonal, then the upper triangle
-                    g[0] += F[0] * F[0] + F[1] * F[1];
-                    g[1] += F[2] * F[2] + F[3] * F[3];
-                    g[2] += F[4] * F[4] + F[5] * F[5];
-                    g[3] += F[6] * F[6] + F[7] * F[7];
-                    const int pa[6] = {0, 0, 0, 1, 1, 2};
-                    const int pb[6] = {1, 2, 3, 2, 3, 3};
+                for (int t = 0; t < MT; ++t)
 #pragma unroll
-                    for (int t = 0; t < 6; ++t) {
-                        const double ar = F[2 * pa[t]], ai = F[2 * pa[t] + 1];
-                        const double br = F[2 * pb[t]], bi = F[2 * pb[t] + 1];
-                        g[4 + 2 * t] += ar * br + ai * bi;
-                        g[5 + 2 * t] += ai * br - ar * bi;
-                    }
-                    if (a.amp != nullptr) {
-                        const double2 ph = twiddle(axis_value(d.origin0, row, d.step0) * uk);
-                        double *o = a.amp + ((int64_t)slot * P + p) * 8;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            o[2 * v] += ph.x * F[2 * v] - ph.y * F[2 * v + 1];
-                            o[2 * v + 1] += ph.x * F[2 * v + 1] + ph.y * F[2 * v];
+                    for (int h = 0; h < 2; ++h) {
+                        const double RR = accC[t][2 * h], IR = accC[t][2 * h + 1];
+                        const double RI = accS[t][2 * h], II = accS[t][2 * h + 1];
+                        const double2 vp = make_double2(RR - II, RI + IR), vm = make_double2(RR + II, IR - RI);
+                        const int64_t th = (tile0 + t) * 2 + h;
+                        double *o = a.spec + th * 512 + lane;
+                        add_spectral(o, first, vp);
+                        add_spectral(o + 256, first, vm);
+                        if (a.amp != nullptr) {
+                            const double c = ((double)(pblk::kRows * (rg * g.na + 2 * t + h)) + 15.5) * g.dq;
+                            add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(c * uk), z);
                         }
                     }
-                }
             }
         }
     }
@@ -240,87 +273,100 @@ __global__ void fill_i32_kernel(int *p, int n, int v)
     if (i < n) p[i] = v;
 }
 
-// Full-detector pixel of pixel p of the evaluated part: the same index (the
-// first rows of a Cartesian detector), or, with nh > 0, column p % nh of row
-// p / nh of a polar detector of 2 nh columns (the half theta < pi).
-__device__ __forceinline__ int64_t full_pixel(int64_t p, int nh)
+// Pixels of a slot tile (t, h), lane column b: (+) and (-), and their mirrors at -q; -1: none.
+template <int POLAR>
+__device__ __forceinline__ void tile_pixels(const CartGeom &cg, const PolGeom &pg, int MT, int64_t th, int b,
+                                            int64_t (&px)[2], int64_t (&mirror)[2])
 {
-    return nh > 0 ? (p / nh) * 2 * nh + p % nh : p;
-}
-
-// out[s][p][v] = scale * sum of the slots of output s (slot_off CSR, ascending);
-// slots hold P pixels, out rows are P_out >= P pixels apart.  nh > 0: the slots
-// hold the half theta < pi of a polar detector, and pixel (i, m + nh) receives
-// conj G of pixel (i, m) (real weights: G(-q) = conj G(q)).
-// A workspace that does not hold the plan's tables (tag mismatch) gives NaN.
-__global__ void spec_reduce_kernel(const unsigned long long *tag_ptr, unsigned long long tag,
-                                   const double *__restrict__ slots, const int *__restrict__ slot_off, int n_out,
-                                   int64_t P, int64_t P_out, int nh, double scale, double *__restrict__ out)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_out * P * 16) return;
-    const int s = (int)(idx / (P * 16));
-    const int64_t pv = idx % (P * 16);
-    const int v = (int)(pv & 15);
-    const int64_t pf = full_pixel(pv >> 4, nh);
-    double *o = out + (int64_t)s * P_out * 16;
-    double val;
-    if (*tag_ptr != tag) {
-        val = __builtin_nan("");
+    px[0] = px[1] = mirror[0] = mirror[1] = -1;
+    const int h = (int)(th & 1), t = (int)((th >> 1) % MT);
+    const int64_t blk = (th >> 1) / MT;
+    if (POLAR) {
+        const int rg = (int)(blk / pg.cols), col = (int)(blk % pg.cols);
+        const int e = 2 * t + h, a = rg * pg.na + e;
+        if (e >= pg.na) return;
+        const int rp = pblk::kRows * a + 16 + b, rm = pblk::kRows * a + 15 - b;
+        if (rp < pg.n0) px[0] = (int64_t)rp * pg.n_out + col;
+        if (rm < pg.n0) px[1] = (int64_t)rm * pg.n_out + col;
+        if (pg.nh > 0)
+            for (int s = 0; s < 2; ++s)
+                if (px[s] >= 0) mirror[s] = px[s] + pg.nh;
     } else {
-        double acc = 0.0;
-        for (int sl = slot_off[s]; sl < slot_off[s + 1]; ++sl) acc += slots[(int64_t)sl * P * 16 + pv];
-        val = scale * acc;
+        const cblk::CellPixels x =
+            cblk::cell_pixels(cg, 4, (int)(blk / cg.nzb), (int)(blk % cg.nzb), 8 * t + 4 * h, b);
+        if (!x.ok) return;
+        px[0] = x.pp;
+        if (x.twoN) px[1] = x.pm;
+        if (x.twoM) {
+            mirror[0] = x.mm;
+            if (x.twoN) mirror[1] = x.mp;
+        }
     }
-    o[pf * 16 + v] = val;
-    if (nh > 0) o[(pf + nh) * 16 + v] = (v >= 5 && (v & 1)) ? -val : val;
 }
 
-// out[i] = NaN for i < n when the workspace tag is not the plan's.
-__global__ void tag_guard_kernel(const unsigned long long *tag_ptr, unsigned long long tag, double *out, int64_t n)
+// out[s][pixel][v] = scale * sum of the slots of output s (slot_off CSR, ascending), one
+// workgroup per (output, tile half, sign), through LDS into pixel order; the mirrored
+// pixels take conj G.  A workspace that does not hold the plan's tables (tag mismatch)
+// gives NaN.
+template <int POLAR>
+__global__ __launch_bounds__(256) void spec_reduce_kernel(const unsigned long long *tag_ptr, unsigned long long tag,
+                                                          const double *__restrict__ slots,
+                                                          const int *__restrict__ slot_off, CartGeom cg, PolGeom pg,
+                                                          int MT, int64_t n_th, int64_t P, double scale,
+                                                          double *__restrict__ out)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && *tag_ptr != tag) out[i] = __builtin_nan("");
-}
-
-// Hermitian completion of spectral matrices on a centro-symmetric Cartesian
-// detector: pixel P - 1 - p sits at -q(p), and with real weights
-// G(-q) = conj G(q): the real diagonal is copied, the imaginary parts of the six
-// upper entries (odd v >= 5) change sign.  Pixels [0, Ph) are given.
-__global__ void mirror_spec_kernel(double *__restrict__ out, int n_out, int64_t P, int64_t Ph)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_out * Ph * 16) return;
-    const int s = (int)(idx / (Ph * 16));
-    const int64_t pv = idx % (Ph * 16);
-    const int64_t p = pv >> 4;
-    const int v = (int)(pv & 15);
-    const int64_t q = P - 1 - p;
-    if (q < Ph) return;
-    double *o = out + (int64_t)s * P * 16;
-    o[q * 16 + v] = (v >= 5 && (v & 1)) ? -o[p * 16 + v] : o[p * 16 + v];
-}
-
-// Coherent total: out = sum of the amplitude slots in order (nh > 0: polar half,
-// pixel (i, m + nh) receives conj A of pixel (i, m)).
-__global__ void amp_reduce_kernel(const unsigned long long *tag_ptr, unsigned long long tag,
-                                  const double *__restrict__ slots, int n_slots, int64_t P, int nh,
-                                  double *__restrict__ out)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= P * 8) return;
-    const int v = (int)(idx & 7);
-    const int64_t pf = full_pixel(idx >> 3, nh);
-    double val;
-    if (*tag_ptr != tag) {
-        val = __builtin_nan("");
-    } else {
-        double s = 0.0;
-        for (int sl = 0; sl < n_slots; ++sl) s += slots[(int64_t)sl * P * 8 + idx];
-        val = s;
+    __shared__ double x[16][17];
+    const int tid = threadIdx.x;
+    const int64_t th = blockIdx.x >> 1;
+    const int sign = blockIdx.x & 1, s = blockIdx.y;
+    {
+        const int lane = tid & 63, e = tid >> 6;
+        double v = __builtin_nan("");
+        if (*tag_ptr == tag) {
+            const double *p = slots + ((th * 2 + sign) * 4 + e) * 64 + lane;
+            double acc = 0.0;
+            for (int sl = slot_off[s]; sl < slot_off[s + 1]; ++sl) acc += p[(int64_t)sl * n_th * 512];
+            v = scale * acc;
+        }
+        x[lane & 15][kPacked[lane >> 4][e]] = v;
     }
-    out[pf * 8 + v] = val;
-    if (nh > 0) out[(pf + nh) * 8 + v] = (v & 1) ? -val : val;
+    __syncthreads();
+    const int b = tid >> 4, v = tid & 15;
+    int64_t px[2], mirror[2];
+    tile_pixels<POLAR>(cg, pg, MT, th, b, px, mirror);
+    const double val = x[b][v];
+    double *o = out + (int64_t)s * P * 16 + v;
+    if (px[sign] >= 0) o[px[sign] * 16] = val;
+    if (mirror[sign] >= 0) o[mirror[sign] * 16] = (v >= 5 && (v & 1)) ? -val : val;
+}
+
+// Coherent total: the amplitude slots summed in order, mirrored pixels conjugated.
+template <int POLAR>
+__global__ __launch_bounds__(256) void amp_reduce_kernel(const unsigned long long *tag_ptr, unsigned long long tag,
+                                                         const double *__restrict__ slots, int n_slots, CartGeom cg,
+                                                         PolGeom pg, int MT, int64_t n_th, double *__restrict__ amp)
+{
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = (int)(idx & 63);
+    const int64_t th = idx >> 6;
+    if (th >= n_th) return;
+    double v[4];
+    const bool ok = *tag_ptr == tag;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = ok ? 0.0 : __builtin_nan("");
+    if (ok)
+        for (int sl = 0; sl < n_slots; ++sl) {
+            const double *p = slots + ((int64_t)sl * n_th + th) * 256 + lane;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
+        }
+    int64_t px[2], mirror[2];
+    tile_pixels<POLAR>(cg, pg, MT, th, lane & 15, px, mirror);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        if (px[s] >= 0) cblk::put_pixel(amp, px[s], lane >> 4, v[2 * s], v[2 * s + 1], false);
+        if (mirror[s] >= 0) cblk::put_pixel(amp, mirror[s], lane >> 4, v[2 * s], -v[2 * s + 1], false);
+    }
 }
 
 int device_cus()
@@ -343,18 +389,28 @@ struct Tables {
     std::vector<int2> items;      // (slot, block), by decreasing cost
 };
 
-Tables make_tables(const Detector &d, const std::vector<int64_t> &off, int64_t K, int64_t W, int64_t n_rot, int mode,
-                   int spec_per_object)
+Tables make_tables(const Detector &d, bool hermitian, const std::vector<int64_t> &off, int64_t K, int64_t W,
+                   int64_t n_rot, int mode, int spec_per_object)
 {
     Tables T;
     ObjectsPlan &p = T.p;
-    const TuneShape ts = current_tune_shape(kTuneObjects, d, W);
-    p.lanes = ts.shape;  // Cartesian: lanes per row; polar: the workgroup shape
-    const int cols = d.kind == NUMAG_GRID_POLAR ? polar_shape_cols(p.lanes) : p.lanes * cart::kB;
-    const int rows = d.kind == NUMAG_GRID_POLAR ? polar_shape_rows(p.lanes) : cart::kThreads / p.lanes;
-    p.col_blocks = (d.n1 + cols - 1) / cols;
-    p.row_blocks = (d.n0 + rows - 1) / rows;
-    const int64_t nblocks = (int64_t)p.col_blocks * p.row_blocks;
+    const TuneShape ts = current_tune_shape(kTuneObjects, objects_detector(d, hermitian), W);
+    if (d.kind == NUMAG_GRID_POLAR) {
+        polar_geometry(d, 4, ts.shape, p.pg, p.mt);
+        p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;
+        p.n_th = p.n_blocks * p.mt * 2;
+    } else {
+        cart_geometry(d, 4, p.cg, p.mt);
+        p.cg.nz = cart_nz(ts.shape);
+        // With one rotation a slot is at least one object, and few objects leave few items:
+        // below six per CU the largest ones set the time, and items of half the columns
+        // (their workgroups' waves share the points) even it out for 9 % more phasors
+        // (96 objects, 256 x 256: 2.69 -> 2.45 ms).
+        if (n_rot == 1 && p.cg.nz == 8 && K * p.cg.nrb * ((p.cg.nzb + 7) / 8) < 6 * 256) p.cg.nz = 4;
+        p.n_blocks = (int64_t)((p.cg.nzb + p.cg.nz - 1) / p.cg.nz) * p.cg.nrb;
+        p.n_th = (int64_t)p.cg.nzb * p.cg.nrb * p.mt * 2;
+    }
+    const int64_t nblocks = p.n_blocks;
     // slot groups wanted (each spans all pixel blocks)
     const int64_t want = std::max<int64_t>(1, (ts.target + nblocks - 1) / std::max<int64_t>(nblocks, 1));
     // object groups: single objects, or contiguous groups of roughly equal point counts
@@ -410,17 +466,8 @@ size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 // they and the accumulators sit in the workspace.
 struct ObjPlanTables {
     Tables T;
-    Detector dk;  // the part of the detector that is summed
     size_t o_off, o_items, o_slots, o_slot_off, o_counter, o_spec, o_amp;
 };
-
-int launch_tag_guard(const unsigned long long *tag_ptr, unsigned long long tag, double *out, int64_t n, hipStream_t st)
-{
-    if (n <= 0) return NUMAG_OK;
-    hipLaunchKernelGGL(tag_guard_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, tag_ptr, tag, out, n);
-    NUMAG_HIP_CHECK(hipGetLastError());
-    return NUMAG_OK;
-}
 
 Detector objects_detector(const Detector &d, bool hermitian)
 {
@@ -435,10 +482,13 @@ Detector objects_detector(const Detector &d, bool hermitian)
 void build_objects_plan(ObjPlan &pl)
 {
     auto c = std::make_shared<ObjPlanTables>();
-    c->dk = objects_detector(pl.d, pl.path == NUMAG_PATH_DIRECT_HERMITIAN);
-    c->T = make_tables(c->dk, pl.off, pl.K, pl.W, pl.n_rot, pl.mode, pl.spec_per_object);
+    const bool hermitian = pl.path == NUMAG_PATH_DIRECT_HERMITIAN;
+    c->T = make_tables(pl.d, hermitian, pl.off, pl.K, pl.W, pl.n_rot, pl.mode, pl.spec_per_object);
     const Tables &T = c->T;
-    const size_t P = (size_t)c->dk.n0 * c->dk.n1;
+    // accumulators of a slot: 256 doubles of spectra and 256 of amplitudes per tile half
+    // and sign pair hold the independent half of the pixels; the whole-detector path asks
+    // for twice that, as a slot of every pixel takes
+    const size_t th = (size_t)T.p.n_th * (hermitian ? 1 : 2);
     size_t used = kPlanTagBytes;
     auto take = [&](size_t bytes) {
         const size_t r = used;
@@ -452,8 +502,8 @@ void build_objects_plan(ObjPlan &pl)
     c->o_slot_off = take(sizeof(int) * T.slot_off.size());
     const size_t image_bytes = used;
     c->o_counter = take(sizeof(int) * 64);
-    c->o_spec = take(sizeof(double) * 16 * (size_t)T.p.n_slots * P);
-    c->o_amp = pl.mode == NUMAG_MODE_SPLIT ? take(sizeof(double) * 8 * (size_t)T.p.n_slots * P) : 0;
+    c->o_spec = take(sizeof(double) * 512 * (size_t)T.p.n_slots * th);
+    c->o_amp = pl.mode == NUMAG_MODE_SPLIT ? take(sizeof(double) * 256 * (size_t)T.p.n_slots * th) : 0;
     pl.ws_bytes = used;
     // host image of the tag and the tables (rotations are filled by the caller)
     pl.image.assign(image_bytes, 0);
@@ -470,10 +520,7 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
 {
     const ObjPlanTables &c = *pl.tables;
     const ObjectsPlan &p = c.T.p;
-    const Detector &d = c.dk;
-    const bool hermitian = pl.path == NUMAG_PATH_DIRECT_HERMITIAN;
-    const int64_t P = (int64_t)d.n0 * d.n1;
-    const int64_t P_full = (int64_t)pl.d.n0 * pl.d.n1;
+    const int64_t P = (int64_t)pl.d.n0 * pl.d.n1;
     char *base = (char *)ws;
     const unsigned long long *tag_ptr = (const unsigned long long *)base;
     const unsigned long long tag = pl.tag;
@@ -481,10 +528,8 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     double *d_spec = (double *)(base + c.o_spec);
     double *d_amp = pl.mode == NUMAG_MODE_SPLIT ? (double *)(base + c.o_amp) : nullptr;
 
-    // zero the accumulators and the counter (kernels, so the sequence can be captured)
-    int rc = launch_fill(d_spec, 16 * (int64_t)p.n_slots * P, 0.0, st);
-    if (rc != NUMAG_OK) return rc;
-    if (d_amp != nullptr && (rc = launch_fill(d_amp, 8 * (int64_t)p.n_slots * P, 0.0, st)) != NUMAG_OK) return rc;
+    // (a kernel, so that the sequence can be captured; the accumulators are written by
+    // the first object of their slot)
     hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, d_counter, 64, 0);
     NUMAG_HIP_CHECK(hipGetLastError());
 
@@ -500,54 +545,54 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     args.items = (const int2 *)(base + c.o_items);
     args.slots = (const int4 *)(base + c.o_slots);
     args.n_items = (int)p.n_items;
-    args.col_blocks = p.col_blocks;
     args.counter = d_counter;
     args.spec = d_spec;
     args.amp = d_amp;
-    const bool pol = d.kind == NUMAG_GRID_POLAR;
-    // persistent grid: as many workgroups as fit the chip at once
-    const int per_cu = pol ? (polar_shape_waves(p.lanes) == 4 ? 2 : 1) : 2;
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(p.n_items, (int64_t)per_cu * device_cus()));
+    const bool pol = pl.d.kind == NUMAG_GRID_POLAR;
+    // persistent grid: as many workgroups as fit the chip at once (two of 4 waves, or one
+    // of 8, per CU)
+    const int64_t fit = (pol ? 2 : 1) * (int64_t)device_cus();
+    const int64_t want = pol ? (p.n_items + pblk::kWaves - 1) / pblk::kWaves : p.n_items;
     {
         TimedLaunch timed(NUMAG_KERNEL_OBJECTS, st);
-        const dim3 g((unsigned)grid);
-        if (pol) {
-            switch (p.lanes) {
-                case 0: hipLaunchKernelGGL((objects_polar_kernel<8, 64, 8, 2>), g, dim3(512), 0, st, args, d); break;
-                case 1: hipLaunchKernelGGL((objects_polar_kernel<4, 64, 8, 1>), g, dim3(256), 0, st, args, d); break;
-                case 2: hipLaunchKernelGGL((objects_polar_kernel<8, 32, 8, 2>), g, dim3(512), 0, st, args, d); break;
-                case 3: hipLaunchKernelGGL((objects_polar_kernel<8, 16, 16, 1>), g, dim3(512), 0, st, args, d); break;
-                default: hipLaunchKernelGGL((objects_polar_kernel<8, 16, 8, 2>), g, dim3(512), 0, st, args, d); break;
-            }
-        } else {
-            switch (p.lanes) {
-                case 8: hipLaunchKernelGGL((objects_kernel<8>), g, dim3(cart::kThreads), 0, st, args, d); break;
-                case 16: hipLaunchKernelGGL((objects_kernel<16>), g, dim3(cart::kThreads), 0, st, args, d); break;
-                case 32: hipLaunchKernelGGL((objects_kernel<32>), g, dim3(cart::kThreads), 0, st, args, d); break;
-                default: hipLaunchKernelGGL((objects_kernel<64>), g, dim3(cart::kThreads), 0, st, args, d); break;
-            }
+        const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, fit)));
+#define NUMAG_LAUNCH_OBJ(MT)                                                                                    \
+    case MT:                                                                                                    \
+        if (pol) hipLaunchKernelGGL((objects_polar_kernel<MT>), g, dim3(pblk::kThreads), 0, st, args, p.pg);     \
+        else hipLaunchKernelGGL((objects_kernel<MT>), g, dim3(cblk::kThreads), 0, st, args, p.cg);              \
+        break
+        switch (p.mt) {
+            NUMAG_LAUNCH_OBJ(1);
+            NUMAG_LAUNCH_OBJ(2);
+            NUMAG_LAUNCH_OBJ(3);
+            NUMAG_LAUNCH_OBJ(4);
+            NUMAG_LAUNCH_OBJ(5);
+            NUMAG_LAUNCH_OBJ(6);
+            NUMAG_LAUNCH_OBJ(7);
+            NUMAG_LAUNCH_OBJ(8);
         }
+#undef NUMAG_LAUNCH_OBJ
     }
     NUMAG_HIP_CHECK(hipGetLastError());
 
-    // the half of a polar detector is mirrored by the reductions, that of a
-    // Cartesian one by the mirror kernels below
-    const int nh = pol && hermitian ? d.n1 : 0;
-    const int64_t n_spec = (int64_t)p.n_out * P * 16;
-    hipLaunchKernelGGL(spec_reduce_kernel, dim3((unsigned)((n_spec + 255) / 256)), dim3(256), 0, st, tag_ptr, tag,
-                       d_spec, (const int *)(base + c.o_slot_off), p.n_out, P, P_full, nh, 1.0 / (double)pl.n_rot,
-                       spec_out);
+    const dim3 gs((unsigned)(p.n_th * 2), p.n_out), ga((unsigned)((p.n_th * 64 + 255) / 256));
+    const int *d_off = (const int *)(base + c.o_slot_off);
+    const double scale = 1.0 / (double)pl.n_rot;
+    if (pol)
+        hipLaunchKernelGGL((spec_reduce_kernel<1>), gs, dim3(256), 0, st, tag_ptr, tag, d_spec, d_off, p.cg, p.pg, p.mt,
+                           p.n_th, P, scale, spec_out);
+    else
+        hipLaunchKernelGGL((spec_reduce_kernel<0>), gs, dim3(256), 0, st, tag_ptr, tag, d_spec, d_off, p.cg, p.pg, p.mt,
+                           p.n_th, P, scale, spec_out);
     NUMAG_HIP_CHECK(hipGetLastError());
     if (d_amp != nullptr) {
-        hipLaunchKernelGGL(amp_reduce_kernel, dim3((unsigned)((P * 8 + 255) / 256)), dim3(256), 0, st, tag_ptr, tag,
-                           d_amp, p.n_slots, P, nh, amp_out);
+        if (pol)
+            hipLaunchKernelGGL((amp_reduce_kernel<1>), ga, dim3(256), 0, st, tag_ptr, tag, d_amp, p.n_slots, p.cg, p.pg,
+                               p.mt, p.n_th, amp_out);
+        else
+            hipLaunchKernelGGL((amp_reduce_kernel<0>), ga, dim3(256), 0, st, tag_ptr, tag, d_amp, p.n_slots, p.cg, p.pg,
+                               p.mt, p.n_th, amp_out);
         NUMAG_HIP_CHECK(hipGetLastError());
-    }
-    if (hermitian && !pol) {
-        hipLaunchKernelGGL(mirror_spec_kernel, dim3((unsigned)((n_spec + 255) / 256)), dim3(256), 0, st, spec_out,
-                           p.n_out, P_full, P);
-        NUMAG_HIP_CHECK(hipGetLastError());
-        if (amp_out != nullptr && d_amp != nullptr) return launch_mirror_cartesian(amp_out, P_full, P, st);
     }
     return NUMAG_OK;
 }

@@ -20,21 +20,21 @@ static int shape_blocks(int shape)
     return blocks[shape];
 }
 
-struct PolarRecLoader {
-    const PointRec *__restrict__ pts;
-};
 template <int CH>
-struct PolarRecLoaderCh : PolarRecLoader {
-    __device__ __forceinline__ cblk::Point<CH> load(int64_t j) const
+struct PolarRecLoader {
+    using Raw = cblk::Point<CH>;
+    const PointRec *__restrict__ pts;
+    __device__ __forceinline__ Raw raw(int64_t j) const
     {
         const PointRec &r = pts[j];
-        cblk::Point<CH> p;
+        Raw p;
         p.m = r.Y;
         p.n = r.Z;
 #pragma unroll
         for (int c = 0; c < CH; ++c) p.w[c] = r.w[cblk::ch_first<CH>() + c];
         return p;
     }
+    __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const { return r; }
 };
 
 // One wave: one theta column, one row group, one point range.  Partials
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(const P
     sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
-    pblk::accumulate<MT, CH>(PolarRecLoaderCh<CH>{{pts}}, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC,
+    pblk::accumulate<MT, CH>(PolarRecLoader<CH>{pts}, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC,
                              accS);
 #pragma unroll
     for (int t = 0; t < MT; ++t)
@@ -108,7 +108,7 @@ int default_polar_shape(const Detector &d)
     return d.n0 <= 128 ? 2 : d.n0 <= 256 ? 3 : 4;
 }
 
-static void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int &mt)
+void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int &mt)
 {
     g.n0 = d.n0;
     g.n_out = d.n_theta;

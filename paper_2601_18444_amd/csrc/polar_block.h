@@ -132,8 +132,8 @@ __device__ __forceinline__ void wave_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Adds the points [jbeg, jend) of `ld` (Point<CH> load(j): m = Y, n = Z) to the wave's
-// tiles: theta direction (sth, cth), row blocks from a0 on.
+// Adds the points [jbeg, jend) of `ld` (the loader concept of cartesian_block.h with
+// m = Y, n = Z) to the wave's tiles: theta direction (sth, cth), row blocks from a0 on.
 template <int MT, int CH, class Loader>
 __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, double sth, double cth,
                                            double dq, int a0, WaveSmem<MT, CH> &sm, v4d (&accC)[MT],
@@ -151,17 +151,18 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         wc[t] = s % CH;
     }
     auto fetch = [&](int64_t j0) {
-        Point<CH> p{};
-        if (j0 + gp < jend) p = ld.load(j0 + gp);
-        return p;
+        typename Loader::Raw r{};
+        if (j0 + gp < jend) r = ld.raw(j0 + gp);
+        return r;
     };
-    Point<CH> p = fetch(jbeg);
+    typename Loader::Raw raw = fetch(jbeg);
 #pragma unroll 1
     for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk) {
+        const Point<CH> p = ld.point(raw);
         const double u = p.m * sth + p.n * cth;
         generate<MT, CH>(sm, a0, dq, u, p);
         wave_fence();
-        p = fetch(j0 + kChunk);
+        raw = fetch(j0 + kChunk);
         const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
 #pragma unroll 1
         for (int s = 0; s < steps; ++s) {

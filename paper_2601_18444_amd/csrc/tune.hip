@@ -14,8 +14,7 @@
 //   direct, polar detector: 1, 0, 2, 3 or 4 for 1, 2, 4, 8 or 16 blocks of 32 q rows
 //     per wave, and the workgroups aimed for;
 //   adjoint: the workgroups aimed for (point blocks x detector ranges);
-//   objects (persistent kernel): lanes per detector row (polar: the workgroup
-//     shape) and the work items aimed for.
+//   objects (persistent kernel): the direct kernels' shapes and the work items aimed for.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
