@@ -21,10 +21,10 @@
 // its first operand, so a wave's operand load is one 16-byte read per lane and tile.
 //
 // Measured, kernel time before (a lane walking the detector rows of four points with a
-// two-term recurrence) and now: 262,144 points, 256 x 256: 6.14 -> 2.05 ms (67 of the
+// two-term recurrence) and now: 262,144 points, 256 x 256: 6.14 -> 2.01 ms (68 of the
 // card's 74.7 TFLOP/s; 2.37 with the coefficients staged through registers, which
 // spilled); error of the gradient against 64 bits 8.2e-14 -> 6.6e-15, the walk of 256
-// columns being gone.  20,000 points, 150 x 181 polar: 228 -> 229 us: every column of an
+// columns being gone.  20,000 points, 150 x 181 polar: 228 -> 226 us: every column of an
 // odd detector is summed, so the multiply-adds fall only from 10 to 8 per term and the
 // column tables (about 200 vector instructions per 32 points and column) take the rest;
 // an even detector needs half of both.
@@ -250,7 +250,8 @@ __global__ __launch_bounds__(kAdjThreads, 2) void adjoint_cartesian_kernel(
             for (int u = 0; u < kAdjNP; ++u) acc[t][u] = cblk::v4d{0.0, 0.0, 0.0, 0.0};
         double2 ctr[kAdjNP];
 #pragma unroll
-        for (int u = 0; u < kAdjNP; ++u) ctr[u] = twiddle(qc * n[u]);
+        for (int u = 0; u < kAdjNP; ++u)
+            ctr[u] = phasor(half_turns(qc), n[u], fabs(n[u]) < phasor_range(fabs(g.originN) + 32.0 * g.stepN));
 #pragma unroll 1
         for (int v = v0; v < v1; ++v, ++i) {
             if (i + 1 < total) stage(i + 1);  // arrives under the products
@@ -281,7 +282,8 @@ __global__ __launch_bounds__(kAdjThreads, 2) void adjoint_cartesian_kernel(
 #pragma unroll
         for (int u = 0; u < kAdjNP; ++u) {
             double2 y, dm;
-            twiddle2(qm * m[u], g.stepM * m[u], y, dm);
+            phasor2(half_turns(qm), m[u], half_turns(g.stepM), m[u],
+                    fabs(m[u]) < phasor_range(fabs(g.originM) + 32.0 * g.stepM), y, dm);
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -365,7 +367,10 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
         double2 first, step;  // centre of the group's first block, centre step (second half)
         pblk::offsets(tab.off, g.dq, u0, first, step);
         double2 adv = make_double2(1.0, 0.0);  // from one row group to the next
-        if (g.nrg > 1) adv = twiddle((double)(pblk::kRows * g.na) * g.dq * u0);
+        if (g.nrg > 1) {
+            const double q = (double)(pblk::kRows * g.na) * g.dq;
+            adv = phasor(half_turns(q), u0, fabs(u0) < phasor_range(q));
+        }
 #pragma unroll 1
         for (int rg = 0; rg < g.nrg; ++rg) {
             if (half != 0) pblk::centres<2 * MT>(tab.ctr[gp], first, step);

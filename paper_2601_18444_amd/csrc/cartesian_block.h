@@ -124,9 +124,11 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     const int zi = wave % g.nz, kg = wave / g.nz, nk = kWaves / g.nz;
     const bool active = zb0 + zi < g.nzb;
     const int r16 = lane & 15, kq = lane >> 4;
-    // phase of this lane's column entry: an offset (first half) or a block centre
-    const double qn = half == 0 ? ((double)wave + 0.5) * g.stepN
-                                : g.originN + ((double)(g.nN - g.B + kOff * (zb0 + wave)) + 7.5) * g.stepN;
+    // coefficient of this lane's column entry: an offset (first half) or a block centre
+    const HalfTurns qn = half_turns(half == 0 ? ((double)wave + 0.5) * g.stepN
+                                              : g.originN + ((double)(g.nN - g.B + kOff * (zb0 + wave)) + 7.5) * g.stepN);
+    // (block centres and rows may lie up to a block beyond the detector)
+    const double range = phasor_range(fmax(fabs(g.originM) + (16.0 * kMaxMT) * g.stepM, fabs(g.originN) + 256.0 * g.stepN));
 
     auto put_row = [&](int b, const Point<CH> &p, int e, double2 y) {
         if (e < g.na) {
@@ -138,11 +140,12 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
             }
         }
     };
-    const double qm0 = axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * wave + half, g.stepM);
+    const HalfTurns qm0 = half_turns(axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * wave + half, g.stepM));
     auto generate = [&](int b, const typename Loader::Raw &raw) {
         const Point<CH> p = ld.point(raw);
+        const bool fast = fmax(fabs(p.m), fabs(p.n)) < range && p.m == p.m && p.n == p.n;
         double2 z, y;
-        twiddle2(qn * p.n, qm0 * p.m, z, y);
+        phasor2(qn, p.n, qm0, p.m, fast, z, y);
         if (half == 0) {
             sm.off[b][gp][8 + wave] = z;
             sm.off[b][gp][7 - wave] = make_double2(z.x, -z.y);
@@ -152,26 +155,36 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         put_row(b, p, 2 * wave + half, y);
 #pragma unroll 1
         for (int e0 = 2 * (wave + kWaves); e0 < g.na; e0 += 2 * kWaves) {
-            const double q = axis_value(g.originM, g.nM - g.A + rb * g.na + e0 + half, g.stepM);
-            put_row(b, p, e0 + half, twiddle(q * p.m));
+            const HalfTurns q = half_turns(axis_value(g.originM, g.nM - g.A + rb * g.na + e0 + half, g.stepM));
+            put_row(b, p, e0 + half, phasor(q, p.m, fast));
         }
     };
+    // point group kg takes 8 / nk consecutive steps of a chunk
     auto sum = [&](int b, int np) {
-        const int steps = active ? (np + 3) >> 2 : 0;
-#pragma unroll 1
-        for (int s = kg; s < steps; s += nk) {
-            const int pt = 4 * s + kq;
-            const double *yp = &sm.y[b][pt][r16];
+        const int s0 = kg * (kChunk / 4) / nk;
+        const int steps = active ? min((kChunk / 4) / nk, ((np + 3) >> 2) - s0) : 0;
+        const double *yp = &sm.y[b][4 * s0 + kq][r16];
+        const double2 *cp = &sm.ctr[b][4 * s0 + kq][zi], *op = &sm.off[b][4 * s0 + kq][r16];
+        auto step = [&](int s) {
             double a[MT];
 #pragma unroll
-            for (int t = 0; t < MT; ++t) a[t] = yp[16 * t];
-            const double2 z = cmul(sm.ctr[b][pt][zi], sm.off[b][pt][r16]);
+            for (int t = 0; t < MT; ++t) a[t] = yp[s * 4 * (16 * MT + 1) + 16 * t];
+            const double2 z = cmul(cp[s * 4 * (kWaves + 1)], op[s * 4 * (kOff + 1)]);
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 accC[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.x, accC[t], 0, 0, 0);
                 accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.y, accS[t], 0, 0, 0);
             }
+        };
+        // four at a time: the LDS addresses are then offsets of one register
+        int s = 0;
+        for (; s + 4 <= steps; s += 4) {
+            step(s);
+            step(s + 1);
+            step(s + 2);
+            step(s + 3);
         }
+        for (; s < steps; ++s) step(s);
     };
 
     generate(0, p);

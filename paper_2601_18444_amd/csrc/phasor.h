@@ -95,22 +95,105 @@ __host__ __device__ __forceinline__ double2 twiddle(double phi)
     return make_double2(c, -s);
 }
 
-// Two unit phasors at once: one range check, and the two chains interleave.
-__device__ __forceinline__ void twiddle2(double p0, double p1, double2 &e0, double2 &e1)
+// ---------------------------------------------------------------------------
+// Unit phasors exp(-i q x) for a coefficient q that many x share (the sum kernels'
+// generation phases, where on gfx950 every vector instruction takes time from the matrix
+// instructions of its SIMD).  q is held in half turns, q / pi = hi + lo, so the reduction
+// is k = rint(hi x), r = (hi x - k) + lo x with fused products: |r| <= 1/2, free of the
+// rounding of the phase itself.  exp(-i q x) = (-1)^k (cos(pi r), -sin(pi r)), both by
+// polynomials in r^2 (Chebyshev interpolants on [0, 1/4], truncation 3e-19 and 1.5e-17;
+// the parity is one shift and two exclusive ors).  22 FP64 and 4 integer instructions,
+// against 46 for a sine and cosine reduced to a quarter turn.  The Horner constants are
+// scalar operands: left to itself the compiler keeps them in vector registers and copies
+// each into the accumulating form of the FMA.  Measured against that sine and cosine
+// (with the sum loops read by constant LDS offsets): 24,000 points, 1000 x 1000 polar
+// 3.40 -> 3.30 ms; adjoint of 262,144 points, 256 x 256, 2.05 -> 2.01 ms.
+// ---------------------------------------------------------------------------
+struct HalfTurns {
+    double hi, lo;
+};
+
+__host__ __device__ __forceinline__ HalfTurns half_turns(double q)
 {
-    double s0, c0, s1, c1;
-    if (__builtin_expect(!(sincos_fast_range(p0) && sincos_fast_range(p1)), 0)) {
-        const double2 r0 = sincos_library(p0), r1 = sincos_library(p1);
-        s0 = r0.x;
-        c0 = r0.y;
-        s1 = r1.x;
-        c1 = r1.y;
+    constexpr double kHi = 0x1.45f306dc9c883p-2, kLo = -0x1.6b01ec5417056p-56;  // 1 / pi
+    HalfTurns t;
+    t.hi = q * kHi;
+    t.lo = fma(q, kLo, fma(q, kHi, -t.hi));
+    return t;
+}
+
+// a b + c with c a scalar constant
+__host__ __device__ __forceinline__ double fma_const(double a, double b, double c)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+#else
+    return fma(a, b, c);
+#endif
+}
+
+// |hi x| < 2^30 (the parity of k is taken from its integer conversion).
+__host__ __device__ __forceinline__ double2 phasor_fast(HalfTurns q, double x)
+{
+    const double t = q.hi * x;
+    const double k = rint(t);
+    const double r = fma(q.lo, x, fma(q.hi, x, -k));
+    const double w = r * r;
+    double s = fma_const(-0x1.9d462020fcc78p-21, w, 0x1.6f7acdb8f6580p-16);  // -sin(pi r) / r
+    s = fma_const(s, w, -0x1.e8f3675ee37ddp-12);
+    s = fma_const(s, w, 0x1.e3074dfaf87afp-8);
+    s = fma_const(s, w, -0x1.5078348551854p-4);
+    s = fma_const(s, w, 0x1.32d2cce627c86p-1);
+    s = fma_const(s, w, -0x1.466bc6775aa7dp+1);
+    s = fma_const(s, w, 0x1.4abbce625be52p+2);
+    s = fma_const(s, w, -0x1.921fb54442d18p+1);
+    s *= r;
+    double c = fma_const(0x1.179a329ef4140p-18, w, -0x1.b6a6feabe52e9p-14);  // (cos(pi r) - 1) / r^2
+    c = fma_const(c, w, 0x1.f9d2c1f3b2167p-10);
+    c = fma_const(c, w, -0x1.a6d1f12b0bef2p-6);
+    c = fma_const(c, w, 0x1.e1f5068620bcbp-3);
+    c = fma_const(c, w, -0x1.55d3c7e3c9051p+0);
+    c = fma_const(c, w, 0x1.03c1f081b5a9fp+2);
+    c = fma_const(c, w, -0x1.3bd3cc9be45dep+2);
+    c = fma(c, w, 1.0);
+    const long long odd = (long long)((unsigned long long)(unsigned int)(int)k << 63);
+#ifdef __HIP_DEVICE_COMPILE__
+    return make_double2(__longlong_as_double(__double_as_longlong(c) ^ odd),
+                        __longlong_as_double(__double_as_longlong(s) ^ odd));
+#else
+    return odd ? make_double2(-c, -s) : make_double2(c, s);
+#endif
+}
+
+// Largest |x| the fast form takes for coefficients up to |q|.
+__host__ __device__ __forceinline__ double phasor_range(double q) { return 0x1p30 / (fabs(q) * 0.3183098861837907 + 0x1p-900); }
+
+// exp(-i q x) through the library (any x; NaN for NaN and infinities), out of line.
+__host__ __device__ __attribute__((noinline)) static double2 phasor_library(HalfTurns q, double x)
+{
+    double s, c;
+    sincos((q.hi * 3.141592653589793) * x, &s, &c);
+    return make_double2(c, -s);
+}
+
+// Two phasors; `fast` is whether both arguments are in range.
+__device__ __forceinline__ void phasor2(HalfTurns q0, double x0, HalfTurns q1, double x1, bool fast, double2 &e0,
+                                        double2 &e1)
+{
+    if (__builtin_expect(!fast, 0)) {
+        e0 = phasor_library(q0, x0);
+        e1 = phasor_library(q1, x1);
     } else {
-        sincos_fast(p0, &s0, &c0);
-        sincos_fast(p1, &s1, &c1);
+        e0 = phasor_fast(q0, x0);
+        e1 = phasor_fast(q1, x1);
     }
-    e0 = make_double2(c0, -s0);
-    e1 = make_double2(c1, -s1);
+}
+
+__device__ __forceinline__ double2 phasor(HalfTurns q, double x, bool fast)
+{
+    return __builtin_expect(!fast, 0) ? phasor_library(q, x) : phasor_fast(q, x);
 }
 
 // origin + i * step

@@ -67,7 +67,7 @@ __device__ __forceinline__ double2 next_term(double k2, double2 x, double2 befor
 __device__ __forceinline__ void offsets(double2 (*off)[17], double dq, double u, double2 &centre, double2 &step)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
-    double2 x = twiddle((half == 0 ? 0.5 : 15.5) * dq * u);
+    double2 x = phasor(half_turns((half == 0 ? 0.5 : 15.5) * dq), u, fabs(u) < phasor_range(16.0 * dq));
     centre = x;
     double2 st = cmul(x, x);  // dq u in the first half
     const double2 so = make_double2(other_half(st.x), other_half(st.y));
@@ -114,7 +114,10 @@ __device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int a0, double dq
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
     double2 centre, step, first = make_double2(1.0, 0.0);
     offsets(sm.off, dq, u, centre, step);
-    if (a0 != 0) first = twiddle((double)(kRows * a0) * dq * u);  // wave-uniform
+    if (a0 != 0) {  // wave-uniform
+        const double q = (double)(kRows * a0) * dq;
+        first = phasor(half_turns(q), u, fabs(u) < phasor_range(q));
+    }
     if (half != 0) {
         if (a0 != 0) centre = cmul(centre, first);
         centres<max_na<MT, CH>()>(sm.ctr[gp], centre, step);
@@ -164,26 +167,35 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         wave_fence();
         raw = fetch(j0 + kChunk);
         const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
-#pragma unroll 1
-        for (int s = 0; s < steps; ++s) {
-            const int pt = 4 * s + kq;
-            const double2 z = sm.off[pt][r16];
-            const double *cp = (const double *)&sm.ctr[pt][0] + part;
+        const double2 *op = &sm.off[kq][r16], *cp = &sm.ctr[kq][0];
+        const double *wp = &sm.w[kq][0];
+        auto step = [&](int s) {
+            const double2 z = op[s * 4 * 17];
+            const double *c = (const double *)(cp + s * 4 * (max_na<MT, CH>() + 1)) + part;
+            const double *w = wp + s * 4 * (CH + 1);
             double a[MT];
             if (CH == 3) {
 #pragma unroll
-                for (int t = 0; t < MT; ++t) a[t] = cp[2 * ea[t]] * sm.w[pt][wc[t]];
+                for (int t = 0; t < MT; ++t) a[t] = c[2 * ea[t]] * w[wc[t]];
             } else {
-                const double w = sm.w[pt][wc[0]];
+                const double w0 = w[wc[0]];
 #pragma unroll
-                for (int t = 0; t < MT; ++t) a[t] = cp[2 * ea[t]] * w;
+                for (int t = 0; t < MT; ++t) a[t] = c[2 * ea[t]] * w0;
             }
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 accC[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.x, accC[t], 0, 0, 0);
                 accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.y, accS[t], 0, 0, 0);
             }
+        };
+        int s = 0;
+        for (; s + 4 <= steps; s += 4) {
+            step(s);
+            step(s + 1);
+            step(s + 2);
+            step(s + 3);
         }
+        for (; s < steps; ++s) step(s);
         wave_fence();
     }
 }

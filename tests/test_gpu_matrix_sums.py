@@ -69,3 +69,24 @@ def test_polar_tiles(orc, n0, n1, chan):
     for W, shape in zip([1, 31, 32, 33, 130, 517], shapes):
         for path in (numag.PATH_DIRECT, numag.PATH_DIRECT_HERMITIAN)[: 1 if n1 % 2 else 2]:
             _check(orc, 1, n0, n1, W, chan, shape, path)
+
+
+@pytest.mark.parametrize("kind,n0,n1", [(0, 33, 40), (1, 40, 12)])
+@pytest.mark.parametrize("scale", [1e-6, 1e4, 3e10])
+def test_far_points(orc, kind, n0, n1, scale):
+    """Phases from far below one turn to beyond the range of the fast phasor (2^30 half
+    turns, where the library's sine and cosine take over); a non-finite position gives
+    non-finite sums.  The tolerance grows with the phase as in _check."""
+    rng = np.random.default_rng(5)
+    W, qmax = 45, 1.3
+    pos, nuc, mag = scale * rng.uniform(-1, 1, (W, 3)), rng.standard_normal(W), rng.standard_normal((W, 3))
+    grid = numag.qgrid(kind, n0, n1, qmax)
+    amp, _ = numag.amplitudes(numag.Sample(pos=pos, nuc=nuc, mag=mag, device=DEV), grid)
+    qy, qz, _ = orc.pixels(kind, n0, n1, qmax)
+    ref = orc.amplitudes(pos, nuc, mag, qy, qz)
+    w = np.concatenate([nuc[:, None], mag], axis=1)
+    tol = 2.0 ** -52 * (8 * qmax * scale + W + 128) * np.abs(w).sum(0)
+    assert np.all(np.abs(amp_to_complex(amp[0]) - ref).max(0) <= tol)
+    pos[7, 2] = np.inf
+    bad, _ = numag.amplitudes(numag.Sample(pos=pos, nuc=nuc, mag=mag, device=DEV), grid)
+    assert not torch.isfinite(bad[0, -1]).all()
