@@ -197,78 +197,98 @@ __device__ __forceinline__ int cart_bin(double qy, double qz, double dq, double 
 }
 
 constexpr int kAzThreads = 256;
+constexpr int kAzCart = 512;  // threads of the Cartesian kernel
+constexpr int kAzLanes = 8;   // lanes per detector row
+constexpr int kAzSets = 4;    // data sets per workgroup
 
-// One workgroup per (data set, bin).  Candidate pixels are the bounding rows of
-// the annulus and, per row, the two column intervals it can cover (widened by
-// two columns); the exact bin test decides membership.
-__global__ __launch_bounds__(kAzThreads) void azimuthal_cartesian_kernel(
-    Detector d, const double *__restrict__ f, int n_bins, double qmax_avg, double *__restrict__ I,
+// One workgroup per bin and group of four data sets, so that the membership of a pixel
+// is decided once for the group.  Candidate pixels are the bounding rows of the annulus
+// and, per row, the two column intervals it can cover (rounded outwards); they are
+// shared by eight lanes, so that the long runs of the rows that touch the annulus from
+// inside do not wait on one, and their pixels are loaded before they are tested.  The
+// squared radius decides all candidates but those within
+// 1e-12 of a bin edge; for these the exact bin test does.  Latency bound (square roots and
+// divisions in FP64): 13 data sets, 256 x 256 pixels in 128 bins, 28 -> 12 us;
+// 48 x 81 in 24 bins, 10.7 -> 5.6 us (one lane per row, one data set per workgroup before).
+__global__ __launch_bounds__(kAzCart) void azimuthal_cartesian_kernel(
+    Detector d, const double *__restrict__ f, int n_f, int n_bins, double qmax_avg, double *__restrict__ I,
     int64_t *__restrict__ count)
 {
     const int b = blockIdx.x;
-    const int set = blockIdx.y;
+    const int set0 = blockIdx.y * kAzSets, ns = min(kAzSets, n_f - set0);
     const int64_t P = (int64_t)d.n0 * d.n1;
-    const double *fs = f + (int64_t)set * P;
     const double dq = qmax_avg / (double)n_bins;
     const double r_in = (double)b * dq;
     const double r_out = (b == n_bins - 1) ? qmax_avg : (double)(b + 1) * dq;
-
-    double sum = 0.0;
-    long long cnt = 0;
-    // index range of an axis covering [lo, hi] (with margin)
-    auto idx_lo = [](double v, double origin, double step, int n) {
+    constexpr double kSlack = 1e-12;
+    const double in2 = r_in * r_in, out2 = r_out * r_out;
+    double sum[kAzSets] = {};
+    int cnt = 0;
+    // index range of an axis covering [lo, hi]
+    auto idx_lo = [](double v, double origin, double step, double inv, int n) {
         if (step == 0.0) return 0;
-        double x = floor((v - origin) / step) - 2.0;
+        double x = floor((v - origin) * inv);
         return (int)fmax(0.0, fmin((double)(n - 1), x));
     };
-    auto idx_hi = [](double v, double origin, double step, int n) {
+    auto idx_hi = [](double v, double origin, double step, double inv, int n) {
         if (step == 0.0) return n - 1;
-        double x = ceil((v - origin) / step) + 2.0;
+        double x = ceil((v - origin) * inv);
         return (int)fmax(0.0, fmin((double)(n - 1), x));
     };
-    const int i_lo = idx_lo(-r_out, d.origin0, d.step0, d.n0);
-    const int i_hi = idx_hi(r_out, d.origin0, d.step0, d.n0);
-    for (int i = i_lo + (int)threadIdx.x; i <= i_hi; i += kAzThreads) {
+    const double inv0 = 1.0 / d.step0, inv1 = 1.0 / d.step1;
+    const int i_lo = idx_lo(-r_out, d.origin0, d.step0, inv0, d.n0);
+    const int i_hi = idx_hi(r_out, d.origin0, d.step0, inv0, d.n0);
+    for (int i = i_lo + (int)threadIdx.x / kAzLanes; i <= i_hi; i += kAzCart / kAzLanes) {
         const double qy = axis_value(d.origin0, i, d.step0);
         const double y2 = qy * qy;
-        const double c_out = sqrt(fmax(0.0, r_out * r_out - y2));
-        const double c_in = (r_in * r_in > y2) ? sqrt(r_in * r_in - y2) : 0.0;
-        // right interval [c_in, c_out] and left interval [-c_out, -c_in]
-        for (int side = 0; side < 2; ++side) {
-            const double lo = side == 0 ? c_in : -c_out;
-            const double hi = side == 0 ? c_out : -c_in;
-            int k_lo = idx_lo(lo, d.origin1, d.step1, d.n1);
-            int k_hi = idx_hi(hi, d.origin1, d.step1, d.n1);
-            if (side == 1) {
-                // avoid visiting columns twice where the intervals overlap
-                const int r_lo = idx_lo(c_in, d.origin1, d.step1, d.n1);
-                if (k_hi >= r_lo) k_hi = r_lo - 1;
-            }
-            for (int k = k_lo; k <= k_hi; ++k) {
-                const double qz = axis_value(d.origin1, k, d.step1);
-                if (cart_bin(qy, qz, dq, qmax_avg, n_bins) == b) {
-                    sum += fs[(int64_t)i * d.n1 + k];
-                    ++cnt;
-                }
+        const double c_out = sqrt(fmax(0.0, out2 - y2));
+        const double c_in = (in2 > y2) ? sqrt(in2 - y2) : 0.0;
+        // right interval [c_in, c_out] and what it leaves of the left one [-c_out, -c_in]
+        const int r_lo = idx_lo(c_in, d.origin1, d.step1, inv1, d.n1);
+        const int r_hi = idx_hi(c_out, d.origin1, d.step1, inv1, d.n1);
+        const int l_lo = idx_lo(-c_out, d.origin1, d.step1, inv1, d.n1);
+        const int l_hi = min(idx_hi(-c_in, d.origin1, d.step1, inv1, d.n1), r_lo - 1);
+        const int nr = max(0, r_hi - r_lo + 1), nl = max(0, l_hi - l_lo + 1);
+        for (int e = (int)threadIdx.x % kAzLanes; e < nr + nl; e += kAzLanes) {
+            const int k = e < nr ? r_lo + e : l_lo + (e - nr);
+            const double *src = f + (int64_t)set0 * P + (int64_t)i * d.n1 + k;
+            double v[kAzSets];
+#pragma unroll
+            for (int s = 0; s < kAzSets; ++s) v[s] = src[(int64_t)min(s, ns - 1) * P];
+            const double qz = axis_value(d.origin1, k, d.step1);
+            const double q2 = qz * qz + y2;
+            if (q2 < in2 * (1.0 - kSlack) || q2 > out2 * (1.0 + kSlack)) continue;
+            const bool inside = q2 > in2 * (1.0 + kSlack) && q2 < out2 * (1.0 - kSlack);
+            if (inside || cart_bin(qy, qz, dq, qmax_avg, n_bins) == b) {
+#pragma unroll
+                for (int s = 0; s < kAzSets; ++s) sum[s] += v[s];
+                ++cnt;
             }
         }
     }
-    __shared__ double s_sum[kAzThreads];
-    __shared__ long long s_cnt[kAzThreads];
-    s_sum[threadIdx.x] = sum;
-    s_cnt[threadIdx.x] = cnt;
+    constexpr int kWaves = kAzCart / 64;
+    __shared__ double s_sum[kAzSets][kWaves];
+    __shared__ int s_cnt[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int s = 0; s < kAzSets; ++s) {
+        const double t = wave_sum(sum[s]);
+        if (lane == 0) s_sum[s][wave] = t;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
+    if (lane == 0) s_cnt[wave] = cnt;
     __syncthreads();
-    for (int w = kAzThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            s_sum[threadIdx.x] += s_sum[threadIdx.x + w];
-            s_cnt[threadIdx.x] += s_cnt[threadIdx.x + w];
+    const int s = threadIdx.x;
+    if (s < ns) {
+        long long n = 0;
+        double t = 0.0;
+        for (int w = 0; w < kWaves; ++w) {
+            n += s_cnt[w];
+            t += s_sum[s][w];
         }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const long long n = s_cnt[0];
-        I[(int64_t)set * n_bins + b] = n > 0 ? s_sum[0] / (double)n : __builtin_nan("");
-        if (count != nullptr && set == 0) count[b] = n;
+        I[(int64_t)(set0 + s) * n_bins + b] = n > 0 ? t / (double)n : __builtin_nan("");
+        if (count != nullptr && set0 + s == 0) count[b] = n;
     }
 }
 
@@ -305,41 +325,66 @@ int launch_azimuthal(const Detector &d, const double *f, int n_f, int n_bins, do
                      double *I, int64_t *count, hipStream_t s)
 {
     if (n_f <= 0 || n_bins <= 0) return NUMAG_OK;
-    dim3 grid(n_bins, n_f);
     if (d.kind == NUMAG_GRID_CARTESIAN)
-        hipLaunchKernelGGL(azimuthal_cartesian_kernel, grid, dim3(kAzThreads), 0, s, d, f, n_bins,
-                           qmax_avg, I, count);
+        hipLaunchKernelGGL(azimuthal_cartesian_kernel, dim3(n_bins, (n_f + kAzSets - 1) / kAzSets), dim3(kAzCart), 0,
+                           s, d, f, n_f, n_bins, qmax_avg, I, count);
     else
-        hipLaunchKernelGGL(azimuthal_polar_kernel, grid, dim3(kAzThreads), 0, s, d, f, n_bins, I, count);
+        hipLaunchKernelGGL(azimuthal_polar_kernel, dim3(n_bins, n_f), dim3(kAzThreads), 0, s, d, f, n_bins, I, count);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }
 
 // ---------------------------------------------------------------------------
-// correlation functions (trapezoid in the order of the samples)
+// correlation functions (trapezoid in the order of the samples, empty bins skipped)
 // ---------------------------------------------------------------------------
-__global__ void correlation_kernel(const double *__restrict__ q, const double *__restrict__ Iq, int n_q,
-                                   int n_f, const double *__restrict__ r, int n_r, double scale,
-                                   double *__restrict__ c, double *__restrict__ p)
+// One wave per data set and radius, a lane per sample: the lower end of a lane's interval
+// is the last valid sample before it (a ballot finds the lane, the wave's previous 64
+// samples hand theirs on).  One thread per radius walked all samples, a division and a
+// sine each: 2 data sets, 200 samples, 256 radii 74 -> 5.0 us.
+__global__ __launch_bounds__(256) void correlation_kernel(const double *__restrict__ q, const double *__restrict__ Iq,
+                                                          int n_q, int n_f, const double *__restrict__ r, int n_r,
+                                                          double scale, double *__restrict__ c,
+                                                          double *__restrict__ p)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_f * n_r) return;
-    const int s = (int)(idx / n_r), t = (int)(idx % n_r);
-    const double rt = r[t];
-    double prev_q = 0.0, prev_y = 0.0, sum = 0.0;
-    for (int b = 0; b < n_q; ++b) {
-        const double Ib = Iq[(int64_t)s * n_q + b];
-        if (isnan(Ib)) continue;
-        const double x = q[b] * rt;
-        const double j0 = (x == 0.0) ? 1.0 : sin(x) / x;
-        const double y = Ib * q[b] * q[b] * j0;
-        sum += 0.5 * (q[b] - prev_q) * (y + prev_y);
-        prev_q = q[b];
-        prev_y = y;
+    const int lane = threadIdx.x & 63;
+    for (int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); idx < (int64_t)n_f * n_r;
+         idx += (int64_t)gridDim.x * 4) {
+        const int s = (int)(idx / n_r), t = (int)(idx % n_r);
+        const double rt = r[t];
+        double carry_q = 0.0, carry_y = 0.0, sum = 0.0;
+        for (int b0 = 0; b0 < n_q; b0 += 64) {
+            const int b = b0 + lane;
+            double qb = 0.0, y = 0.0;
+            bool valid = false;
+            if (b < n_q) {
+                const double Ib = Iq[(int64_t)s * n_q + b];
+                valid = !isnan(Ib);
+                qb = q[b];
+                const double x = qb * rt;
+                const double j0 = (x == 0.0) ? 1.0 : sin(x) / x;
+                y = Ib * qb * qb * j0;
+            }
+            const unsigned long long mask = __ballot(valid), below = mask & ((1ull << lane) - 1);
+            const int from = below != 0 ? 63 - __builtin_clzll(below) : 0;
+            double prev_q = __shfl(qb, from), prev_y = __shfl(y, from);
+            if (below == 0) {
+                prev_q = carry_q;
+                prev_y = carry_y;
+            }
+            if (valid) sum += 0.5 * (qb - prev_q) * (y + prev_y);
+            if (mask != 0) {
+                const int last = 63 - __builtin_clzll(mask);
+                carry_q = __shfl(qb, last);
+                carry_y = __shfl(y, last);
+            }
+        }
+        sum = wave_sum(sum);
+        if (lane == 0) {
+            const double cv = scale * sum / (2.0 * 3.141592653589793 * 3.141592653589793);
+            c[idx] = cv;
+            p[idx] = rt * rt * cv;
+        }
     }
-    const double cv = scale * sum / (2.0 * 3.141592653589793 * 3.141592653589793);
-    c[idx] = cv;
-    p[idx] = rt * rt * cv;
 }
 
 int launch_correlation(const double *q, const double *I, int n_q, int n_f, const double *r, int n_r,
@@ -347,8 +392,8 @@ int launch_correlation(const double *q, const double *I, int n_q, int n_f, const
 {
     const int64_t n = (int64_t)n_f * n_r;
     if (n <= 0) return NUMAG_OK;
-    hipLaunchKernelGGL(correlation_kernel, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, q, I, n_q,
-                       n_f, r, n_r, scale, c, p);
+    const int64_t wgs = n < ((int64_t)1 << 32) ? (n + 3) / 4 : (int64_t)1 << 30;
+    hipLaunchKernelGGL(correlation_kernel, dim3((unsigned)wgs), dim3(256), 0, s, q, I, n_q, n_f, r, n_r, scale, c, p);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

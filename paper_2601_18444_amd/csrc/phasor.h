@@ -16,6 +16,13 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b)
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
+// v summed over the wave, in every lane (fixed order).
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
 
 // sin x and cos x in FP64 for the sum kernels' generation phases.
 // Cody-Waite reduction (Cody & Waite, Software Manual for the Elementary

@@ -1,0 +1,65 @@
+"""Edges of the map analysis kernels: lanes of a row, wave and workgroup remainders, groups
+of data sets, empty bins.  Tolerances are the rounding of sums of n terms in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_18444_amd import numag
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+EPS = 2.0 ** -52
+
+
+@pytest.mark.parametrize("n0,n1", [(1, 9), (2, 2), (17, 64), (33, 40), (130, 257)])
+@pytest.mark.parametrize("n_f,n_bins,frac", [(1, 1, 1.0), (4, 7, 0.7), (5, 33, 1.0), (13, 64, 1.5)])
+def test_azimuthal_groups(orc, n0, n1, n_f, n_bins, frac):
+    rng = np.random.default_rng(n0 + 7 * n_f)
+    f = rng.standard_normal((n_f, n0 * n1))
+    grid = numag.qgrid(0, n0, n1, 1.3)
+    I, count = numag.azimuthal_average(grid, torch.as_tensor(f, device=DEV), n_bins, 1.3 * frac)
+    Iref, cref = orc.azimuthal_average(0, n0, n1, 1.3, f, n_bins, 1.3 * frac)
+    assert np.array_equal(count.cpu().numpy(), cref)
+    I = I.cpu().numpy()
+    assert np.array_equal(np.isnan(I), np.isnan(Iref))
+    some = cref > 0
+    assert np.all(np.abs(I - Iref)[:, some] <= EPS * n0 * n1 * np.abs(f).max())
+
+
+@pytest.mark.parametrize("n_q", [1, 63, 64, 65, 128, 200])
+@pytest.mark.parametrize("empty", ["none", "some", "block", "all"])
+def test_correlation_empty_bins(orc, n_q, empty):
+    rng = np.random.default_rng(n_q)
+    q = np.sort(rng.uniform(0.0, 2.0, n_q))
+    I = rng.uniform(0.5, 2.0, (3, n_q))
+    if empty == "some":
+        I[:, rng.uniform(size=n_q) < 0.3] = np.nan
+    elif empty == "block":
+        I[1, n_q // 3: n_q // 3 + 66] = np.nan
+    elif empty == "all":
+        I[2] = np.nan
+    r = np.concatenate([[0.0], rng.uniform(0.1, 50.0, 6)])
+    c, p = numag.correlation(*(torch.as_tensor(x, device=DEV) for x in (q, I, r)))
+    cref, pref = orc.correlation(q, I, r)
+    # the sum of |terms| is at most q_max max(I q^2); a sine's argument carries q r eps
+    tol = EPS * (n_q + 60.0 * 2) * 2.0 * 2.0 * 4.0
+    assert np.all(np.abs(c.cpu().numpy() - cref) <= tol)
+    assert np.all(np.abs(p.cpu().numpy() - pref) <= tol * r * r)
+
+
+@pytest.mark.parametrize("n_q,n_theta", [(1, 1), (3, 63), (65, 64), (130, 131)])
+@pytest.mark.parametrize("k_max", [0, 3, 4, 9])
+def test_angular_orders(orc, n_q, n_theta, k_max):
+    rng = np.random.default_rng(n_q + k_max)
+    f = rng.standard_normal((2, n_q * n_theta))
+    Is, Ic, As, Ac = (x.cpu().numpy() for x in numag.angular_spectrum(
+        numag.qgrid(1, n_q, n_theta, 1.0), torch.as_tensor(f, device=DEV), k_max))
+    for s in range(2):
+        Isr, Icr = orc.angular_spectrum(f[s], n_q, n_theta, k_max)
+        # a column's weight is h / pi; its phase k theta <= 2 pi k_max carries its own rounding
+        tol = 2 * EPS * (n_theta + 8 * k_max + 8) * np.abs(f).max()
+        assert np.abs(Is[s] - Isr).max() <= tol and np.abs(Ic[s] - Icr).max() <= tol
+        Asr, Acr = orc.modal_amplitudes(Isr, Icr)
+        norm = np.sqrt(Isr.sum(0) ** 2 + Icr.sum(0) ** 2).sum()
+        rel = 4 * n_q * (k_max + 1) * (tol + EPS) / norm
+        assert np.abs(As[s] - Asr).max() <= rel and np.abs(Ac[s] - Acr).max() <= rel
