@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
         for (int rg = 0; rg < g.nrg; ++rg) {
             if (half != 0) pblk::centres<2 * MT>(tab.ctr[gp], first, step);
             if (g.nrg > 1) first = cmul(first, adv);
-            pblk::wave_fence();
+            wave_fence();
             cblk::v4d acc[MT][kPolNP];
 #pragma unroll
             for (int t = 0; t < MT; ++t)
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
                         const double2 y = tab.ctr[16 * u + pt][2 * t + h];
                         G[u] = fma(y.x, acc[t][u][2 * h], fma(y.y, acc[t][u][2 * h + 1], G[u]));
                     }
-            pblk::wave_fence();
+            wave_fence();
         }
     }
 #pragma unroll

@@ -23,6 +23,13 @@ __device__ __forceinline__ double wave_sum(double v)
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
+// LDS operations of a wave complete in order: this only keeps the compiler from
+// moving reads and writes across.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // sin x and cos x in FP64 for the sum kernels' generation phases.
 // Cody-Waite reduction (Cody & Waite, Software Manual for the Elementary

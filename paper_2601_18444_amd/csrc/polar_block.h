@@ -127,14 +127,6 @@ __device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int a0, double dq
     }
 }
 
-// LDS operations of a wave complete in order: this only keeps the compiler from
-// moving reads and writes of the tables across.
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Adds the points [jbeg, jend) of `ld` (the loader concept of cartesian_block.h with
 // m = Y, n = Z) to the wave's tiles: theta direction (sth, cth), row blocks from a0 on.
 template <int MT, int CH, class Loader>

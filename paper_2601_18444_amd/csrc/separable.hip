@@ -4,16 +4,23 @@
 // the lab phase q.r = q_y y + q_z z does not involve x, so the DSFT of Sec. 3.3
 // factors exactly:
 //   S_c(y, z)   = sum_x w_c(x, y, z)                      (projection along the beam)
-//   T_c(y, k)   = sum_z S_c(y, z) exp(-i q_z(k) z)         (real x complex contraction)
-//   F_c(i, k)   = sum_y exp(-i q_y(i) y) T_c(y, k)         (complex x complex contraction)
+//   T_c(y, k)   = sum_z S_c(y, z) exp(-i q_z(k) z)
+//   F_c(i, k)   = sum_y exp(-i q_y(i) y) T_c(y, k)
 // The two contractions are dense GEMMs and run on MFMA:
-//   NUMAG_PATH_SEPARABLE_F64:    FP64 operands and accumulation on
-//                                v_mfma_f64_16x16x4f64 (_HERMITIAN: the second
-//                                contraction on half of the detector rows, the
-//                                rest mirrored by S(-q) = conj S(q));
-//   NUMAG_PATH_SEPARABLE_BF16X3 / _BF16X6: every operand split into 2 or 3 bf16
-//                                parts, 3 or 6 split products per real product on
-//                                v_mfma_f32_16x16x32_bf16, FP32 accumulation.
+//   NUMAG_PATH_SEPARABLE_F64 (and _HERMITIAN, the same sums): FP64 operands and
+//                                accumulation on v_mfma_f64_16x16x4f64.  The detector
+//                                is symmetric about q = 0 on both axes and S is real,
+//                                so T is needed at |q_z| only, its real and imaginary
+//                                parts are two real products, and so are those of the
+//                                second contraction with cos(|q_y| y) and sin(|q_y| y):
+//                                with the four sums RR, RI, IR, II of a cell
+//                                (|q_y|, |q_z|), S(+,+) = (RR - II) + i (RI + IR),
+//                                S(+,-) = (RR + II) + i (IR - RI), and S(-q) =
+//                                conj S(q): a quarter of the complex product's
+//                                multiply-adds;
+//   NUMAG_PATH_SEPARABLE_BF16X3 / _BF16X6: complex products, every operand split into
+//                                2 or 3 bf16 parts, 3 or 6 split products per real
+//                                product on v_mfma_f32_16x16x32_bf16, FP32 accumulation.
 // Twiddles are generated in FP64 into the workspace; the projection is a
 // fixed-order FP64 sum.
 //
@@ -32,23 +39,26 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // Padded sizes of the operands, so that the matrix-core loads need no bounds
 // checks: every padding entry is zero.
 //   S  [sets][ny16][nzk]    projections (ny16 = ny rounded up to 32, nzk = nz to 16)
-//   Ez [nzk][n1p]           column twiddles (n1p = n1 rounded up to 64)
-//   T  [sets][ny16][n1p]    first contraction (complex)
-//   Ey [n0p][nyk]           row twiddles (n0p = n0 to 32, nyk = ny to 16)
+//   Ez [nzk][nbp]           column twiddles of the nb values |q_z| (nbp: to 32)
+//   T  [sets][ny16][nbp]    first contraction (real and imaginary part)
+//   Ey [tile][nyk][16]      row twiddles (nyk = ny to 16): a tile holds 8 of the na values
+//                           |q_y|, value 4 h + e in row 8 h + e (cosine) and 8 h + 4 + e
+//                           (minus sine), so that a lane's accumulator registers 2 h and
+//                           2 h + 1 are the two parts of one value
 // nzk and nyk are the contraction depths, multiples of 16 so that the FP64
 // kernels' loops (four or two K steps of 4 per iteration) need no remainder.
+// n0p and n1p are the BF16 paths' padded detector rows and columns.
 struct SepDims {
-    int ny, nz, n0, n1, ny16, nzk, nyk, n0p, n1p;
+    int ny, nz, n0, n1, ny16, nzk, nyk, n0p, n1p, na, nb, nta, nbp;
 };
 
 struct SepLayout {
     size_t ey, ez, s, t, total;
 };
 
-// Paddings: rows of S and T (ny16) to the first contraction's 32-row wave tiles,
-// detector rows and columns to 32 and 64 (the BF16 paths' tiles; the FP64 tiles
-// are 16 x 16).
-constexpr int kC1M = 32;
+// Paddings: rows of S and T (ny16) and |q_z| values to the first contraction's 32 x 32
+// wave tiles, detector rows and columns of the BF16 paths to 32 and 64.
+constexpr int kC1M = 32, kC1N = 32;
 constexpr int kC2M = 32, kC2N = 64;
 constexpr int kKStep = 16;  // padding of the contraction depths
 // K steps of 4 per loop iteration of the first contraction (all their fragments
@@ -71,6 +81,10 @@ static SepDims sep_dims(const numag_regular &g, const Detector &d)
     m.nyk = round_up(m.ny, kKStep);
     m.n0p = round_up(m.n0, kC2M);
     m.n1p = round_up(m.n1, kC2N);
+    m.na = (m.n0 + 1) / 2;
+    m.nb = (m.n1 + 1) / 2;
+    m.nta = (m.na + 7) / 8;
+    m.nbp = round_up(m.nb, kC1N);
     return m;
 }
 
@@ -79,10 +93,10 @@ static SepLayout sep_layout(const numag_regular &g, const Detector &d, int64_t n
     const SepDims m = sep_dims(g, d);
     const size_t sets = 4 * (size_t)n_snap;
     SepLayout L{};
-    L.ey = al((size_t)m.n0p * m.nyk * sizeof(double2));
-    L.ez = al((size_t)m.nzk * m.n1p * sizeof(double2));
+    L.ey = al((size_t)m.nta * m.nyk * 16 * sizeof(double));
+    L.ez = al((size_t)m.nzk * m.nbp * sizeof(double2));
     L.s = al(sets * m.ny16 * m.nzk * sizeof(double));
-    L.t = al(sets * m.ny16 * m.n1p * sizeof(double2));
+    L.t = al(sets * m.ny16 * m.nbp * sizeof(double2));
     L.total = L.ey + L.ez + L.s + L.t;
     return L;
 }
@@ -109,9 +123,8 @@ constexpr int kProjUnroll = 8;    // loads in flight per thread
 // then mag), one per thread of a slice; x is split into 4 slices summed by 4
 // threads in x order, the slices added in a fixed order through LDS.  Output
 // S[4 b + c][iy][iz].
-// The remaining workgroups: twiddles Ey[i][iy] = exp(-i q_y(i) y_iy) and
-// Ez[iz][k] = exp(-i q_z(k) z_iz), zeros in the padding, and zeros in the
-// padding of S.
+// The remaining workgroups: twiddles exp(-i |q_y| y_iy) and exp(-i |q_z| z_iz), zeros in
+// the padding, and zeros in the padding of S.
 // The weights are read once, with 8-byte non-temporal loads: measured on the
 // 537 MB of 64 snapshots of a 64^3 grid in this layout, 77 us (7.0 TB/s) against
 // 82 us with 16-byte loads of two adjacent columns per thread, and 88 us with
@@ -135,7 +148,7 @@ __global__ __launch_bounds__(256) void sep_prepare_kernel(Detector d, numag_regu
                                                           const double *__restrict__ nuc,
                                                           const double *__restrict__ mag, int n_proj, int n_snap,
                                                           int tw, int pad_s, double *__restrict__ S,
-                                                          double2 *__restrict__ ey, double2 *__restrict__ ez)
+                                                          double *__restrict__ ey, double2 *__restrict__ ez)
 {
     const int64_t nyz = (int64_t)g.n[1] * g.n[2];
     const int64_t W = (int64_t)g.n[0] * nyz;
@@ -167,17 +180,21 @@ __global__ __launch_bounds__(256) void sep_prepare_kernel(Detector d, numag_regu
     }
     const int64_t idx = ((int64_t)blockIdx.x - (int64_t)n_proj * n_snap) * blockDim.x + threadIdx.x;
     // tw == 0: no FP64 twiddles (the BF16 paths write their own), padding of S only
-    const int64_t ne = tw ? (int64_t)m.n0p * m.nyk : 0;
-    const int64_t nez = tw ? (int64_t)m.nzk * m.n1p : 0;
+    const int64_t ne = tw ? (int64_t)m.nta * m.nyk * 8 : 0;  // one thread per value and iy
+    const int64_t nez = tw ? (int64_t)m.nzk * m.nbp : 0;
     if (idx < ne) {
-        const int i = (int)(idx / m.nyk), iy = (int)(idx % m.nyk);
+        const int e = (int)(idx % 8), iy = (int)(idx / 8 % m.nyk), t = (int)(idx / 8 / m.nyk);
         const double y = g.origin[1] + (double)iy * g.step[1];
-        ey[idx] = (i < d.n0 && iy < m.ny) ? twiddle(axis_value(d.origin0, i, d.step0) * y) : make_double2(0.0, 0.0);
+        const int i = m.n0 - m.na + 8 * t + e;
+        const double2 v = (i < m.n0 && iy < m.ny) ? twiddle(axis_value(d.origin0, i, d.step0) * y) : make_double2(0.0, 0.0);
+        double *o = ey + idx / 8 * 16 + 8 * (e >> 2) + (e & 3);
+        o[0] = v.x;
+        o[4] = v.y;
     } else if (idx < ne + nez) {
         const int64_t r = idx - ne;
-        const int iz = (int)(r / m.n1p), k = (int)(r % m.n1p);
+        const int iz = (int)(r / m.nbp), k = m.n1 - m.nb + (int)(r % m.nbp);
         const double z = g.origin[2] + (double)iz * g.step[2];
-        ez[r] = (iz < m.nz && k < d.n1) ? twiddle(axis_value(d.origin1, k, d.step1) * z) : make_double2(0.0, 0.0);
+        ez[r] = (iz < m.nz && k < m.n1) ? twiddle(axis_value(d.origin1, k, d.step1) * z) : make_double2(0.0, 0.0);
     } else if (pad_s) {
         // padding of S: rows iy >= ny and columns iz >= nz of every channel set
         const int64_t r = idx - ne - nez;
@@ -193,14 +210,12 @@ __global__ __launch_bounds__(256) void sep_prepare_kernel(Detector d, numag_regu
 // Both contractions run on v_mfma_f64_16x16x4f64.  Lane layout: lane l holds
 // A[l % 16][l / 16] and B[l / 16][l % 16] of a K step of 4; accumulator register
 // r holds D[4 r + l / 16][l % 16].  A wave owns 16 x 16 output tiles (MI x NI of
-// them in the first contraction; in the second, one pixel tile of CSW channel
-// sets).  Every output element takes the same instruction sequence whatever the
+// them in the first contraction; in the second, one tile of 8 x 16 cells of CSW
+// channel sets).  Every output element takes the same instruction sequence whatever the
 // tile shape or the channel sets a wave holds, so neither changes a result: a
 // batch of snapshots gives each snapshot its single-call sums bit for bit.
 // The 4 x 4 x 4 form issues its flops at a higher rate, but its register-blocked
-// tiles need 2.5 times the operand loads per flop.  Measured on 64 snapshots
-// (ny = nz = 64, 256 x 256 detector) against register-blocked 4 x 4 x 4 tiles:
-// first contraction 41 -> 27 us, second 236 -> 181 us, bit-identical results.
+// tiles need 2.5 times the operand loads per flop.
 
 // T[c][iy][k] = sum_iz S[c][iy][iz] Ez[iz][k] (real x complex: two products per
 // step, into independent accumulators).
@@ -210,7 +225,7 @@ __global__ __launch_bounds__(256) void sep_contract1_f64(const double *__restric
 {
     constexpr int TM = 16 * MI, TN = 16 * NI;
     const int lane = threadIdx.x & 63;
-    const int tm = m.ny16 / TM, tn = m.n1p / TN;
+    const int tm = m.ny16 / TM, tn = m.nbp / TN;
     const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (tile >= (int64_t)n_sets * tm * tn) return;
     const int c = (int)(tile / ((int64_t)tm * tn));
@@ -218,7 +233,7 @@ __global__ __launch_bounds__(256) void sep_contract1_f64(const double *__restric
     const int i0 = (rem / tn) * TM, k0 = (rem % tn) * TN;
     const int r16 = lane & 15, kq = lane >> 4;
     const double *pa = S + (int64_t)c * m.ny16 * m.nzk + (int64_t)(i0 + r16) * m.nzk + kq;  // + 16 mi nzk + z0
-    const double2 *pb = Ez + (int64_t)kq * m.n1p + k0 + r16;                                 // + z0 n1p + 16 ni
+    const double2 *pb = Ez + (int64_t)kq * m.nbp + k0 + r16;                                 // + z0 n1p + 16 ni
     v4d accR[MI][NI], accI[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -228,7 +243,7 @@ __global__ __launch_bounds__(256) void sep_contract1_f64(const double *__restric
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) a[mi] = pa[(int64_t)16 * mi * m.nzk + z0];
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) b[ni] = pb[(int64_t)z0 * m.n1p + 16 * ni];
+        for (int ni = 0; ni < NI; ++ni) b[ni] = pb[(int64_t)z0 * m.nbp + 16 * ni];
     };
     auto mma = [&](const double (&a)[MI], const double2 (&b)[NI]) {
 #pragma unroll
@@ -249,56 +264,54 @@ __global__ __launch_bounds__(256) void sep_contract1_f64(const double *__restric
 #pragma unroll
         for (int u = 0; u < kC1Steps; ++u) mma(a[u], b[u]);
     }
-    double2 *Tc = T + (int64_t)c * m.ny16 * m.n1p;
+    double2 *Tc = T + (int64_t)c * m.ny16 * m.nbp;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                Tc[(int64_t)(i0 + 16 * mi + 4 * r + kq) * m.n1p + k0 + 16 * ni + r16] =
+                Tc[(int64_t)(i0 + 16 * mi + 4 * r + kq) * m.nbp + k0 + 16 * ni + r16] =
                     make_double2(accR[mi][ni][r], accI[mi][ni][r]);
 }
 
-// F[c][i][k] = sum_iy Ey[i][iy] T[c][iy][k]  ->  amp[c / 4][(i n1 + k)][c % 4]
+// The cells (|q_y|, |q_z|) of every set, F = sum_iy Ey T in their four real parts, and
+// from them the pixels amp[c / 4][(i n1 + k)][c % 4].
 //
-// This contraction carries nine tenths of the flops; the complex product is four
-// real products per K step.  A wave owns one 16 x 16 pixel tile of CSW channel
-// sets: CSW = 4 holds all four channel sets of a snapshot and shares the Ey
-// fragment between them; CSW = 1 (four times the waves, for small batches) puts
-// the four channel sets of a tile in the four waves of one workgroup, which write
-// the same records together.  With CSW = 4 the result leaves through LDS: a lane
-// holds four rows of one column, so a direct store instruction would scatter 16
-// bytes into each of 64 pixel records; staged by rows, every store instruction
-// writes 16 whole records (1 KB) of one row (170 against 190 us for 64 snapshots;
-// 123 against 154 us on the Hermitian half).  Measured alternatives: larger
-// register tiles (32 x 32, 32 x 64 pixels) lose occupancy and run slower, a
-// deeper prefetch ring (four one-step buffers) gains without LDS stores but loses
-// with them, a persistent grid-stride loop over tiles gains nothing, non-temporal
-// stores of the result more than double the time, and the complex product as
-// three real products (Gauss's trick, with the sums A + B and C + D as extra
-// operand planes) cut the MFMA work by a quarter but added half again to the
-// operand loads (1.5 times slower, with the earlier tiles).  A16: the result
-// pointer is 16-byte aligned (one 16-byte store per channel).  HERM: only rows
-// [0, ceil(n0 / 2)) are contracted, and each of their pixels p also writes the
-// conjugate at the mirrored pixel P - 1 - p (S(-q) = conj S(q) for real weights
-// on the symmetric Cartesian detector); the middle row of an odd n0 is contracted
-// for every column and mirrors nothing.
-template <int CSW, bool A16, bool HERM>
-__global__ __launch_bounds__(256) void sep_contract2_f64(const double2 *__restrict__ Ey, const double2 *__restrict__ T,
+// A wave owns one tile of 8 x 16 cells (up to 512 pixels) of CSW channel sets: CSW = 4
+// holds all four channel sets of a snapshot and shares the Ey fragment between them;
+// CSW = 1 (four times the waves, for small batches) puts the four channel sets of a tile
+// in the four waves of one workgroup, which write the same records together.  With
+// CSW = 4 the result leaves through LDS: a lane holds two values |q_y| of one column, so
+// a direct store instruction would scatter 16 bytes into each of 64 pixel records; staged
+// by rows, every store instruction writes 16 whole records (1 KB) of one detector row
+// (the staged entries are rotated by the column, so that neither side has bank
+// conflicts).  Bound by the stores and, before them, the matrix products, which do not
+// overlap much: 64 snapshots of 64 x 64 x 64 cells on 256 x 256 pixels 182 -> 74 us against
+// the complex products over every pixel (268 MB at 6.7 TB/s: 40 us; 2.1 GFLOP: 29 us), the
+// first contraction 30 -> 17 us.  Non-temporal stores of the result were slower.
+// A16: the result pointer is 16-byte aligned (one 16-byte store per channel).
+template <bool A16>
+__device__ __forceinline__ void put_amp(double *o, double2 v)
+{
+    if (A16) {
+        *(double2 *)o = v;
+    } else {
+        o[0] = v.x;
+        o[1] = v.y;
+    }
+}
+
+template <int CSW, bool A16>
+__global__ __launch_bounds__(256, 4) void sep_contract2_f64(const double *__restrict__ Ey, const double2 *__restrict__ T,
                                                          SepDims m, int n_sets, double *__restrict__ amp)
 {
     static_assert(CSW == 1 || CSW == 4, "one or four channel sets per wave");
-    static_assert(kC2M % 16 == 0 && kC2N % 16 == 0, "tiles inside the padding");
-    const int lane = threadIdx.x & 63;
-    const int nr = HERM ? (m.n0 + 1) / 2 : m.n0;  // contracted rows
-    const int tm = (nr + 15) / 16, tn = (m.n1 + 15) / 16;
-    const int64_t tiles = (int64_t)tm * tn;
-    // a wave past the last tile works on tile 0 and stores nothing (the LDS store
-    // path has workgroup barriers)
-    const int64_t tile_w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const bool active = tile_w < (int64_t)(n_sets / CSW) * tiles;
-    const int64_t tile = active ? tile_w : 0;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tn = (m.nb + 15) / 16;
+    const int64_t tiles = (int64_t)m.nta * tn;
+    const int64_t tile = (int64_t)blockIdx.x * 4 + w;
+    if (tile >= (int64_t)(n_sets / CSW) * tiles) return;  // no workgroup barriers below
     int64_t c0;
     int rem;
     if (CSW == 4) {
@@ -309,40 +322,32 @@ __global__ __launch_bounds__(256) void sep_contract2_f64(const double2 *__restri
         c0 = 4 * (tile / (4 * tiles)) + (r2 & 3);
         rem = (int)(r2 >> 2);
     }
-    const int i0 = (rem / tn) * 16, k0 = (rem % tn) * 16;
+    const int ta = rem / tn, k0 = (rem % tn) * 16;
     const int r16 = lane & 15, kq = lane >> 4;
-    const int64_t cs = (int64_t)m.ny16 * m.n1p;  // one channel set of T
+    const int64_t cs = (int64_t)m.ny16 * m.nbp;  // one channel set of T
     // this lane's operand streams (every index stays inside the padded arrays)
-    const double2 *pa = Ey + (int64_t)(i0 + r16) * m.nyk + kq;               // + y0
-    const double2 *pb = T + c0 * cs + (int64_t)kq * m.n1p + k0 + r16;        // + ch cs + y0 n1p
-    v4d accR[CSW], accI[CSW];
+    const double *pa = Ey + ((int64_t)ta * m.nyk + kq) * 16 + r16;     // + 16 y0
+    const double2 *pb = T + c0 * cs + (int64_t)kq * m.nbp + k0 + r16;  // + ch cs + y0 nbp
+    v4d accC[CSW], accS[CSW];
 #pragma unroll
-    for (int ch = 0; ch < CSW; ++ch) accR[ch] = accI[ch] = v4d{0.0, 0.0, 0.0, 0.0};
-    auto load = [&](int y0, double2 &a, double2 (&b)[CSW]) {
-        a = pa[y0];
+    for (int ch = 0; ch < CSW; ++ch) accC[ch] = accS[ch] = v4d{0.0, 0.0, 0.0, 0.0};
+    auto load = [&](int y0, double &a, double2 (&b)[CSW]) {
+        a = pa[16 * y0];
 #pragma unroll
-        for (int ch = 0; ch < CSW; ++ch) b[ch] = pb[ch * cs + (int64_t)y0 * m.n1p];
+        for (int ch = 0; ch < CSW; ++ch) b[ch] = pb[ch * cs + (int64_t)y0 * m.nbp];
     };
-    // Two passes, so that the two products an accumulator takes per K step are issued
-    // 2 CSW instructions apart (each accumulator takes them in the same order).
-    auto mma = [&](const double2 &a, const double2 (&b)[CSW]) {
+    auto mma = [&](double a, const double2 (&b)[CSW]) {
 #pragma unroll
         for (int ch = 0; ch < CSW; ++ch) {
-            accR[ch] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[ch].x, accR[ch], 0, 0, 0);
-            accI[ch] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[ch].y, accI[ch], 0, 0, 0);
-        }
-#pragma unroll
-        for (int ch = 0; ch < CSW; ++ch) {
-            accR[ch] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b[ch].y, accR[ch], 0, 0, 0);
-            accI[ch] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[ch].x, accI[ch], 0, 0, 0);
+            accC[ch] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[ch].x, accC[ch], 0, 0, 0);
+            accS[ch] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[ch].y, accS[ch], 0, 0, 0);
         }
     };
     // Two register buffers of one K step each: the next step's fragments load while
-    // this one's MFMAs run (three waves per SIMD).  nyk is a multiple of 8, so an
-    // iteration takes two steps and needs no exit test; the last iteration's
-    // prefetch reloads an in-bounds step.  Measured against loading two or four
-    // steps and then running their MFMAs: 181 against 197 and 204 us.
-    double2 a0, b0[CSW], a1, b1[CSW];
+    // this one's MFMAs run.  nyk is a multiple of 8, so an iteration takes two steps and
+    // needs no exit test; the last iteration's prefetch reloads an in-bounds step.
+    double a0, a1;
+    double2 b0[CSW], b1[CSW];
     load(0, a0, b0);
     for (int y0 = 0; y0 < m.nyk; y0 += 8) {
         load(y0 + 4, a1, b1);
@@ -350,68 +355,65 @@ __global__ __launch_bounds__(256) void sep_contract2_f64(const double2 *__restri
         load(min(y0 + 8, m.nyk - 4), a0, b0);
         mma(a1, b1);
     }
-    const int col = k0 + r16;
+    // cell (e, k) of this lane's registers 2 h, 2 h + 1: e = 8 ta + 4 h + kq, k = k0 + r16;
+    // pixels (n0 - na + e, n1 - nb + k) and their mirror images, which the middle row and
+    // column of an odd detector do not have
     const int64_t P = (int64_t)m.n0 * m.n1;
-    if (CSW == 4) {
-        __shared__ double2 stage[4][4][16][4];  // [wave][row of the group][column][channel]
-        const int w = threadIdx.x >> 6;
+    const int ip = m.n0 - m.na, kp = m.n1 - m.nb;
+    const int i_mid = m.n0 & 1 ? 0 : -1, k_mid = m.n1 & 1 ? 0 : -1;
+    auto plus = [&](int ch, int h) {
+        return make_double2(accC[ch][2 * h] - accS[ch][2 * h + 1], accS[ch][2 * h] + accC[ch][2 * h + 1]);
+    };
+    auto minus = [&](int ch, int h) {
+        return make_double2(accC[ch][2 * h] + accS[ch][2 * h + 1], accC[ch][2 * h + 1] - accS[ch][2 * h]);
+    };
+    if constexpr (CSW == 4) {
+        __shared__ double2 stage[4][4][16][4];  // [wave][value of the half tile][column][channel]
         const int px = lane >> 2, chl = lane & 3;  // the record part this lane stores
         double *dst = amp + (c0 >> 2) * P * 8 + 2 * chl;
+        auto entry = [&](int s, int k, int ch) -> double2 & { return stage[w][s][k][(ch + (k >> 1)) & 3]; };
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int q = 0; q < 4; ++q) {
+            const int h = q >> 1;
+            const bool diff = q & 1;  // the pixels (+, -) and (-, +), else (+, +) and (-, -)
+            wave_fence();
 #pragma unroll
-            for (int ch = 0; ch < CSW; ++ch) stage[w][kq][r16][ch] = make_double2(accR[ch][r], accI[ch][r]);
-            __syncthreads();
+            for (int ch = 0; ch < 4; ++ch) entry(kq, r16, ch) = diff ? minus(ch, h) : plus(ch, h);
+            wave_fence();
+            // columns ascending and descending
+            const int ka = k0 + px, kd = k0 + 15 - px;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int row = i0 + 4 * r + s;
-                if (!active || row >= nr) continue;
-                if (k0 + px < m.n1) {
-                    const double2 v = stage[w][s][px][chl];
-                    double *o = dst + ((int64_t)row * m.n1 + k0 + px) * 8;
-                    if (A16) {
-                        *(double2 *)o = v;
-                    } else {
-                        o[0] = v.x;
-                        o[1] = v.y;
-                    }
-                }
-                // mirrored pixels of this row segment, P - 1 - p, ascending in px
-                const int cm = k0 + 15 - px;
-                if (HERM && row < m.n0 - nr && cm < m.n1) {
-                    const double2 v = stage[w][s][15 - px][chl];
-                    double *o = dst + (P - 1 - ((int64_t)row * m.n1 + cm)) * 8;
-                    if (A16) {
-                        *(double2 *)o = make_double2(v.x, -v.y);
-                    } else {
-                        o[0] = v.x;
-                        o[1] = -v.y;
-                    }
+                const int e = 8 * ta + 4 * h + s;
+                if (e >= m.na) continue;
+                const double2 va = entry(s, px, chl), vd = entry(s, 15 - px, chl);
+                double *up = dst + (int64_t)(ip + e) * m.n1 * 8, *down = dst + (int64_t)(m.n0 - 1 - ip - e) * m.n1 * 8;
+                if (diff) {
+                    if (kd < m.nb && kd != k_mid) put_amp<A16>(up + (int64_t)(m.n1 - 1 - kp - kd) * 8, vd);
+                    if (ka < m.nb && e != i_mid)
+                        put_amp<A16>(down + (int64_t)(kp + ka) * 8, make_double2(va.x, -va.y));
+                } else {
+                    if (ka < m.nb) put_amp<A16>(up + (int64_t)(kp + ka) * 8, va);
+                    if (kd < m.nb && kd != k_mid && e != i_mid)
+                        put_amp<A16>(down + (int64_t)(m.n1 - 1 - kp - kd) * 8, make_double2(vd.x, -vd.y));
                 }
             }
-            __syncthreads();
         }
-        return;
-    }
-    if (!active) return;
-    double *dst = amp + (c0 >> 2) * P * 8 + 2 * (c0 & 3);
+    } else {
+        double *dst = amp + (c0 >> 2) * P * 8 + 2 * (c0 & 3);
+        const int k = k0 + r16;
+        if (k >= m.nb) return;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = i0 + 4 * r + kq;
-        if (row >= nr || col >= m.n1) continue;
-        const int64_t p = (int64_t)row * m.n1 + col;
-        const bool mirror = HERM && row < m.n0 - nr;
-        double *o = dst + p * 8;
-        double *om = dst + (P - 1 - p) * 8;
-        if (A16) {
-            ((double2 *)o)[0] = make_double2(accR[0][r], accI[0][r]);
-            if (mirror) ((double2 *)om)[0] = make_double2(accR[0][r], -accI[0][r]);
-        } else {
-            o[0] = accR[0][r];
-            o[1] = accI[0][r];
-            if (mirror) {
-                om[0] = accR[0][r];
-                om[1] = -accI[0][r];
+        for (int h = 0; h < 2; ++h) {
+            const int e = 8 * ta + 4 * h + kq;
+            if (e >= m.na) continue;
+            const double2 vp = plus(0, h), vm = minus(0, h);
+            double *up = dst + (int64_t)(ip + e) * m.n1 * 8, *down = dst + (int64_t)(m.n0 - 1 - ip - e) * m.n1 * 8;
+            put_amp<A16>(up + (int64_t)(kp + k) * 8, vp);
+            if (k != k_mid) put_amp<A16>(up + (int64_t)(m.n1 - 1 - kp - k) * 8, vm);
+            if (e != i_mid) {
+                put_amp<A16>(down + (int64_t)(kp + k) * 8, make_double2(vm.x, -vm.y));
+                if (k != k_mid) put_amp<A16>(down + (int64_t)(m.n1 - 1 - kp - k) * 8, make_double2(vp.x, -vp.y));
             }
         }
     }
@@ -676,64 +678,53 @@ static int launch_bf16_path(const SepDims &m, const BfLayout &B, const Detector 
     return NUMAG_OK;
 }
 
-// FP64 path for snapshots [b0, b1): projection (+ twiddles when tw), then both
-// contractions; every buffer offset by the first snapshot.
-static int launch_f64_chunk(const double *nuc, const double *mag, const numag_regular &g, const Detector &d,
-                            const SepDims &m, int64_t b0, int64_t b1, bool tw, bool herm, double2 *ey, double2 *ez,
-                            double *S, double2 *T, double *amp, hipStream_t s)
+// FP64 path: projections and twiddles, then both contractions.
+static int launch_f64_path(const double *nuc, const double *mag, const numag_regular &g, const Detector &d,
+                           const SepDims &m, int64_t nb, double *ey, double2 *ez, double *S, double2 *T, double *amp,
+                           hipStream_t s)
 {
-    const int64_t W = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    const int64_t nb = b1 - b0;
     const int sets = (int)(4 * nb);
     const int64_t sstride = (int64_t)m.ny16 * m.nzk;
-    if (nuc != nullptr) nuc += b0 * W;
-    if (mag != nullptr) mag += b0 * W * 3;
-    S += 4 * b0 * sstride;
-    T += 4 * b0 * (int64_t)m.ny16 * m.n1p;
-    amp += b0 * (int64_t)d.n0 * d.n1 * 8;
     const int64_t nyz = (int64_t)m.ny * m.nz;
     const int64_t n_proj = (4 * nyz + kProjThreads - 1) / kProjThreads;
     const bool pad_s = m.ny16 != m.ny || m.nzk != m.nz;
-    const int64_t n_elem = (tw ? (int64_t)m.n0p * m.nyk + (int64_t)m.nzk * m.n1p : 0) +
-                           (pad_s ? (int64_t)sets * sstride : 0);
+    const int64_t n_elem =
+        (int64_t)m.nta * m.nyk * 8 + (int64_t)m.nzk * m.nbp + (pad_s ? (int64_t)sets * sstride : 0);
     const int64_t n_tw = (n_elem + 255) / 256;
     hipLaunchKernelGGL(sep_prepare_kernel, dim3((unsigned)(n_proj * nb + n_tw)), dim3(256), 0, s, d, g, m, nuc, mag,
-                       (int)n_proj, (int)nb, tw ? 1 : 0, pad_s ? 1 : 0, S, ey, ez);
+                       (int)n_proj, (int)nb, 1, pad_s ? 1 : 0, S, ey, ez);
     NUMAG_HIP_CHECK(hipGetLastError());
-    // first contraction: 32 x 64 or 16 x 64 outputs per wave when that still makes
-    // a few workgroups per CU, else 16 x 16
-    const int64_t t1big = (int64_t)sets * (m.ny16 / 32) * (m.n1p / 64);
-    const int64_t t1mid = (int64_t)sets * (m.ny16 / 16) * (m.n1p / 64);
+    // first contraction: 32 x 32 outputs per wave when that still makes a few waves per
+    // SIMD, else 16 x 16
+    const int64_t t1big = (int64_t)sets * (m.ny16 / 32) * (m.nbp / 32);
     if (t1big >= 2048) {
-        hipLaunchKernelGGL((sep_contract1_f64<2, 4>), dim3((unsigned)((t1big + 3) / 4)), dim3(256), 0, s, S, ez, m,
-                           sets, T);
-    } else if (t1mid >= 2048) {
-        hipLaunchKernelGGL((sep_contract1_f64<1, 4>), dim3((unsigned)((t1mid + 3) / 4)), dim3(256), 0, s, S, ez, m,
+        hipLaunchKernelGGL((sep_contract1_f64<2, 2>), dim3((unsigned)((t1big + 3) / 4)), dim3(256), 0, s, S, ez, m,
                            sets, T);
     } else {
-        const int64_t t1 = (int64_t)sets * (m.ny16 / 16) * (m.n1p / 16);
+        const int64_t t1 = (int64_t)sets * (m.ny16 / 16) * (m.nbp / 16);
         hipLaunchKernelGGL((sep_contract1_f64<1, 1>), dim3((unsigned)((t1 + 3) / 4)), dim3(256), 0, s, S, ez, m, sets,
                            T);
     }
     NUMAG_HIP_CHECK(hipGetLastError());
-    // second contraction: all four channel sets of a pixel tile in one wave when
-    // that still makes 1024 workgroups, else one channel set per wave
-    const int nr = herm ? (d.n0 + 1) / 2 : d.n0;  // contracted rows
-    const int64_t t2 = nb * ((nr + 15) / 16) * ((d.n1 + 15) / 16);  // pixel tiles of all snapshots
+    // second contraction: all four channel sets of a tile in one wave when that still
+    // makes one wave per SIMD (64 x 64 x 64 cells, 256 x 256 pixels, the whole call: 8
+    // snapshots 33.9 us against 38.1 with one channel set per wave, 64 snapshots 174
+    // against 199, 4 snapshots 26.4 against 26.1), else one channel set per wave
+    const int64_t t2 = nb * m.nta * ((m.nb + 15) / 16);  // tiles of all snapshots
     const bool a16 = ((uintptr_t)amp % 16) == 0;
     const unsigned g4 = (unsigned)((t2 + 3) / 4), g1 = (unsigned)t2;  // 4 waves per workgroup
-#define NUMAG_LAUNCH_C2(CSW, A16, HERM, G) \
-    hipLaunchKernelGGL((sep_contract2_f64<CSW, A16, HERM>), dim3(G), dim3(256), 0, s, ey, T, m, sets, amp)
-    const int variant = (t2 >= 4096 ? 4 : 0) + (a16 ? 2 : 0) + (herm ? 1 : 0);
-    switch (variant) {
-        case 0: NUMAG_LAUNCH_C2(1, false, false, g1); break;
-        case 1: NUMAG_LAUNCH_C2(1, false, true, g1); break;
-        case 2: NUMAG_LAUNCH_C2(1, true, false, g1); break;
-        case 3: NUMAG_LAUNCH_C2(1, true, true, g1); break;
-        case 4: NUMAG_LAUNCH_C2(4, false, false, g4); break;
-        case 5: NUMAG_LAUNCH_C2(4, false, true, g4); break;
-        case 6: NUMAG_LAUNCH_C2(4, true, false, g4); break;
-        default: NUMAG_LAUNCH_C2(4, true, true, g4); break;
+#define NUMAG_LAUNCH_C2(CSW, A16, G) \
+    hipLaunchKernelGGL((sep_contract2_f64<CSW, A16>), dim3(G), dim3(256), 0, s, ey, T, m, sets, amp)
+    if (t2 >= 1024) {
+        if (a16)
+            NUMAG_LAUNCH_C2(4, true, g4);
+        else
+            NUMAG_LAUNCH_C2(4, false, g4);
+    } else {
+        if (a16)
+            NUMAG_LAUNCH_C2(1, true, g1);
+        else
+            NUMAG_LAUNCH_C2(1, false, g1);
     }
 #undef NUMAG_LAUNCH_C2
     NUMAG_HIP_CHECK(hipGetLastError());
@@ -745,8 +736,7 @@ int launch_separable(const double *nuc, const double *mag, const numag_regular &
 {
     const SepLayout L = sep_layout(g, d, n_snap);
     const SepDims m = sep_dims(g, d);
-    const bool herm = path == NUMAG_PATH_SEPARABLE_F64_HERMITIAN;
-    const bool f64 = path == NUMAG_PATH_SEPARABLE_F64 || herm;
+    const bool f64 = path == NUMAG_PATH_SEPARABLE_F64 || path == NUMAG_PATH_SEPARABLE_F64_HERMITIAN;
     if (ws_bytes < separable_workspace_bytes(g, d, path, n_snap) || ws == nullptr) {
         set_error("numag_amplitudes: workspace too small for the separable path");
         return NUMAG_E_WORKSPACE;
@@ -754,14 +744,14 @@ int launch_separable(const double *nuc, const double *mag, const numag_regular &
     const int64_t nyz = (int64_t)m.ny * m.nz;
     const bool pad_s = m.ny16 != m.ny || m.nzk != m.nz;
     if ((4 * nyz + kProjThreads - 1) / kProjThreads * n_snap +
-            ((int64_t)m.n0p * m.nyk + (int64_t)m.nzk * m.n1p + (pad_s ? 4 * n_snap * m.ny16 * m.nzk : 0)) / 256 + 1 >
+            ((int64_t)m.nta * m.nyk * 8 + (int64_t)m.nzk * m.nbp + (pad_s ? 4 * n_snap * m.ny16 * m.nzk : 0)) / 256 + 1 >
         0x7fffffffLL) {
         set_error("numag_amplitudes: too many snapshots for one separable call");
         return NUMAG_E_INVALID;
     }
     // FP64 path: Ey, Ez, S, T.  BF16 paths: S, then their split operands.
     char *base = (char *)ws;
-    double2 *ey = f64 ? (double2 *)base : nullptr;
+    double *ey = f64 ? (double *)base : nullptr;
     double2 *ez = f64 ? (double2 *)(base + L.ey) : nullptr;
     double *S = (double *)(f64 ? base + L.ey + L.ez : base);
     double2 *T = f64 ? (double2 *)(base + L.ey + L.ez + L.s) : nullptr;
@@ -777,13 +767,10 @@ int launch_separable(const double *nuc, const double *mag, const numag_regular &
         return B.np == 3 ? launch_bf16_path<3>(m, B, d, g, S, sets, bbase, amp, s)
                          : launch_bf16_path<2>(m, B, d, g, S, sets, bbase, amp, s);
     }
-    // One launch sequence for the whole batch.  Splitting the batch into chunks on two
-    // streams, so that the projection (HBM-bound) of a chunk runs beside the second
-    // contraction of the previous one, was measured slower for 64 snapshots: 0.30, 0.32
-    // and 0.37 ms for 2, 4 and 8 chunks against 0.27-0.29 ms for one sequence (0.27
-    // against 0.20 ms on the Hermitian half); the two kernels slow each other down more
-    // than the overlap saves.
-    return launch_f64_chunk(nuc, mag, g, d, m, 0, n_snap, true, herm, ey, ez, S, T, amp, s);
+    // One launch sequence for the whole batch: chunks of it on two streams, so that the
+    // projection (HBM-bound) of one runs beside the second contraction of another, were
+    // measured slower (the two kernels slow each other down more than the overlap saves).
+    return launch_f64_path(nuc, mag, g, d, m, n_snap, ey, ez, S, T, amp, s);
 }
 
 }  // namespace numag

@@ -90,3 +90,31 @@ def test_far_points(orc, kind, n0, n1, scale):
     pos[7, 2] = np.inf
     bad, _ = numag.amplitudes(numag.Sample(pos=pos, nuc=nuc, mag=mag, device=DEV), grid)
     assert not torch.isfinite(bad[0, -1]).all()
+
+
+@pytest.mark.parametrize("n0,n1", [(1, 1), (2, 31), (15, 2), (16, 32), (17, 33), (33, 64), (64, 95)])
+@pytest.mark.parametrize("n", [(2, 1, 1), (3, 4, 17), (2, 33, 15)])
+def test_separable_cells(orc, n0, n1, n):
+    """Tiles of 8 x 16 cells, middle rows and columns, both channel splits of the second
+    contraction (a large batch holds all channels in a wave), unaligned results."""
+    rng = np.random.default_rng(100 * n0 + n1 + n[2])
+    qmax, step, origin = 1.3, (1.1, 0.9, 1.2), (-1.0, -3.0, -8.0)
+    W = n[0] * n[1] * n[2]
+    B = 4 if n[2] != 17 else 180
+    nuc, mag = rng.standard_normal((B, W)), rng.standard_normal((B, W, 3))
+    grid, points = numag.qgrid(0, n0, n1, qmax), numag.regular_grid(n, origin, step)
+    amp = numag.amplitudes_snapshots(points, grid, nuc=nuc, mag=mag, device=DEV)
+    shifted = torch.empty(amp.numel() + 1, dtype=torch.float64, device=DEV)[1:].reshape(amp.shape)
+    numag.amplitudes_snapshots(points, grid, nuc=nuc, mag=mag, device=DEV, out=shifted,
+                               path=numag.PATH_SEPARABLE_F64_HERMITIAN)
+    assert torch.equal(amp, shifted)
+    one = numag.amplitudes_snapshots(points, grid, nuc=nuc[-1:], mag=mag[-1:], device=DEV)
+    assert torch.equal(amp[-1:], one)
+    pos = synth.box_lattice(n, step, origin)
+    qy, qz, _ = orc.pixels(0, n0, n1, qmax)
+    phase = qmax * (np.abs(pos[:, 1]).max() + np.abs(pos[:, 2]).max())
+    for b in (0, B - 1):
+        ref = orc.amplitudes(pos, nuc[b], mag[b], qy, qz)
+        w = np.concatenate([nuc[b][:, None], mag[b]], axis=1)
+        tol = 2.0 ** -52 * (4 * phase + W + 128) * np.abs(w).sum(0)
+        assert np.all(np.abs(amp_to_complex(amp[b]) - ref).max(0) <= tol)
