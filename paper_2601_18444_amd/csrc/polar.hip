@@ -8,6 +8,7 @@
 // The rest is the tables: about 240 vector instructions per 32 points and column.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "polar_block.h"
 
@@ -20,32 +21,33 @@ static int shape_blocks(int shape)
     return blocks[shape];
 }
 
-template <int CH>
+template <int CH, int NW>
 struct PolarRecLoader {
-    using Raw = cblk::Point<CH>;
-    const PointRec *__restrict__ pts;
+    using Rec = typename std::conditional<NW == CH, PointRec, PairRec>::type;
+    using Raw = cblk::Point<NW>;
+    const Rec *__restrict__ pts;
     __device__ __forceinline__ Raw raw(int64_t j) const
     {
-        const PointRec &r = pts[j];
+        const Rec &r = pts[j];
         Raw p;
         p.m = r.Y;
         p.n = r.Z;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) p.w[c] = r.w[cblk::ch_first<CH>() + c];
+        for (int c = 0; c < NW; ++c) p.w[c] = r.w[(NW == 3 ? 1 : 0) + c];
         return p;
     }
-    __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const { return r; }
+    __device__ __forceinline__ Raw point(const Raw &r) const { return r; }
 };
 
 // One wave: one theta column, one row group, one point range.  Partials
 // [split][row group][column][tile][half][4][64] (store == 0), or amp (1: written,
 // 2: added).
-template <int MT, int CH>
-__global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
-                                                                         int64_t per, PolGeom g, int store,
-                                                                         double *__restrict__ out)
+template <int MT, int CH, int NW>
+__global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(
+    const typename PolarRecLoader<CH, NW>::Rec *__restrict__ pts, int64_t W, int64_t per, PolGeom g, int store,
+    double *__restrict__ out)
 {
-    __shared__ pblk::WaveSmem<MT, CH> sm[pblk::kWaves];
+    __shared__ pblk::WaveSmem<MT, CH, NW> sm[pblk::kWaves];
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
     const int col = blockIdx.x * pblk::kWaves + wave, rg = blockIdx.y;
     if (col >= g.cols) return;  // no workgroup barriers below
@@ -55,8 +57,8 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(const P
     sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
-    pblk::accumulate<MT, CH>(PolarRecLoader<CH>{pts}, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC,
-                             accS);
+    pblk::accumulate<MT, CH, NW>(PolarRecLoader<CH, NW>{pts}, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC,
+                                 accS);
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -193,8 +195,8 @@ size_t polar_partial_bytes(const PolarPlan &p)
     return p.nsplit > 1 ? polar_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
 }
 
-template <int CH>
-static void launch_polar_tiles(const PointRec *pts, int64_t W, const PolarPlan &p, int store, double *out,
+template <int CH, int NW = CH>
+static void launch_polar_tiles(const typename PolarRecLoader<CH, NW>::Rec *pts, int64_t W, const PolarPlan &p, int store, double *out,
                                hipStream_t s)
 {
     const dim3 grid((p.g.cols + pblk::kWaves - 1) / pblk::kWaves, p.g.nrg, p.nsplit), block(pblk::kThreads);
@@ -202,7 +204,7 @@ static void launch_polar_tiles(const PointRec *pts, int64_t W, const PolarPlan &
 #define NUMAG_LAUNCH_POLAR(MT)   \
     case MT:                     \
         if constexpr (MT <= 2 * CH) \
-            hipLaunchKernelGGL((direct_polar_kernel<MT, CH>), grid, block, 0, s, pts, W, p.per, p.g, store, out); \
+            hipLaunchKernelGGL((direct_polar_kernel<MT, CH, NW>), grid, block, 0, s, pts, W, p.per, p.g, store, out); \
         break
     switch (p.mt) {
         NUMAG_LAUNCH_POLAR(1);
@@ -217,27 +219,47 @@ static void launch_polar_tiles(const PointRec *pts, int64_t W, const PolarPlan &
 #undef NUMAG_LAUNCH_POLAR
 }
 
+static int combine_polar(const PolarPlan &p, const double *partial, double *amp, int accumulate, hipStream_t s)
+{
+    NUMAG_HIP_CHECK(hipGetLastError());
+    if (p.nsplit <= 1) return NUMAG_OK;
+    const int64_t n = (int64_t)p.g.nrg * p.g.cols * p.mt * 128;
+    hipLaunchKernelGGL(polar_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
+                       p.channels, p.nsplit, accumulate, amp);
+    NUMAG_HIP_CHECK(hipGetLastError());
+    return NUMAG_OK;
+}
+
 int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, double *partial, double *amp,
                         int accumulate, hipStream_t s)
 {
-    const bool split = p.nsplit > 1;
-    const int store = split ? 0 : (accumulate ? 2 : 1);
+    const int store = p.nsplit > 1 ? 0 : (accumulate ? 2 : 1);
     {
         TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
-        double *out = split ? partial : amp;
+        double *out = p.nsplit > 1 ? partial : amp;
         switch (p.channels) {
             case 1: launch_polar_tiles<1>(pts, W, p, store, out, s); break;
             case 3: launch_polar_tiles<3>(pts, W, p, store, out, s); break;
             default: launch_polar_tiles<4>(pts, W, p, store, out, s); break;
         }
     }
-    NUMAG_HIP_CHECK(hipGetLastError());
-    if (!split) return NUMAG_OK;
-    const int64_t n = (int64_t)p.g.nrg * p.g.cols * p.mt * 128;
-    hipLaunchKernelGGL(polar_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
-                       p.channels, p.nsplit, accumulate, amp);
-    NUMAG_HIP_CHECK(hipGetLastError());
-    return NUMAG_OK;
+    return combine_polar(p, partial, amp, accumulate, s);
+}
+
+int launch_polar_pairs(const PairRec *pts, int64_t n, const PolarPlan &p, double *partial, double *amp, hipStream_t s)
+{
+    const int store = p.nsplit > 1 ? 0 : 1;
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        double *out = p.nsplit > 1 ? partial : amp;
+        switch (p.channels) {
+            case 1: launch_polar_tiles<1, 2>(pts, n, p, store, out, s); break;
+            case 2: launch_polar_tiles<2, 4>(pts, n, p, store, out, s); break;
+            case 3: launch_polar_tiles<3, 6>(pts, n, p, store, out, s); break;
+            default: launch_polar_tiles<4, 8>(pts, n, p, store, out, s); break;
+        }
+    }
+    return combine_polar(p, partial, amp, 0, s);
 }
 
 }  // namespace numag

@@ -41,11 +41,12 @@ constexpr int kMaxNA = 16;    // row blocks per wave
 template <int MT, int CH>
 constexpr int max_na() { return 8 * MT / CH < kMaxNA ? 8 * MT / CH : kMaxNA; }
 
-template <int MT, int CH>
+// NW weights per point: CH, or 2 CH for pairs of points at u and -u (accumulate below).
+template <int MT, int CH, int NW = CH>
 struct WaveSmem {
     double2 off[kChunk][17];
     double2 ctr[kChunk][max_na<MT, CH>() + 1];
-    double w[kChunk][CH + 1];
+    double w[kChunk][NW + 1];
 };
 
 // Value of v in the other half of the wave (lane ^ 32).
@@ -108,8 +109,8 @@ __device__ __forceinline__ void centres(double2 *ctr, double2 a, double2 step)
 
 // Tables of a chunk: point gp = lane % 32 of the wave at u, weights p.w, centres of the
 // row blocks from a0 on.
-template <int MT, int CH>
-__device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int a0, double dq, double u, const Point<CH> &p)
+template <int MT, int CH, int NW>
+__device__ __forceinline__ void generate(WaveSmem<MT, CH, NW> &sm, int a0, double dq, double u, const Point<NW> &p)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
     double2 centre, step, first = make_double2(1.0, 0.0);
@@ -123,19 +124,26 @@ __device__ __forceinline__ void generate(WaveSmem<MT, CH> &sm, int a0, double dq
         centres<max_na<MT, CH>()>(sm.ctr[gp], centre, step);
     } else {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) sm.w[gp][c] = p.w[c];
+        for (int c = 0; c < NW; ++c) sm.w[gp][c] = p.w[c];
     }
 }
 
 // Adds the points [jbeg, jend) of `ld` (the loader concept of cartesian_block.h with
 // m = Y, n = Z) to the wave's tiles: theta direction (sth, cth), row blocks from a0 on.
-template <int MT, int CH, class Loader>
+//
+// With 2 CH weights a point stands for a pair at u and -u with weights f+ and f-: given
+// f+ + f- (even entries) and f+ - f- (odd ones),
+//   f+ exp(-i q u) + f- exp(i q u) = (f+ + f-) cos(q u) - i (f+ - f-) sin(q u),
+// so RR and II, which make up the real parts, take the first, RI and IR the second.
+template <int MT, int CH, int NW, class Loader>
 __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, double sth, double cth,
-                                           double dq, int a0, WaveSmem<MT, CH> &sm, v4d (&accC)[MT],
+                                           double dq, int a0, WaveSmem<MT, CH, NW> &sm, v4d (&accC)[MT],
                                            v4d (&accS)[MT])
 {
     const int lane = threadIdx.x & 63, gp = lane & 31;
     const int r16 = lane & 15, kq = lane >> 4;
+    constexpr bool kPairs = NW != CH;
+    static_assert(NW == CH || NW == 2 * CH, "one weight per channel, or two of a pair");
     // this lane's matrix row: slot 8 t + 4 (r16 / 8) + r16 % 4, part (r16 / 4) % 2
     const int part = (r16 >> 2) & 1;
     int ea[MT], wc[MT];
@@ -153,9 +161,9 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     typename Loader::Raw raw = fetch(jbeg);
 #pragma unroll 1
     for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk) {
-        const Point<CH> p = ld.point(raw);
+        const Point<NW> p = ld.point(raw);
         const double u = p.m * sth + p.n * cth;
-        generate<MT, CH>(sm, a0, dq, u, p);
+        generate<MT, CH, NW>(sm, a0, dq, u, p);
         wave_fence();
         raw = fetch(j0 + kChunk);
         const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
@@ -164,9 +172,16 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         auto step = [&](int s) {
             const double2 z = op[s * 4 * 17];
             const double *c = (const double *)(cp + s * 4 * (max_na<MT, CH>() + 1)) + part;
-            const double *w = wp + s * 4 * (CH + 1);
-            double a[MT];
-            if (CH == 3) {
+            const double *w = wp + s * 4 * (NW + 1);
+            double a[MT], b[kPairs ? MT : 1];
+            if (kPairs) {
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    const double y = c[2 * ea[t]];
+                    a[t] = y * w[2 * wc[CH == 3 ? t : 0] + part];
+                    b[t] = y * w[2 * wc[CH == 3 ? t : 0] + 1 - part];
+                }
+            } else if (CH == 3) {
 #pragma unroll
                 for (int t = 0; t < MT; ++t) a[t] = c[2 * ea[t]] * w[wc[t]];
             } else {
@@ -177,7 +192,7 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 accC[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.x, accC[t], 0, 0, 0);
-                accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.y, accS[t], 0, 0, 0);
+                accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(kPairs ? b[t] : a[t], z.y, accS[t], 0, 0, 0);
             }
         };
         int s = 0;
@@ -213,8 +228,8 @@ __device__ __forceinline__ void put_slot(double *__restrict__ amp, const PolGeom
         put(first + c, v);
         if (c == 0 && !add) {  // channels outside the set
             if (CH == 3) put(0, make_double2(0.0, 0.0));
-            if (CH == 1)
-                for (int ch = 1; ch < 4; ++ch) put(ch, make_double2(0.0, 0.0));
+            if (CH <= 2)
+                for (int ch = CH; ch < 4; ++ch) put(ch, make_double2(0.0, 0.0));
         }
     }
 }

@@ -58,4 +58,11 @@ struct alignas(64) PointRec {
     double pad[2];
 };
 
+// A pair of points at (Y, Z) and (-Y, -Z): the sums (even) and differences (odd entries) of
+// their weights, per channel.
+struct PairRec {
+    double Y, Z;
+    double w[8];
+};
+
 }  // namespace numag

@@ -63,3 +63,22 @@ def test_angular_orders(orc, n_q, n_theta, k_max):
         norm = np.sqrt(Isr.sum(0) ** 2 + Icr.sum(0) ** 2).sum()
         rel = 4 * n_q * (k_max + 1) * (tol + EPS) / norm
         assert np.abs(As[s] - Asr).max() <= rel and np.abs(Ac[s] - Acr).max() <= rel
+
+
+@pytest.mark.parametrize("kind,n0,n1", [(0, 1, 1), (0, 1, 8), (0, 9, 2), (0, 33, 65), (1, 2, 2), (1, 35, 4), (1, 40, 66),
+                                        (1, 12, 15)])
+@pytest.mark.parametrize("rkind,r0,r1", [(0, 1, 1), (0, 17, 34), (1, 1, 3), (1, 33, 6), (1, 150, 9), (1, 500, 2)])
+def test_correlation_2d_routes(orc, kind, n0, n1, rkind, r0, r1):
+    """Factored, paired and plain sums, one to five data sets: single rows and columns,
+    detectors with and without a middle pixel, row blocks of the polar real-space grid."""
+    rng = np.random.default_rng(n0 + 3 * n1 + r0)
+    qmax, rmax = 1.1, 30.0
+    grid, rgrid = numag.qgrid(kind, n0, n1, qmax), numag.qgrid(rkind, r0, r1, rmax)
+    f = rng.standard_normal((5, n0 * n1))
+    area = np.pi * qmax ** 2 if kind else (2 * qmax if n0 > 1 else 1) * (2 * qmax if n1 > 1 else 1)
+    # sums of n terms |wq f| <= wq max|f| of phases up to 4 qmax rmax
+    tol = EPS * (16 * qmax * rmax + n0 * n1 + 128) * area * np.abs(f).max()
+    for n_f in (1, 2, 3, 4, 5):
+        C = numag.correlation_2d(grid, torch.as_tensor(f[:n_f], device=DEV), rgrid).cpu().numpy()
+        ref = orc.correlation_2d(kind, n0, n1, qmax, f[:n_f], rkind, r0, r1, rmax)
+        assert np.abs(C[..., 0] + 1j * C[..., 1] - ref).max() <= tol
