@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void adjoint_cartesian_kernel(
     double m[kAdjNP], n[kAdjNP], G[kAdjNP];
     double2 off[kAdjNP][4], adv[kAdjNP];
     // centre of the first column block of the split
-    const double qc = g.originN + ((double)(g.nN - g.B + 16 * v0) + 7.5) * g.stepN;
+    const double qc = ((double)(16 * v0) + g.firstN + 7.5) * g.stepN;
 #pragma unroll
     for (int u = 0; u < kAdjNP; ++u) {
         const int64_t j = j0 + 16 * u;
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void adjoint_cartesian_kernel(
         double2 ctr[kAdjNP];
 #pragma unroll
         for (int u = 0; u < kAdjNP; ++u)
-            ctr[u] = phasor(half_turns(qc), n[u], fabs(n[u]) < phasor_range(fabs(g.originN) + 32.0 * g.stepN));
+            ctr[u] = phasor(half_turns(qc), n[u], fabs(n[u]) < phasor_range((g.B + 32.0) * g.stepN));
 #pragma unroll 1
         for (int v = v0; v < v1; ++v, ++i) {
             if (i + 1 < total) stage(i + 1);  // arrives under the products
@@ -278,12 +278,12 @@ __global__ __launch_bounds__(kAdjThreads, 2) void adjoint_cartesian_kernel(
             __syncthreads();
         }
         // fold the tiles of this row block: rows a = 2 t + h
-        const double qm = axis_value(g.originM, g.nM - g.A + rb * g.na, g.stepM);
+        const double qm = ((double)(rb * g.na) + g.firstM) * g.stepM;
 #pragma unroll
         for (int u = 0; u < kAdjNP; ++u) {
             double2 y, dm;
             phasor2(half_turns(qm), m[u], half_turns(g.stepM), m[u],
-                    fabs(m[u]) < phasor_range(fabs(g.originM) + 32.0 * g.stepM), y, dm);
+                    fabs(m[u]) < phasor_range((g.A + 32.0) * g.stepM), y, dm);
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll

@@ -126,9 +126,9 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     const int r16 = lane & 15, kq = lane >> 4;
     // coefficient of this lane's column entry: an offset (first half) or a block centre
     const HalfTurns qn = half_turns(half == 0 ? ((double)wave + 0.5) * g.stepN
-                                              : g.originN + ((double)(g.nN - g.B + kOff * (zb0 + wave)) + 7.5) * g.stepN);
+                                              : ((double)(kOff * (zb0 + wave)) + g.firstN + 7.5) * g.stepN);
     // (block centres and rows may lie up to a block beyond the detector)
-    const double range = phasor_range(fmax(fabs(g.originM) + (16.0 * kMaxMT) * g.stepM, fabs(g.originN) + 256.0 * g.stepN));
+    const double range = phasor_range(fmax((g.A + 16.0 * kMaxMT) * g.stepM, (g.B + 256.0) * g.stepN));
 
     auto put_row = [&](int b, const Point<CH> &p, int e, double2 y) {
         if (e < g.na) {
@@ -140,7 +140,7 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
             }
         }
     };
-    const HalfTurns qm0 = half_turns(axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * wave + half, g.stepM));
+    const HalfTurns qm0 = half_turns(((double)(rb * g.na + 2 * wave + half) + g.firstM) * g.stepM);
     auto generate = [&](int b, const typename Loader::Raw &raw) {
         const Point<CH> p = ld.point(raw);
         const bool fast = fmax(fabs(p.m), fabs(p.n)) < range && p.m == p.m && p.n == p.n;
@@ -155,7 +155,7 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         put_row(b, p, 2 * wave + half, y);
 #pragma unroll 1
         for (int e0 = 2 * (wave + kWaves); e0 < g.na; e0 += 2 * kWaves) {
-            const HalfTurns q = half_turns(axis_value(g.originM, g.nM - g.A + rb * g.na + e0 + half, g.stepM));
+            const HalfTurns q = half_turns(((double)(rb * g.na + e0 + half) + g.firstM) * g.stepM);
             put_row(b, p, e0 + half, phasor(q, p.m, fast));
         }
     };

@@ -286,9 +286,9 @@ void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt)
         g.nrb = nrb;
         g.nzb = nzb;
         g.swapped = sw;
-        g.originM = sw ? d.origin1 : d.origin0;
+        g.firstM = nM % 2 == 0 ? 0.5 : 0.0;
         g.stepM = sw ? d.step1 : d.step0;
-        g.originN = sw ? d.origin0 : d.origin1;
+        g.firstN = nN % 2 == 0 ? 0.5 : 0.0;
         g.stepN = sw ? d.step0 : d.step1;
         g.strideM = sw ? 1 : d.n1;
         g.strideN = sw ? d.n1 : 1;

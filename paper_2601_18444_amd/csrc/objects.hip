@@ -191,7 +191,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
                 if (a.amp != nullptr) {
                     const double2 X = object_yz(a, ld.R, k);
                     Xm = g.swapped ? X.y : X.x;
-                    z = twiddle(axis_value(g.originN, g.nN - g.B + cblk::kOff * zb + (lane & 15), g.stepN) *
+                    z = twiddle(((double)(cblk::kOff * zb + (lane & 15)) + g.firstN) * g.stepN *
                                 (g.swapped ? X.x : X.y));
                 }
                 cblk::finish<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
                     add_spectral(o, first, vp);
                     add_spectral(o + 256, first, vm);
                     if (a.amp != nullptr) {
-                        const double qm = axis_value(g.originM, g.nM - g.A + rb * g.na + 2 * t + h, g.stepM);
+                        const double qm = ((double)(rb * g.na + 2 * t + h) + g.firstM) * g.stepM;
                         add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(qm * Xm), z);
                     }
                 });

@@ -24,14 +24,16 @@ struct Detector {
 // Work split of a Cartesian direct sum over cells |q_M|, |q_N| (cartesian_block.h).
 // M is the axis packed into matrix rows (the detector rows unless swapped), N the
 // other; A and B count the |q| values, nM and nN the detector's.  |q| value k of an
-// axis of n values with K = ceil(n / 2) of them is axis_value(origin, n - K + k, step).
+// axis is (k + first) step, first = 0 on an odd axis and 1/2 on an even one: the pixels
+// n - K + k and K - 1 - k, K = ceil(n / 2), lie at +-|q| within the rounding of the
+// detector's axis.
 struct CartGeom {
     int A, B, nM, nN;
     int na;                 // |q_M| values per row block
     int nz;                 // column blocks (16 |q_N| values) per workgroup: 1, 2, 4 or 8
     int nrb, nzb;           // row blocks and column blocks of the detector
     int swapped;            // M is the column axis of the detector
-    double originM, stepM, originN, stepN;
+    double firstM, stepM, firstN, stepN;
     int64_t strideM, strideN;  // pixels
 };
 
