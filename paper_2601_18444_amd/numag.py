@@ -131,8 +131,12 @@ def kernel_timer_read(kernel: int):
     return ms.value, n.value
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream(device=None) -> int:
+    """Handle of the current stream of `device` (default: the current device).  (Raw: a
+    torch.cuda.Stream object per call takes 2.9 us, this 0.3, of the 3 to 10 us a small call
+    has.)"""
+    index = None if device is None else device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
 
 def _dev(x, device, shape=None):
@@ -152,7 +156,7 @@ def _dev(x, device, shape=None):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 _ws_cache: dict = {}
@@ -162,8 +166,8 @@ def workspace(nbytes: int, device) -> torch.Tensor:
     """A cached device workspace of at least nbytes, one per (device, stream): calls
     on one stream run in order and may share it, calls on different streams may
     overlap and must not."""
-    dev = torch.device(device)
-    key = (str(dev), torch.cuda.current_stream(dev).cuda_stream)
+    dev = device if isinstance(device, torch.device) else torch.device(device)
+    key = (torch.cuda.current_device() if dev.index is None else dev.index, _stream(dev))
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=dev)
