@@ -193,10 +193,11 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
 #pragma unroll 1
     for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk, b ^= 1) {
         if (j0 + kChunk < jend) {
-            p = q;
-            if (j0 + 2 * kChunk + gp < jend) q = ld.raw(j0 + 2 * kChunk + gp);  // a whole chunk ahead of its use
+            // q holds the next chunk's points, and takes those of the one after as soon as
+            // they are used (handing a second set on by a copy would wait for its load here)
+            generate(b ^ 1, q);
+            if (j0 + 2 * kChunk + gp < jend) q = ld.raw(j0 + 2 * kChunk + gp);
             else q = typename Loader::Raw{};
-            generate(b ^ 1, p);
         }
         sum(b, (int)min((int64_t)kChunk, jend - j0));
         __syncthreads();

@@ -28,8 +28,8 @@
 // coalesced wave-wide row; the reduction puts them into pixel order.
 //
 // Measured, kernel time before (10.5 vector FP64 instructions per term over every pixel)
-// and now: 16 particles (96,000 points) x 24 rotations, 128 x 128: 14.2 -> 5.67 ms (4.04 of
-// it multiply-adds at 74.7 TFLOP/s); 96 objects (240,000 points) split, 256 x 256: 6.19 -> 2.49 ms
+// and now: 16 particles (96,000 points) x 24 rotations, 128 x 128: 14.2 -> 5.70 ms (4.04 of
+// it multiply-adds at 74.7 TFLOP/s); 96 objects (240,000 points) split, 256 x 256: 6.19 -> 2.50 ms
 // (1.68; the largest object's items run alone at the end).
 #include <algorithm>
 #include <cmath>
