@@ -192,13 +192,14 @@ struct PrepLoader {
 // (store == 0; combined below), or straight into amp (1: written, 2: added).
 template <int MT, int CH>
 __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(const PointRec *__restrict__ pts,
-                                                                              int64_t W, int64_t per, CartGeom g,
-                                                                              int store, double *__restrict__ out)
+                                                                              int64_t W, int64_t per, int nsplit,
+                                                                              CartGeom g, int store,
+                                                                              double *__restrict__ out)
 {
     __shared__ cblk::Smem<MT> sm;
     const int lane = threadIdx.x & 63;
-    const int zb0 = blockIdx.x * g.nz, rb = blockIdx.y;
-    const int64_t jbeg = (int64_t)blockIdx.z * per;
+    const int zb0 = (int)(blockIdx.x / nsplit) * g.nz, rb = blockIdx.y, split = (int)(blockIdx.x % nsplit);
+    const int64_t jbeg = (int64_t)split * per;
     const int64_t jend = min(W, jbeg + per);
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(con
     const int zb = zb0 + cblk::wave_id() % g.nz;
     cblk::finish<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
         if (store == 0) {
-            double *o = out + (((((int64_t)blockIdx.z * g.nrb + rb) * g.nzb + zb) * MT + t) * 2 + h) * 256 + lane;
+            double *o = out + (((((int64_t)split * g.nrb + rb) * g.nzb + zb) * MT + t) * 2 + h) * 256 + lane;
             o[0] = vp.x;
             o[64] = vp.y;
             o[128] = vm.x;
@@ -259,40 +260,41 @@ int env_target()
 // Work split of the Cartesian sums.
 // ---------------------------------------------------------------------------
 constexpr int64_t kCartCUs = 256;     // one workgroup of 8 waves per CU at a time
-constexpr int kMaxSplits = 65535;     // grid.z
+constexpr int kMaxSplits = 65535;
 
-// Rows, columns and strides of the cells, row blocks for `channels`; the orientation
-// with fewer matrix tiles (thin detectors put their short axis into the packed rows).
+// Rows, columns and strides of the cells, row blocks for `channels`, with the detector's
+// rows (sw = 0) or columns packed into the matrix rows; the number of matrix tiles.
+static int64_t oriented_geometry(const Detector &d, int channels, int sw, CartGeom &g, int &mt)
+{
+    g.nM = sw ? d.n1 : d.n0;
+    g.nN = sw ? d.n0 : d.n1;
+    g.A = (g.nM + 1) / 2;
+    g.B = (g.nN + 1) / 2;
+    const int per_block = 8 * cblk::kMaxMT / channels;  // |q_M| values of a full row block
+    g.nrb = (g.A + per_block - 1) / per_block;
+    g.na = (g.A + g.nrb - 1) / g.nrb;
+    mt = (g.na * channels + 7) / 8;
+    g.nzb = (g.B + cblk::kOff - 1) / cblk::kOff;
+    g.swapped = sw;
+    g.firstM = g.nM % 2 == 0 ? 0.5 : 0.0;
+    g.stepM = sw ? d.step1 : d.step0;
+    g.firstN = g.nN % 2 == 0 ? 0.5 : 0.0;
+    g.stepN = sw ? d.step0 : d.step1;
+    g.strideM = sw ? 1 : d.n1;
+    g.strideN = sw ? d.n1 : 1;
+    return (int64_t)g.nrb * mt * g.nzb;
+}
+
+// The orientation with fewer matrix tiles (thin detectors put their short axis into the
+// packed rows).
 void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt)
 {
-    int64_t best = -1;
-    for (int sw = 0; sw < 2; ++sw) {
-        const int nM = sw ? d.n1 : d.n0, nN = sw ? d.n0 : d.n1;
-        const int A = (nM + 1) / 2, B = (nN + 1) / 2;
-        const int per_block = 8 * cblk::kMaxMT / channels;  // |q_M| values of a full row block
-        const int nrb = (A + per_block - 1) / per_block;
-        const int na = (A + nrb - 1) / nrb;
-        const int m = (na * channels + 7) / 8;
-        const int nzb = (B + cblk::kOff - 1) / cblk::kOff;
-        const int64_t tiles = (int64_t)nrb * m * nzb;
-        if (best >= 0 && tiles >= best) continue;
-        best = tiles;
-        mt = m;
-        g.A = A;
-        g.B = B;
-        g.nM = nM;
-        g.nN = nN;
-        g.na = na;
-        g.nrb = nrb;
-        g.nzb = nzb;
-        g.swapped = sw;
-        g.firstM = nM % 2 == 0 ? 0.5 : 0.0;
-        g.stepM = sw ? d.step1 : d.step0;
-        g.firstN = nN % 2 == 0 ? 0.5 : 0.0;
-        g.stepN = sw ? d.step0 : d.step1;
-        g.strideM = sw ? 1 : d.n1;
-        g.strideN = sw ? d.n1 : 1;
-    }
+    CartGeom t{};
+    int m = 0;
+    const int64_t rows = oriented_geometry(d, channels, 0, g, mt);
+    if (oriented_geometry(d, channels, 1, t, m) >= rows) return;
+    g = t;
+    mt = m;
 }
 
 // Column blocks per workgroup of a launch shape (the labels are those tables hold).
@@ -317,48 +319,81 @@ static void cart_splits(CartPlan &p, int64_t W, int64_t target, size_t max_parti
     p.nsplit = (int)std::max<int64_t>(1, (W + per - 1) / per);
 }
 
-// Estimated time (cycles) of a split, from the pipe counts: a matrix instruction
-// holds the FP64 pipe of its SIMD 64 cycles, a vector one 4, a sincos about 27 of
-// them; partial sums move at about 1700 bytes a cycle each way.
+// Estimated time (cycles) of a plan, from the pipe counts: a matrix instruction holds
+// the FP64 pipe of its SIMD 66 cycles, a vector one 4 (the tables take about 150 per chunk
+// and wave, and 90 per pass over the rows); partial sums move at about 1700 bytes a cycle
+// each way.  Workgroups whose column blocks run out are cheaper and are launched last.
 static double cart_cost(const CartPlan &p, int64_t W)
 {
     const double pts = (double)std::min<int64_t>(p.per, std::max<int64_t>(W, 1));
     const double chunks = std::ceil(pts / cblk::kChunk), steps = std::ceil(pts / 4.0);
-    // steps of the busiest SIMD: two column blocks, one, or a share of one
-    const double share = p.g.nz == 8 ? (p.g.nzb > 4 ? 2.0 : 1.0) : p.g.nz / 4.0;
-    const double busy = share * steps * (128.0 * p.mt + 60.0);
     const double passes = std::ceil(p.g.na / 16.0);
-    const double gen = 2.0 * (150.0 + passes * (150.0 + 8.0 * p.channels));
-    const int64_t wgs = (int64_t)p.col_groups * p.g.nrb * p.nsplit;
-    const double rounds = std::ceil((double)wgs / (double)kCartCUs);
+    const double fixed = 4000.0 + chunks * 2.0 * (300.0 + passes * (180.0 + 10.0 * p.channels)) +
+                         (p.g.nz < 8 ? 400.0 * p.mt : 0.0);
+    const double step = 132.0 * p.mt + 60.0;
+    // a workgroup of `blocks` column blocks: the steps of its busiest SIMD
+    auto cycles = [&](int blocks) {
+        const double share = p.g.nz == 8 ? (blocks > 4 ? 2.0 : 1.0) : p.g.nz / 4.0;
+        return fixed + share * steps * step;
+    };
+    const double full = (double)(p.g.nzb / p.g.nz) * p.g.nrb * p.nsplit, last = (double)p.g.nrb * p.nsplit;
+    const int rest = p.g.nzb % p.g.nz;
+    double t = 0.0;
+    if (rest == 0 || full == 0.0) {
+        t = std::ceil((rest == 0 ? full : last) / (double)kCartCUs) * cycles(rest == 0 ? p.g.nz : rest);
+    } else {
+        const double cf = cycles(p.g.nz), cl = cycles(rest);
+        const double even = (full * cf + last * cl) / (double)kCartCUs;
+        t = full + last <= (double)kCartCUs ? cf : std::max(std::ceil(full / (double)kCartCUs) * cf, even + 0.5 * cl);
+    }
     const double bytes = (double)cart_split_bytes(p.g, p.mt) * p.nsplit;
-    const double reduce = p.g.nz < 8 ? 400.0 * p.mt : 0.0;
-    return rounds * (4000.0 + chunks * gen + busy + reduce) + (p.nsplit > 1 ? 8000.0 + 2.0 * bytes / 1700.0 : 0.0);
+    return t + (p.nsplit > 1 ? 8000.0 + 2.0 * bytes / 1700.0 : 0.0);
 }
 
-static CartPlan cart_default_plan(const Detector &d, int64_t W, int channels, size_t max_partial)
+// The cheapest of the plans for `shapes` and `targets` (0: 1 to 4 rounds of the CUs), in both
+// orientations unless one takes a quarter more tiles.  Column blocks that do not fill the
+// last workgroup, and an orientation with fewer tiles but more of those, cost most where
+// one round is all there is; measured against one round of equal workgroups in the
+// orientation with fewer tiles: 20,000 points, 500 x 600 pixels 961 -> 823 us; 8,000,
+// 999 x 801 1047 -> 920; 50,000, 150 x 150 285 -> 258; 4,169, 128 x 128 unchanged.
+template <size_t N>
+static CartPlan cheapest_plan(const Detector &d, int64_t W, int channels, size_t max_partial, const int (&shapes)[N],
+                              int64_t target)
 {
     CartPlan best{};
     double best_cost = -1.0;
-    for (int shape : {32, 16, 64, 8}) {
-        CartPlan p{};
-        p.channels = channels;
-        p.shape = shape;
-        cart_geometry(d, channels, p.g, p.mt);
-        p.g.nz = cart_nz(shape);
-        if (p.g.nz > 2 && p.g.nz / 2 >= p.g.nzb) continue;  // column blocks that no wave would have
-        const int64_t blocks = (int64_t)((p.g.nzb + p.g.nz - 1) / p.g.nz) * p.g.nrb;
-        for (int rounds : {1, 2, 3, 4}) {
-            const int64_t target = env_target() > 0 ? env_target() : std::max<int64_t>(rounds * kCartCUs, blocks);
-            cart_splits(p, W, target, max_partial);
-            const double cost = cart_cost(p, W);
-            if (best_cost < 0.0 || cost < 0.98 * best_cost) {
-                best_cost = cost;
-                best = p;
+    CartPlan o[2]{};
+    int64_t tiles[2];
+    for (int sw = 0; sw < 2; ++sw) {
+        o[sw].channels = channels;
+        tiles[sw] = oriented_geometry(d, channels, sw, o[sw].g, o[sw].mt);
+    }
+    const int first = tiles[1] < tiles[0] ? 1 : 0;
+    for (int k = 0; k < 2; ++k) {
+        CartPlan &p = o[k == 0 ? first : 1 - first];
+        if (k == 1 && 4 * tiles[1 - first] > 5 * tiles[first]) break;
+        for (int shape : shapes) {
+            p.shape = shape;
+            p.g.nz = cart_nz(shape);
+            if (N > 1 && p.g.nz > 2 && p.g.nz / 2 >= p.g.nzb) continue;  // column blocks that no wave would have
+            const int64_t blocks = (int64_t)((p.g.nzb + p.g.nz - 1) / p.g.nz) * p.g.nrb;
+            for (int rounds = 1; rounds <= 4; ++rounds) {
+                cart_splits(p, W, target > 0 ? target : std::max<int64_t>(rounds * kCartCUs, blocks), max_partial);
+                const double cost = cart_cost(p, W);
+                if (best_cost < 0.0 || cost < 0.98 * best_cost) {
+                    best_cost = cost;
+                    best = p;
+                }
+                if (target > 0) break;
             }
         }
     }
     return best;
+}
+
+static CartPlan cart_default_plan(const Detector &d, int64_t W, int channels, size_t max_partial)
+{
+    return cheapest_plan(d, W, channels, max_partial, {32, 16, 64, 8}, env_target());
 }
 
 TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
@@ -402,13 +437,7 @@ CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool 
     if (!tuned_shape(kTuneDirect, key, W, &ts) || !valid_tune_shape(kTuneDirect, key, ts))
         return cart_default_plan(d, W, channels, max_partial);
     if (ts.target == 0) ts.target = default_tune_shape(kTuneDirect, key, W).target;
-    CartPlan p{};
-    p.channels = channels;
-    p.shape = ts.shape;
-    cart_geometry(d, channels, p.g, p.mt);
-    p.g.nz = cart_nz(ts.shape);
-    cart_splits(p, W, ts.target, max_partial);
-    return p;
+    return cheapest_plan(d, W, channels, max_partial, {ts.shape}, ts.target);
 }
 
 size_t cart_partial_bytes(const CartPlan &p)
@@ -419,9 +448,10 @@ size_t cart_partial_bytes(const CartPlan &p)
 template <int CH>
 static void launch_cart_tiles(const PointRec *pts, int64_t W, const CartPlan &p, int store, double *out, hipStream_t s)
 {
-    const dim3 grid(p.col_groups, p.g.nrb, p.nsplit), block(cblk::kThreads);
+    // full column groups first
+    const dim3 grid((unsigned)(p.nsplit * p.col_groups), p.g.nrb), block(cblk::kThreads);
 #define NUMAG_LAUNCH_CART(MT) \
-    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH>), grid, block, 0, s, pts, W, p.per, p.g, store, out)
+    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH>), grid, block, 0, s, pts, W, p.per, p.nsplit, p.g, store, out)
     switch (p.mt) {
         case 1: NUMAG_LAUNCH_CART(1); break;
         case 2: NUMAG_LAUNCH_CART(2); break;
