@@ -319,35 +319,75 @@ static void cart_splits(CartPlan &p, int64_t W, int64_t target, size_t max_parti
     p.nsplit = (int)std::max<int64_t>(1, (W + per - 1) / per);
 }
 
-// Estimated time (cycles) of a plan, from the pipe counts: a matrix instruction holds
-// the FP64 pipe of its SIMD 66 cycles, a vector one 4 (the tables take about 150 per chunk
-// and wave, and 90 per pass over the rows); partial sums move at about 1700 bytes a cycle
-// each way.  Workgroups whose column blocks run out are cheaper and are launched last.
+// Estimates in cycles.  A matrix instruction holds the FP64 pipe of its SIMD 66 cycles; the
+// tables of a chunk with what comes with them (loads, barrier, the waits that the sums do
+// not cover) were fitted to the times of 50,000 points on 150 x 150 pixels with 1, 2, 4 and
+// 8 column blocks per workgroup; the object kernel, which rotates the points as well, takes
+// 3280 (16 particles x 24 rotations, 128 x 128 pixels).
+static double table_cycles(const CartGeom &g, int channels)
+{
+    return 2.0 * (550.0 + std::ceil(g.na / 16.0) * (410.0 + 10.0 * channels));
+}
+// one step (4 points) of the busiest SIMD of a workgroup with `blocks` column blocks
+static double step_cycles(const CartGeom &g, int mt, int blocks)
+{
+    return (g.nz == 8 ? (blocks > 4 ? 2.0 : 1.0) : g.nz / 4.0) * (132.0 * mt + 60.0);
+}
+
+// Estimated time of a plan: partial sums move at about 1700 bytes a cycle each way.
+// Workgroups whose column blocks run out are cheaper and are launched last.
 static double cart_cost(const CartPlan &p, int64_t W)
 {
     const double pts = (double)std::min<int64_t>(p.per, std::max<int64_t>(W, 1));
-    const double chunks = std::ceil(pts / cblk::kChunk), steps = std::ceil(pts / 4.0);
-    const double passes = std::ceil(p.g.na / 16.0);
-    const double fixed = 4000.0 + chunks * 2.0 * (300.0 + passes * (180.0 + 10.0 * p.channels)) +
+    const double steps = std::ceil(pts / 4.0);
+    const double fixed = 4000.0 + std::ceil(pts / cblk::kChunk) * table_cycles(p.g, p.channels) +
                          (p.g.nz < 8 ? 400.0 * p.mt : 0.0);
-    const double step = 132.0 * p.mt + 60.0;
-    // a workgroup of `blocks` column blocks: the steps of its busiest SIMD
-    auto cycles = [&](int blocks) {
-        const double share = p.g.nz == 8 ? (blocks > 4 ? 2.0 : 1.0) : p.g.nz / 4.0;
-        return fixed + share * steps * step;
-    };
     const double full = (double)(p.g.nzb / p.g.nz) * p.g.nrb * p.nsplit, last = (double)p.g.nrb * p.nsplit;
     const int rest = p.g.nzb % p.g.nz;
+    const double cf = fixed + steps * step_cycles(p.g, p.mt, p.g.nz), cl = fixed + steps * step_cycles(p.g, p.mt, rest);
     double t = 0.0;
-    if (rest == 0 || full == 0.0) {
-        t = std::ceil((rest == 0 ? full : last) / (double)kCartCUs) * cycles(rest == 0 ? p.g.nz : rest);
+    if (rest == 0) {
+        t = std::ceil(full / (double)kCartCUs) * cf;
+    } else if (full == 0.0) {
+        t = std::ceil(last / (double)kCartCUs) * cl;
+    } else if (full + last <= (double)kCartCUs) {
+        t = cf;
     } else {
-        const double cf = cycles(p.g.nz), cl = cycles(rest);
-        const double even = (full * cf + last * cl) / (double)kCartCUs;
-        t = full + last <= (double)kCartCUs ? cf : std::max(std::ceil(full / (double)kCartCUs) * cf, even + 0.5 * cl);
+        t = std::max(std::ceil(full / (double)kCartCUs) * cf, (full * cf + last * cl) / (double)kCartCUs + 0.5 * cl);
     }
     const double bytes = (double)cart_split_bytes(p.g, p.mt) * p.nsplit;
     return t + (p.nsplit > 1 ? 8000.0 + 2.0 * bytes / 1700.0 : 0.0);
+}
+
+constexpr double kObjTables = 3280.0;
+
+// Cycles of a chunk of the object kernel, summed over the workgroups of a detector.
+static double chunk_cycles(const CartGeom &g, int mt)
+{
+    const int full = g.nzb / g.nz, rest = g.nzb % g.nz;
+    const double steps = cblk::kChunk / 4.0, tables = kObjTables;
+    return g.nrb * (full * (tables + steps * step_cycles(g, mt, g.nz)) +
+                    (rest > 0 ? tables + steps * step_cycles(g, mt, rest) : 0.0));
+}
+
+double cart_objects_geometry(const Detector &d, int shape, CartGeom &g, int &mt, double *group)
+{
+    CartGeom t[2]{};
+    int m[2];
+    double c[2];
+    for (int sw = 0; sw < 2; ++sw) {
+        oriented_geometry(d, 4, sw, t[sw], m[sw]);
+        t[sw].nz = cart_nz(shape);
+        c[sw] = chunk_cycles(t[sw], m[sw]);
+    }
+    const int k = c[1] < c[0] ? 1 : 0;
+    g = t[k];
+    mt = m[k];
+    if (group != nullptr) {
+        group[0] = kObjTables + cblk::kChunk / 4.0 * step_cycles(g, mt, g.nz);
+        group[1] = kObjTables + cblk::kChunk / 4.0 * step_cycles(g, mt, g.nzb % g.nz);
+    }
+    return c[k];
 }
 
 // The cheapest of the plans for `shapes` and `targets` (0: 1 to 4 rounds of the CUs), in both
@@ -411,10 +451,18 @@ TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
             // last ones even the load out; 16 particles x 24 rotations on 128 x 128 take
             // 6.0 ms with half as many, 5.74 with these, 5.64 with twice as many)
             if (d.kind == NUMAG_GRID_POLAR) return TuneShape{default_polar_shape(d), 16384};
+            // column blocks per workgroup: the fewest cycles of a chunk (objects.hip, where
+            // the objects are known, also weighs how evenly their items fill the chip)
             CartGeom g{};
-            int mt = 0;
-            cart_geometry(d, 4, g, mt);
-            return TuneShape{g.nzb > 4 ? 32 : g.nzb > 2 ? 16 : g.nzb > 1 ? 64 : 8, 2048};
+            int mt = 0, best = 32;
+            double least = -1.0;
+            for (int shape : {16, 32, 64, 8}) {
+                const double c = cart_objects_geometry(d, shape, g, mt, nullptr);
+                if (least >= 0.0 && c >= least) continue;
+                least = c;
+                best = shape;
+            }
+            return TuneShape{best, 2048};
         }
     }
 }

@@ -106,6 +106,10 @@ TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W);
 CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial = 0);
 // Cells, row blocks and matrix tiles of detector d for `channels` (cartesian_block.h).
 void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt);
+// The geometry of the object sums (four channels, column blocks of `shape`) in the cheaper
+// orientation; its cycles per chunk of points, and (group) those of a workgroup of all its
+// column blocks and of the last, partial one.
+double cart_objects_geometry(const Detector &d, int shape, CartGeom &g, int &mt, double *group);
 // Column blocks per workgroup of a launch shape.
 int cart_nz(int shape);
 // Bytes of partial sums (0 when one split writes the sums directly).

@@ -389,24 +389,66 @@ struct Tables {
     std::vector<int2> items;      // (slot, block), by decreasing cost
 };
 
+// Column blocks per workgroup of a Cartesian plan (as a launch shape).  Eight share the row
+// tables; fewer make more items and, where the last workgroup of a row would be half empty,
+// fewer idle SIMDs.  Time of the item queue, largest first: whole rounds of the CUs for
+// objects of one size, with the cheaper items of partial workgroups filling the last, else
+// all items over the CUs plus three quarters of the largest.
+// (With 8, 4, 2 and 1: 6 objects x 8 rotations, 170 x 180 pixels 1090, 952, 821, 1023 us; 30
+// objects, 90 x 90, one rotation 123, 114, 85, 129; 4 objects, 200 x 100, one rotation 974,
+// 639, 413, 271; 10 x 10, 150 x 150 1101, 1284, 1232, 1469.  20 x 10, 100 x 145, with the
+// other axis packed 528 -> 390.  96 unequal objects, 256 x 256, one rotation 2.69 ms with 8,
+// 2.45 with 4.)
+int cart_shape(const Detector &d, const std::vector<int64_t> &off, int64_t K, int64_t W, int64_t n_rot, int64_t target)
+{
+    const double cus = (double)device_cus();
+    int64_t most = 1;  // points of the largest object
+    for (int64_t k = 0; k < K; ++k) most = std::max(most, off[k + 1] - off[k]);
+    const bool equal = (double)most * (double)K <= 1.1 * (double)W;
+    const double all = (double)std::max<int64_t>(W, 1) * (double)n_rot;
+    int best = 32;
+    double least = -1.0;
+    for (int shape : {16, 32, 64, 8}) {
+        CartGeom g{};
+        int mt = 0;
+        double group[2] = {};
+        const double sum = cart_objects_geometry(d, shape, g, mt, group);
+        const int64_t full = g.nzb / g.nz, rest = g.nzb % g.nz > 0 ? 1 : 0;
+        const int64_t want = std::max<int64_t>(1, (target + (full + rest) * g.nrb - 1) / ((full + rest) * g.nrb));
+        double t;
+        if (equal) {
+            const int64_t per_object = std::min<int64_t>(n_rot, (std::max(want, K) + K - 1) / K);
+            const double slots = (double)(K * per_object);
+            const double slot = (double)most * (double)((n_rot + per_object - 1) / per_object);
+            const double nf = slots * (double)(full * g.nrb), nl = slots * (double)(rest * g.nrb);
+            t = slot * (nf == 0.0 ? std::ceil(nl / cus) * group[1]
+                                  : std::max(std::ceil(nf / cus) * group[0],
+                                             nl == 0.0 ? 0.0 : (nf * group[0] + nl * group[1]) / cus + 0.5 * group[1]));
+        } else {
+            t = all * sum / cus + 0.75 * std::max((double)most, all / (double)want) * group[full > 0 ? 0 : 1];
+        }
+        if (least >= 0.0 && t >= 0.98 * least) continue;
+        least = t;
+        best = shape;
+    }
+    return best;
+}
+
 Tables make_tables(const Detector &d, bool hermitian, const std::vector<int64_t> &off, int64_t K, int64_t W,
                    int64_t n_rot, int mode, int spec_per_object)
 {
     Tables T;
     ObjectsPlan &p = T.p;
-    const TuneShape ts = current_tune_shape(kTuneObjects, objects_detector(d, hermitian), W);
+    const Detector key = objects_detector(d, hermitian);
+    const TuneShape ts = current_tune_shape(kTuneObjects, key, W);
+    TuneShape entry{};
+    const bool tuned = tuned_shape(kTuneObjects, key, W, &entry) && valid_tune_shape(kTuneObjects, key, entry);
     if (d.kind == NUMAG_GRID_POLAR) {
         polar_geometry(d, 4, ts.shape, p.pg, p.mt);
         p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;
         p.n_th = p.n_blocks * p.mt * 2;
     } else {
-        cart_geometry(d, 4, p.cg, p.mt);
-        p.cg.nz = cart_nz(ts.shape);
-        // With one rotation a slot is at least one object, and few objects leave few items:
-        // below six per CU the largest ones set the time, and items of half the columns
-        // (their workgroups' waves share the points) even it out for 9 % more phasors
-        // (96 objects, 256 x 256: 2.69 -> 2.45 ms).
-        if (n_rot == 1 && p.cg.nz == 8 && K * p.cg.nrb * ((p.cg.nzb + 7) / 8) < 6 * 256) p.cg.nz = 4;
+        cart_objects_geometry(d, tuned ? ts.shape : cart_shape(d, off, K, W, n_rot, ts.target), p.cg, p.mt, nullptr);
         p.n_blocks = (int64_t)((p.cg.nzb + p.cg.nz - 1) / p.cg.nz) * p.cg.nrb;
         p.n_th = (int64_t)p.cg.nzb * p.cg.nrb * p.mt * 2;
     }
