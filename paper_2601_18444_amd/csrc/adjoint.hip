@@ -24,7 +24,7 @@
 // two-term recurrence) and now: 262,144 points, 256 x 256: 6.14 -> 2.01 ms (68 of the
 // card's 74.7 TFLOP/s; 2.37 with the coefficients staged through registers, which
 // spilled); error of the gradient against 64 bits 8.2e-14 -> 6.6e-15, the walk of 256
-// columns being gone.  20,000 points, 150 x 181 polar: 228 -> 226 us: every column of an
+// columns being gone.  20,000 points, 150 x 181 polar: 228 -> 222 us: every column of an
 // odd detector is summed, so the multiply-adds fall only from 10 to 8 per term and the
 // column tables (about 200 vector instructions per 32 points and column) take the rest;
 // an even detector needs half of both.
@@ -364,6 +364,7 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
         if (cl == 0) sincos_cw((2.0 * 3.141592653589793 * (double)(col + lane)) / (double)g.n_out, &dir.x, &dir.y);
         const double sth = lane_value(dir.x, cl), cth = lane_value(dir.y, cl);
         const double u0 = Y * sth + Z * cth;
+        __builtin_amdgcn_s_setprio(2);  // as in polar_block.h: tables before products
         double2 first, step;  // centre of the group's first block, centre step (second half)
         pblk::offsets(tab.off, g.dq, u0, first, step);
         double2 adv = make_double2(1.0, 0.0);  // from one row group to the next
@@ -376,6 +377,7 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
             if (half != 0) pblk::centres<2 * MT>(tab.ctr[gp], first, step);
             if (g.nrg > 1) first = cmul(first, adv);
             wave_fence();
+            __builtin_amdgcn_s_setprio(0);
             cblk::v4d acc[MT][kPolNP];
 #pragma unroll
             for (int t = 0; t < MT; ++t)

@@ -16,7 +16,7 @@
 //  - Polar real-space grid, and a detector that has the pixel at -q for every one at q (a
 //    Cartesian one, a polar one with an even number of columns): the polar sums with the
 //    two pixels as one point of two weights (polar_block.h), half the points, four data
-//    sets a pass.  200 x 360 pixels to 150 x 240 points, 2 sets: 232 us, against 450 over
+//    sets a pass.  200 x 360 pixels to 150 x 240 points, 2 sets: 226 us, against 450 over
 //    all pixels in three channels.
 //  - else: the direct sums over all pixels, their weight channels carrying up to four data
 //    sets at once: one set alone in channel 0 (the kernels' one-channel form), two or three

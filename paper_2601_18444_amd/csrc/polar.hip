@@ -3,8 +3,8 @@
 //
 // Measured, kernel time before (lanes walking q rows with a two-term recurrence, about
 // 10 vector FP64 instructions per term, every column summed) and now:
-//   100,003 points, 256 x 360       5.30 -> 1.34 ms (0.99 of it multiply-adds at 74.7 TFLOP/s)
-//   24,000 points, 1000 x 1000      9.55 -> 3.30 ms (2.6)
+//   100,003 points, 256 x 360       5.30 -> 1.28 ms (0.99 of it multiply-adds at 74.7 TFLOP/s)
+//   24,000 points, 1000 x 1000      9.55 -> 3.22 ms (2.6)
 // The rest is the tables: about 240 vector instructions per 32 points and column.
 #include <algorithm>
 #include <cmath>

@@ -163,8 +163,13 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     for (int64_t j0 = jbeg; j0 < jend; j0 += kChunk) {
         const Point<NW> p = ld.point(raw);
         const double u = p.m * sth + p.n * cth;
+        // A wave that builds tables goes first: its short instructions otherwise wait for a
+        // matrix instruction of the SIMD's other wave each, and both end up building at the
+        // same time (100,003 points, 256 x 360: 1.39 -> 1.33 ms).
+        __builtin_amdgcn_s_setprio(2);
         generate<MT, CH, NW>(sm, a0, dq, u, p);
         wave_fence();
+        __builtin_amdgcn_s_setprio(0);
         raw = fetch(j0 + kChunk);
         const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
         const double2 *op = &sm.off[kq][r16], *cp = &sm.ctr[kq][0];
