@@ -159,8 +159,21 @@ DirectLayout direct_layout(const numag_sample *s, const Detector &d)
 
 // Direct sums of one rotation: prep + sum + combine into amp (P x 8 doubles).  hermitian: evaluate half of the (centro-
 // symmetric) detector and complete it by S(-q) = conj S(q) (real weights).
+// Whether a Cartesian sum reads the sample itself instead of records prepared in a launch of
+// their own: every workgroup of a point range then rotates its points again, about 1.3e-5 us
+// per point and workgroup on the whole chip, which has to stay below what the preparation
+// takes, 3.5 us and 4e-5 us per point.  Measured per call, prepared and direct: 500 points,
+// 48 x 81 pixels 25.3 and 21.0 us; 4,169, 128 x 128 36.0 and 34.0; 200,000, 32 x 32 94.8 and
+// 90.1; and on the other side 30,011, 201 x 333 in three channels 270.6 and 274.6; 100,000,
+// 256 x 256 838 and 844.
+bool reads_sample(const CartPlan &p, int64_t W)
+{
+    return (1.3 * (double)p.col_groups * (double)p.g.nrb - 4.0) * (double)W < 1.5e5;
+}
+
+// keep_points: the caller reads the prepared points from the workspace afterwards.
 int run_direct(const numag_sample *s, const Rot &R, const Detector &d, double *amp, void *ws,
-               hipStream_t st, bool hermitian = false)
+               hipStream_t st, bool hermitian = false, bool keep_points = false)
 {
     DirectLayout L = direct_layout(s, d);
     Carve cv(ws);
@@ -172,12 +185,17 @@ int run_direct(const numag_sample *s, const Rot &R, const Detector &d, double *a
     }
     // channels summed: a sample without nuclear (magnetic) weights skips those FMAs
     const int channels = s->nuc == nullptr ? 3 : (s->mag == nullptr ? 1 : 4);
+    CartPlan plan{};
+    if (d.kind == NUMAG_GRID_CARTESIAN) {
+        plan = plan_direct_cartesian(d, s->n_points, channels, hermitian);
+        if (!keep_points && s->regular == nullptr && s->obj_pos == nullptr && reads_sample(plan, s->n_points))
+            return launch_sample_cartesian(s->pos, s->nuc, s->mag, R, s->n_points, plan, part, amp, st);
+    }
     int rc = launch_prepare_points(s->pos, s->nuc, s->mag, 0, s->n_points, s->regular, s->obj_offsets,
                                    s->n_objects, s->obj_pos, R, pts, st);
     if (rc != NUMAG_OK) return rc;
     if (d.kind == NUMAG_GRID_CARTESIAN)
-        return launch_direct_cartesian(pts, s->n_points, plan_direct_cartesian(d, s->n_points, channels, hermitian),
-                                       part, amp, 0, st);
+        return launch_direct_cartesian(pts, s->n_points, plan, part, amp, 0, st);
     return launch_direct_polar(pts, s->n_points, plan_direct_polar(d, s->n_points, channels, hermitian), part, amp, 0,
                                st);
 }
@@ -753,7 +771,7 @@ int numag_grad_path(const numag_sample *sample, const double *rot, const numag_q
     void *gws = cv.take(gbytes);
     const Rot R = rot_of(rot, 0);
     if (amp_in == nullptr) {
-        rc = run_direct(sample, R, d, amp, direct_ws, st, hermitian);
+        rc = run_direct(sample, R, d, amp, direct_ws, st, hermitian, true);
         if (rc != NUMAG_OK) return rc;
         amp_in = amp;
     } else {

@@ -188,12 +188,50 @@ struct PrepLoader {
     __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const { return r; }
 };
 
+// Points straight from a sample (no object offsets), the record's arithmetic.
+template <int CH>
+struct SampleLoader {
+    struct Raw {
+        double x[3], n, m[3];
+    };
+    const double *__restrict__ pos, *__restrict__ nuc, *__restrict__ mag;
+    Rot R;
+    int swapped;
+    __device__ __forceinline__ Raw raw(int64_t j) const
+    {
+        Raw r{};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) r.x[i] = pos[3 * j + i];
+        if (CH != 3) r.n = nuc[j];
+        if (CH != 1) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) r.m[i] = mag[3 * j + i];
+        }
+        return r;
+    }
+    __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const
+    {
+        auto row = [&](int i, const double (&v)[3]) {
+            return R.m[3 * i] * v[0] + R.m[3 * i + 1] * v[1] + R.m[3 * i + 2] * v[2];
+        };
+        cblk::Point<CH> p;
+        const double Y = row(1, r.x), Z = row(2, r.x);
+        p.m = swapped ? Z : Y;
+        p.n = swapped ? Y : Z;
+        if (CH != 3) p.w[0] = r.n;
+        if (CH != 1) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) p.w[(CH == 4 ? 1 : 0) + i] = row(i, r.m);
+        }
+        return p;
+    }
+};
+
 // Where a workgroup's sums go: partials [split][row block][column block][tile][half][4][64]
 // (store == 0; combined below), or straight into amp (1: written, 2: added).
-template <int MT, int CH>
-__global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(const PointRec *__restrict__ pts,
-                                                                              int64_t W, int64_t per, int nsplit,
-                                                                              CartGeom g, int store,
+template <int MT, int CH, class Loader>
+__global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(Loader ld, int64_t W, int64_t per,
+                                                                              int nsplit, CartGeom g, int store,
                                                                               double *__restrict__ out)
 {
     __shared__ cblk::Smem<MT> sm;
@@ -203,8 +241,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(con
     const int64_t jend = min(W, jbeg + per);
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
-    const PrepLoader<CH> ld{pts, g.swapped};
-    typename PrepLoader<CH>::Raw p, q;
+    typename Loader::Raw p, q;
     cblk::first_points(ld, jbeg, jend, p, q);
     cblk::accumulate<MT, CH>(ld, jbeg, jend, g, rb, zb0, sm, p, q, accC, accS);
     const int zb = zb0 + cblk::wave_id() % g.nz;
@@ -493,13 +530,14 @@ size_t cart_partial_bytes(const CartPlan &p)
     return p.nsplit > 1 ? cart_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
 }
 
-template <int CH>
-static void launch_cart_tiles(const PointRec *pts, int64_t W, const CartPlan &p, int store, double *out, hipStream_t s)
+template <int CH, class Loader>
+static void launch_cart_tiles(const Loader &ld, int64_t W, const CartPlan &p, int store, double *out, hipStream_t s)
 {
     // full column groups first
     const dim3 grid((unsigned)(p.nsplit * p.col_groups), p.g.nrb), block(cblk::kThreads);
-#define NUMAG_LAUNCH_CART(MT) \
-    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH>), grid, block, 0, s, pts, W, p.per, p.nsplit, p.g, store, out)
+#define NUMAG_LAUNCH_CART(MT)                                                                                     \
+    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH, Loader>), grid, block, 0, s, ld, W, p.per, p.nsplit, p.g, \
+                       store, out)
     switch (p.mt) {
         case 1: NUMAG_LAUNCH_CART(1); break;
         case 2: NUMAG_LAUNCH_CART(2); break;
@@ -513,27 +551,49 @@ static void launch_cart_tiles(const PointRec *pts, int64_t W, const CartPlan &p,
 #undef NUMAG_LAUNCH_CART
 }
 
-int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
-                            int accumulate, hipStream_t s)
+static int combine_cartesian(const CartPlan &p, const double *partial, double *amp, int accumulate, hipStream_t s)
 {
-    const bool split = p.nsplit > 1;
-    const int store = split ? 0 : (accumulate ? 2 : 1);
-    {
-        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
-        double *out = split ? partial : amp;
-        switch (p.channels) {
-            case 1: launch_cart_tiles<1>(pts, W, p, store, out, s); break;
-            case 3: launch_cart_tiles<3>(pts, W, p, store, out, s); break;
-            default: launch_cart_tiles<4>(pts, W, p, store, out, s); break;
-        }
-    }
     NUMAG_HIP_CHECK(hipGetLastError());
-    if (!split) return NUMAG_OK;
+    if (p.nsplit <= 1) return NUMAG_OK;
     const int64_t n = (int64_t)p.g.nrb * p.g.nzb * p.mt * 128;
     hipLaunchKernelGGL(cart_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
                        p.channels, p.nsplit, accumulate, amp);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
+}
+
+int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
+                            int accumulate, hipStream_t s)
+{
+    const int store = p.nsplit > 1 ? 0 : (accumulate ? 2 : 1);
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        double *out = p.nsplit > 1 ? partial : amp;
+        const int sw = p.g.swapped;
+        switch (p.channels) {
+            case 1: launch_cart_tiles<1>(PrepLoader<1>{pts, sw}, W, p, store, out, s); break;
+            case 3: launch_cart_tiles<3>(PrepLoader<3>{pts, sw}, W, p, store, out, s); break;
+            default: launch_cart_tiles<4>(PrepLoader<4>{pts, sw}, W, p, store, out, s); break;
+        }
+    }
+    return combine_cartesian(p, partial, amp, accumulate, s);
+}
+
+int launch_sample_cartesian(const double *pos, const double *nuc, const double *mag, const Rot &R, int64_t W,
+                            const CartPlan &p, double *partial, double *amp, hipStream_t s)
+{
+    const int store = p.nsplit > 1 ? 0 : 1;
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        double *out = p.nsplit > 1 ? partial : amp;
+        const int sw = p.g.swapped;
+        switch (p.channels) {
+            case 1: launch_cart_tiles<1>(SampleLoader<1>{pos, nuc, mag, R, sw}, W, p, store, out, s); break;
+            case 3: launch_cart_tiles<3>(SampleLoader<3>{pos, nuc, mag, R, sw}, W, p, store, out, s); break;
+            default: launch_cart_tiles<4>(SampleLoader<4>{pos, nuc, mag, R, sw}, W, p, store, out, s); break;
+        }
+    }
+    return combine_cartesian(p, partial, amp, 0, s);
 }
 
 __global__ void fill_kernel(double *__restrict__ out, int64_t n, double value)

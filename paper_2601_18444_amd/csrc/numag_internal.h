@@ -117,6 +117,10 @@ size_t cart_partial_bytes(const CartPlan &p);
 // Writes (accumulate: adds) the sums of all pixels of the detector to amp [P][8].
 int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
                             int accumulate, hipStream_t s);
+// The same from a sample's arrays, rotated by R as they are read (no object offsets; the
+// arrays of channels outside the plan's set are not read).
+int launch_sample_cartesian(const double *pos, const double *nuc, const double *mag, const Rot &R, int64_t W,
+                            const CartPlan &p, double *partial, double *amp, hipStream_t s);
 
 // Polar detector direct sum (polar_block.h).
 constexpr int kPolarShapeCount = 5;
