@@ -6,10 +6,11 @@ A step is one pass of the whole hot path over the 64^3 vortex grid on a
   the 128-bin azimuthal average, the correlation function (256 radii), the
   regular-grid separable sums on the matrix cores (when built), and the loss
   gradient through the adjoint sum.
-`value` counts the terms the step evaluates one by one -- W*P for the direct
-sums and W*P for the adjoint sums -- over the time of the whole step (every
-other part of the step, the separable matrix-core sums included, adds time but
-no terms); the separable path's equivalent-term rate and the rate of the direct
+`value` counts the (point, pixel) terms of the direct sums, W*P, and of the
+adjoint sums, W*P (the four pixels +-q_y, +-q_z of a cell share four real sums
+over the points, one multiply-add per term and channel), over the time of the
+whole step (every other part of the step, the separable matrix-core sums
+included, adds time but no terms); the separable path's equivalent-term rate and the rate of the direct
 call alone are reported under `paths`.  Inputs are resident in HBM before
 timing starts.  Prints one JSON line.
 """
@@ -33,10 +34,10 @@ PEAK_FP64_VALU = 256 * 2.4e9 * 64 * 2  # 78.6 TFLOP/s: 256 CUs x 64 FP64 FMA lan
 PEAK_FP32_VALU = 157.3e12              # packed FP32 vector peak (datasheet)
 PEAK_FP64_MFMA = 78.6e12               # FP64 dense matrix peak (datasheet)
 PEAK_HBM = 8.0e12                      # HBM3E bytes/s (datasheet)
-# algorithmic work of one (point, pixel) term: the phase q.X (2 FMA) and the
-# four channel sums, real and imaginary parts (8 FMA); the sine and cosine are
-# not counted
-FLOPS_PER_TERM = 20
+# algorithmic work of one (point, pixel) term: one real multiply-add per channel. The
+# weights are real and the detector symmetric about q = 0, so the four pixels of a cell
+# (+-q_y, +-q_z) follow from four real sums; the phasors are not counted
+FLOPS_PER_TERM = 8
 PROFILES = os.path.join(ROOT, "profiles")
 # kernel -> (library timer id, sources that define it, file holding its HBM counters)
 KERNELS = {
@@ -344,8 +345,8 @@ def measure_snapshots(torch, numag, synth, n_snap=64):
         e1.record()
         torch.cuda.synchronize()
         t_bf[name] = e0.elapsed_time(e1) / reps
-    flops = n_snap * 4 * (64 * 64 * 256 * 4 + 256 * 64 * 256 * 8)  # both contractions, four channels
-    flops_h = n_snap * 4 * (64 * 64 * 256 * 4 + 128 * 64 * 256 * 8)  # the Hermitian variant's executed flops
+    # both contractions, four channels, in real parity sums (the Hermitian variant runs the same)
+    flops = flops_h = n_snap * 4 * (64 * 64 * 256 * 2 + 256 * 64 * 256 * 2)
     # the call's kernels run one after the other, so its bound is the projection's HBM time
     # (the weights read once, the projections written) plus the contractions' matrix-core time
     hbm_bytes = n_snap * W * 32 + n_snap * 4 * 64 * 64 * 8
@@ -785,7 +786,7 @@ def main():
     t_adj = avg_ms(ev["adjoint"])
     t_sep = avg_ms(ev["separable"]) if have_sep else None
     terms = W * P
-    # terms evaluated one by one per step: the direct sums and the adjoint sums
+    # terms per step: the direct sums and the adjoint sums
     value = 2 * terms / (ms_per_step * 1e-3) / 1e9
 
     dominant = max(kernel_ms, key=lambda k: kernel_ms[k])
@@ -817,8 +818,7 @@ def main():
         },
         "tuning": tuning,
         "paths": {
-            # the step rate if the separable call's equivalent terms (W P, not evaluated
-            # one by one) were counted too
+            # the step rate if the separable call's equivalent terms (W P) were counted too
             "step_Gterm_s_with_separable_equivalent": round((3 if have_sep else 2) * terms / (ms_per_step * 1e-3)
                                                             / 1e9, 2),
             "direct_Gterm_s": round(terms / (t_direct * 1e-3) / 1e9, 2),
@@ -830,7 +830,7 @@ def main():
             "adjoint_Gterm_s": round(terms / (t_adj * 1e-3) / 1e9, 2),
             "adjoint_ms": round(t_adj, 4),
             "adjoint_kernel_ms": round(kernel_ms["adjoint_cartesian_kernel"], 4),
-            # the adjoint kernel against the same FP64 VALU peak (20 flops per term)
+            # the adjoint kernel against the same FP64 VALU peak (8 flops per term)
             "adjoint_roofline": {
                 "achieved": round(FLOPS_PER_TERM * terms / (kernel_ms["adjoint_cartesian_kernel"] * 1e-3) / 1e12, 3),
                 "frac": round(FLOPS_PER_TERM * terms / (kernel_ms["adjoint_cartesian_kernel"] * 1e-3)

@@ -85,7 +85,7 @@ int env_target();
 // ---------------------------------------------------------------------------
 enum { kTuneDirect = 0, kTuneAdjoint = 1, kTuneObjects = 2, kTuneKernelCount = 3 };
 struct TuneShape {
-    int shape;   // Cartesian direct / objects: lanes per row; polar direct: workgroup shape; adjoint: 0
+    int shape;   // Cartesian: column blocks (cart_nz); polar: row blocks per wave; adjoint: 0
     int target;  // workgroups (objects: work items) a launch aims for
 };
 int tune_wclass(int64_t W);
