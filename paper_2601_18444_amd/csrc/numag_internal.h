@@ -143,6 +143,9 @@ PolarPlan plan_direct_polar(const Detector &d, int64_t W, int channels, bool her
 size_t polar_partial_bytes(const PolarPlan &p);
 int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, double *partial, double *amp,
                         int accumulate, hipStream_t s);
+// The same from a sample's arrays, as launch_sample_cartesian.
+int launch_sample_polar(const double *pos, const double *nuc, const double *mag, const Rot &R, int64_t W,
+                        const PolarPlan &p, double *partial, double *amp, hipStream_t s);
 // Sums of 1 to 4 channels over pairs of points.
 int launch_polar_pairs(const PairRec *pts, int64_t n, const PolarPlan &p, double *partial, double *amp, hipStream_t s);
 // out[i] = value for i < n (a kernel, so that callers may capture it in a graph).

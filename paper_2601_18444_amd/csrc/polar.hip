@@ -39,13 +39,49 @@ struct PolarRecLoader {
     __device__ __forceinline__ Raw point(const Raw &r) const { return r; }
 };
 
+// Points straight from a sample (no object offsets), with the arithmetic of the records.
+template <int CH>
+struct PolarSampleLoader {
+    struct Raw {
+        double x[3], n, m[3];
+    };
+    const double *__restrict__ pos, *__restrict__ nuc, *__restrict__ mag;
+    Rot R;
+    __device__ __forceinline__ Raw raw(int64_t j) const
+    {
+        Raw r{};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) r.x[i] = pos[3 * j + i];
+        if (CH != 3) r.n = nuc[j];
+        if (CH != 1) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) r.m[i] = mag[3 * j + i];
+        }
+        return r;
+    }
+    __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const
+    {
+        auto row = [&](int i, const double (&v)[3]) {
+            return R.m[3 * i] * v[0] + R.m[3 * i + 1] * v[1] + R.m[3 * i + 2] * v[2];
+        };
+        cblk::Point<CH> p;
+        p.m = row(1, r.x);
+        p.n = row(2, r.x);
+        if (CH != 3) p.w[0] = r.n;
+        if (CH != 1) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) p.w[(CH == 4 ? 1 : 0) + i] = row(i, r.m);
+        }
+        return p;
+    }
+};
+
 // One wave: one theta column, one row group, one point range.  Partials
 // [split][row group][column][tile][half][4][64] (store == 0), or amp (1: written,
 // 2: added).
-template <int MT, int CH, int NW>
-__global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(
-    const typename PolarRecLoader<CH, NW>::Rec *__restrict__ pts, int64_t W, int64_t per, PolGeom g, int store,
-    double *__restrict__ out)
+template <int MT, int CH, int NW, class Loader>
+__global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(Loader ld, int64_t W, int64_t per, PolGeom g,
+                                                                         int store, double *__restrict__ out)
 {
     __shared__ pblk::WaveSmem<MT, CH, NW> sm[pblk::kWaves];
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
@@ -57,8 +93,7 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(
     sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
-    pblk::accumulate<MT, CH, NW>(PolarRecLoader<CH, NW>{pts}, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC,
-                                 accS);
+    pblk::accumulate<MT, CH, NW>(ld, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -195,8 +230,8 @@ size_t polar_partial_bytes(const PolarPlan &p)
     return p.nsplit > 1 ? polar_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
 }
 
-template <int CH, int NW = CH>
-static void launch_polar_tiles(const typename PolarRecLoader<CH, NW>::Rec *pts, int64_t W, const PolarPlan &p, int store, double *out,
+template <int CH, int NW, class Loader>
+static void launch_polar_tiles(const Loader &ld, int64_t W, const PolarPlan &p, int store, double *out,
                                hipStream_t s)
 {
     const dim3 grid((p.g.cols + pblk::kWaves - 1) / pblk::kWaves, p.g.nrg, p.nsplit), block(pblk::kThreads);
@@ -204,7 +239,7 @@ static void launch_polar_tiles(const typename PolarRecLoader<CH, NW>::Rec *pts, 
 #define NUMAG_LAUNCH_POLAR(MT)   \
     case MT:                     \
         if constexpr (MT <= 2 * CH) \
-            hipLaunchKernelGGL((direct_polar_kernel<MT, CH, NW>), grid, block, 0, s, pts, W, p.per, p.g, store, out); \
+            hipLaunchKernelGGL((direct_polar_kernel<MT, CH, NW, Loader>), grid, block, 0, s, ld, W, p.per, p.g, store, out); \
         break
     switch (p.mt) {
         NUMAG_LAUNCH_POLAR(1);
@@ -238,12 +273,28 @@ int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, doub
         TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
         double *out = p.nsplit > 1 ? partial : amp;
         switch (p.channels) {
-            case 1: launch_polar_tiles<1>(pts, W, p, store, out, s); break;
-            case 3: launch_polar_tiles<3>(pts, W, p, store, out, s); break;
-            default: launch_polar_tiles<4>(pts, W, p, store, out, s); break;
+            case 1: launch_polar_tiles<1, 1>(PolarRecLoader<1, 1>{pts}, W, p, store, out, s); break;
+            case 3: launch_polar_tiles<3, 3>(PolarRecLoader<3, 3>{pts}, W, p, store, out, s); break;
+            default: launch_polar_tiles<4, 4>(PolarRecLoader<4, 4>{pts}, W, p, store, out, s); break;
         }
     }
     return combine_polar(p, partial, amp, accumulate, s);
+}
+
+int launch_sample_polar(const double *pos, const double *nuc, const double *mag, const Rot &R, int64_t W,
+                        const PolarPlan &p, double *partial, double *amp, hipStream_t s)
+{
+    const int store = p.nsplit > 1 ? 0 : 1;
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        double *out = p.nsplit > 1 ? partial : amp;
+        switch (p.channels) {
+            case 1: launch_polar_tiles<1, 1>(PolarSampleLoader<1>{pos, nuc, mag, R}, W, p, store, out, s); break;
+            case 3: launch_polar_tiles<3, 3>(PolarSampleLoader<3>{pos, nuc, mag, R}, W, p, store, out, s); break;
+            default: launch_polar_tiles<4, 4>(PolarSampleLoader<4>{pos, nuc, mag, R}, W, p, store, out, s); break;
+        }
+    }
+    return combine_polar(p, partial, amp, 0, s);
 }
 
 int launch_polar_pairs(const PairRec *pts, int64_t n, const PolarPlan &p, double *partial, double *amp, hipStream_t s)
@@ -253,10 +304,10 @@ int launch_polar_pairs(const PairRec *pts, int64_t n, const PolarPlan &p, double
         TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
         double *out = p.nsplit > 1 ? partial : amp;
         switch (p.channels) {
-            case 1: launch_polar_tiles<1, 2>(pts, n, p, store, out, s); break;
-            case 2: launch_polar_tiles<2, 4>(pts, n, p, store, out, s); break;
-            case 3: launch_polar_tiles<3, 6>(pts, n, p, store, out, s); break;
-            default: launch_polar_tiles<4, 8>(pts, n, p, store, out, s); break;
+            case 1: launch_polar_tiles<1, 2>(PolarRecLoader<1, 2>{pts}, n, p, store, out, s); break;
+            case 2: launch_polar_tiles<2, 4>(PolarRecLoader<2, 4>{pts}, n, p, store, out, s); break;
+            case 3: launch_polar_tiles<3, 6>(PolarRecLoader<3, 6>{pts}, n, p, store, out, s); break;
+            default: launch_polar_tiles<4, 8>(PolarRecLoader<4, 8>{pts}, n, p, store, out, s); break;
         }
     }
     return combine_polar(p, partial, amp, 0, s);

@@ -121,13 +121,14 @@ def test_separable_cells(orc, n0, n1, n):
 
 
 @pytest.mark.parametrize("chan", [0, 1, 2])
+@pytest.mark.parametrize("kind", [0, 1])
 @pytest.mark.parametrize("n0,n1,W", [(5, 7, 1), (33, 20, 31), (48, 81, 33), (20, 300, 500), (64, 64, 4169)])
-def test_points_straight_from_the_sample(n0, n1, W, chan):
-    """Small Cartesian sums read and rotate the sample in the sum kernel; an object offset of
+def test_points_straight_from_the_sample(kind, n0, n1, W, chan):
+    """Small sums read and rotate the sample in the sum kernel; an object offset of
     zero sends the same points through their preparation."""
     rng = np.random.default_rng(W + chan)
     w = dict(nuc=rng.standard_normal(W) if chan != 2 else None, mag=rng.standard_normal((W, 3)) if chan != 1 else None)
-    pos, R, grid = rng.uniform(-9, 9, (W, 3)), synth.sample_rotation(21.0, 64.0), numag.qgrid(0, n0, n1, 1.3)
+    pos, R, grid = rng.uniform(-9, 9, (W, 3)), synth.sample_rotation(21.0, 64.0), numag.qgrid(kind, n0, n1, 1.3)
     one = numag.Sample(pos=pos, device=DEV, **w)
     off = numag.Sample(pos=pos, obj_pos=np.zeros((1, 3)), obj_offsets=[0, W], device=DEV, **w)
     a, _ = numag.amplitudes(one, grid, rot=R)
