@@ -77,23 +77,18 @@ extern "C" {
    meets the 1e-4 gate of the matrix-core path on every observable; they are
    provided for speed comparisons. */
 #define NUMAG_PATH_SEPARABLE_BF16X3 2
-/* Direct path on half of a detector that is symmetric about q = 0 (every
-   Cartesian detector; a polar one with an even n_theta), the other half filled
-   by S(-q) = conj S(q), which holds because the weights are real: half the
-   work, the same sums up to rounding (the mirrored pixel takes the conjugate
-   of its partner's sum instead of a sum over its own q, which differs from -q
-   by at most an ulp).  All modes: in DILUTE / SPLIT the spectral matrices
-   follow G(-q) = conj G(q) and the coherent total A(-q) = conj A(q), for
-   every rotation. */
+/* The direct path where every pixel has its mirror image at -q (every Cartesian
+   detector; a polar one with an even n_theta, others are refused): with real
+   weights S(-q) = conj S(q), so the sums of mirrored pixels are conjugates and
+   spectral matrices G(-q) = conj G(q), for every rotation.  NUMAG_PATH_DIRECT uses
+   the same symmetry where it holds, so both paths give the same results at the
+   same cost there; their tuned launch shapes are looked up separately. */
 #define NUMAG_PATH_DIRECT_HERMITIAN 3
 #define NUMAG_PATH_SEPARABLE_BF16X6 4  /* see NUMAG_PATH_SEPARABLE_BF16X3 */
-/* FP64 separable path on half of the (symmetric) Cartesian detector: the second
-   contraction runs on rows [0, ceil(n0 / 2)) only and writes each pixel's
-   conjugate at the mirrored pixel, S(-q) = conj S(q) for real weights -- half of
-   the dominant contraction's work.  The computed rows equal the full path's bit
-   for bit; a mirrored pixel takes its partner's conjugate instead of a sum over
-   its own q (which differs from -q by at most an ulp).  Same arguments,
-   workspace and outputs as NUMAG_PATH_SEPARABLE_F64. */
+/* The FP64 separable path by another name: the contractions of
+   NUMAG_PATH_SEPARABLE_F64 run on the cells (|q_y|, |q_z|) and write mirrored
+   pixels as conjugates, S(-q) = conj S(q) for real weights, so the results are the
+   same bit for bit.  Same arguments, workspace and outputs. */
 #define NUMAG_PATH_SEPARABLE_F64_HERMITIAN 5
 
 /* ---- object modes (Sec. 3.3, summation relation and dilute limit) -------- */
@@ -359,9 +354,8 @@ int numag_correlation(const double *q, const double *I, int32_t n_q, int32_t n_f
  *             NUMAG_MODE_COHERENT) bytes.
  * numag_grad is numag_grad_path with NUMAG_PATH_DIRECT.  With
  * NUMAG_PATH_DIRECT_HERMITIAN (a polar detector needs an even n_theta) the
- * sums (when amp_in is NULL) and the adjoint run on half of the detector: the
- * residual weight of each pixel's mirror p' (at -q within an ulp) is folded
- * onto it as a(p) + conj a(p'), since Re[a(p') exp(+i q.X)] =
+ * result is the same.  The residual weight of each pixel's mirror p' (at -q within
+ * an ulp) is folded onto it as a(p) + conj a(p'), since Re[a(p') exp(+i q.X)] =
  * Re[conj a(p') exp(-i q.X)]; this holds for any target and loss weights.  The
  * loss is evaluated over the whole detector.
  */

@@ -427,8 +427,8 @@ class BatchedOrientations:
 
     The graph reads the sample's device arrays at replay time, so weights may
     be updated in place between replays; rotations and object offsets are fixed
-    at construction.  path=PATH_DIRECT_HERMITIAN sums half of a symmetric
-    detector and completes the spectral matrices by G(-q) = conj G(q)."""
+    at construction.  path=PATH_DIRECT_HERMITIAN asks
+    for a symmetric detector, whose spectral matrices obey G(-q) = conj G(q)."""
 
     def __init__(self, sample: Sample, grid: QGrid, rotations, spec_per_object: bool = True, path: int = PATH_DIRECT):
         self.sample, self.grid, self.path = sample, grid, path
@@ -558,7 +558,7 @@ def angular_spectrum(grid: QGrid, f: torch.Tensor, k_max: int, amplitudes: bool 
 def grad(sample: Sample, grid: QGrid, c: Consts, weight: torch.Tensor, target: Optional[torch.Tensor] = None,
          rot=None, amp: Optional[torch.Tensor] = None, want_nuc=True, want_mag=True, path=PATH_DIRECT):
     """numag_grad_path.  Returns (loss [1] or None, dnuc [W] or None, dmag [W, 3] or None).
-    path=PATH_DIRECT_HERMITIAN runs the sums and the adjoint on half of the detector."""
+    path=PATH_DIRECT_HERMITIAN asks for a symmetric detector."""
     r, n_rot = _rot_array(rot)
     if n_rot != 1:
         raise ValueError("grad takes one rotation")
@@ -579,8 +579,7 @@ def grad(sample: Sample, grid: QGrid, c: Consts, weight: torch.Tensor, target: O
 class UnpolarizedCrossSection(torch.autograd.Function):
     """Unpolarized 2D cross section (Sec. 2.4) as a differentiable function of
     the nuclear and magnetic weights; backward is the adjoint Fourier sum.
-    path=PATH_DIRECT_HERMITIAN runs the sums and the adjoint on half of a
-    symmetric detector."""
+    path=PATH_DIRECT_HERMITIAN asks for a symmetric detector."""
 
     @staticmethod
     def forward(ctx, nuc, mag, sample: Sample, grid: QGrid, c: Consts, rot=None, path=PATH_DIRECT):
