@@ -269,26 +269,28 @@ int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Det
 __global__ __launch_bounds__(256) void angular_spectrum_kernel(Detector d, const double *__restrict__ f, int k_max,
                                                                double *__restrict__ Is, double *__restrict__ Ic)
 {
-    const int row = blockIdx.x, set = blockIdx.y;
+    const int set = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t P = (int64_t)d.n0 * d.n1;
-    const double *fr = f + (int64_t)set * P + (int64_t)row * d.n1;
     const double h = 2.0 * 3.141592653589793 / (double)d.n1;
-    for (int k = wave; k <= k_max; k += 4) {
-        double ss = 0.0, cc = 0.0;
-        for (int m = lane; m < d.n1; m += 64) {
-            double s0, c0;
-            sincos_cw((double)k * (h * (double)m), &s0, &c0);
-            ss += fr[m] * s0;
-            cc += fr[m] * c0;
-        }
-        ss = wave_sum(ss);
-        cc = wave_sum(cc);
-        if (lane == 0) {
-            const double pref = h * ((k == 0 ? 1.0 : 2.0) / (2.0 * 3.141592653589793));
-            const int64_t o = ((int64_t)set * d.n0 + row) * (k_max + 1) + k;
-            Is[o] = pref * ss;
-            Ic[o] = pref * cc;
+    for (int row = blockIdx.x; row < d.n0; row += gridDim.x) {
+        const double *fr = f + (int64_t)set * P + (int64_t)row * d.n1;
+        for (int k = wave; k <= k_max; k += 4) {
+            double ss = 0.0, cc = 0.0;
+            for (int m = lane; m < d.n1; m += 64) {
+                double s0, c0;
+                sincos_cw((double)k * (h * (double)m), &s0, &c0);
+                ss += fr[m] * s0;
+                cc += fr[m] * c0;
+            }
+            ss = wave_sum(ss);
+            cc = wave_sum(cc);
+            if (lane == 0) {
+                const double pref = h * ((k == 0 ? 1.0 : 2.0) / (2.0 * 3.141592653589793));
+                const int64_t o = ((int64_t)set * d.n0 + row) * (k_max + 1) + k;
+                Is[o] = pref * ss;
+                Ic[o] = pref * cc;
+            }
         }
     }
 }
@@ -331,7 +333,8 @@ int launch_angular_spectrum(const Detector &d, const double *f, int n_f, int k_m
                             double *As, double *Ac, hipStream_t s)
 {
     if (n_f <= 0) return NUMAG_OK;
-    hipLaunchKernelGGL(angular_spectrum_kernel, dim3(d.n0, n_f), dim3(256), 0, s, d, f, k_max, Is, Ic);
+    hipLaunchKernelGGL(angular_spectrum_kernel, dim3((unsigned)std::min<int64_t>(d.n0, max_workgroups(256)), n_f),
+                       dim3(256), 0, s, d, f, k_max, Is, Ic);
     NUMAG_HIP_CHECK(hipGetLastError());
     if (As != nullptr && Ac != nullptr) {
         hipLaunchKernelGGL(modal_amplitude_kernel, dim3(n_f), dim3(256), 0, s, Is, Ic, d.n0, k_max, As, Ac);

@@ -47,6 +47,10 @@ struct TimedLaunch {
     }
 };
 
+// Most workgroups of `threads` a launch takes along x: a grid of 2^32 threads or more is
+// not refused but truncated to 32 bits, so kernels that may be asked for more loop.
+constexpr int64_t max_workgroups(int threads) { return ((int64_t)1 << 31) / threads; }
+
 Detector make_detector(const numag_qgrid &g);
 
 // Validation of a numag_amplitudes request (sample, detector, rotations, path and

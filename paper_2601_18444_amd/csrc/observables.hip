@@ -253,81 +253,83 @@ __global__ __launch_bounds__(kAzCart) void azimuthal_cartesian_kernel(
     Detector d, const double *__restrict__ f, int n_f, int n_bins, double qmax_avg, double *__restrict__ I,
     int64_t *__restrict__ count)
 {
-    const int b = blockIdx.x;
     const int set0 = blockIdx.y * kAzSets, ns = min(kAzSets, n_f - set0);
     const int64_t P = (int64_t)d.n0 * d.n1;
     const double dq = qmax_avg / (double)n_bins;
-    const double r_in = (double)b * dq;
-    const double r_out = (b == n_bins - 1) ? qmax_avg : (double)(b + 1) * dq;
-    constexpr double kSlack = 1e-12;
-    const double in2 = r_in * r_in, out2 = r_out * r_out;
-    double sum[kAzSets] = {};
-    int cnt = 0;
-    // index range of an axis covering [lo, hi]
-    auto idx_lo = [](double v, double origin, double step, double inv, int n) {
-        if (step == 0.0) return 0;
-        double x = floor((v - origin) * inv);
-        return (int)fmax(0.0, fmin((double)(n - 1), x));
-    };
-    auto idx_hi = [](double v, double origin, double step, double inv, int n) {
-        if (step == 0.0) return n - 1;
-        double x = ceil((v - origin) * inv);
-        return (int)fmax(0.0, fmin((double)(n - 1), x));
-    };
-    const double inv0 = 1.0 / d.step0, inv1 = 1.0 / d.step1;
-    const int i_lo = idx_lo(-r_out, d.origin0, d.step0, inv0, d.n0);
-    const int i_hi = idx_hi(r_out, d.origin0, d.step0, inv0, d.n0);
-    for (int i = i_lo + (int)threadIdx.x / kAzLanes; i <= i_hi; i += kAzCart / kAzLanes) {
-        const double qy = axis_value(d.origin0, i, d.step0);
-        const double y2 = qy * qy;
-        const double c_out = sqrt(fmax(0.0, out2 - y2));
-        const double c_in = (in2 > y2) ? sqrt(in2 - y2) : 0.0;
-        // right interval [c_in, c_out] and what it leaves of the left one [-c_out, -c_in]
-        const int r_lo = idx_lo(c_in, d.origin1, d.step1, inv1, d.n1);
-        const int r_hi = idx_hi(c_out, d.origin1, d.step1, inv1, d.n1);
-        const int l_lo = idx_lo(-c_out, d.origin1, d.step1, inv1, d.n1);
-        const int l_hi = min(idx_hi(-c_in, d.origin1, d.step1, inv1, d.n1), r_lo - 1);
-        const int nr = max(0, r_hi - r_lo + 1), nl = max(0, l_hi - l_lo + 1);
-        for (int e = (int)threadIdx.x % kAzLanes; e < nr + nl; e += kAzLanes) {
-            const int k = e < nr ? r_lo + e : l_lo + (e - nr);
-            const double *src = f + (int64_t)set0 * P + (int64_t)i * d.n1 + k;
-            double v[kAzSets];
+    for (int b = blockIdx.x; b < n_bins; b += gridDim.x) {
+        const double r_in = (double)b * dq;
+        const double r_out = (b == n_bins - 1) ? qmax_avg : (double)(b + 1) * dq;
+        constexpr double kSlack = 1e-12;
+        const double in2 = r_in * r_in, out2 = r_out * r_out;
+        double sum[kAzSets] = {};
+        int cnt = 0;
+        // index range of an axis covering [lo, hi]
+        auto idx_lo = [](double v, double origin, double step, double inv, int n) {
+            if (step == 0.0) return 0;
+            double x = floor((v - origin) * inv);
+            return (int)fmax(0.0, fmin((double)(n - 1), x));
+        };
+        auto idx_hi = [](double v, double origin, double step, double inv, int n) {
+            if (step == 0.0) return n - 1;
+            double x = ceil((v - origin) * inv);
+            return (int)fmax(0.0, fmin((double)(n - 1), x));
+        };
+        const double inv0 = 1.0 / d.step0, inv1 = 1.0 / d.step1;
+        const int i_lo = idx_lo(-r_out, d.origin0, d.step0, inv0, d.n0);
+        const int i_hi = idx_hi(r_out, d.origin0, d.step0, inv0, d.n0);
+        for (int i = i_lo + (int)threadIdx.x / kAzLanes; i <= i_hi; i += kAzCart / kAzLanes) {
+            const double qy = axis_value(d.origin0, i, d.step0);
+            const double y2 = qy * qy;
+            const double c_out = sqrt(fmax(0.0, out2 - y2));
+            const double c_in = (in2 > y2) ? sqrt(in2 - y2) : 0.0;
+            // right interval [c_in, c_out] and what it leaves of the left one [-c_out, -c_in]
+            const int r_lo = idx_lo(c_in, d.origin1, d.step1, inv1, d.n1);
+            const int r_hi = idx_hi(c_out, d.origin1, d.step1, inv1, d.n1);
+            const int l_lo = idx_lo(-c_out, d.origin1, d.step1, inv1, d.n1);
+            const int l_hi = min(idx_hi(-c_in, d.origin1, d.step1, inv1, d.n1), r_lo - 1);
+            const int nr = max(0, r_hi - r_lo + 1), nl = max(0, l_hi - l_lo + 1);
+            for (int e = (int)threadIdx.x % kAzLanes; e < nr + nl; e += kAzLanes) {
+                const int k = e < nr ? r_lo + e : l_lo + (e - nr);
+                const double *src = f + (int64_t)set0 * P + (int64_t)i * d.n1 + k;
+                double v[kAzSets];
 #pragma unroll
-            for (int s = 0; s < kAzSets; ++s) v[s] = src[(int64_t)min(s, ns - 1) * P];
-            const double qz = axis_value(d.origin1, k, d.step1);
-            const double q2 = qz * qz + y2;
-            if (q2 < in2 * (1.0 - kSlack) || q2 > out2 * (1.0 + kSlack)) continue;
-            const bool inside = q2 > in2 * (1.0 + kSlack) && q2 < out2 * (1.0 - kSlack);
-            if (inside || cart_bin(qy, qz, dq, qmax_avg, n_bins) == b) {
+                for (int s = 0; s < kAzSets; ++s) v[s] = src[(int64_t)min(s, ns - 1) * P];
+                const double qz = axis_value(d.origin1, k, d.step1);
+                const double q2 = qz * qz + y2;
+                if (q2 < in2 * (1.0 - kSlack) || q2 > out2 * (1.0 + kSlack)) continue;
+                const bool inside = q2 > in2 * (1.0 + kSlack) && q2 < out2 * (1.0 - kSlack);
+                if (inside || cart_bin(qy, qz, dq, qmax_avg, n_bins) == b) {
 #pragma unroll
-                for (int s = 0; s < kAzSets; ++s) sum[s] += v[s];
-                ++cnt;
+                    for (int s = 0; s < kAzSets; ++s) sum[s] += v[s];
+                    ++cnt;
+                }
             }
         }
-    }
-    constexpr int kWaves = kAzCart / 64;
-    __shared__ double s_sum[kAzSets][kWaves];
-    __shared__ int s_cnt[kWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        constexpr int kWaves = kAzCart / 64;
+        __shared__ double s_sum[kAzSets][kWaves];
+        __shared__ int s_cnt[kWaves];
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int s = 0; s < kAzSets; ++s) {
-        const double t = wave_sum(sum[s]);
-        if (lane == 0) s_sum[s][wave] = t;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
-    if (lane == 0) s_cnt[wave] = cnt;
-    __syncthreads();
-    const int s = threadIdx.x;
-    if (s < ns) {
-        long long n = 0;
-        double t = 0.0;
-        for (int w = 0; w < kWaves; ++w) {
-            n += s_cnt[w];
-            t += s_sum[s][w];
+        for (int s = 0; s < kAzSets; ++s) {
+            const double t = wave_sum(sum[s]);
+            if (lane == 0) s_sum[s][wave] = t;
         }
-        I[(int64_t)(set0 + s) * n_bins + b] = n > 0 ? t / (double)n : __builtin_nan("");
-        if (count != nullptr && set0 + s == 0) count[b] = n;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
+        if (lane == 0) s_cnt[wave] = cnt;
+        __syncthreads();
+        const int s = threadIdx.x;
+        if (s < ns) {
+            long long n = 0;
+            double t = 0.0;
+            for (int w = 0; w < kWaves; ++w) {
+                n += s_cnt[w];
+                t += s_sum[s][w];
+            }
+            I[(int64_t)(set0 + s) * n_bins + b] = n > 0 ? t / (double)n : __builtin_nan("");
+            if (count != nullptr && set0 + s == 0) count[b] = n;
+        }
+        __syncthreads();
     }
 }
 
@@ -365,8 +367,10 @@ int launch_azimuthal(const Detector &d, const double *f, int n_f, int n_bins, do
 {
     if (n_f <= 0 || n_bins <= 0) return NUMAG_OK;
     if (d.kind == NUMAG_GRID_CARTESIAN)
-        hipLaunchKernelGGL(azimuthal_cartesian_kernel, dim3(n_bins, (n_f + kAzSets - 1) / kAzSets), dim3(kAzCart), 0,
-                           s, d, f, n_f, n_bins, qmax_avg, I, count);
+        hipLaunchKernelGGL(azimuthal_cartesian_kernel,
+                           dim3((unsigned)std::min<int64_t>(n_bins, max_workgroups(kAzCart)),
+                                (n_f + kAzSets - 1) / kAzSets),
+                           dim3(kAzCart), 0, s, d, f, n_f, n_bins, qmax_avg, I, count);
     else
         hipLaunchKernelGGL(azimuthal_polar_kernel, dim3(n_bins, n_f), dim3(kAzThreads), 0, s, d, f, n_bins, I, count);
     NUMAG_HIP_CHECK(hipGetLastError());
@@ -431,7 +435,7 @@ int launch_correlation(const double *q, const double *I, int n_q, int n_f, const
 {
     const int64_t n = (int64_t)n_f * n_r;
     if (n <= 0) return NUMAG_OK;
-    const int64_t wgs = n < ((int64_t)1 << 32) ? (n + 3) / 4 : (int64_t)1 << 30;
+    const int64_t wgs = std::min<int64_t>((n + 3) / 4, max_workgroups(256));
     hipLaunchKernelGGL(correlation_kernel, dim3((unsigned)wgs), dim3(256), 0, s, q, I, n_q, n_f, r, n_r, scale, c, p);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;

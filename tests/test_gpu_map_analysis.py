@@ -82,3 +82,37 @@ def test_correlation_2d_routes(orc, kind, n0, n1, rkind, r0, r1):
         C = numag.correlation_2d(grid, torch.as_tensor(f[:n_f], device=DEV), rgrid).cpu().numpy()
         ref = orc.correlation_2d(kind, n0, n1, qmax, f[:n_f], rkind, r0, r1, rmax)
         assert np.abs(C[..., 0] + 1j * C[..., 1] - ref).max() <= tol
+
+
+def test_correlation_of_more_results_than_a_grid_of_waves():
+    """2^26 and more results: with a wave for each, their threads pass 2^32."""
+    n_f, n_r = 8192, 8193
+    q = torch.tensor([0.1, 0.25], dtype=torch.float64, device=DEV)
+    I = torch.linspace(0.5, 2.0, n_f * 2, dtype=torch.float64, device=DEV).reshape(n_f, 2)
+    r = torch.linspace(0.0, 5.0, n_r, dtype=torch.float64, device=DEV)
+    c, p = numag.correlation(q, I, r)
+    x = q[:, None] * r[None]
+    j0 = torch.where(x == 0, torch.ones_like(x), torch.sin(x) / torch.where(x == 0, torch.ones_like(x), x))
+    y = q[:, None] ** 2 * j0
+    ref = (0.5 * I[:, :1] * (0.1 + 0.15) * y[0] + 0.5 * I[:, 1:] * 0.15 * y[1]) / (2.0 * np.pi ** 2)
+    # two samples: every rounding is of the size of the terms, at most 2 q^2
+    assert (c - ref).abs().max().item() <= 64 * EPS
+    assert (p - r * r * ref).abs().max().item() <= 64 * EPS * 25.0
+
+
+def test_azimuthal_of_more_bins_than_a_grid_of_workgroups():
+    n_bins = (1 << 23) + 3
+    f = torch.linspace(1.0, 2.0, 16, dtype=torch.float64, device=DEV)[None]
+    I, count = numag.azimuthal_average(numag.qgrid(0, 4, 4, 1.0), f, n_bins, 1.5)
+    assert int(count.sum()) == 16 and int(count.min()) == 0
+    assert torch.equal(torch.isnan(I[0]), count == 0)
+    mean = torch.where(count > 0, I[0], torch.zeros_like(I[0]))
+    assert abs((mean * count).sum().item() - f.sum().item()) <= 64 * EPS * 16
+
+
+def test_angular_spectrum_of_more_rows_than_a_grid_of_workgroups():
+    n_q = (1 << 24) + 5
+    f = torch.linspace(1.0, 2.0, 2 * n_q, dtype=torch.float64, device=DEV)[None]
+    Is, Ic, _, _ = numag.angular_spectrum(numag.qgrid(1, n_q, 2, 1.0), f, 0, amplitudes=False)
+    assert (Ic[0, :, 0] - f[0].reshape(n_q, 2).mean(1)).abs().max().item() <= 16 * EPS
+    assert Is.abs().max().item() == 0.0
