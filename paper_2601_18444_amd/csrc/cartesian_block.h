@@ -30,6 +30,7 @@
 // barrier per chunk, its points loaded one chunk ahead of their use.
 #pragma once
 
+#include "nonfinite.h"
 #include "numag_internal.h"
 #include "phasor.h"
 
@@ -205,28 +206,29 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
 }
 
 // Hands the finished sums to put(t, h, S(+,+), S(+,-)): slot 8 t + 4 h + lane / 16, column
-// lane % 16 of the block.  With several point groups they are first added, in a fixed
-// order, through LDS (one tile at a time; group k < 2 then puts half k): every wave of
-// the workgroup has to call this.
+// lane % 16 of the block.
 template <int MT, class Put>
-__device__ __forceinline__ void finish(const CartGeom &g, int zb0, Smem<MT> &sm, const v4d (&accC)[MT],
-                                       const v4d (&accS)[MT], const Put &put)
+__device__ __forceinline__ void finish_whole(const v4d (&accC)[MT], const v4d (&accS)[MT], const Put &put)
+{
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const double RR = accC[t][2 * h], IR = accC[t][2 * h + 1], RI = accS[t][2 * h], II = accS[t][2 * h + 1];
+            put(t, h, make_double2(RR - II, RI + IR), make_double2(RR + II, IR - RI));
+        }
+}
+
+// The same with several point groups, which are first added, in a fixed order, through LDS
+// (one tile at a time; group k < 2 then puts half k): every wave of the workgroup has to
+// call this.
+template <int MT, class Put>
+__device__ __forceinline__ void finish_groups(const CartGeom &g, int zb0, Smem<MT> &sm, const v4d (&accC)[MT],
+                                              const v4d (&accS)[MT], const Put &put)
 {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int zi = wave % g.nz, kg = wave / g.nz, nk = kWaves / g.nz;
     const bool active = zb0 + zi < g.nzb;
-    auto out = [&](int t, int h, double RR, double IR, double RI, double II) {
-        put(t, h, make_double2(RR - II, RI + IR), make_double2(RR + II, IR - RI));
-    };
-    if (nk == 1) {
-        if (!active) return;
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                out(t, h, accC[t][2 * h], accC[t][2 * h + 1], accS[t][2 * h], accS[t][2 * h + 1]);
-        return;
-    }
     double *red = (double *)&sm;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
@@ -245,10 +247,21 @@ __device__ __forceinline__ void finish(const CartGeom &g, int zb0, Smem<MT> &sm,
                 v[2] += p[(4 + 2 * kg) * 64];
                 v[3] += p[(5 + 2 * kg) * 64];
             }
-            out(t, kg, v[0], v[1], v[2], v[3]);
+            put(t, kg, make_double2(v[0] - v[3], v[2] + v[1]), make_double2(v[0] + v[3], v[1] - v[2]));
         }
         __syncthreads();
     }
+}
+
+// Whichever of the two the launch shape needs.
+template <int MT, class Put>
+__device__ __forceinline__ void finish(const CartGeom &g, int zb0, Smem<MT> &sm, const v4d (&accC)[MT],
+                                       const v4d (&accS)[MT], const Put &put)
+{
+    if (g.nz != kWaves)
+        finish_groups<MT>(g, zb0, sm, accC, accS, put);
+    else if (zb0 + wave_id() < g.nzb)
+        finish_whole<MT>(accC, accS, put);
 }
 
 // The pixels +-|q| of a cell's slot on the two axes.
@@ -283,24 +296,25 @@ __device__ __forceinline__ void put_pixel(double *__restrict__ amp, int64_t p, i
     o[1] = add ? o[1] + im : im;
 }
 
+// which: 1 for S(+,+) and its mirror, 2 for S(+,-), 3 for both.
 __device__ __forceinline__ void put_cell(double *__restrict__ amp, const CellPixels &x, int ch, double2 vp, double2 vm,
-                                         bool add)
+                                         bool add, int which = 3)
 {
-    put_pixel(amp, x.pp, ch, vp.x, vp.y, add);
-    if (x.twoN) put_pixel(amp, x.pm, ch, vm.x, vm.y, add);
+    if (which & 1) put_pixel(amp, x.pp, ch, vp.x, vp.y, add);
+    if (x.twoN && (which & 2)) put_pixel(amp, x.pm, ch, vm.x, vm.y, add);
     if (x.twoM) {
-        put_pixel(amp, x.mm, ch, vp.x, -vp.y, add);
-        if (x.twoN) put_pixel(amp, x.mp, ch, vm.x, -vm.y, add);
+        if (which & 1) put_pixel(amp, x.mm, ch, vp.x, -vp.y, add);
+        if (x.twoN && (which & 2)) put_pixel(amp, x.mp, ch, vm.x, -vm.y, add);
     }
 }
 
 // A slot's channel and, from the lane that holds its first channel, the exact zeros
 // of the channels outside the set.
 __device__ __forceinline__ void put_slot(double *__restrict__ amp, const CellPixels &x, int CH, double2 vp, double2 vm,
-                                         bool add)
+                                         bool add, int which = 3)
 {
     const int first = CH == 3 ? 1 : 0;
-    put_cell(amp, x, first + x.c, vp, vm, add);
+    put_cell(amp, x, first + x.c, vp, vm, add, which);
     if (x.c == 0 && !add) {
         const double2 o = make_double2(0.0, 0.0);
         if (CH == 3) put_cell(amp, x, 0, o, o, false);
@@ -308,6 +322,23 @@ __device__ __forceinline__ void put_slot(double *__restrict__ amp, const CellPix
             for (int ch = 1; ch < 4; ++ch) put_cell(amp, x, ch, o, o, false);
     }
 }
+
+// A slot's sums vp, vm over the points [j0, j1) of src (nonfinite.h), which of them (1, 2)
+// being NaN: |q_M| value a, |q_N| value b, channel ch.
+__device__ __forceinline__ void repair(const CartGeom &g, const PointSource &src, int64_t j0, int64_t j1, int a, int b,
+                                       int ch, int which, double2 &vp, double2 &vm)
+{
+    const double qm = ((double)a + g.firstM) * g.stepM, qn = ((double)b + g.firstN) * g.stepN;
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+        if (!(which >> k & 1)) continue;
+        const double q = k == 0 ? qn : -qn;
+        const double2 v = nonfinite_sum(src, j0, j1, ch, g.swapped ? q : qm, g.swapped ? qm : q, k == 0 ? vp : vm);
+        (k == 0 ? vp : vm) = v;
+    }
+}
+
+__device__ __forceinline__ int which_nan(double2 vp, double2 vm) { return (is_nan(vp) ? 1 : 0) | (is_nan(vm) ? 2 : 0); }
 
 }  // namespace cblk
 }  // namespace numag

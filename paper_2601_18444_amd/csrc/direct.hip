@@ -186,6 +186,7 @@ struct PrepLoader {
         return p;
     }
     __device__ __forceinline__ cblk::Point<CH> point(const Raw &r) const { return r; }
+    __host__ __device__ __forceinline__ PointSource source() const { return PointSource{pts, nullptr, nullptr, nullptr, Rot{}}; }
 };
 
 // Points straight from a sample (no object offsets), the record's arithmetic.
@@ -225,13 +226,16 @@ struct SampleLoader {
         }
         return p;
     }
+    __host__ __device__ __forceinline__ PointSource source() const { return PointSource{nullptr, pos, nuc, mag, R}; }
 };
 
 // Where a workgroup's sums go: partials [split][row block][column block][tile][half][4][64]
-// (store == 0; combined below), or straight into amp (1: written, 2: added).
-template <int MT, int CH, class Loader>
+// (PARTIAL; combined below), or straight into amp (written, or with `add` added).  Two
+// kernels: a small call waits for its instructions to be fetched (4,169 points, 128 x 128:
+// the partial sums' kernel 30.3 us with both in one, 43 kB, 28.3 without, 18 kB).
+template <int MT, int CH, bool PARTIAL, class Loader>
 __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(Loader ld, int64_t W, int64_t per,
-                                                                              int nsplit, CartGeom g, int store,
+                                                                              int nsplit, CartGeom g, int add,
                                                                               double *__restrict__ out)
 {
     __shared__ cblk::Smem<MT> sm;
@@ -245,8 +249,9 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(Loa
     cblk::first_points(ld, jbeg, jend, p, q);
     cblk::accumulate<MT, CH>(ld, jbeg, jend, g, rb, zb0, sm, p, q, accC, accS);
     const int zb = zb0 + cblk::wave_id() % g.nz;
+    unsigned bad = 0;  // NaN sums of this lane, two bits per tile half
     cblk::finish<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
-        if (store == 0) {
+        if (PARTIAL) {
             double *o = out + (((((int64_t)split * g.nrb + rb) * g.nzb + zb) * MT + t) * 2 + h) * 256 + lane;
             o[0] = vp.x;
             o[64] = vp.y;
@@ -254,14 +259,29 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void direct_cartesian_kernel(Loa
             o[192] = vm.y;
         } else {
             const cblk::CellPixels x = cblk::cell_pixels(g, CH, rb, zb, 8 * t + 4 * h + (lane >> 4), lane & 15);
-            if (x.ok) cblk::put_slot(out, x, CH, vp, vm, store == 2);
+            if (x.ok) {
+                const int nan = cblk::which_nan(vp, vm);
+                bad |= (unsigned)nan << (2 * (2 * t + h));
+                cblk::put_slot(out, x, CH, vp, vm, add != 0, 3 & ~nan);
+            }
         }
     });
+    while (!PARTIAL && __builtin_expect(bad != 0, 0)) {
+        const int i = __builtin_ctz(bad) >> 1, which = (int)(bad >> (2 * i) & 3);
+        bad &= ~(3u << (2 * i));
+        const int s = 4 * i + (lane >> 4);
+        const cblk::CellPixels x = cblk::cell_pixels(g, CH, rb, zb, s, lane & 15);
+        const int ch = cblk::ch_first<CH>() + x.c;
+        double2 vp = make_double2(__builtin_nan(""), __builtin_nan("")), vm = vp;
+        cblk::repair(g, ld.source(), jbeg, jend, rb * g.na + s / CH, cblk::kOff * zb + (lane & 15), ch, which, vp, vm);
+        cblk::put_cell(out, x, ch, vp, vm, add != 0, which);
+    }
 }
 
 // Fixed-order sum of the split partials, written (or added) to the pixels.
-__global__ __launch_bounds__(256) void cart_combine_kernel(const double *__restrict__ part, CartGeom g, int MT, int CH,
-                                                           int nsplit, int accumulate, double *__restrict__ amp)
+__global__ __launch_bounds__(256, 8) void cart_combine_kernel(const double *__restrict__ part, CartGeom g, int MT, int CH,
+                                                           int nsplit, PointSource src, int64_t W, int accumulate,
+                                                           double *__restrict__ amp)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int lane = (int)(idx & 63);
@@ -270,8 +290,8 @@ __global__ __launch_bounds__(256) void cart_combine_kernel(const double *__restr
     if (block >= blocks) return;
     const int h = (int)(block & 1), t = (int)((block >> 1) % MT);
     const int64_t rz = (block >> 1) / MT;
-    const cblk::CellPixels x =
-        cblk::cell_pixels(g, CH, (int)(rz / g.nzb), (int)(rz % g.nzb), 8 * t + 4 * h + (lane >> 4), lane & 15);
+    const int rb = (int)(rz / g.nzb), zb = (int)(rz % g.nzb), slot = 8 * t + 4 * h + (lane >> 4);
+    const cblk::CellPixels x = cblk::cell_pixels(g, CH, rb, zb, slot, lane & 15);
     if (!x.ok) return;
     const double *p = part + block * 256 + lane;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -280,7 +300,12 @@ __global__ __launch_bounds__(256) void cart_combine_kernel(const double *__restr
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
     }
-    cblk::put_slot(amp, x, CH, make_double2(v[0], v[1]), make_double2(v[2], v[3]), accumulate != 0);
+    double2 vp = make_double2(v[0], v[1]), vm = make_double2(v[2], v[3]);
+    const int nan = cblk::which_nan(vp, vm);
+    if (__builtin_expect(nan != 0, 0))
+        cblk::repair(g, src, 0, W, rb * g.na + slot / CH, cblk::kOff * zb + (lane & 15), (CH == 3 ? 1 : 0) + x.c, nan,
+                     vp, vm);
+    cblk::put_slot(amp, x, CH, vp, vm, accumulate != 0);
 }
 
 int env_target()
@@ -530,14 +555,14 @@ size_t cart_partial_bytes(const CartPlan &p)
     return p.nsplit > 1 ? cart_split_bytes(p.g, p.mt) * (size_t)p.nsplit : 0;
 }
 
-template <int CH, class Loader>
-static void launch_cart_tiles(const Loader &ld, int64_t W, const CartPlan &p, int store, double *out, hipStream_t s)
+template <int CH, bool PARTIAL, class Loader>
+static void launch_cart_tiles(const Loader &ld, int64_t W, const CartPlan &p, int add, double *out, hipStream_t s)
 {
     // full column groups first
     const dim3 grid((unsigned)(p.nsplit * p.col_groups), p.g.nrb), block(cblk::kThreads);
-#define NUMAG_LAUNCH_CART(MT)                                                                                     \
-    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH, Loader>), grid, block, 0, s, ld, W, p.per, p.nsplit, p.g, \
-                       store, out)
+#define NUMAG_LAUNCH_CART(MT)                                                                                       \
+    hipLaunchKernelGGL((direct_cartesian_kernel<MT, CH, PARTIAL, Loader>), grid, block, 0, s, ld, W, p.per, p.nsplit, \
+                       p.g, add, out)
     switch (p.mt) {
         case 1: NUMAG_LAUNCH_CART(1); break;
         case 2: NUMAG_LAUNCH_CART(2); break;
@@ -551,49 +576,53 @@ static void launch_cart_tiles(const Loader &ld, int64_t W, const CartPlan &p, in
 #undef NUMAG_LAUNCH_CART
 }
 
-static int combine_cartesian(const CartPlan &p, const double *partial, double *amp, int accumulate, hipStream_t s)
+static int combine_cartesian(const CartPlan &p, const PointSource &src, int64_t W, const double *partial, double *amp,
+                             int accumulate, hipStream_t s)
 {
     NUMAG_HIP_CHECK(hipGetLastError());
     if (p.nsplit <= 1) return NUMAG_OK;
     const int64_t n = (int64_t)p.g.nrb * p.g.nzb * p.mt * 128;
     hipLaunchKernelGGL(cart_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
-                       p.channels, p.nsplit, accumulate, amp);
+                       p.channels, p.nsplit, src, W, accumulate, amp);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
+}
+
+// The sum kernel, and the combine if the points are split.
+template <int CH, class Loader>
+static int sum_cartesian(const Loader &ld, int64_t W, const CartPlan &p, double *partial, double *amp, int accumulate,
+                         hipStream_t s)
+{
+    {
+        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
+        if (p.nsplit > 1)
+            launch_cart_tiles<CH, true>(ld, W, p, 0, partial, s);
+        else
+            launch_cart_tiles<CH, false>(ld, W, p, accumulate, amp, s);
+    }
+    return combine_cartesian(p, ld.source(), W, partial, amp, accumulate, s);
 }
 
 int launch_direct_cartesian(const PointRec *pts, int64_t W, const CartPlan &p, double *partial, double *amp,
                             int accumulate, hipStream_t s)
 {
-    const int store = p.nsplit > 1 ? 0 : (accumulate ? 2 : 1);
-    {
-        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
-        double *out = p.nsplit > 1 ? partial : amp;
-        const int sw = p.g.swapped;
-        switch (p.channels) {
-            case 1: launch_cart_tiles<1>(PrepLoader<1>{pts, sw}, W, p, store, out, s); break;
-            case 3: launch_cart_tiles<3>(PrepLoader<3>{pts, sw}, W, p, store, out, s); break;
-            default: launch_cart_tiles<4>(PrepLoader<4>{pts, sw}, W, p, store, out, s); break;
-        }
+    const int sw = p.g.swapped;
+    switch (p.channels) {
+        case 1: return sum_cartesian<1>(PrepLoader<1>{pts, sw}, W, p, partial, amp, accumulate, s);
+        case 3: return sum_cartesian<3>(PrepLoader<3>{pts, sw}, W, p, partial, amp, accumulate, s);
+        default: return sum_cartesian<4>(PrepLoader<4>{pts, sw}, W, p, partial, amp, accumulate, s);
     }
-    return combine_cartesian(p, partial, amp, accumulate, s);
 }
 
 int launch_sample_cartesian(const double *pos, const double *nuc, const double *mag, const Rot &R, int64_t W,
                             const CartPlan &p, double *partial, double *amp, hipStream_t s)
 {
-    const int store = p.nsplit > 1 ? 0 : 1;
-    {
-        TimedLaunch timed(NUMAG_KERNEL_DIRECT, s);
-        double *out = p.nsplit > 1 ? partial : amp;
-        const int sw = p.g.swapped;
-        switch (p.channels) {
-            case 1: launch_cart_tiles<1>(SampleLoader<1>{pos, nuc, mag, R, sw}, W, p, store, out, s); break;
-            case 3: launch_cart_tiles<3>(SampleLoader<3>{pos, nuc, mag, R, sw}, W, p, store, out, s); break;
-            default: launch_cart_tiles<4>(SampleLoader<4>{pos, nuc, mag, R, sw}, W, p, store, out, s); break;
-        }
+    const int sw = p.g.swapped;
+    switch (p.channels) {
+        case 1: return sum_cartesian<1>(SampleLoader<1>{pos, nuc, mag, R, sw}, W, p, partial, amp, 0, s);
+        case 3: return sum_cartesian<3>(SampleLoader<3>{pos, nuc, mag, R, sw}, W, p, partial, amp, 0, s);
+        default: return sum_cartesian<4>(SampleLoader<4>{pos, nuc, mag, R, sw}, W, p, partial, amp, 0, s);
     }
-    return combine_cartesian(p, partial, amp, 0, s);
 }
 
 __global__ void fill_kernel(double *__restrict__ out, int64_t n, double value)

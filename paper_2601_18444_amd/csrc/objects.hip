@@ -114,18 +114,19 @@ struct ObjArgs {
 // channel, the imaginary part in the other.
 __device__ constexpr int kPacked[4][4] = {{0, 4, 6, 8}, {1, 5, 12, 10}, {2, 14, 7, 11}, {3, 15, 13, 9}};
 
-// Adds (first: writes) F F^H of one sign to the lane's four accumulators o[64 e].
+// Adds (first: writes) F F^H of one sign to the lane's four accumulators o[64 e].  (Fused
+// products are written out, so that every inlined copy rounds alike.)
 __device__ __forceinline__ void add_spectral(double *__restrict__ o, bool first, double2 F)
 {
     const int g = (threadIdx.x & 63) >> 4;
     double v[4];
-    v[0] = F.x * F.x + F.y * F.y;
+    v[0] = fma(F.x, F.x, F.y * F.y);
 #pragma unroll
     for (int e = 1; e < 4; ++e) {
         const double ox = __shfl_xor(F.x, 16 * e), oy = __shfl_xor(F.y, 16 * e);
         // Re F_a conj(F_b) is symmetric; Im of the smaller channel a (the other lane's)
         // with b (this one's) is a_i b_r - a_r b_i
-        v[e] = g < (g ^ e) ? F.x * ox + F.y * oy : oy * F.x - ox * F.y;
+        v[e] = g < (g ^ e) ? fma(F.x, ox, F.y * oy) : fma(oy, F.x, -(ox * F.y));
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[64 * e] = first ? v[e] : o[64 * e] + v[e];
@@ -135,7 +136,10 @@ __device__ __forceinline__ void add_spectral(double *__restrict__ o, bool first,
 __device__ __forceinline__ void add_amplitude(double *__restrict__ o, bool first, double2 vp, double2 vm, double2 y,
                                               double2 z)
 {
-    const double2 a = cmul(cmul(y, z), vp), b = cmul(cmul(y, make_double2(z.x, -z.y)), vm);
+    auto mul = [](double2 u, double2 v) {
+        return make_double2(fma(u.x, v.x, -(u.y * v.y)), fma(u.x, v.y, u.y * v.x));
+    };
+    const double2 a = mul(mul(y, z), vp), b = mul(mul(y, make_double2(z.x, -z.y)), vm);
     o[0] = first ? a.x : o[0] + a.x;
     o[64] = first ? a.y : o[64] + a.y;
     o[128] = first ? b.x : o[128] + b.x;
@@ -151,6 +155,42 @@ __device__ __forceinline__ double2 object_yz(const ObjArgs &a, const Rot &R, int
                         R.m[6] * o[0] + R.m[7] * o[1] + R.m[8] * o[2]);
 }
 
+// An object's sum v, if NaN, over its points [j0, j1) under the rotation R (in memory) from
+// its terms that are not finite (nonfinite.h).
+__device__ __forceinline__ double2 object_repair(const ObjArgs &a, const double *R, int64_t j0, int64_t j1, double qy,
+                                                 double qz, double2 v)
+{
+    if (!is_nan(v)) return v;
+    const int ch = (threadIdx.x & 63) >> 4;
+    return nonfinite_terms([&](int64_t j, double &Y, double &Z,
+                               double &w) { sample_point(a.pos, a.nuc, a.mag, R, ch, j, Y, Z, w); },
+                           j0, j1, qy, qz, v);
+}
+
+// Sums of an object put aside by a wave that holds a NaN among them, until the matrix
+// accumulators are free: which of its tile halves (wave-uniform).
+template <int MT>
+struct Aside {
+    double2 v[2 * MT][2];
+    unsigned which;
+    __device__ __forceinline__ Aside() : which(0) {}
+    __device__ __forceinline__ void take(int i, double2 vp, double2 vm)
+    {
+        v[i][0] = vp;
+        v[i][1] = vm;
+        which |= 1u << i;
+    }
+};
+
+// Whether a wave may hold a NaN among its finished sums (the parts of all tiles added up).
+template <int MT>
+__device__ __forceinline__ bool may_hold_nan(const cblk::v4d (&accC)[MT], const cblk::v4d (&accS)[MT])
+{
+    double s = 0.0;
+    cblk::finish_whole<MT>(accC, accS, [&](int, int, double2 vp, double2 vm) { s += (vp.x + vp.y) + (vm.x + vm.y); });
+    return __any(s != s) != 0;
+}
+
 template <int MT>
 __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, CartGeom g)
 {
@@ -160,6 +200,9 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
     const int lane = threadIdx.x & 63;
     const int groups = (g.nzb + g.nz - 1) / g.nz;
     const int64_t tiles = (int64_t)g.nrb * g.nzb * MT;
+    if (4 * g.na < 8 * MT) {  // rows no slot writes: no stray NaN for may_hold_nan
+        for (int i = threadIdx.x; i < (int)(sizeof(sm.y) / sizeof(double)); i += cblk::kThreads) (&sm.y[0][0][0])[i] = 0.0;
+    }
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
         __syncthreads();
@@ -194,16 +237,48 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
                     z = twiddle(((double)(cblk::kOff * zb + (lane & 15)) + g.firstN) * g.stepN *
                                 (g.swapped ? X.x : X.y));
                 }
-                cblk::finish<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
-                    const int64_t th = (tile0 + t) * 2 + h;
+                auto add = [&](int i, double2 vp, double2 vm) {
+                    const int64_t th = tile0 * 2 + i;
                     double *o = a.spec + th * 512 + lane;
                     add_spectral(o, first, vp);
                     add_spectral(o + 256, first, vm);
                     if (a.amp != nullptr) {
-                        const double qm = ((double)(rb * g.na + 2 * t + h) + g.firstM) * g.stepM;
+                        const double qm = ((double)(rb * g.na + i) + g.firstM) * g.stepM;
                         add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(qm * Xm), z);
                     }
-                });
+                };
+                Aside<MT> aside;
+                const int b = cblk::kOff * zb + (lane & 15);
+                auto put_aside = [&](int t, int h, double2 vp, double2 vm) { aside.take(2 * t + h, vp, vm); };
+                auto put = [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); };
+                if (g.nz != cblk::kWaves) {
+                    cblk::finish_groups<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
+                        if (__builtin_expect(__any(is_nan(vp) || is_nan(vm)) != 0, 0))
+                            put_aside(t, h, vp, vm);
+                        else
+                            put(t, h, vp, vm);
+                    });
+                } else if (zb < g.nzb) {
+                    if (__builtin_expect(may_hold_nan<MT>(accC, accS), 0))
+                        cblk::finish_whole<MT>(accC, accS, put_aside);
+                    else
+                        cblk::finish_whole<MT>(accC, accS, put);
+                }
+                while (__builtin_expect(aside.which != 0, 0)) {
+                    const int i = __builtin_ctz(aside.which);
+                    aside.which &= aside.which - 1;
+                    const double qm = ((double)(rb * g.na + i) + g.firstM) * g.stepM;
+                    const double qn = ((double)b + g.firstN) * g.stepN;
+                    const bool on = i < g.na && rb * g.na + i < g.A && b < g.B;
+                    double2 v[2] = {aside.v[i][0], aside.v[i][1]};
+#pragma unroll 1
+                    for (int s = 0; on && s < 2; ++s) {
+                        const double q = s == 0 ? qn : -qn;
+                        v[s] = object_repair(a, a.rot + 9 * (int64_t)r, a.off[k], a.off[k + 1], g.swapped ? q : qm,
+                                             g.swapped ? qm : q, v[s]);
+                    }
+                    add(i, v[0], v[1]);
+                }
             }
         }
     }
@@ -246,22 +321,38 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void objects_polar_kernel(ObjArg
                     uk = X.x * sth + X.y * cth;
                     z = twiddle(((double)(lane & 15) + 0.5) * g.dq * uk);
                 }
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const double RR = accC[t][2 * h], IR = accC[t][2 * h + 1];
-                        const double RI = accS[t][2 * h], II = accS[t][2 * h + 1];
-                        const double2 vp = make_double2(RR - II, RI + IR), vm = make_double2(RR + II, IR - RI);
-                        const int64_t th = (tile0 + t) * 2 + h;
-                        double *o = a.spec + th * 512 + lane;
-                        add_spectral(o, first, vp);
-                        add_spectral(o + 256, first, vm);
-                        if (a.amp != nullptr) {
-                            const double c = ((double)(pblk::kRows * (rg * g.na + 2 * t + h)) + 15.5) * g.dq;
-                            add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(c * uk), z);
-                        }
+                auto add = [&](int i, double2 vp, double2 vm) {
+                    const int64_t th = tile0 * 2 + i;
+                    double *o = a.spec + th * 512 + lane;
+                    add_spectral(o, first, vp);
+                    add_spectral(o + 256, first, vm);
+                    if (a.amp != nullptr) {
+                        const double c = ((double)(pblk::kRows * (rg * g.na + i)) + 15.5) * g.dq;
+                        add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(c * uk), z);
                     }
+                };
+                auto row = [&](int i, int s) { return pblk::slot_row(g, rg, i, lane & 15, s); };
+                Aside<MT> aside;
+                if (__builtin_expect(may_hold_nan<MT>(accC, accS), 0))
+                    cblk::finish_whole<MT>(accC, accS, [&](int t, int h, double2 vp, double2 vm) {
+                        aside.take(2 * t + h, vp, vm);
+                    });
+                else
+                    cblk::finish_whole<MT>(accC, accS,
+                                           [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); });
+                while (__builtin_expect(aside.which != 0, 0)) {
+                    const int i = __builtin_ctz(aside.which);
+                    aside.which &= aside.which - 1;
+                    double2 v[2] = {aside.v[i][0], aside.v[i][1]};
+#pragma unroll 1
+                    for (int s = 0; s < 2; ++s) {
+                        const double q = (double)row(i, s) * g.dq;
+                        if (i < g.na && row(i, s) < g.n0)
+                            v[s] = object_repair(a, a.rot + 9 * (int64_t)r, a.off[k], a.off[k + 1], q * sth, q * cth,
+                                                 v[s]);
+                    }
+                    add(i, v[0], v[1]);
+                }
             }
         }
     }

@@ -37,6 +37,13 @@ struct PolarRecLoader {
         return p;
     }
     __device__ __forceinline__ Raw point(const Raw &r) const { return r; }
+    // (pairs: none, their caller sees to infinite weights)
+    __host__ __device__ __forceinline__ PointSource source() const
+    {
+        PointSource s{};
+        if constexpr (NW == CH) s.rec = pts;
+        return s;
+    }
 };
 
 // Points straight from a sample (no object offsets), with the arithmetic of the records.
@@ -74,6 +81,7 @@ struct PolarSampleLoader {
         }
         return p;
     }
+    __host__ __device__ __forceinline__ PointSource source() const { return PointSource{nullptr, pos, nuc, mag, R}; }
 };
 
 // One wave: one theta column, one row group, one point range.  Partials
@@ -94,6 +102,7 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(Loader 
     cblk::v4d accC[MT], accS[MT];
     cblk::zero<MT>(accC, accS);
     pblk::accumulate<MT, CH, NW>(ld, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
+    unsigned bad = 0;  // NaN sums of this lane, two bits per tile half
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -108,14 +117,25 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(Loader 
                 o[128] = vm.x;
                 o[192] = vm.y;
             } else {
-                pblk::put_slot(out, g, CH, rg, col, 8 * t + 4 * h + (lane >> 4), lane & 15, vp, vm, store == 2);
+                const int slot = 8 * t + 4 * h + (lane >> 4);
+                const int nan = NW == CH ? pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0;
+                bad |= (unsigned)nan << (2 * (2 * t + h));
+                pblk::put_slot(out, g, CH, rg, col, slot, lane & 15, vp, vm, store == 2, 3 & ~nan);
             }
         }
+    while (NW == CH && __builtin_expect(bad != 0, 0)) {
+        const int i = __builtin_ctz(bad) >> 1, which = (int)(bad >> (2 * i) & 3), slot = 4 * i + (lane >> 4);
+        bad &= ~(3u << (2 * i));
+        double2 vp = make_double2(__builtin_nan(""), __builtin_nan("")), vm = vp;
+        pblk::repair(g, ld.source(), jbeg, jend, CH, rg, slot, lane & 15, sth, cth, which, vp, vm);
+        pblk::put_slot(out, g, CH, rg, col, slot, lane & 15, vp, vm, store == 2, which);
+    }
 }
 
 // Fixed-order sum of the split partials, written (or added) to the pixels.
 __global__ __launch_bounds__(256) void polar_combine_kernel(const double *__restrict__ part, PolGeom g, int MT, int CH,
-                                                            int nsplit, int accumulate, double *__restrict__ amp)
+                                                            int nsplit, PointSource src, int64_t W, int accumulate,
+                                                            double *__restrict__ amp)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int lane = (int)(idx & 63);
@@ -131,8 +151,15 @@ __global__ __launch_bounds__(256) void polar_combine_kernel(const double *__rest
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
     }
-    pblk::put_slot(amp, g, CH, (int)(rc / g.cols), (int)(rc % g.cols), 8 * t + 4 * h + (lane >> 4), lane & 15,
-                   make_double2(v[0], v[1]), make_double2(v[2], v[3]), accumulate != 0);
+    const int rg = (int)(rc / g.cols), col = (int)(rc % g.cols), slot = 8 * t + 4 * h + (lane >> 4);
+    double2 vp = make_double2(v[0], v[1]), vm = make_double2(v[2], v[3]);
+    const int nan = W > 0 ? pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0;
+    if (__builtin_expect(nan != 0, 0)) {
+        double sth, cth;
+        sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
+        pblk::repair(g, src, 0, W, CH, rg, slot, lane & 15, sth, cth, nan, vp, vm);
+    }
+    pblk::put_slot(amp, g, CH, rg, col, slot, lane & 15, vp, vm, accumulate != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -254,13 +281,15 @@ static void launch_polar_tiles(const Loader &ld, int64_t W, const PolarPlan &p, 
 #undef NUMAG_LAUNCH_POLAR
 }
 
-static int combine_polar(const PolarPlan &p, const double *partial, double *amp, int accumulate, hipStream_t s)
+// src, W: the points, for results that are not finite (W = 0: left as they are).
+static int combine_polar(const PolarPlan &p, const PointSource &src, int64_t W, const double *partial, double *amp,
+                         int accumulate, hipStream_t s)
 {
     NUMAG_HIP_CHECK(hipGetLastError());
     if (p.nsplit <= 1) return NUMAG_OK;
     const int64_t n = (int64_t)p.g.nrg * p.g.cols * p.mt * 128;
     hipLaunchKernelGGL(polar_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
-                       p.channels, p.nsplit, accumulate, amp);
+                       p.channels, p.nsplit, src, W, accumulate, amp);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }
@@ -278,7 +307,7 @@ int launch_direct_polar(const PointRec *pts, int64_t W, const PolarPlan &p, doub
             default: launch_polar_tiles<4, 4>(PolarRecLoader<4, 4>{pts}, W, p, store, out, s); break;
         }
     }
-    return combine_polar(p, partial, amp, accumulate, s);
+    return combine_polar(p, PointSource{pts, nullptr, nullptr, nullptr, Rot{}}, W, partial, amp, accumulate, s);
 }
 
 int launch_sample_polar(const double *pos, const double *nuc, const double *mag, const Rot &R, int64_t W,
@@ -294,7 +323,7 @@ int launch_sample_polar(const double *pos, const double *nuc, const double *mag,
             default: launch_polar_tiles<4, 4>(PolarSampleLoader<4>{pos, nuc, mag, R}, W, p, store, out, s); break;
         }
     }
-    return combine_polar(p, partial, amp, 0, s);
+    return combine_polar(p, PointSource{nullptr, pos, nuc, mag, R}, W, partial, amp, 0, s);
 }
 
 int launch_polar_pairs(const PairRec *pts, int64_t n, const PolarPlan &p, double *partial, double *amp, hipStream_t s)
@@ -310,7 +339,7 @@ int launch_polar_pairs(const PairRec *pts, int64_t n, const PolarPlan &p, double
             default: launch_polar_tiles<4, 8>(PolarRecLoader<4, 8>{pts}, n, p, store, out, s); break;
         }
     }
-    return combine_polar(p, partial, amp, 0, s);
+    return combine_polar(p, PointSource{}, 0, partial, amp, 0, s);
 }
 
 }  // namespace numag

@@ -212,20 +212,27 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     }
 }
 
-// The rows of block a, offset b: 32 a + 16 + b and 32 a + 15 - b, at the mirrored column
-// too (nh > 0: column m + nh holds the conjugates).
-__device__ __forceinline__ void put_slot(double *__restrict__ amp, const PolGeom &g, int CH, int rg, int col, int s,
-                                         int b, double2 vp, double2 vm, bool add)
+// Rows of block a, offset b: 32 a + 16 + b (k = 0) and 32 a + 15 - b (k = 1).
+__device__ __forceinline__ int slot_row(const PolGeom &g, int rg, int e, int b, int k)
 {
-    const int e = s / CH, c = s - e * CH, a = rg * g.na + e;
+    const int a = kRows * (rg * g.na + e);
+    return k == 0 ? a + 16 + b : a + 15 - b;
+}
+
+// Writes (add: adds) the two rows of slot s, offset b, at the mirrored column too (nh > 0:
+// column m + nh holds the conjugates).  which: 1 for the first row, 2 for the second.
+__device__ __forceinline__ void put_slot(double *__restrict__ amp, const PolGeom &g, int CH, int rg, int col, int s,
+                                         int b, double2 vp, double2 vm, bool add, int which = 3)
+{
+    const int e = s / CH, c = s - e * CH;
     if (e >= g.na) return;
     const int first = CH == 3 ? 1 : 0;
-    const int row[2] = {kRows * a + 16 + b, kRows * a + 15 - b};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        if (row[k] >= g.n0) continue;
+        const int row = slot_row(g, rg, e, b, k);
+        if (row >= g.n0 || !(which >> k & 1)) continue;
         const double2 v = k == 0 ? vp : vm;
-        const int64_t p = (int64_t)row[k] * g.n_out + col;
+        const int64_t p = (int64_t)row * g.n_out + col;
         auto put = [&](int ch, double2 x) {
             cblk::put_pixel(amp, p, ch, x.x, x.y, add);
             if (g.nh > 0) cblk::put_pixel(amp, p + g.nh, ch, x.x, -x.y, add);
@@ -236,6 +243,30 @@ __device__ __forceinline__ void put_slot(double *__restrict__ amp, const PolGeom
             if (CH <= 2)
                 for (int ch = CH; ch < 4; ++ch) put(ch, make_double2(0.0, 0.0));
         }
+    }
+}
+
+// Which of a slot's sums are NaN on the detector (1, 2).
+__device__ __forceinline__ int which_nan(const PolGeom &g, int CH, int rg, int s, int b, double2 vp, double2 vm)
+{
+    const int e = s / CH;
+    if (e >= g.na) return 0;
+    return (is_nan(vp) && slot_row(g, rg, e, b, 0) < g.n0 ? 1 : 0) |
+           (is_nan(vm) && slot_row(g, rg, e, b, 1) < g.n0 ? 2 : 0);
+}
+
+// A slot's sums vp, vm over the points [j0, j1) of src (nonfinite.h), which of them (1, 2)
+// being NaN, at the direction (sth, cth).
+__device__ __forceinline__ void repair(const PolGeom &g, const PointSource &src, int64_t j0, int64_t j1, int CH, int rg,
+                                       int s, int b, double sth, double cth, int which, double2 &vp, double2 &vm)
+{
+    const int e = s / CH, ch = s - e * CH + (CH == 3 ? 1 : 0);
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+        if (!(which >> k & 1)) continue;
+        const double q = (double)slot_row(g, rg, e, b, k) * g.dq;
+        const double2 v = nonfinite_sum(src, j0, j1, ch, q * sth, q * cth, k == 0 ? vp : vm);
+        (k == 0 ? vp : vm) = v;
     }
 }
 
