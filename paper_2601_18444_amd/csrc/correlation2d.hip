@@ -23,6 +23,8 @@
 //    in channels 1-3, four in all four.
 #include <algorithm>
 
+#include "nonfinite.h"
+#include "nonfinite.h"
 #include "numag_internal.h"
 #include "phasor.h"
 
@@ -125,18 +127,39 @@ __global__ void corr2d_weights_kernel(Detector d, const double *__restrict__ f, 
     }
 }
 
-// C_out[set0 + c][t] = channel c0 + c of amp[t], c < m
-__global__ void corr2d_scatter_kernel(const double *__restrict__ amp, int64_t R, int m, int set0, int c0,
-                                      double *__restrict__ out)
+// C_out[set0 + c][t] = channel c0 + c of amp[t], c < m.  A value that came out as NaN is
+// formed again from the terms of the pixels whose data are not finite (nonfinite.h; whichever
+// way the sums were taken).
+__global__ void corr2d_scatter_kernel(const double *__restrict__ amp, int64_t R, int m, int set0, int c0, Detector d,
+                                      Detector rd, const double *__restrict__ f, double *__restrict__ out)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= R * 4) return;
     const int64_t t = i / 4;
     const int c = (int)(i % 4);
     if (c >= m) return;
+    double2 v = make_double2(amp[t * 8 + 2 * (c0 + c)], amp[t * 8 + 2 * (c0 + c) + 1]);
+    if (__builtin_expect(is_nan(v), 0)) {
+        const int64_t P = (int64_t)d.n0 * d.n1;
+        const double *fs = f + (int64_t)(set0 + c) * P;
+        double ry, rz, unused;
+        quadrature_pixel(rd, (int)(t / rd.n1), (int)(t % rd.n1), ry, rz, unused);
+        v = nonfinite_terms(
+            [&](int64_t p, double &Y, double &Z, double &w) {
+                w = fs[p];
+                Y = Z = 0.0;
+                if (isfinite(w)) return;
+                double wq;
+                quadrature_pixel(d, (int)(p / d.n1), (int)(p % d.n1), Y, Z, wq);
+                w *= wq;
+                Y = -Y;
+                Z = -Z;
+            },
+            0, P, ry, rz, v);
+    }
     double *o = out + ((int64_t)(set0 + c) * R + t) * 2;
-    o[0] = amp[t * 8 + 2 * (c0 + c)];
-    o[1] = amp[t * 8 + 2 * (c0 + c) + 1];
+    o[0] = v.x;
+    o[1] = v.y;
 }
 
 static size_t al2(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -230,7 +253,8 @@ int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Det
             hipLaunchKernelGGL(corr2d_weights_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, d, f, n_f,
                                set0, nuc, mag);
             NUMAG_HIP_CHECK(hipGetLastError());
-            rc = launch_separable(nuc, mag, pixel_grid(d), rd, NUMAG_PATH_SEPARABLE_F64, 1, amp, part, L.part, s);
+            rc = launch_separable(nuc, mag, pixel_grid(d), rd, NUMAG_PATH_SEPARABLE_F64, 1, amp, part, L.part, s,
+                                  true);
         } else if (route == kPairs) {
             const int64_t n = n_pairs(d);
             hipLaunchKernelGGL(corr2d_pairs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d, f, n_f,
@@ -252,7 +276,7 @@ int launch_correlation_2d(const Detector &d, const double *f, int n_f, const Det
         }
         if (rc != NUMAG_OK) return rc;
         hipLaunchKernelGGL(corr2d_scatter_kernel, dim3((unsigned)((R * 4 + 255) / 256)), dim3(256), 0, s, amp, R, m,
-                           set0, c0, C);
+                           set0, c0, d, rd, f, C);
         NUMAG_HIP_CHECK(hipGetLastError());
     }
     return NUMAG_OK;

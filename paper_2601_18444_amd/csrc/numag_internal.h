@@ -233,9 +233,11 @@ int launch_angular_spectrum(const Detector &d, const double *f, int n_f, int k_m
                             double *As, double *Ac, hipStream_t s);
 
 // regular-grid separable path on the matrix cores, for n_snap weight snapshots
-// (nuc [n_snap][W], mag [n_snap][W][3]; amp [n_snap][P][8]).
+// (nuc [n_snap][W], mag [n_snap][W][3]; amp [n_snap][P][8]).  pixels: the points are the
+// pixels of a detector, their coordinates rounded as its axes are.
 int launch_separable(const double *nuc, const double *mag, const numag_regular &g, const Detector &d,
-                     int path, int64_t n_snap, double *amp, void *ws, size_t ws_bytes, hipStream_t s);
+                     int path, int64_t n_snap, double *amp, void *ws, size_t ws_bytes, hipStream_t s,
+                     bool pixels = false);
 size_t separable_workspace_bytes(const numag_regular &g, const Detector &d, int path, int64_t n_snap);
 
 }  // namespace numag

@@ -126,6 +126,7 @@ constexpr int kProjUnroll = 8;    // loads in flight per thread
 // The remaining workgroups: twiddles exp(-i |q_y| y_iy) and exp(-i |q_z| z_iz) of the
 // values |q| (k + 1/2) step on an even axis and k step on an odd one, zeros in
 // the padding, and zeros in the padding of S.
+// pixels: the points are a detector's pixels, rounded as its axes are.
 // The weights are read once, with 8-byte non-temporal loads: measured on the
 // 537 MB of 64 snapshots of a 64^3 grid in this layout, 77 us (7.0 TB/s) against
 // 82 us with 16-byte loads of two adjacent columns per thread, and 88 us with
@@ -148,7 +149,7 @@ __device__ __forceinline__ double project_column(const double *__restrict__ src,
 __global__ __launch_bounds__(256) void sep_prepare_kernel(Detector d, numag_regular g, SepDims m,
                                                           const double *__restrict__ nuc,
                                                           const double *__restrict__ mag, int n_proj, int n_snap,
-                                                          int tw, int pad_s, double *__restrict__ S,
+                                                          int tw, int pad_s, int pixels, double *__restrict__ S,
                                                           double *__restrict__ ey, double2 *__restrict__ ez)
 {
     const int64_t nyz = (int64_t)g.n[1] * g.n[2];
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(256) void sep_prepare_kernel(Detector d, numag_regu
     const int64_t nez = tw ? (int64_t)m.nzk * m.nbp : 0;
     if (idx < ne) {
         const int e = (int)(idx % 8), iy = (int)(idx / 8 % m.nyk), t = (int)(idx / 8 / m.nyk);
-        const double y = g.origin[1] + (double)iy * g.step[1];
+        const double y = pixels ? axis_value(g.origin[1], iy, g.step[1]) : g.origin[1] + (double)iy * g.step[1];
         const int k = 8 * t + e;
         const double2 v = (k < m.na && iy < m.ny) ? twiddle(((double)k + (m.n0 & 1 ? 0.0 : 0.5)) * d.step0 * y)
                                                   : make_double2(0.0, 0.0);
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(256) void sep_prepare_kernel(Detector d, numag_regu
     } else if (idx < ne + nez) {
         const int64_t r = idx - ne;
         const int iz = (int)(r / m.nbp), k = (int)(r % m.nbp);
-        const double z = g.origin[2] + (double)iz * g.step[2];
+        const double z = pixels ? axis_value(g.origin[2], iz, g.step[2]) : g.origin[2] + (double)iz * g.step[2];
         ez[r] = (iz < m.nz && k < m.nb) ? twiddle(((double)k + (m.n1 & 1 ? 0.0 : 0.5)) * d.step1 * z)
                                         : make_double2(0.0, 0.0);
     } else if (pad_s) {
@@ -684,7 +685,7 @@ static int launch_bf16_path(const SepDims &m, const BfLayout &B, const Detector 
 // FP64 path: projections and twiddles, then both contractions.
 static int launch_f64_path(const double *nuc, const double *mag, const numag_regular &g, const Detector &d,
                            const SepDims &m, int64_t nb, double *ey, double2 *ez, double *S, double2 *T, double *amp,
-                           hipStream_t s)
+                           bool pixels, hipStream_t s)
 {
     const int sets = (int)(4 * nb);
     const int64_t sstride = (int64_t)m.ny16 * m.nzk;
@@ -695,7 +696,7 @@ static int launch_f64_path(const double *nuc, const double *mag, const numag_reg
         (int64_t)m.nta * m.nyk * 8 + (int64_t)m.nzk * m.nbp + (pad_s ? (int64_t)sets * sstride : 0);
     const int64_t n_tw = (n_elem + 255) / 256;
     hipLaunchKernelGGL(sep_prepare_kernel, dim3((unsigned)(n_proj * nb + n_tw)), dim3(256), 0, s, d, g, m, nuc, mag,
-                       (int)n_proj, (int)nb, 1, pad_s ? 1 : 0, S, ey, ez);
+                       (int)n_proj, (int)nb, 1, pad_s ? 1 : 0, pixels ? 1 : 0, S, ey, ez);
     NUMAG_HIP_CHECK(hipGetLastError());
     // first contraction: 32 x 32 outputs per wave when that still makes a few waves per
     // SIMD, else 16 x 16
@@ -735,7 +736,7 @@ static int launch_f64_path(const double *nuc, const double *mag, const numag_reg
 }
 
 int launch_separable(const double *nuc, const double *mag, const numag_regular &g, const Detector &d, int path,
-                     int64_t n_snap, double *amp, void *ws, size_t ws_bytes, hipStream_t s)
+                     int64_t n_snap, double *amp, void *ws, size_t ws_bytes, hipStream_t s, bool pixels)
 {
     const SepLayout L = sep_layout(g, d, n_snap);
     const SepDims m = sep_dims(g, d);
@@ -763,7 +764,7 @@ int launch_separable(const double *nuc, const double *mag, const numag_regular &
         const int64_t n_proj = (4 * nyz + kProjThreads - 1) / kProjThreads;
         const int64_t n_tw = ((pad_s ? (int64_t)sets * m.ny16 * m.nzk : 0) + 255) / 256;
         hipLaunchKernelGGL(sep_prepare_kernel, dim3((unsigned)(n_proj * n_snap + n_tw)), dim3(256), 0, s, d, g, m, nuc,
-                           mag, (int)n_proj, (int)n_snap, 0, pad_s ? 1 : 0, S, nullptr, nullptr);
+                           mag, (int)n_proj, (int)n_snap, 0, pad_s ? 1 : 0, 0, S, nullptr, nullptr);
         NUMAG_HIP_CHECK(hipGetLastError());
         const BfLayout B = bf_layout(m, path, n_snap);
         char *bbase = base + L.s;
@@ -773,7 +774,7 @@ int launch_separable(const double *nuc, const double *mag, const numag_regular &
     // One launch sequence for the whole batch: chunks of it on two streams, so that the
     // projection (HBM-bound) of one runs beside the second contraction of another, were
     // measured slower (the two kernels slow each other down more than the overlap saves).
-    return launch_f64_path(nuc, mag, g, d, m, n_snap, ey, ez, S, T, amp, s);
+    return launch_f64_path(nuc, mag, g, d, m, n_snap, ey, ez, S, T, amp, pixels, s);
 }
 
 }  // namespace numag

@@ -17,12 +17,14 @@ DEV = "cuda:0"
 QMAX = 1.3
 
 
-def _terms(w, phase):
-    """Sums over the infinite weights of w cos, -w sin, and where a part is well conditioned."""
-    c, s = np.cos(phase), -np.sin(phase)
+def _terms(w, a, b):
+    """Sums over the infinite weights of w cos, -w sin of the phase a + b, and where a part is
+    well conditioned: its sine or cosine not small, or zero because a and b are."""
+    c, s = np.cos(a + b), -np.sin(a + b)
+    zero = (a == 0.0) & (b == 0.0)
     with np.errstate(invalid="ignore"):
-        re, im = (w * c).sum(-1), (w * np.where(phase == 0.0, 0.0, s)).sum(-1)
-    return re, im, np.abs(c).min(-1) > 1e-9, (np.abs(s).min(-1) > 1e-9) | (phase == 0.0).any(-1)
+        re, im = (w * c).sum(-1), (w * np.where(zero, 0.0, s)).sum(-1)
+    return re, im, np.abs(c).min(-1) > 1e-9, (np.where(zero, 1.0, np.abs(s)) > 1e-9).all(-1)
 
 
 def _same(got, ref, ok):
@@ -56,7 +58,7 @@ def test_coherent_sums(orc, kind, n0, n1, W, infs, route):
     a = amp[0].cpu().numpy()  # [P, 4, 2] (a complex product of an infinite part would add NaN)
     qy, qz, _ = orc.pixels(kind, n0, n1, QMAX)
     X = pos[at] @ R.T
-    re, im, okr, oki = _terms(nuc[at], qy[:, None] * X[:, 1] + qz[:, None] * X[:, 2])
+    re, im, okr, oki = _terms(nuc[at], qy[:, None] * X[:, 1], qz[:, None] * X[:, 2])
     _same(a[:, 0, 0], re, okr)
     _same(a[:, 0, 1], im, oki)
     finite = dict(chans, nuc=np.where(np.isfinite(nuc), nuc, 0.0))
@@ -103,3 +105,45 @@ def test_objects(orc, kind, n0, n1, mode):
         # the object's phase mixes an infinite real and imaginary part: NaN or infinite
         assert not torch.isfinite(amp[0, :, 0]).any()
         assert torch.equal(amp[0, :, 1:], amp0[0, :, 1:])
+
+
+@pytest.mark.parametrize("kd,n0,n1", [(0, 6, 9), (0, 40, 33), (1, 6, 9), (1, 40, 8)])
+@pytest.mark.parametrize("kr,r0,r1", [(0, 5, 6), (0, 40, 37), (1, 5, 7), (1, 40, 6)])
+@pytest.mark.parametrize("m", [1, 3, 5])
+@pytest.mark.parametrize("infs", [[np.inf], [np.inf, -np.inf], [np.nan]])
+def test_correlation_2d(orc, kd, n0, n1, kr, r0, r1, m, infs):
+    rng = np.random.default_rng(n0 + r0 + m)
+    grid, rgrid = numag.qgrid(kd, n0, n1, QMAX), numag.qgrid(kr, r0, r1, 7.0)
+    f = rng.uniform(0.5, 2.0, (m, n0 * n1))
+    clean = numag.correlation_2d(grid, torch.as_tensor(f, device=DEV), rgrid)
+    at = n1 + rng.choice(n0 * n1 - n1, len(infs), replace=False)  # (q = 0 has no weight on a polar detector)
+    f[m - 1, at] = infs
+    C = numag.correlation_2d(grid, torch.as_tensor(f, device=DEV), rgrid)
+    qy, qz, _ = orc.pixels(kd, n0, n1, QMAX)
+    ry, rz, _ = orc.pixels(kr, r0, r1, 7.0)
+    re, im, okr, oki = _terms(f[m - 1, at], -ry[:, None] * qy[at], -rz[:, None] * qz[at])
+    got = C[m - 1].cpu().numpy()
+    _same(got[:, 0], re, okr)
+    _same(got[:, 1], im, oki)
+    assert torch.equal(C[: m - 1], clean[: m - 1])
+
+
+@pytest.mark.parametrize("kd,n0,n1", [(0, 6, 9), (0, 40, 33), (1, 6, 9), (1, 40, 8)])
+@pytest.mark.parametrize("kr,r0,r1", [(0, 5, 6), (0, 40, 37), (1, 5, 7), (1, 40, 6)])
+@pytest.mark.parametrize("m", [1, 3, 5])
+@pytest.mark.parametrize("infs", [[np.inf], [np.inf, -np.inf], [np.nan]])
+def test_correlation_2d(orc, kd, n0, n1, kr, r0, r1, m, infs):
+    rng = np.random.default_rng(n0 + r0 + m)
+    grid, rgrid = numag.qgrid(kd, n0, n1, QMAX), numag.qgrid(kr, r0, r1, 7.0)
+    f = rng.uniform(0.5, 2.0, (m, n0 * n1))
+    clean = numag.correlation_2d(grid, torch.as_tensor(f, device=DEV), rgrid)
+    at = n1 + rng.choice(n0 * n1 - n1, len(infs), replace=False)  # (q = 0 has no weight on a polar detector)
+    f[m - 1, at] = infs
+    C = numag.correlation_2d(grid, torch.as_tensor(f, device=DEV), rgrid)
+    qy, qz, _ = orc.pixels(kd, n0, n1, QMAX)
+    ry, rz, _ = orc.pixels(kr, r0, r1, 7.0)
+    re, im, okr, oki = _terms(f[m - 1, at], -ry[:, None] * qy[at], -rz[:, None] * qz[at])
+    got = C[m - 1].cpu().numpy()
+    _same(got[:, 0], re, okr)
+    _same(got[:, 1], im, oki)
+    assert torch.equal(C[: m - 1], clean[: m - 1])
