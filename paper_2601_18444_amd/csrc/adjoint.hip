@@ -32,6 +32,7 @@
 #include <cmath>
 
 #include "cartesian_block.h"
+#include "nonfinite.h"
 #include "polar_block.h"
 
 namespace numag {
@@ -421,14 +422,63 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
     }
 }
 
-__global__ void grad_finalize_kernel(const double *__restrict__ gpart, int nsplit, int64_t W, Rot R,
-                                     double *__restrict__ dnuc, double *__restrict__ dmag)
+// What the residual weights are formed from.
+struct Residual {
+    Detector d;
+    numag_consts k;
+    const double *amp, *target, *weight;
+};
+
+// A point's four sums, those that came out as NaN formed again from the pixels whose residual
+// weights are not finite (nonfinite.h): a weight, target or amplitude of infinity makes
+// inf - inf in a cell's coefficients where the pixel's own term is infinite.
+__device__ __forceinline__ void repair_gradient(const Residual &r, double Y, double Z, double (&g)[4])
+{
+    const int64_t P = (int64_t)r.d.n0 * r.d.n1;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    bool any[4] = {false, false, false, false};
+    const bool point = isfinite(Y) && isfinite(Z);
+#pragma unroll 1
+    for (int64_t p = 0; p < P; ++p) {
+        bool finite = point && isfinite(r.weight[p]) && (r.target == nullptr || isfinite(r.target[p]));
+        for (int v = 0; v < 8; ++v) finite = finite && isfinite(r.amp[8 * p + v]);
+        if (finite) continue;
+        double a[8], sn, cs;
+        residual_pixel(r.d, r.k, p, r.amp, r.target, r.weight, a);
+        const int row = (int)(p / r.d.n1), col = (int)(p % r.d.n1);
+        double phi;
+        if (r.d.kind == NUMAG_GRID_CARTESIAN) {
+            phi = axis_value(r.d.origin0, row, r.d.step0) * Y + axis_value(r.d.origin1, col, r.d.step1) * Z;
+        } else {
+            pixel_qhat(r.d, p, sn, cs);
+            phi = (double)row * r.d.step0 * (Y * sn + Z * cs);
+        }
+        const double2 e = phasor_signs(phi);
+        bool all = true;
+        for (int c = 0; c < 4; ++c) {
+            if (!point || !isfinite(a[2 * c]) || !isfinite(a[2 * c + 1])) {
+                s[c] = fma(-a[2 * c + 1], e.y, fma(a[2 * c], e.x, s[c]));
+                any[c] = true;
+            }
+            all = all && any[c] && s[c] != s[c];
+        }
+        if (all) break;
+    }
+    for (int c = 0; c < 4; ++c)
+        if (any[c] && g[c] != g[c]) g[c] = s[c];
+}
+
+__global__ __launch_bounds__(256, 8) void grad_finalize_kernel(const double *__restrict__ gpart, int nsplit, int64_t W, Rot R,
+                                     const PointRec *__restrict__ pts, Residual res, double *__restrict__ dnuc,
+                                     double *__restrict__ dmag)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= W) return;
     double g[4] = {0.0, 0.0, 0.0, 0.0};
     for (int s = 0; s < nsplit; ++s)
         for (int v = 0; v < 4; ++v) g[v] += gpart[((int64_t)s * W + j) * 4 + v];
+    if (__builtin_expect(g[0] != g[0] || g[1] != g[1] || g[2] != g[2] || g[3] != g[3], 0))
+        repair_gradient(res, pts[j].Y, pts[j].Z, g);
     if (dnuc != nullptr) dnuc[j] = g[0];
     if (dmag != nullptr) {
         for (int b = 0; b < 3; ++b)
@@ -617,7 +667,7 @@ int launch_grad(const PointRec *pts, int64_t W, const Detector &d, const numag_c
     }
     NUMAG_HIP_CHECK(hipGetLastError());
     hipLaunchKernelGGL(grad_finalize_kernel, dim3((unsigned)((W + 255) / 256)), dim3(256), 0, s, gpart, p.nsplit, W, R,
-                       dnuc, dmag);
+                       pts, Residual{d, c, amp, target, weight}, dnuc, dmag);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

@@ -147,3 +147,45 @@ def test_correlation_2d(orc, kd, n0, n1, kr, r0, r1, m, infs):
     _same(got[:, 0], re, okr)
     _same(got[:, 1], im, oki)
     assert torch.equal(C[: m - 1], clean[: m - 1])
+
+
+@pytest.mark.parametrize("kind,n0,n1", [(0, 9, 14), (0, 40, 33), (1, 9, 7), (1, 40, 8)])
+@pytest.mark.parametrize("what", ["weight", "target", "upstream", "two"])
+@pytest.mark.parametrize("path", [numag.PATH_DIRECT, numag.PATH_DIRECT_HERMITIAN])
+def test_gradient(orc, kind, n0, n1, what, path):
+    """The gradient with an infinite loss weight, target or upstream gradient at one pixel (or
+    two): each point's sums are what those pixels' terms Re(a exp(-i q.X)) make them."""
+    if path == numag.PATH_DIRECT_HERMITIAN and kind == 1 and n1 % 2:
+        pytest.skip("the half path needs an even n_theta")
+    W = 200
+    pos, nuc, mag, _ = _case(W, [], 7 + n0)
+    R, grid, c = synth.sample_rotation(33.0, 71.0), numag.qgrid(kind, n0, n1, QMAX), numag.consts(V=2.0, bH=0.7)
+    s = numag.Sample(pos=pos, nuc=nuc, mag=mag, device=DEV)
+    amp = numag.amplitudes(s, grid, rot=R, path=path)[0][0]
+    A = amp.cpu().numpy()
+    rng = np.random.default_rng(n1)
+    w, T = rng.uniform(0.5, 1.5, n0 * n1), rng.uniform(0.0, 1.0, n0 * n1)
+    at = [2 * n1 + 3] if what != "two" else [2 * n1 + 3, 5 * n1 + 2]
+    (T if what == "target" else w)[at] = np.inf
+    tgt = None if what == "upstream" else torch.as_tensor(T, device=DEV)
+    _, dn, dm = numag.grad(s, grid, c, weight=torch.as_tensor(w, device=DEV), target=tgt, rot=R, amp=amp, path=path)
+    qy, qz, qh = orc.pixels(kind, n0, n1, QMAX)
+    X = pos @ R.T
+    g = np.zeros((W, 4))
+    ok = np.ones(W, dtype=bool)
+    with np.errstate(invalid="ignore"):
+        for p in at:
+            qhat = qh[p]
+            M = A[p, 1:, 0] + 1j * A[p, 1:, 1]
+            V = M - qhat * (qhat @ M)
+            cf = 1.0 / 2.0
+            I = cf * (A[p, 0] @ A[p, 0] + 0.49 * np.vdot(V, V).real)
+            G = 2.0 * cf * (w[p] if what == "upstream" else 2.0 * w[p] * (I - T[p]))
+            ar = np.concatenate([[G * A[p, 0, 0]], G * 0.49 * V.real])
+            ai = -np.concatenate([[G * A[p, 0, 1]], G * 0.49 * V.imag])
+            phi = qy[p] * X[:, 1] + qz[p] * X[:, 2]
+            g += ar[None] * np.cos(phi)[:, None] + ai[None] * np.sin(phi)[:, None]
+            ok &= (np.abs(np.cos(phi)) > 1e-9) & (np.abs(np.sin(phi)) > 1e-9)
+        _same(dn.cpu().numpy(), g[:, 0], ok)
+        ref = np.stack([R[0, b] * g[:, 1] + R[1, b] * g[:, 2] + R[2, b] * g[:, 3] for b in range(3)], axis=1)
+    _same(dm.cpu().numpy(), ref, np.broadcast_to(ok[:, None], ref.shape))
