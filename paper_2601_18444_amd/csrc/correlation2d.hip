@@ -11,7 +11,7 @@
 // exp(+i q.r), with real weights wq_p f_p; the real-space grid plays the role of
 // the detector.
 //  - Cartesian detector and Cartesian real-space grid: the pixels are a regular grid, and
-//    the sum factors (separable.hip), four data sets a pass.  220 x 190 pixels to 180 x 170
+//    the sum factors (separable.hip), four data sets a pass; but for thin grids (factored()).  220 x 190 pixels to 180 x 170
 //    points, 4 sets: 36 us, against 306 as a direct sum.
 //  - Polar real-space grid, and a detector that has the pixel at -q for every one at q (a
 //    Cartesian one, a polar one with an even number of columns): the polar sums with the
@@ -166,12 +166,6 @@ static size_t al2(size_t b) { return (b + 255) & ~(size_t)255; }
 
 enum Route { kSeparable, kPairs, kDirect };
 
-static Route corr2d_route(const Detector &d, const Detector &rd)
-{
-    if (rd.kind == NUMAG_GRID_CARTESIAN) return d.kind == NUMAG_GRID_CARTESIAN ? kSeparable : kDirect;
-    return has_pairs(d) ? kPairs : kDirect;
-}
-
 // The pixels of a Cartesian detector at -q, as a regular grid of one layer.
 static numag_regular pixel_grid(const Detector &d)
 {
@@ -185,6 +179,34 @@ static numag_regular pixel_grid(const Detector &d)
     g.step[1] = -d.step0;
     g.step[2] = -d.step1;
     return g;
+}
+
+// Whether the sum over a Cartesian detector's pixels is factored (a Cartesian real-space
+// grid).  The factored sum takes a step per four detector rows and one per four columns, one
+// after the other where the detector is long and few waves share its steps, and holds the
+// first contraction for every row; the direct sums take pixels x points.  In cycles, the
+// factored sums from 1000 x 2, 2 x 1000 and 2000 x 3 pixels to as many points (61, 48 and
+// 125 us; the direct sums 18, 18 and 27 to 30); 2000 x 20 to 20 x 2000 is 137 and 125 to 236,
+// 32 x 32 18 and 22, 100 x 100 to 30 x 30 22 and 45 to 53.  A thin pair of grids (10^5 x 10 to
+// 10 x 10^5) would need 320 GB where the direct sums' records take 128 MB, which bounds it,
+// and a launch takes 2^31 threads.
+static bool factored(const Detector &d, const Detector &rd)
+{
+    const int64_t P = (int64_t)d.n0 * d.n1, R = (int64_t)rd.n0 * rd.n1;
+    const double na = (rd.n0 + 1) / 2, nb = (rd.n1 + 1) / 2, ny = d.n0, nz = d.n1;
+    if (16 * P + 16 * (na * ny + nb * nz) > (double)((int64_t)1 << 31)) return false;
+    const size_t ws = separable_workspace_bytes(pixel_grid(d), rd, NUMAG_PATH_SEPARABLE_F64, 1);
+    if (ws > (size_t)(P + R) * 64 + ((size_t)256 << 20)) return false;
+    const double flops = 16.0 * ny * nb * nz + 32.0 * na * nb * ny;
+    const double f = 46000.0 + 113.0 * ny + 72.0 * nz + flops / 15000.0;
+    return f <= 38000.0 + 0.1 * (double)P + cart_default_cost(rd, P, 4);
+}
+
+static Route corr2d_route(const Detector &d, const Detector &rd)
+{
+    if (rd.kind == NUMAG_GRID_CARTESIAN)
+        return d.kind == NUMAG_GRID_CARTESIAN && factored(d, rd) ? kSeparable : kDirect;
+    return has_pairs(d) ? kPairs : kDirect;
 }
 
 // Bytes of split partial sums, whatever the channel set.

@@ -498,6 +498,11 @@ static CartPlan cart_default_plan(const Detector &d, int64_t W, int channels, si
     return cheapest_plan(d, W, channels, max_partial, {32, 16, 64, 8}, env_target());
 }
 
+double cart_default_cost(const Detector &d, int64_t W, int channels)
+{
+    return cart_cost(cart_default_plan(d, W, channels, 0), W);
+}
+
 TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
 {
     switch (kernel) {

@@ -108,6 +108,8 @@ TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W);
 // first ceil(n0 / 2) rows); either way every pixel is written, the mirrored ones as
 // conjugates.  max_partial > 0 caps the bytes of partial sums.
 CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool hermitian, size_t max_partial = 0);
+// Estimated cycles of that sum under the library's own launch shape.
+double cart_default_cost(const Detector &d, int64_t W, int channels);
 // Cells, row blocks and matrix tiles of detector d for `channels` (cartesian_block.h).
 void cart_geometry(const Detector &d, int channels, CartGeom &g, int &mt);
 // The geometry of the object sums (four channels, column blocks of `shape`) in the cheaper

@@ -338,3 +338,15 @@ def test_separable_hermitian_path_validates():
     h = ctypes.c_void_p()
     assert lib.numag_plan_create(ctypes.byref(so), 1, None, ctypes.byref(grid), H64, numag.MODE_DILUTE, 1,
                                  ctypes.byref(h)) == numag.E_INVALID
+
+
+def test_correlation_2d_workspace_of_thin_grids_stays_near_the_records():
+    """The factored sum of a thin pair of Cartesian grids would hold an intermediate far
+    larger than its input and output (320 GB here); such a call takes the direct sums."""
+    def size(d, r):
+        return numag._lib.numag_correlation_2d_workspace_size(ctypes.byref(numag.qgrid(0, *d, 1.0)),
+                                                              ctypes.byref(numag.qgrid(0, *r, 30.0)))
+
+    for d, r in [((100000, 10), (10, 100000)), ((10, 100000), (100000, 10)), ((5000, 5000), (300, 300)),
+                 ((16400, 16400), (4, 4)), ((300, 200), (200, 300))]:
+        assert 0 < size(d, r) <= 128 * (d[0] * d[1] + r[0] * r[1]) + (1 << 30), (d, r)

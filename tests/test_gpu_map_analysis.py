@@ -116,3 +116,37 @@ def test_angular_spectrum_of_more_rows_than_a_grid_of_workgroups():
     Is, Ic, _, _ = numag.angular_spectrum(numag.qgrid(1, n_q, 2, 1.0), f, 0, amplitudes=False)
     assert (Ic[0, :, 0] - f[0].reshape(n_q, 2).mean(1)).abs().max().item() <= 16 * EPS
     assert Is.abs().max().item() == 0.0
+
+
+@pytest.mark.parametrize("d,r", [((500, 2), (2, 500)), ((2, 500), (500, 2)), ((700, 3), (300, 2)), ((90, 70), (3, 5)),
+                                 ((60, 50), (40, 41)), ((3, 600), (33, 70))])
+def test_correlation_2d_of_thin_grids(orc, d, r):
+    """Cartesian grids on both sides of the choice between factored and direct sums."""
+    rng = np.random.default_rng(d[0] + r[0])
+    qmax, rmax = 1.1, 30.0
+    grid, rgrid = numag.qgrid(0, *d, qmax), numag.qgrid(0, *r, rmax)
+    f = rng.standard_normal((5, d[0] * d[1]))
+    tol = EPS * (16 * qmax * rmax + d[0] * d[1] + 128) * (2 * qmax) ** 2 * np.abs(f).max()
+    for n_f in (1, 3, 5):
+        C = numag.correlation_2d(grid, torch.as_tensor(f[:n_f], device=DEV), rgrid).cpu().numpy()
+        ref = orc.correlation_2d(0, *d, qmax, f[:n_f], 0, *r, rmax)
+        assert np.abs(C[..., 0] + 1j * C[..., 1] - ref).max() <= tol
+
+
+def test_correlation_2d_of_more_pixels_than_a_grid_of_columns():
+    """2^28 pixels and more: the factored sum's preparation would pass 2^32 threads."""
+    n, m, qmax, rmax = 16400, 4, 1.1, 30.0
+    f = torch.rand((1, n * n), dtype=torch.float64, device=DEV)
+    C = numag.correlation_2d(numag.qgrid(0, n, n, qmax), f, numag.qgrid(0, m, m, rmax))
+    q = -qmax + torch.arange(n, dtype=torch.float64, device=DEV) * (2 * qmax / (n - 1))
+    r = -rmax + torch.arange(m, dtype=torch.float64, device=DEV) * (2 * rmax / (m - 1))
+    h = torch.full((n,), 2 * qmax / (n - 1), dtype=torch.float64, device=DEV)
+    h[0] *= 0.5
+    h[-1] *= 0.5
+    ph = r[:, None] * q[None]
+    c, s = torch.cos(ph) * h, torch.sin(ph) * h
+    F = f.reshape(n, n)
+    Fc, Fs = F @ c.T, F @ s.T
+    ref = torch.stack([c @ Fc - s @ Fs, c @ Fs + s @ Fc], dim=-1).reshape(m * m, 2)
+    # partial sums of up to n n terms of at most (2 qmax / n)^2, added over splits
+    assert (C[0] - ref).abs().max().item() <= EPS * (16 * qmax * rmax + 4 * n + 128) * (2 * qmax) ** 2
