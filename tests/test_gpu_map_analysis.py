@@ -150,3 +150,19 @@ def test_correlation_2d_of_more_pixels_than_a_grid_of_columns():
     ref = torch.stack([c @ Fc - s @ Fs, c @ Fs + s @ Fc], dim=-1).reshape(m * m, 2)
     # partial sums of up to n n terms of at most (2 qmax / n)^2, added over splits
     assert (C[0] - ref).abs().max().item() <= EPS * (16 * qmax * rmax + 4 * n + 128) * (2 * qmax) ** 2
+
+
+@pytest.mark.parametrize("n_q", [1, 5, 30, 130])
+@pytest.mark.parametrize("n_r", [700, 1100, 2200, 5000, 9000, 18000, 36000])
+def test_correlation_lanes_per_result(orc, n_q, n_r):
+    """As many results as take 64, 32, ... 1 lanes each, with empty bins."""
+    rng = np.random.default_rng(n_q + n_r)
+    q = np.sort(rng.uniform(0.0, 2.0, n_q))
+    I = rng.uniform(0.5, 2.0, (2, n_q))
+    I[:, rng.uniform(size=n_q) < 0.3] = np.nan
+    r = rng.uniform(0.0, 50.0, n_r)
+    c, p = numag.correlation(*(torch.as_tensor(x, device=DEV) for x in (q, I, r)))
+    cref, pref = orc.correlation(q, I, r)
+    tol = EPS * (n_q + 60.0 * 2) * 2.0 * 2.0 * 4.0  # as in test_correlation_empty_bins
+    assert np.all(np.abs(c.cpu().numpy() - cref) <= tol)
+    assert np.all(np.abs(p.cpu().numpy() - pref) <= tol * r * r)
