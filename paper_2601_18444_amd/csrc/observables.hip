@@ -114,20 +114,25 @@ __device__ __forceinline__ Forms forms_from_spectra(const double *__restrict__ g
 // observables, 168 MB, took 38 us, now 26), and the sets are taken last to first: amplitudes
 // that were just written are then read while they are still in the 256 MB last-level cache
 // (64 sets of 256 x 256 to two observables, 335 MB: 75 us first to last, 54 last to first).
+// Small detectors put several sets into a workgroup (20,000 sets of 4 x 4 pixels to 13
+// observables 14.8 us with one, 9.4).
 template <bool AMP>
 __global__ __launch_bounds__(256) void cross_section_kernel(Detector d, int64_t n_sets, const double *__restrict__ in,
                                                             numag_consts k, uint32_t mask, int n_out,
                                                             double *__restrict__ out)
 {
     const int64_t P = (int64_t)d.n0 * d.n1;
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    // a detector of at most half a workgroup's pixels: several sets per workgroup
+    const int per = P <= 128 ? 256 / (int)P : 1, sub = per > 1 ? (int)threadIdx.x / (int)P : 0;
+    if (sub >= per) return;
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x - (per > 1 ? sub * P : 0);
     if (p >= P) return;
     const double Ph[3] = {k.P[0], k.P[1], k.P[2]};
     double s, c;
     pixel_qhat(d, p, s, c);
     const double cf = k.scale / k.V;
     const double b2 = k.bH * k.bH;
-    for (int64_t set = n_sets - 1 - (int64_t)blockIdx.y; set >= 0; set -= gridDim.y) {
+    for (int64_t set = n_sets - 1 - ((int64_t)blockIdx.y * per + sub); set >= 0; set -= (int64_t)gridDim.y * per) {
         const int64_t idx = set * P + p;
         const Forms f = AMP ? forms_from_amplitudes(in + idx * 8, Ph, s, c) : forms_from_spectra(in + idx * 16, Ph, s, c);
         double obs[13];
@@ -169,7 +174,8 @@ int launch_cross_section(const Detector &d, int64_t n_sets, const double *amp, c
     const int64_t n = n_sets * P;
     if (n <= 0) return NUMAG_OK;
     const int n_out = __builtin_popcount(mask);
-    const dim3 grid((unsigned)((P + 255) / 256), (unsigned)std::min<int64_t>(n_sets, 65535));
+    const int64_t per = P <= 128 ? 256 / P : 1;
+    const dim3 grid((unsigned)((P + 255) / 256), (unsigned)std::min<int64_t>((n_sets + per - 1) / per, 65535));
     if (amp != nullptr)
         hipLaunchKernelGGL((cross_section_kernel<true>), grid, dim3(256), 0, s, d, n_sets, amp, c, mask, n_out, out);
     else

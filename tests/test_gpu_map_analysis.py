@@ -166,3 +166,20 @@ def test_correlation_lanes_per_result(orc, n_q, n_r):
     tol = EPS * (n_q + 60.0 * 2) * 2.0 * 2.0 * 4.0  # as in test_correlation_empty_bins
     assert np.all(np.abs(c.cpu().numpy() - cref) <= tol)
     assert np.all(np.abs(p.cpu().numpy() - pref) <= tol * r * r)
+
+
+@pytest.mark.parametrize("kind,n0,n1", [(0, 1, 1), (0, 5, 5), (0, 8, 16), (0, 3, 43), (1, 4, 6), (1, 10, 13)])
+@pytest.mark.parametrize("n_sets", [1, 2, 11, 300])
+def test_cross_sections_of_small_detectors(kind, n0, n1, n_sets):
+    """Detectors of at most 128 pixels put several sets into a workgroup: bit for bit the
+    cross sections of each set alone."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n0 + n_sets)
+    grid, c = numag.qgrid(kind, n0, n1, 1.3), numag.consts(V=2.0, bH=0.7, P=(0.0, 0.6, 0.8))
+    amp = torch.randn((n_sets, n0 * n1, 4, 2), generator=g, device=DEV, dtype=torch.float64)
+    spec = torch.randn((n_sets, n0 * n1, 16), generator=g, device=DEV, dtype=torch.float64)
+    for kw in (dict(amp=amp), dict(spec=spec)):
+        xs = numag.cross_section(grid, c=c, obs=numag.OBSERVABLES, **kw)
+        for k in {0, n_sets // 2, n_sets - 1}:
+            one = numag.cross_section(grid, c=c, obs=numag.OBSERVABLES, **{a: t[k:k + 1] for a, t in kw.items()})
+            assert torch.equal(xs[k:k + 1], one)
