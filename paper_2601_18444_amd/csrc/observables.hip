@@ -242,20 +242,21 @@ __device__ __forceinline__ int cart_bin(double qy, double qz, double dq, double 
 }
 
 constexpr int kAzThreads = 256;
-constexpr int kAzCart = 512;  // threads of the Cartesian kernel
-constexpr int kAzLanes = 8;   // lanes per detector row
 constexpr int kAzSets = 4;    // data sets per workgroup
 
 // One workgroup per bin and group of four data sets, so that the membership of a pixel
 // is decided once for the group.  Candidate pixels are the bounding rows of the annulus
 // and, per row, the two column intervals it can cover (rounded outwards); they are
-// shared by eight lanes, so that the long runs of the rows that touch the annulus from
-// inside do not wait on one, and their pixels are loaded before they are tested.  The
+// shared by LANES lanes: eight so that the long runs of the rows that touch the annulus from
+// inside do not wait on one; two where rows have few pixels (2000 x 3 pixels, 100 bins 18.7
+// -> 8.7 us); one, and half the threads, where the bins more than fill the chip, so that idle
+// lanes count and runs do not (256 x 256 in 8192 bins 51 -> 22 us).  Their pixels are loaded before they are tested.  The
 // squared radius decides all candidates but those within
 // 1e-12 of a bin edge; for these the exact bin test does.  Latency bound (square roots and
 // divisions in FP64): 13 data sets, 256 x 256 pixels in 128 bins, 28 -> 12 us;
 // 48 x 81 in 24 bins, 10.7 -> 5.6 us (one lane per row, one data set per workgroup before).
-__global__ __launch_bounds__(kAzCart) void azimuthal_cartesian_kernel(
+template <int LANES, int THREADS>
+__global__ __launch_bounds__(THREADS) void azimuthal_cartesian_kernel(
     Detector d, const double *__restrict__ f, int n_f, int n_bins, double qmax_avg, double *__restrict__ I,
     int64_t *__restrict__ count)
 {
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(kAzCart) void azimuthal_cartesian_kernel(
         const double inv0 = 1.0 / d.step0, inv1 = 1.0 / d.step1;
         const int i_lo = idx_lo(-r_out, d.origin0, d.step0, inv0, d.n0);
         const int i_hi = idx_hi(r_out, d.origin0, d.step0, inv0, d.n0);
-        for (int i = i_lo + (int)threadIdx.x / kAzLanes; i <= i_hi; i += kAzCart / kAzLanes) {
+        for (int i = i_lo + (int)threadIdx.x / LANES; i <= i_hi; i += THREADS / LANES) {
             const double qy = axis_value(d.origin0, i, d.step0);
             const double y2 = qy * qy;
             const double c_out = sqrt(fmax(0.0, out2 - y2));
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(kAzCart) void azimuthal_cartesian_kernel(
             const int l_lo = idx_lo(-c_out, d.origin1, d.step1, inv1, d.n1);
             const int l_hi = min(idx_hi(-c_in, d.origin1, d.step1, inv1, d.n1), r_lo - 1);
             const int nr = max(0, r_hi - r_lo + 1), nl = max(0, l_hi - l_lo + 1);
-            for (int e = (int)threadIdx.x % kAzLanes; e < nr + nl; e += kAzLanes) {
+            for (int e = (int)threadIdx.x % LANES; e < nr + nl; e += LANES) {
                 const int k = e < nr ? r_lo + e : l_lo + (e - nr);
                 const double *src = f + (int64_t)set0 * P + (int64_t)i * d.n1 + k;
                 double v[kAzSets];
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(kAzCart) void azimuthal_cartesian_kernel(
                 }
             }
         }
-        constexpr int kWaves = kAzCart / 64;
+        constexpr int kWaves = THREADS / 64;
         __shared__ double s_sum[kAzSets][kWaves];
         __shared__ int s_cnt[kWaves];
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -372,12 +373,20 @@ int launch_azimuthal(const Detector &d, const double *f, int n_f, int n_bins, do
                      double *I, int64_t *count, hipStream_t s)
 {
     if (n_f <= 0 || n_bins <= 0) return NUMAG_OK;
-    if (d.kind == NUMAG_GRID_CARTESIAN)
-        hipLaunchKernelGGL(azimuthal_cartesian_kernel,
-                           dim3((unsigned)std::min<int64_t>(n_bins, max_workgroups(kAzCart)),
-                                (n_f + kAzSets - 1) / kAzSets),
-                           dim3(kAzCart), 0, s, d, f, n_f, n_bins, qmax_avg, I, count);
-    else
+    if (d.kind == NUMAG_GRID_CARTESIAN) {
+        const int groups = (n_f + kAzSets - 1) / kAzSets;
+#define NUMAG_LAUNCH_AZ(LANES, THREADS)                                                                              \
+    hipLaunchKernelGGL((azimuthal_cartesian_kernel<LANES, THREADS>),                                                 \
+                       dim3((unsigned)std::min<int64_t>(n_bins, max_workgroups(THREADS)), groups), dim3(THREADS), 0, \
+                       s, d, f, n_f, n_bins, qmax_avg, I, count)
+        if (d.n0 >= 128 && (int64_t)n_bins * groups > 2048)
+            NUMAG_LAUNCH_AZ(1, 256);
+        else if (d.n1 <= 16)
+            NUMAG_LAUNCH_AZ(2, 512);
+        else
+            NUMAG_LAUNCH_AZ(8, 512);
+#undef NUMAG_LAUNCH_AZ
+    } else
         hipLaunchKernelGGL(azimuthal_polar_kernel, dim3(n_bins, n_f), dim3(kAzThreads), 0, s, d, f, n_bins, I, count);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;

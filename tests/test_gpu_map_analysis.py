@@ -183,3 +183,18 @@ def test_cross_sections_of_small_detectors(kind, n0, n1, n_sets):
         for k in {0, n_sets // 2, n_sets - 1}:
             one = numag.cross_section(grid, c=c, obs=numag.OBSERVABLES, **{a: t[k:k + 1] for a, t in kw.items()})
             assert torch.equal(xs[k:k + 1], one)
+
+
+@pytest.mark.parametrize("n0,n1,n_f,n_bins", [(500, 3, 2, 40), (1, 16, 1, 5), (129, 16, 5, 1100), (130, 40, 5, 1100),
+                                              (128, 30, 1, 2049), (127, 30, 1, 2049), (600, 17, 9, 700)])
+def test_azimuthal_lanes(orc, n0, n1, n_f, n_bins):
+    """Thin detectors and more bins than fill the chip: other splits of the rows."""
+    rng = np.random.default_rng(n0 + n_f)
+    f = rng.standard_normal((n_f, n0 * n1))
+    I, count = numag.azimuthal_average(numag.qgrid(0, n0, n1, 1.3), torch.as_tensor(f, device=DEV), n_bins, 1.5)
+    Iref, cref = orc.azimuthal_average(0, n0, n1, 1.3, f, n_bins, 1.5)
+    assert np.array_equal(count.cpu().numpy(), cref)
+    I = I.cpu().numpy()
+    assert np.array_equal(np.isnan(I), np.isnan(Iref))
+    some = cref > 0
+    assert np.all(np.abs(I - Iref)[:, some] <= EPS * n0 * n1 * np.abs(f).max())
