@@ -198,3 +198,16 @@ def test_azimuthal_lanes(orc, n0, n1, n_f, n_bins):
     assert np.array_equal(np.isnan(I), np.isnan(Iref))
     some = cref > 0
     assert np.all(np.abs(I - Iref)[:, some] <= EPS * n0 * n1 * np.abs(f).max())
+
+
+@pytest.mark.parametrize("n_theta", [1, 4, 5, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("k_max", [0, 1, 7, 16, 70])
+def test_angular_lanes_per_order(orc, n_theta, k_max):
+    rng = np.random.default_rng(n_theta + k_max)
+    f = rng.standard_normal((2, 6 * n_theta))
+    Is, Ic, _, _ = (x if x is None else x.cpu().numpy() for x in numag.angular_spectrum(
+        numag.qgrid(1, 6, n_theta, 1.0), torch.as_tensor(f, device=DEV), k_max, amplitudes=False))
+    for s in range(2):
+        Isr, Icr = orc.angular_spectrum(f[s], 6, n_theta, k_max)
+        tol = 2 * EPS * (n_theta + 8 * k_max + 8) * np.abs(f).max()  # as in test_angular_orders
+        assert np.abs(Is[s] - Isr).max() <= tol and np.abs(Ic[s] - Icr).max() <= tol
