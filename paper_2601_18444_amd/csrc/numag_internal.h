@@ -165,7 +165,7 @@ struct ObjectsPlan {
     PolGeom pg;      // polar detector
     int mt;          // matrix tiles per wave
     int64_t n_blocks;  // pixel blocks (items per slot)
-    int64_t n_th;    // tile halves of the detector (accumulator rows of a slot)
+    int64_t strips;  // accumulator strips of a slot (sixteen pixels each)
     int n_slots;     // accumulator slots (object set x rotation range)
     int n_out;       // spectral matrices written (K per object, or 1)
     int64_t n_items;

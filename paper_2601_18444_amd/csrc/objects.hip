@@ -22,10 +22,11 @@
 // the products of the current one.
 //
 // Accumulators hold only the independent half of the pixels (G(-q) = conj G(q) for
-// real weights), in the order the lanes hold them: lane l has channel g = l / 16 of
-// the pixels of one slot, takes the other channels from lanes l ^ 16, 32, 48 and
-// keeps four of the sixteen reals of G (kPacked), so that every access is a
-// coalesced wave-wide row; the reduction puts them into pixel order.
+// real weights), in strips of sixteen (the columns of a |q_N| block at one |q_M| value and
+// sign, or sixteen q rows of a theta column) in the order the lanes hold them: lane l has
+// channel g = l / 16 of the strip's pixels, takes the other channels from lanes
+// l ^ 16, 32, 48 and keeps four of the sixteen reals of G (kPacked), so that every access is
+// a coalesced wave-wide row; the reduction puts them into pixel order.
 //
 // Measured, kernel time before (10.5 vector FP64 instructions per term over every pixel)
 // and now: 16 particles (96,000 points) x 24 rotations, 128 x 128: 14.2 -> 5.70 ms (4.04 of
@@ -105,90 +106,75 @@ struct ObjArgs {
     const int4 *slots;       // (object lo, object hi, rotation lo, rotation hi)
     int n_items;
     int *counter;
-    double *spec;            // [n_slots][tiles][2 halves][2 signs][4][64]
-    double *amp;             // [n_slots][tiles][2 halves][4][64] or null (split mode)
+    double *spec;            // [n_slots][strips][4][64]
+    double *amp;             // [n_slots][strips][2][64] or null (split mode)
 };
+
+// Strips of a slot: [row block][column block][value of the block][sign], or [column][row
+// group][value][half].  Kernels of up to two tiles a wave, on detectors that may fill little of
+// them (one row block or group then), pass over the values and halves beyond the detector,
+// which take no accumulators: 3000 objects of 20 points on 8 x 40 polar pixels 123 MB of
+// workspace instead of 492.  In the larger ones, where they are few, a branch would cost more.
+constexpr int kExactTiles = 2;
+__host__ __device__ __forceinline__ int block_values(int na, int mt) { return mt <= kExactTiles ? na : 2 * mt; }
+__host__ __device__ __forceinline__ int64_t slot_strips(const CartGeom &g, int mt)
+{
+    return 2 * (int64_t)g.nrb * g.nzb * block_values(g.na, mt);
+}
+__host__ __device__ __forceinline__ int64_t column_strips(const PolGeom &g, int mt)
+{
+    return mt <= kExactTiles ? (g.n0 + 15) / 16 : (int64_t)g.nrg * 4 * mt;
+}
+__host__ __device__ __forceinline__ int64_t slot_strips(const PolGeom &g, int mt) { return g.cols * column_strips(g, mt); }
+// Lines of strips: blocks (Cartesian) or columns.
+__host__ __device__ __forceinline__ int64_t slot_lines(const CartGeom &g) { return (int64_t)g.nrb * g.nzb; }
+__host__ __device__ __forceinline__ int64_t slot_lines(const PolGeom &g) { return g.cols; }
 
 // Entry of the packed spectral matrix that lane group g keeps in row e: its own diagonal
 // entry, then one real of the pair (g, g ^ e): the real part in the group of the smaller
 // channel, the imaginary part in the other.
 __device__ constexpr int kPacked[4][4] = {{0, 4, 6, 8}, {1, 5, 12, 10}, {2, 14, 7, 11}, {3, 15, 13, 9}};
 
-// Adds (first: writes) F F^H of one sign to the lane's four accumulators o[64 e].  (Fused
-// products are written out, so that every inlined copy rounds alike.)
-__device__ __forceinline__ void add_spectral(double *__restrict__ o, bool first, double2 F)
+// The four entries of F F^H that a lane keeps.
+__device__ __forceinline__ void spectral_part(double2 F, double (&v)[4])
 {
     const int g = (threadIdx.x & 63) >> 4;
-    double v[4];
-    v[0] = fma(F.x, F.x, F.y * F.y);
+    v[0] = F.x * F.x + F.y * F.y;
 #pragma unroll
     for (int e = 1; e < 4; ++e) {
         const double ox = __shfl_xor(F.x, 16 * e), oy = __shfl_xor(F.y, 16 * e);
         // Re F_a conj(F_b) is symmetric; Im of the smaller channel a (the other lane's)
         // with b (this one's) is a_i b_r - a_r b_i
-        v[e] = g < (g ^ e) ? fma(F.x, ox, F.y * oy) : fma(oy, F.x, -(ox * F.y));
+        v[e] = g < (g ^ e) ? F.x * ox + F.y * oy : oy * F.x - ox * F.y;
     }
+}
+
+// Adds (first: writes) F F^H to the lane's four accumulators o[64 e].
+__device__ __forceinline__ void add_spectral(double *__restrict__ o, bool first, double2 F)
+{
+    double v[4];
+    spectral_part(F, v);
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[64 * e] = first ? v[e] : o[64 * e] + v[e];
 }
 
-// Adds (first: writes) one channel of the pixel pair times the object's phasors y z, y conj z.
-__device__ __forceinline__ void add_amplitude(double *__restrict__ o, bool first, double2 vp, double2 vm, double2 y,
-                                              double2 z)
+// Adds (first: writes) one channel of a pixel times the object's phasor y z.
+__device__ __forceinline__ void add_amplitude(double *__restrict__ o, bool first, double2 v, double2 y, double2 z)
 {
-    auto mul = [](double2 u, double2 v) {
-        return make_double2(fma(u.x, v.x, -(u.y * v.y)), fma(u.x, v.y, u.y * v.x));
-    };
-    const double2 a = mul(mul(y, z), vp), b = mul(mul(y, make_double2(z.x, -z.y)), vm);
-    o[0] = first ? a.x : o[0] + a.x;
-    o[64] = first ? a.y : o[64] + a.y;
-    o[128] = first ? b.x : o[128] + b.x;
-    o[192] = first ? b.y : o[192] + b.y;
+    const double2 r = cmul(cmul(y, z), v);
+    o[0] = first ? r.x : o[0] + r.x;
+    o[64] = first ? r.y : o[64] + r.y;
 }
 
+// Where the reductions flag results that are not finite, behind the item counter.
+constexpr int kNonfinite = 32;
+
 // Lab position (Y, Z) of object k.
-__device__ __forceinline__ double2 object_yz(const ObjArgs &a, const Rot &R, int k)
+__device__ __forceinline__ double2 object_yz(const ObjArgs &a, const double *R, int k)
 {
     if (a.obj_pos == nullptr) return make_double2(0.0, 0.0);
     const double *o = a.obj_pos + 3 * (int64_t)k;
-    return make_double2(R.m[3] * o[0] + R.m[4] * o[1] + R.m[5] * o[2],
-                        R.m[6] * o[0] + R.m[7] * o[1] + R.m[8] * o[2]);
-}
-
-// An object's sum v, if NaN, over its points [j0, j1) under the rotation R (in memory) from
-// its terms that are not finite (nonfinite.h).
-__device__ __forceinline__ double2 object_repair(const ObjArgs &a, const double *R, int64_t j0, int64_t j1, double qy,
-                                                 double qz, double2 v)
-{
-    if (!is_nan(v)) return v;
-    const int ch = (threadIdx.x & 63) >> 4;
-    return nonfinite_terms([&](int64_t j, double &Y, double &Z,
-                               double &w) { sample_point(a.pos, a.nuc, a.mag, R, ch, j, Y, Z, w); },
-                           j0, j1, qy, qz, v);
-}
-
-// Sums of an object put aside by a wave that holds a NaN among them, until the matrix
-// accumulators are free: which of its tile halves (wave-uniform).
-template <int MT>
-struct Aside {
-    double2 v[2 * MT][2];
-    unsigned which;
-    __device__ __forceinline__ Aside() : which(0) {}
-    __device__ __forceinline__ void take(int i, double2 vp, double2 vm)
-    {
-        v[i][0] = vp;
-        v[i][1] = vm;
-        which |= 1u << i;
-    }
-};
-
-// Whether a wave may hold a NaN among its finished sums (the parts of all tiles added up).
-template <int MT>
-__device__ __forceinline__ bool may_hold_nan(const cblk::v4d (&accC)[MT], const cblk::v4d (&accS)[MT])
-{
-    double s = 0.0;
-    cblk::finish_whole<MT>(accC, accS, [&](int, int, double2 vp, double2 vm) { s += (vp.x + vp.y) + (vm.x + vm.y); });
-    return __any(s != s) != 0;
+    return make_double2(R[3] * o[0] + R[4] * o[1] + R[5] * o[2], R[6] * o[0] + R[7] * o[1] + R[8] * o[2]);
 }
 
 template <int MT>
@@ -199,10 +185,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
     const int lane = threadIdx.x & 63;
     const int groups = (g.nzb + g.nz - 1) / g.nz;
-    const int64_t tiles = (int64_t)g.nrb * g.nzb * MT;
-    if (4 * g.na < 8 * MT) {  // rows no slot writes: no stray NaN for may_hold_nan
-        for (int i = threadIdx.x; i < (int)(sizeof(sm.y) / sizeof(double)); i += cblk::kThreads) (&sm.y[0][0][0])[i] = 0.0;
-    }
+    const int64_t strips = slot_strips(g, MT);
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
         __syncthreads();
@@ -216,7 +199,7 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
         const int4 sv = a.slots[slot];
         const int k0 = __builtin_amdgcn_readfirstlane(sv.x), k1 = __builtin_amdgcn_readfirstlane(sv.y);
         const int r0 = __builtin_amdgcn_readfirstlane(sv.z), r1 = __builtin_amdgcn_readfirstlane(sv.w);
-        const int64_t tile0 = slot * tiles + ((int64_t)rb * g.nzb + zb) * MT;
+        const int64_t strip0 = slot * strips + 2 * ((int64_t)rb * g.nzb + zb) * block_values(g.na, MT);
         RotLoader ld{a.pos, a.nuc, a.mag, uniform_rot(a.rot + 9 * (int64_t)r0), g.swapped};
         RotLoader::Raw p, q;
         cblk::first_points(ld, a.off[k0], a.off[k0 + 1], p, q);
@@ -232,53 +215,26 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
                 double2 z = make_double2(1.0, 0.0);
                 double Xm = 0.0;
                 if (a.amp != nullptr) {
-                    const double2 X = object_yz(a, ld.R, k);
+                    const double2 X = object_yz(a, ld.R.m, k);
                     Xm = g.swapped ? X.y : X.x;
                     z = twiddle(((double)(cblk::kOff * zb + (lane & 15)) + g.firstN) * g.stepN *
                                 (g.swapped ? X.x : X.y));
                 }
                 auto add = [&](int i, double2 vp, double2 vm) {
-                    const int64_t th = tile0 * 2 + i;
-                    double *o = a.spec + th * 512 + lane;
+                    if (MT <= kExactTiles && i >= g.na) return;
+                    const int64_t strip = strip0 + 2 * i;
+                    double *o = a.spec + strip * 256 + lane;
                     add_spectral(o, first, vp);
                     add_spectral(o + 256, first, vm);
                     if (a.amp != nullptr) {
                         const double qm = ((double)(rb * g.na + i) + g.firstM) * g.stepM;
-                        add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(qm * Xm), z);
+                        double *u = a.amp + strip * 128 + lane;
+                        add_amplitude(u, first, vp, twiddle(qm * Xm), z);
+                        add_amplitude(u + 128, first, vm, twiddle(qm * Xm), make_double2(z.x, -z.y));
                     }
                 };
-                Aside<MT> aside;
-                const int b = cblk::kOff * zb + (lane & 15);
-                auto put_aside = [&](int t, int h, double2 vp, double2 vm) { aside.take(2 * t + h, vp, vm); };
-                auto put = [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); };
-                if (g.nz != cblk::kWaves) {
-                    cblk::finish_groups<MT>(g, zb0, sm, accC, accS, [&](int t, int h, double2 vp, double2 vm) {
-                        if (__builtin_expect(__any(is_nan(vp) || is_nan(vm)) != 0, 0))
-                            put_aside(t, h, vp, vm);
-                        else
-                            put(t, h, vp, vm);
-                    });
-                } else if (zb < g.nzb) {
-                    if (__builtin_expect(may_hold_nan<MT>(accC, accS), 0))
-                        cblk::finish_whole<MT>(accC, accS, put_aside);
-                    else
-                        cblk::finish_whole<MT>(accC, accS, put);
-                }
-                while (__builtin_expect(aside.which != 0, 0)) {
-                    const int i = __builtin_ctz(aside.which);
-                    aside.which &= aside.which - 1;
-                    const double qm = ((double)(rb * g.na + i) + g.firstM) * g.stepM;
-                    const double qn = ((double)b + g.firstN) * g.stepN;
-                    const bool on = i < g.na && rb * g.na + i < g.A && b < g.B;
-                    double2 v[2] = {aside.v[i][0], aside.v[i][1]};
-#pragma unroll 1
-                    for (int s = 0; on && s < 2; ++s) {
-                        const double q = s == 0 ? qn : -qn;
-                        v[s] = object_repair(a, a.rot + 9 * (int64_t)r, a.off[k], a.off[k + 1], g.swapped ? q : qm,
-                                             g.swapped ? qm : q, v[s]);
-                    }
-                    add(i, v[0], v[1]);
-                }
+                cblk::finish<MT>(g, zb0, sm, accC, accS,
+                                 [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); });
             }
         }
     }
@@ -291,7 +247,7 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void objects_polar_kernel(ObjArg
     __shared__ pblk::WaveSmem<MT, 4> sm[pblk::kWaves];
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
-    const int64_t tiles = (int64_t)g.nrg * g.cols * MT;
+    const int64_t strips = slot_strips(g, MT), per_col = column_strips(g, MT);
     for (;;) {
         int it = 0;
         if (lane == 0) it = atomicAdd(a.counter, 1);
@@ -303,7 +259,7 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void objects_polar_kernel(ObjArg
         const int4 sv = a.slots[slot];
         const int k0 = __builtin_amdgcn_readfirstlane(sv.x), k1 = __builtin_amdgcn_readfirstlane(sv.y);
         const int r0 = __builtin_amdgcn_readfirstlane(sv.z), r1 = __builtin_amdgcn_readfirstlane(sv.w);
-        const int64_t tile0 = slot * tiles + ((int64_t)rg * g.cols + col) * MT;
+        const int64_t strip0 = slot * strips + col * per_col + 2 * (int64_t)rg * block_values(g.na, MT);
         double sth, cth;
         sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
         RotLoader ld{a.pos, a.nuc, a.mag, Rot{}, 0};
@@ -312,47 +268,33 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void objects_polar_kernel(ObjArg
             for (int k = k0; k < k1; ++k) {
                 cblk::v4d accC[MT], accS[MT];
                 cblk::zero<MT>(accC, accS);
-                pblk::accumulate<MT, 4>(ld, a.off[k], a.off[k + 1], sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
+                pblk::accumulate<MT, 4, 4>(ld, a.off[k], a.off[k + 1], sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
                 const bool first = r == r0 && k == k0;
                 double uk = 0.0;
                 double2 z = make_double2(1.0, 0.0);
                 if (a.amp != nullptr) {
-                    const double2 X = object_yz(a, ld.R, k);
+                    const double2 X = object_yz(a, ld.R.m, k);
                     uk = X.x * sth + X.y * cth;
                     z = twiddle(((double)(lane & 15) + 0.5) * g.dq * uk);
                 }
                 auto add = [&](int i, double2 vp, double2 vm) {
-                    const int64_t th = tile0 * 2 + i;
-                    double *o = a.spec + th * 512 + lane;
-                    add_spectral(o, first, vp);
-                    add_spectral(o + 256, first, vm);
+                    // rows 32 a + 15 - b, 32 a + 16 + b
+                    const int64_t strip = strip0 + 2 * i;
+                    const bool all = MT > kExactTiles, lower = all || (i < g.na && 2 * (rg * g.na + i) < per_col);
+                    const bool upper = all || (i < g.na && 2 * (rg * g.na + i) + 1 < per_col);
+                    double *o = a.spec + strip * 256 + lane;
+                    if (upper) add_spectral(o + 256, first, vp);
+                    if (lower) add_spectral(o, first, vm);
                     if (a.amp != nullptr) {
                         const double c = ((double)(pblk::kRows * (rg * g.na + i)) + 15.5) * g.dq;
-                        add_amplitude(a.amp + th * 256 + lane, first, vp, vm, twiddle(c * uk), z);
+                        const double2 y = twiddle(c * uk);
+                        double *u = a.amp + strip * 128 + lane;
+                        if (upper) add_amplitude(u + 128, first, vp, y, z);
+                        if (lower) add_amplitude(u, first, vm, y, make_double2(z.x, -z.y));
                     }
                 };
-                auto row = [&](int i, int s) { return pblk::slot_row(g, rg, i, lane & 15, s); };
-                Aside<MT> aside;
-                if (__builtin_expect(may_hold_nan<MT>(accC, accS), 0))
-                    cblk::finish_whole<MT>(accC, accS, [&](int t, int h, double2 vp, double2 vm) {
-                        aside.take(2 * t + h, vp, vm);
-                    });
-                else
-                    cblk::finish_whole<MT>(accC, accS,
-                                           [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); });
-                while (__builtin_expect(aside.which != 0, 0)) {
-                    const int i = __builtin_ctz(aside.which);
-                    aside.which &= aside.which - 1;
-                    double2 v[2] = {aside.v[i][0], aside.v[i][1]};
-#pragma unroll 1
-                    for (int s = 0; s < 2; ++s) {
-                        const double q = (double)row(i, s) * g.dq;
-                        if (i < g.na && row(i, s) < g.n0)
-                            v[s] = object_repair(a, a.rot + 9 * (int64_t)r, a.off[k], a.off[k + 1], q * sth, q * cth,
-                                                 v[s]);
-                    }
-                    add(i, v[0], v[1]);
-                }
+                cblk::finish_whole<MT>(accC, accS,
+                                       [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); });
             }
         }
     }
@@ -364,99 +306,225 @@ __global__ void fill_i32_kernel(int *p, int n, int v)
     if (i < n) p[i] = v;
 }
 
-// Pixels of a slot tile (t, h), lane column b: (+) and (-), and their mirrors at -q; -1: none.
-template <int POLAR>
-__device__ __forceinline__ void tile_pixels(const CartGeom &cg, const PolGeom &pg, int MT, int64_t th, int b,
-                                            int64_t (&px)[2], int64_t (&mirror)[2])
+// Pixel of lane column b of strip `at` of a line (row and column block, or column) and its
+// mirror at -q; -1: none.
+__device__ __forceinline__ void strip_pixel(const CartGeom &g, int mt, int line, int at, int b, int64_t &px,
+                                            int64_t &mirror)
 {
-    px[0] = px[1] = mirror[0] = mirror[1] = -1;
-    const int h = (int)(th & 1), t = (int)((th >> 1) % MT);
-    const int64_t blk = (th >> 1) / MT;
-    if (POLAR) {
-        const int rg = (int)(blk / pg.cols), col = (int)(blk % pg.cols);
-        const int e = 2 * t + h, a = rg * pg.na + e;
-        if (e >= pg.na) return;
-        const int rp = pblk::kRows * a + 16 + b, rm = pblk::kRows * a + 15 - b;
-        if (rp < pg.n0) px[0] = (int64_t)rp * pg.n_out + col;
-        if (rm < pg.n0) px[1] = (int64_t)rm * pg.n_out + col;
-        if (pg.nh > 0)
-            for (int s = 0; s < 2; ++s)
-                if (px[s] >= 0) mirror[s] = px[s] + pg.nh;
-    } else {
-        const cblk::CellPixels x =
-            cblk::cell_pixels(cg, 4, (int)(blk / cg.nzb), (int)(blk % cg.nzb), 8 * t + 4 * h, b);
-        if (!x.ok) return;
-        px[0] = x.pp;
-        if (x.twoN) px[1] = x.pm;
-        if (x.twoM) {
-            mirror[0] = x.mm;
-            if (x.twoN) mirror[1] = x.mp;
-        }
+    const int rb = g.nrb == 1 ? 0 : line / g.nzb, a = rb * g.na + (at >> 1), jb = cblk::kOff * (line - rb * g.nzb) + b;
+    px = mirror = -1;
+    if (jb >= g.B) return;
+    const int ip = g.nM - g.A + a, im = g.A - 1 - a, jp = g.nN - g.B + jb, jm = g.B - 1 - jb;
+    if ((at & 1) == 0) {
+        px = ip * g.strideM + jp * g.strideN;
+        if (ip != im) mirror = im * g.strideM + jm * g.strideN;
+    } else if (jp != jm) {
+        px = ip * g.strideM + jm * g.strideN;
+        if (ip != im) mirror = im * g.strideM + jp * g.strideN;
     }
 }
-
-// out[s][pixel][v] = scale * sum of the slots of output s (slot_off CSR, ascending), one
-// workgroup per (output, tile half, sign), through LDS into pixel order; the mirrored
-// pixels take conj G.  A workspace that does not hold the plan's tables (tag mismatch)
-// gives NaN.
-template <int POLAR>
-__global__ __launch_bounds__(256) void spec_reduce_kernel(const unsigned long long *tag_ptr, unsigned long long tag,
-                                                          const double *__restrict__ slots,
-                                                          const int *__restrict__ slot_off, CartGeom cg, PolGeom pg,
-                                                          int MT, int64_t n_th, int64_t P, double scale,
-                                                          double *__restrict__ out)
+__device__ __forceinline__ int strip_row(const PolGeom &g, int mt, int at, int b)
 {
-    __shared__ double x[16][17];
-    const int tid = threadIdx.x;
-    const int64_t th = blockIdx.x >> 1;
-    const int sign = blockIdx.x & 1, s = blockIdx.y;
-    {
-        const int lane = tid & 63, e = tid >> 6;
-        double v = __builtin_nan("");
-        if (*tag_ptr == tag) {
-            const double *p = slots + ((th * 2 + sign) * 4 + e) * 64 + lane;
-            double acc = 0.0;
-            for (int sl = slot_off[s]; sl < slot_off[s + 1]; ++sl) acc += p[(int64_t)sl * n_th * 512];
-            v = scale * acc;
-        }
-        x[lane & 15][kPacked[lane >> 4][e]] = v;
+    const int per = block_values(g.na, mt), rg = g.nrg == 1 ? 0 : (at >> 1) / per;
+    return pblk::slot_row(g, rg, (at >> 1) - rg * per, b, at & 1 ? 0 : 1);
+}
+__device__ __forceinline__ void strip_pixel(const PolGeom &g, int mt, int line, int at, int b, int64_t &px,
+                                            int64_t &mirror)
+{
+    const int row = strip_row(g, mt, at, b);
+    px = row < g.n0 ? (int64_t)row * g.n_out + line : -1;
+    mirror = px >= 0 && g.nh > 0 ? px + g.nh : -1;
+}
+
+// Whether a strip has pixels (the matrix rows of the others hold what was in memory).
+__device__ __forceinline__ bool strip_inside(const CartGeom &g, int mt, int line, int at)
+{
+    const int i = at >> 1;
+    return i < g.na && (g.nrb == 1 || line / g.nzb * g.na + i < g.A);
+}
+__device__ __forceinline__ bool strip_inside(const PolGeom &g, int mt, int line, int at)
+{
+    if (mt <= kExactTiles) return true;
+    const int per = block_values(g.na, mt), rg = g.nrg == 1 ? 0 : (at >> 1) / per, i = (at >> 1) - rg * per;
+    return i < g.na && pblk::kRows * (rg * g.na + i) + 16 * (at & 1) < g.n0;
+}
+
+// (q_y, q_z) of lane column b of a strip.
+__device__ __forceinline__ double2 strip_q(const CartGeom &g, int mt, int line, int at, int b)
+{
+    const int rb = line / g.nzb;
+    const double qm = ((double)(rb * g.na + (at >> 1)) + g.firstM) * g.stepM;
+    const double qn = ((double)(cblk::kOff * (line - rb * g.nzb) + b) + g.firstN) * g.stepN;
+    const double n = at & 1 ? -qn : qn;
+    return g.swapped ? make_double2(n, qm) : make_double2(qm, n);
+}
+__device__ __forceinline__ double2 strip_q(const PolGeom &g, int mt, int line, int at, int b)
+{
+    const double q = (double)strip_row(g, mt, at, b) * g.dq;
+    double sth, cth;
+    sincos_cw((2.0 * 3.141592653589793 * (double)line) / (double)g.n_out, &sth, &cth);
+    return make_double2(q * sth, q * cth);
+}
+
+// out[s][pixel][v] = scale * sum of the slots of output s (slot_off CSR; null: all n_slots),
+// in an order fixed by their number: the Q parts of a workgroup take contiguous shares, added
+// up in turn.  PLANES = 16: spectra; 8: the coherent total, amplitudes (re, im) of the
+// channels.  A workgroup takes a strip, through LDS into pixel order; the mirrored pixels take
+// the conjugates.  A workspace that does not hold the plan's tables (tag mismatch) gives NaN.
+template <int PLANES, int Q, class Geom>
+__global__ __launch_bounds__(16 * PLANES * Q) void reduce_kernel(ObjArgs a, const double *__restrict__ slots,
+                                                                 const int *__restrict__ slot_off, int n_slots, Geom g,
+                                                                 int mt, int line0, int out0, int64_t P, double scale,
+                                                                 double *__restrict__ out)
+{
+    constexpr int kStrip = 16 * PLANES;
+    __shared__ double x[Q][16][PLANES + 1];
+    const int part = Q == 1 ? 0 : threadIdx.x / kStrip, tid = Q == 1 ? threadIdx.x : threadIdx.x % kStrip;
+    const int line = line0 + blockIdx.y, s = out0 + blockIdx.z, at = blockIdx.x;
+    const uint32_t strip = (uint32_t)line * gridDim.x + at, strips = (uint32_t)slot_lines(g) * gridDim.x;
+    if (!strip_inside(g, mt, line, at)) return;
+    const bool ok = *a.tag_ptr == a.tag;
+    double acc = 0.0;
+    if (ok) {
+        const int lo = slot_off != nullptr ? slot_off[s] : 0, hi = slot_off != nullptr ? slot_off[s + 1] : n_slots;
+        const int first = Q == 1 ? lo : lo + (int)((int64_t)(hi - lo) * part / Q);
+        const int last = Q == 1 ? hi : lo + (int)((int64_t)(hi - lo) * (part + 1) / Q);
+        const double *p = slots + ((int64_t)first * strips + strip) * kStrip + tid;
+        const int64_t slot = (int64_t)strips * kStrip;
+#pragma unroll(Q == 1 ? 2 : 8)
+        for (int i = first; i < last; ++i, p += slot) acc += *p;
     }
+    const int lane = tid & 63, e = tid >> 6;
+    x[part][lane & 15][PLANES == 16 ? kPacked[lane >> 4][e] : 2 * (lane >> 4) + e] = acc;
+    if (acc != acc) a.counter[kNonfinite] = 1;
     __syncthreads();
-    const int b = tid >> 4, v = tid & 15;
-    int64_t px[2], mirror[2];
-    tile_pixels<POLAR>(cg, pg, MT, th, b, px, mirror);
-    const double val = x[b][v];
-    double *o = out + (int64_t)s * P * 16 + v;
-    if (px[sign] >= 0) o[px[sign] * 16] = val;
-    if (mirror[sign] >= 0) o[mirror[sign] * 16] = (v >= 5 && (v & 1)) ? -val : val;
+    if (part != 0) return;
+    const int b = tid / PLANES, v = tid % PLANES;
+    double sum = x[0][b][v];
+#pragma unroll
+    for (int q = 1; q < Q; ++q) sum += x[q][b][v];
+    const double val = ok ? scale * sum : __builtin_nan("");
+    int64_t px, mirror;
+    strip_pixel(g, mt, line, at, b, px, mirror);
+    double *o = out + (int64_t)s * P * PLANES + v;
+    const bool imag = (v & 1) != 0 && (PLANES == 8 || v >= 5);
+    if (px >= 0) o[px * PLANES] = val;
+    if (mirror >= 0) o[mirror * PLANES] = imag ? -val : val;
 }
 
-// Coherent total: the amplitude slots summed in order, mirrored pixels conjugated.
-template <int POLAR>
-__global__ __launch_bounds__(256) void amp_reduce_kernel(const unsigned long long *tag_ptr, unsigned long long tag,
-                                                         const double *__restrict__ slots, int n_slots, CartGeom cg,
-                                                         PolGeom pg, int MT, int64_t n_th, double *__restrict__ amp)
+// Four parts a workgroup where an output has more than 64 slots: a part reads one after
+// another.  (A part's waves read 512 bytes each: what they compute besides counts, so every
+// workgroup takes one strip without a loop, and lines and outputs beyond a grid's 65,535 have
+// launches of their own.  500 outputs of 8 x 40 polar pixels, half of the detector: 54 us with
+// the tiles' padding, 20 now.)
+template <int PLANES, class Geom>
+int launch_reduce(const ObjArgs &a, const double *slots, const int *slot_off, int n_slots, int n_out,
+                  const Geom &g, int mt, int64_t P, double scale, double *out, hipStream_t st)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int lane = (int)(idx & 63);
-    const int64_t th = idx >> 6;
-    if (th >= n_th) return;
-    double v[4];
-    const bool ok = *tag_ptr == tag;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = ok ? 0.0 : __builtin_nan("");
-    if (ok)
-        for (int sl = 0; sl < n_slots; ++sl) {
-            const double *p = slots + ((int64_t)sl * n_th + th) * 256 + lane;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
+    const bool split = n_slots > 64 * (int64_t)n_out;
+    const int threads = 16 * PLANES * (split ? 4 : 1);
+    const int64_t lines = slot_lines(g), per = slot_strips(g, mt) / lines;
+    constexpr int kMost = 65535;
+    for (int64_t line0 = 0; line0 < lines; line0 += kMost)
+        for (int out0 = 0; out0 < n_out; out0 += kMost) {
+            const dim3 grid((unsigned)per, (unsigned)std::min<int64_t>(lines - line0, kMost),
+                            (unsigned)std::min(n_out - out0, kMost));
+            if (split)
+                hipLaunchKernelGGL((reduce_kernel<PLANES, 4, Geom>), grid, dim3(threads), 0, st, a, slots, slot_off,
+                                   n_slots, g, mt, (int)line0, out0, P, scale, out);
+            else
+                hipLaunchKernelGGL((reduce_kernel<PLANES, 1, Geom>), grid, dim3(threads), 0, st, a, slots, slot_off,
+                                   n_slots, g, mt, (int)line0, out0, P, scale, out);
+            NUMAG_HIP_CHECK(hipGetLastError());
         }
-    int64_t px[2], mirror[2];
-    tile_pixels<POLAR>(cg, pg, MT, th, lane & 15, px, mirror);
+    return NUMAG_OK;
+}
+
+// Results that came out as NaN, formed again term by term from the objects that hold a weight
+// that is not finite: the matrix-core sums form a pixel as RR - II and the like, which is NaN
+// where the terms' sum is infinite (nonfinite.h), and the other objects cannot change an
+// infinite sum.  Nothing to do unless a reduction has set the flag (a launch of its own, since
+// in the reductions its registers would take their occupancy).  A wave takes the strip of one
+// output.
+template <int PLANES, class Geom>
+__device__ __forceinline__ void repair_strip(const ObjArgs &a, const Geom &g, int mt, int line, int at, int lo, int hi,
+                                             double scale, double *__restrict__ out)
+{
+    constexpr int N = PLANES / 4;
+    const int lane = threadIdx.x & 63, ch = lane >> 4, b = lane & 15;
+    int64_t px, mirror;
+    strip_pixel(g, mt, line, at, b, px, mirror);
+    bool nan[N];
+    bool any = false;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        if (px[s] >= 0) cblk::put_pixel(amp, px[s], lane >> 4, v[2 * s], v[2 * s + 1], false);
-        if (mirror[s] >= 0) cblk::put_pixel(amp, mirror[s], lane >> 4, v[2 * s], -v[2 * s + 1], false);
+    for (int e = 0; e < N; ++e) {
+        const int v = PLANES == 16 ? kPacked[ch][e] : 2 * ch + e;
+        const double was = px >= 0 ? out[px * PLANES + v] : 0.0;
+        nan[e] = was != was;
+        any = any || nan[e];
+    }
+    if (!__any(any)) return;
+    const double2 q = strip_q(g, mt, line, at, b);
+    double sum[N] = {};
+    bool found = false;
+    for (int sl = lo; sl < hi; ++sl) {
+        const int4 sv = a.slots[sl];
+        for (int k = sv.x; k < sv.y; ++k) {
+            bool finite = true;
+            for (int64_t j = a.off[k] + lane; j < a.off[k + 1]; j += 64) {
+                if (a.nuc != nullptr) finite = finite && isfinite(a.nuc[j]);
+                if (a.mag != nullptr)
+                    finite = finite && isfinite(a.mag[3 * j]) && isfinite(a.mag[3 * j + 1]) && isfinite(a.mag[3 * j + 2]);
+            }
+            if (__all(finite)) continue;
+            found = true;
+            for (int r = sv.z; r < sv.w; ++r) {
+                const double *R = a.rot + 9 * (int64_t)r;
+                double2 F = make_double2(0.0, 0.0);
+                for (int64_t j = a.off[k]; j < a.off[k + 1]; ++j) {
+                    double Y, Z, v;
+                    sample_point(a.pos, a.nuc, a.mag, R, ch, j, Y, Z, v);
+                    const double2 e = twiddle(q.x * Y + q.y * Z);
+                    F.x += v * e.x;
+                    F.y += v * e.y;
+                }
+                if constexpr (PLANES == 16) {
+                    double v[4];
+                    spectral_part(F, v);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] += v[e];
+                } else {
+                    const double2 X = object_yz(a, R, k), v = cmul(twiddle(q.x * X.x + q.y * X.y), F);
+                    sum[0] += v.x;
+                    sum[1] += v.y;
+                }
+            }
+        }
+    }
+    if (!found) return;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        if (!nan[e]) continue;
+        const int v = PLANES == 16 ? kPacked[ch][e] : 2 * ch + e;
+        const double val = scale * sum[e];
+        if (px >= 0) out[px * PLANES + v] = val;
+        if (mirror >= 0) out[mirror * PLANES + v] = (v & 1) != 0 && (PLANES == 8 || v >= 5) ? -val : val;
+    }
+}
+
+template <class Geom>
+__global__ __launch_bounds__(256) void nonfinite_objects_kernel(ObjArgs a, const int *__restrict__ slot_off, int n_slots,
+                                                                int n_out, Geom g, int mt, int64_t P, double scale,
+                                                                double *__restrict__ spec, double *__restrict__ amp)
+{
+    if (a.counter[kNonfinite] == 0 || *a.tag_ptr != a.tag) return;
+    const int strips = (int)slot_strips(g, mt), per = strips / (int)slot_lines(g);
+    for (int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); w < (int64_t)n_out * strips;
+         w += (int64_t)gridDim.x * 4) {
+        const int s = (int)(w / strips), strip = (int)(w % strips), line = strip / per, at = strip - line * per;
+        if (!strip_inside(g, mt, line, at)) continue;
+        repair_strip<16>(a, g, mt, line, at, slot_off[s], slot_off[s + 1], scale, spec + (int64_t)s * P * 16);
+        if (amp != nullptr) repair_strip<8>(a, g, mt, line, at, 0, n_slots, 1.0, amp);
     }
 }
 
@@ -537,11 +605,11 @@ Tables make_tables(const Detector &d, bool hermitian, const std::vector<int64_t>
     if (d.kind == NUMAG_GRID_POLAR) {
         polar_geometry(d, 4, ts.shape, p.pg, p.mt);
         p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;
-        p.n_th = p.n_blocks * p.mt * 2;
+        p.strips = slot_strips(p.pg, p.mt);
     } else {
         cart_objects_geometry(d, tuned ? ts.shape : cart_shape(d, off, K, W, n_rot, ts.target), p.cg, p.mt, nullptr);
         p.n_blocks = (int64_t)((p.cg.nzb + p.cg.nz - 1) / p.cg.nz) * p.cg.nrb;
-        p.n_th = (int64_t)p.cg.nzb * p.cg.nrb * p.mt * 2;
+        p.strips = slot_strips(p.cg, p.mt);
     }
     const int64_t nblocks = p.n_blocks;
     // slot groups wanted (each spans all pixel blocks)
@@ -618,10 +686,6 @@ void build_objects_plan(ObjPlan &pl)
     const bool hermitian = pl.path == NUMAG_PATH_DIRECT_HERMITIAN;
     c->T = make_tables(pl.d, hermitian, pl.off, pl.K, pl.W, pl.n_rot, pl.mode, pl.spec_per_object);
     const Tables &T = c->T;
-    // accumulators of a slot: 256 doubles of spectra and 256 of amplitudes per tile half
-    // and sign pair hold the independent half of the pixels; the whole-detector path asks
-    // for twice that, as a slot of every pixel takes
-    const size_t th = (size_t)T.p.n_th * (hermitian ? 1 : 2);
     size_t used = kPlanTagBytes;
     auto take = [&](size_t bytes) {
         const size_t r = used;
@@ -635,8 +699,10 @@ void build_objects_plan(ObjPlan &pl)
     c->o_slot_off = take(sizeof(int) * T.slot_off.size());
     const size_t image_bytes = used;
     c->o_counter = take(sizeof(int) * 64);
-    c->o_spec = take(sizeof(double) * 512 * (size_t)T.p.n_slots * th);
-    c->o_amp = pl.mode == NUMAG_MODE_SPLIT ? take(sizeof(double) * 256 * (size_t)T.p.n_slots * th) : 0;
+    c->o_spec = take(sizeof(double) * 256 * (size_t)T.p.n_slots * T.p.strips);
+    c->o_amp = pl.mode == NUMAG_MODE_SPLIT ? take(sizeof(double) * 128 * (size_t)T.p.n_slots * T.p.strips) : 0;
+    // both paths sum the same pixels; the whole-detector one's size stays the larger
+    if (!hermitian) take(1);
     pl.ws_bytes = used;
     // host image of the tag and the tables (rotations are filled by the caller)
     pl.image.assign(image_bytes, 0);
@@ -686,13 +752,13 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     // of 8, per CU)
     const int64_t fit = (pol ? 2 : 1) * (int64_t)device_cus();
     const int64_t want = pol ? (p.n_items + pblk::kWaves - 1) / pblk::kWaves : p.n_items;
+    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, fit)));
     {
         TimedLaunch timed(NUMAG_KERNEL_OBJECTS, st);
-        const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, fit)));
 #define NUMAG_LAUNCH_OBJ(MT)                                                                                    \
     case MT:                                                                                                    \
-        if (pol) hipLaunchKernelGGL((objects_polar_kernel<MT>), g, dim3(pblk::kThreads), 0, st, args, p.pg);     \
-        else hipLaunchKernelGGL((objects_kernel<MT>), g, dim3(cblk::kThreads), 0, st, args, p.cg);              \
+        if (pol) hipLaunchKernelGGL((objects_polar_kernel<MT>), grid, dim3(pblk::kThreads), 0, st, args, p.pg);     \
+        else hipLaunchKernelGGL((objects_kernel<MT>), grid, dim3(cblk::kThreads), 0, st, args, p.cg);              \
         break
         switch (p.mt) {
             NUMAG_LAUNCH_OBJ(1);
@@ -707,27 +773,20 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
 #undef NUMAG_LAUNCH_OBJ
     }
     NUMAG_HIP_CHECK(hipGetLastError());
-
-    const dim3 gs((unsigned)(p.n_th * 2), p.n_out), ga((unsigned)((p.n_th * 64 + 255) / 256));
     const int *d_off = (const int *)(base + c.o_slot_off);
     const double scale = 1.0 / (double)pl.n_rot;
-    if (pol)
-        hipLaunchKernelGGL((spec_reduce_kernel<1>), gs, dim3(256), 0, st, tag_ptr, tag, d_spec, d_off, p.cg, p.pg, p.mt,
-                           p.n_th, P, scale, spec_out);
-    else
-        hipLaunchKernelGGL((spec_reduce_kernel<0>), gs, dim3(256), 0, st, tag_ptr, tag, d_spec, d_off, p.cg, p.pg, p.mt,
-                           p.n_th, P, scale, spec_out);
-    NUMAG_HIP_CHECK(hipGetLastError());
-    if (d_amp != nullptr) {
-        if (pol)
-            hipLaunchKernelGGL((amp_reduce_kernel<1>), ga, dim3(256), 0, st, tag_ptr, tag, d_amp, p.n_slots, p.cg, p.pg,
-                               p.mt, p.n_th, amp_out);
-        else
-            hipLaunchKernelGGL((amp_reduce_kernel<0>), ga, dim3(256), 0, st, tag_ptr, tag, d_amp, p.n_slots, p.cg, p.pg,
-                               p.mt, p.n_th, amp_out);
+    const auto finish = [&](const auto &g) {
+        int rc = launch_reduce<16>(args, d_spec, d_off, p.n_slots, p.n_out, g, p.mt, P, scale, spec_out, st);
+        if (rc == NUMAG_OK && d_amp != nullptr)
+            rc = launch_reduce<8>(args, d_amp, nullptr, p.n_slots, 1, g, p.mt, P, 1.0, amp_out, st);
+        if (rc != NUMAG_OK) return rc;
+        const dim3 grid((unsigned)std::min<int64_t>((p.n_out * p.strips + 3) / 4, 2 * (int64_t)device_cus()));
+        hipLaunchKernelGGL((nonfinite_objects_kernel<std::decay_t<decltype(g)>>), grid, dim3(256), 0, st, args, d_off,
+                           p.n_slots, p.n_out, g, p.mt, P, scale, spec_out, d_amp != nullptr ? amp_out : nullptr);
         NUMAG_HIP_CHECK(hipGetLastError());
-    }
-    return NUMAG_OK;
+        return NUMAG_OK;
+    };
+    return pol ? finish(p.pg) : finish(p.cg);
 }
 
 }  // namespace numag

@@ -350,3 +350,22 @@ def test_correlation_2d_workspace_of_thin_grids_stays_near_the_records():
     for d, r in [((100000, 10), (10, 100000)), ((10, 100000), (100000, 10)), ((5000, 5000), (300, 300)),
                  ((16400, 16400), (4, 4)), ((300, 200), (200, 300))]:
         assert 0 < size(d, r) <= 128 * (d[0] * d[1] + r[0] * r[1]) + (1 << 30), (d, r)
+
+
+@pytest.mark.parametrize("kind,n0,n1", [(0, 8, 40), (1, 8, 40), (0, 5, 64), (1, 16, 64)])
+def test_object_accumulators_follow_the_detector(kind, n0, n1):
+    """One accumulator slot per object: sixteen reals of the spectrum and eight of the
+    amplitude for each independent pixel, rounded up to blocks of 16 along one axis (and 16
+    pixels more on a Cartesian detector), not to the tiles of the matrix instructions."""
+    K, per = 3000, 20
+    s = _cpu_sample(W=K * per, K=K, offsets=np.arange(K + 1, dtype=np.int64) * per)
+    grid = numag.qgrid(kind, n0, n1, 1.0)
+    nws = numag._lib.numag_workspace_size(ctypes.byref(s), 1, ctypes.byref(grid), numag.PATH_DIRECT_HERMITIAN,
+                                          numag.MODE_DILUTE)
+    if kind == 1:
+        pixels = -(-n0 // 16) * 16 * (n1 // 2)
+    else:
+        a, b = sorted((n0, n1))
+        pixels = min((a + 1) // 2 * (-(-((b + 1) // 2) // 16) * 16), (b + 1) // 2 * (-(-((a + 1) // 2) // 16) * 16)) * 2
+    tables = 8 * 1024 * 1024
+    assert 0 < nws <= K * pixels * 24 * 8 * 1.02 + tables

@@ -410,3 +410,29 @@ def test_batched_orientations_graph_replay_polar(orc, path):
     qy, qz, _ = orc.pixels(1, 40, 36, qmax)
     Fs = [orc.amplitudes(cfg["pos"][sl], cfg["nuc"][sl], cfg["mag"][sl], qy, qz, R=R) for R in rots]
     _check_spec(ref[k].cpu().numpy(), orc.spectral(np.stack(Fs)) / len(rots))
+
+
+@pytest.mark.parametrize("kind,n0,n1,path", [(0, 3, 5, 0), (1, 3, 4, 0), (1, 3, 4, 3), (1, 40, 6, 3)])
+def test_very_many_small_objects(orc, kind, n0, n1, path):
+    """More objects than a grid has rows (65,535), each a slot and an output of its own, of
+    0 to 3 points: the spectra of the first, the last and those around the limit against the
+    oracle, and all of them together against the sum."""
+    K = 66_000 if n0 < 40 else 3000
+    rng = np.random.default_rng(70)
+    cfg = _objects(71, rng.integers(0, 4, size=K), spread=20.0)
+    qmax = 0.9
+    grid = numag.qgrid(kind, n0, n1, qmax)
+    qy, qz, _ = orc.pixels(kind, n0, n1, qmax)
+    amp, spec = numag.amplitudes(_sample(cfg), grid, path=path, mode=numag.MODE_SPLIT, spec_per_object=True)
+    spec = spec.cpu().numpy()
+    off = cfg["obj_offsets"]
+    total = 0.0
+    for k in (0, 1, 2, K // 2, min(K, 65_535) - 1, min(K, 65_536) - 1, K - 2, K - 1):
+        sl = slice(off[k], off[k + 1])
+        if off[k + 1] == off[k]:
+            assert np.count_nonzero(spec[k]) == 0
+            continue
+        _check_spec(spec[k], orc.spectral(orc.amplitudes(cfg["pos"][sl], cfg["nuc"][sl], cfg["mag"][sl], qy, qz)[None]))
+    amp1, tot = numag.amplitudes(_sample(cfg), grid, path=path, mode=numag.MODE_SPLIT)
+    assert max_norm_err(tot[0].cpu().numpy(), spec.sum(axis=0)) <= 1e-12
+    assert max_norm_err(amp1.cpu().numpy(), amp.cpu().numpy()) <= 1e-12
