@@ -11,7 +11,7 @@
 // of its range with the matrix building blocks of the direct sums, then F F^H (and,
 // in split mode, exp(-i q.R r^k) F for the coherent total) goes into the slot's FP64
 // accumulators, which no other item touches.  Items are sorted by cost and handed out by
-// a persistent kernel through an atomic counter -- to workgroups of 8 waves on a
+// a persistent kernel through an atomic counter (small polar ones in order) -- to workgroups of 8 waves on a
 // Cartesian detector (cartesian_block.h), to single waves on a polar one
 // (polar_block.h); slots are reduced in a fixed order, so results are reproducible
 // bit for bit.
@@ -106,6 +106,7 @@ struct ObjArgs {
     const int4 *slots;       // (object lo, object hi, rotation lo, rotation hi)
     int n_items;
     int *counter;
+    int rounds;              // turns that every wave takes without the counter (polar)
     double *spec;            // [n_slots][strips][4][64]
     double *amp;             // [n_slots][strips][2][64] or null (split mode)
 };
@@ -242,16 +243,19 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
 
 // A work item belongs to one wave: (slot, theta column and row group).
 template <int MT>
-__global__ __launch_bounds__(pblk::kThreads, 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
+__global__ __launch_bounds__(pblk::kThreads, MT == 1 ? 3 : 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
 {
     __shared__ pblk::WaveSmem<MT, 4> sm[pblk::kWaves];
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
     const int64_t strips = slot_strips(g, MT), per_col = column_strips(g, MT);
-    for (;;) {
-        int it = 0;
-        if (lane == 0) it = atomicAdd(a.counter, 1);
-        it = __builtin_amdgcn_readfirstlane(it);
+    const int waves = (int)gridDim.x * pblk::kWaves;
+    for (int turn = 0;; ++turn) {
+        int it = turn * waves + (int)blockIdx.x * pblk::kWaves + wave;
+        if (turn >= a.rounds) {
+            if (lane == 0) it = atomicAdd(a.counter, 1) + a.rounds * waves;
+            it = __builtin_amdgcn_readfirstlane(it);
+        }
         if (it >= a.n_items) break;
         const int2 item = a.items[it];
         const int slot = __builtin_amdgcn_readfirstlane(item.x), blk = __builtin_amdgcn_readfirstlane(item.y);
@@ -748,11 +752,20 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     args.spec = d_spec;
     args.amp = d_amp;
     const bool pol = pl.d.kind == NUMAG_GRID_POLAR;
-    // persistent grid: as many workgroups as fit the chip at once (two of 4 waves, or one
-    // of 8, per CU)
-    const int64_t fit = (pol ? 2 : 1) * (int64_t)device_cus();
+    // persistent grid: as many workgroups as fit the chip at once (two of 4 waves, three of one
+    // tile, or one of 8 waves, per CU; the third: 73 -> 62 us and 101 -> 86 in the cases below)
+    const int64_t fit = (!pol ? 1 : p.mt == 1 ? 3 : 2) * (int64_t)device_cus();
     const int64_t want = pol ? (p.n_items + pblk::kWaves - 1) / pblk::kWaves : p.n_items;
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, fit)));
+    // The counter takes an atomic every 12 ns, 25 us for a turn of the chip's waves: small items
+    // would wait for it.  They are sorted by cost, so waves that take them in order end within
+    // one item of each other; larger ones the counter evens out better.  The line is at an item
+    // of 25 us, 160 points, rotations and tiles (500 objects of 40 points, two rotations, one
+    // tile, all by the counter and now: 8 x 40 pixels 260 -> 62 us, 16 x 64 397 -> 86; of four
+    // tiles, 200 x 120: 730 by the counter, 790 in order).
+    const int64_t waves = (int64_t)grid.x * pblk::kWaves;
+    const bool small = (double)pl.W * (double)pl.n_rot * p.mt < 160.0 * (double)p.n_slots;
+    args.rounds = small ? (int)(p.n_items / waves + 1) : 0;
     {
         TimedLaunch timed(NUMAG_KERNEL_OBJECTS, st);
 #define NUMAG_LAUNCH_OBJ(MT)                                                                                    \
