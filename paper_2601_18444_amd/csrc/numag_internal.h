@@ -132,7 +132,7 @@ int launch_sample_cartesian(const double *pos, const double *nuc, const double *
 constexpr int kPolarShapeCount = 5;
 struct PolarPlan {
     PolGeom g;
-    int mt;          // 16-row matrix tiles per wave
+    int mt;          // 16-row matrix tiles per wave; 0, -1: one, two of 4 rows
     int shape;       // launch shape: 1, 0, 2, 3, 4 for 1, 2, 4, 8 or 16 row blocks of 32 per wave
     int channels;    // channels summed: 4 (N, M), 3 (M only) or 1 (N only); the rest are written as 0
     int nsplit;      // point ranges summed by different workgroups

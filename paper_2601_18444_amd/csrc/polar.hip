@@ -84,12 +84,17 @@ struct PolarSampleLoader {
     __host__ __device__ __forceinline__ PointSource source() const { return PointSource{nullptr, pos, nuc, mag, R}; }
 };
 
+// Workgroups per CU: registers and LDS allow two, and three of the tiles of 4 x 16.
+__host__ __device__ constexpr int polar_per_cu(int mt) { return mt > 0 ? 2 : 3; }
+
 // One wave: one theta column, one row group, one point range.  Partials
-// [split][row group][column][tile][half][4][64] (store == 0), or amp (1: written,
-// 2: added).
+// [split][row group][column][tile][half][4][64] (store == 0; [tile][2][64] of the 4 x 16
+// tiles), or amp (1: written, 2: added).
 template <int MT, int CH, int NW, class Loader>
-__global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(Loader ld, int64_t W, int64_t per, PolGeom g,
-                                                                         int store, double *__restrict__ out)
+__global__ __launch_bounds__(pblk::kThreads, polar_per_cu(MT)) void direct_polar_kernel(Loader ld, int64_t W,
+                                                                                        int64_t per, PolGeom g,
+                                                                                        int store,
+                                                                                        double *__restrict__ out)
 {
     __shared__ pblk::WaveSmem<MT, CH, NW> sm[pblk::kWaves];
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
@@ -99,32 +104,42 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(Loader 
     const int64_t jend = min(W, jbeg + per);
     double sth, cth;
     sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
-    cblk::v4d accC[MT], accS[MT];
-    cblk::zero<MT>(accC, accS);
+    constexpr int N = pblk::Tiles<MT>::N;
+    typename pblk::Tiles<MT>::T accC[N] = {}, accS[N] = {};
     pblk::accumulate<MT, CH, NW>(ld, jbeg, jend, sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
-    unsigned bad = 0;  // NaN sums of this lane, two bits per tile half
+    const int64_t block = (((int64_t)blockIdx.z * g.nrg + rg) * g.cols + col) * N;
+    unsigned bad = 0;  // NaN sums of this lane, two bits per tile half (or tile)
+    // `which` (1, 2) of slot's sums vp, vm, put away unless NaN
+    auto put = [&](int i, int slot, double2 vp, double2 vm, int which) {
+        const int nan = which & (NW == CH ? pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0);
+        bad |= (unsigned)nan << (2 * i);
+        pblk::put_slot(out, g, CH, rg, col, slot, lane & 15, vp, vm, store == 2, which & ~nan);
+    };
+    if constexpr (MT > 0) {
+        cblk::finish_whole<MT>(accC, accS, [&](int t, int h, double2 vp, double2 vm) {
+            if (store != 0) return put(2 * t + h, 8 * t + 4 * h + (lane >> 4), vp, vm, 3);
+            double *o = out + ((block + t) * 2 + h) * 256 + lane;
+            o[0] = vp.x;
+            o[64] = vp.y;
+            o[128] = vm.x;
+            o[192] = vm.y;
+        });
+    } else {
 #pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const double RR = accC[t][2 * h], IR = accC[t][2 * h + 1], RI = accS[t][2 * h], II = accS[t][2 * h + 1];
-            const double2 vp = make_double2(RR - II, RI + IR), vm = make_double2(RR + II, IR - RI);
-            if (store == 0) {
-                double *o = out +
-                            (((((int64_t)blockIdx.z * g.nrg + rg) * g.cols + col) * MT + t) * 2 + h) * 256 + lane;
-                o[0] = vp.x;
-                o[64] = vp.y;
-                o[128] = vm.x;
-                o[192] = vm.y;
-            } else {
-                const int slot = 8 * t + 4 * h + (lane >> 4);
-                const int nan = NW == CH ? pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0;
-                bad |= (unsigned)nan << (2 * (2 * t + h));
-                pblk::put_slot(out, g, CH, rg, col, slot, lane & 15, vp, vm, store == 2, 3 & ~nan);
+        for (int t = 0; t < N; ++t) {
+            const double2 v = pblk::few_rows(accC[t], accS[t]);
+            if (store != 0) {
+                put(t, 2 * t + (lane >> 4 & 1), v, v, 1 + (lane >> 5));
+                continue;
             }
+            double *o = out + (block + t) * 128 + lane;
+            o[0] = v.x;
+            o[64] = v.y;
         }
+    }
     while (NW == CH && __builtin_expect(bad != 0, 0)) {
-        const int i = __builtin_ctz(bad) >> 1, which = (int)(bad >> (2 * i) & 3), slot = 4 * i + (lane >> 4);
+        const int i = __builtin_ctz(bad) >> 1, which = (int)(bad >> (2 * i) & 3);
+        const int slot = MT > 0 ? 4 * i + (lane >> 4) : 2 * i + (lane >> 4 & 1);
         bad &= ~(3u << (2 * i));
         double2 vp = make_double2(__builtin_nan(""), __builtin_nan("")), vm = vp;
         pblk::repair(g, ld.source(), jbeg, jend, CH, rg, slot, lane & 15, sth, cth, which, vp, vm);
@@ -132,34 +147,38 @@ __global__ __launch_bounds__(pblk::kThreads, 2) void direct_polar_kernel(Loader 
     }
 }
 
-// Fixed-order sum of the split partials, written (or added) to the pixels.
-__global__ __launch_bounds__(256) void polar_combine_kernel(const double *__restrict__ part, PolGeom g, int MT, int CH,
+// Fixed-order sum of the split partials, written (or added) to the pixels: blocks of a row
+// group, column and tile half (tile of 4 x 16: FEW).
+template <bool FEW>
+__global__ __launch_bounds__(256) void polar_combine_kernel(const double *__restrict__ part, PolGeom g, int n, int CH,
                                                             int nsplit, PointSource src, int64_t W, int accumulate,
                                                             double *__restrict__ amp)
 {
+    constexpr int V = FEW ? 2 : 4;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int lane = (int)(idx & 63);
-    const int64_t block = idx >> 6;  // (row group, column, tile, half)
-    const int64_t blocks = (int64_t)g.nrg * g.cols * MT * 2;
+    const int64_t block = idx >> 6;
+    const int64_t blocks = (int64_t)g.nrg * g.cols * n;
     if (block >= blocks) return;
-    const int h = (int)(block & 1), t = (int)((block >> 1) % MT);
-    const int64_t rc = (block >> 1) / MT;
-    const double *p = part + block * 256 + lane;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    const int i = (int)(block % n);
+    const int64_t rc = block / n;
+    const double *p = part + block * (64 * V) + lane;
+    double v[V] = {};
 #pragma unroll 4
-    for (int s = 0; s < nsplit; ++s, p += blocks * 256) {
+    for (int s = 0; s < nsplit; ++s, p += blocks * (64 * V)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] += p[64 * k];
+        for (int k = 0; k < V; ++k) v[k] += p[64 * k];
     }
-    const int rg = (int)(rc / g.cols), col = (int)(rc % g.cols), slot = 8 * t + 4 * h + (lane >> 4);
-    double2 vp = make_double2(v[0], v[1]), vm = make_double2(v[2], v[3]);
-    const int nan = W > 0 ? pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0;
+    const int rg = (int)(rc / g.cols), col = (int)(rc % g.cols);
+    const int slot = FEW ? 2 * i + (lane >> 4 & 1) : 4 * i + (lane >> 4), which = FEW ? 1 + (lane >> 5) : 3;
+    double2 vp = make_double2(v[0], v[1]), vm = make_double2(v[V - 2], v[V - 1]);
+    const int nan = W > 0 ? which & pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0;
     if (__builtin_expect(nan != 0, 0)) {
         double sth, cth;
         sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
         pblk::repair(g, src, 0, W, CH, rg, slot, lane & 15, sth, cth, nan, vp, vm);
     }
-    pblk::put_slot(amp, g, CH, rg, col, slot, lane & 15, vp, vm, accumulate != 0);
+    pblk::put_slot(amp, g, CH, rg, col, slot, lane & 15, vp, vm, accumulate != 0, which);
 }
 
 // ---------------------------------------------------------------------------
@@ -187,7 +206,17 @@ void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int 
     mt = (g.na * channels + 7) / 8;
 }
 
-static size_t polar_split_bytes(const PolGeom &g, int mt) { return (size_t)g.nrg * g.cols * mt * 512 * sizeof(double); }
+// The direct sums' tiles: of 4 x 16 (PolarPlan::mt <= 0) where a wave's slots fit two.
+static void direct_polar_geometry(const Detector &d, int channels, PolarPlan &p)
+{
+    polar_geometry(d, channels, p.shape, p.g, p.mt);
+    if (p.g.na * channels <= 4) p.mt = p.g.na * channels <= 2 ? 0 : -1;
+}
+
+static size_t polar_split_bytes(const PolGeom &g, int mt)
+{
+    return (size_t)g.nrg * g.cols * (mt > 0 ? mt * 512 : (1 - mt) * 128) * sizeof(double);
+}
 
 static void polar_splits(PolarPlan &p, int64_t W, int64_t target, size_t max_partial)
 {
@@ -202,9 +231,9 @@ static void polar_splits(PolarPlan &p, int64_t W, int64_t target, size_t max_par
     p.nsplit = (int)std::max<int64_t>(1, (W + per - 1) / per);
 }
 
-// Rounds of 512 workgroups (two per CU) times the cycles of one split (a matrix
-// instruction holds its SIMD's FP64 pipe 64 cycles, the tables of a chunk take about
-// 150 vector instructions of 4), plus the partial sums at about 1700 bytes a cycle.
+// Rounds of the workgroups that fit the chip times the cycles of one split (a matrix
+// instruction holds its SIMD's FP64 pipe 64 cycles, one of 4 x 16 20, the tables of a chunk
+// take about 150 vector instructions of 4), plus the partial sums at about 1700 bytes a cycle.
 static PolarPlan polar_default_plan(const Detector &d, int64_t W, int channels, size_t max_partial, int64_t target)
 {
     PolarPlan best{};
@@ -213,14 +242,16 @@ static PolarPlan polar_default_plan(const Detector &d, int64_t W, int channels, 
         PolarPlan p{};
         p.channels = channels;
         p.shape = default_polar_shape(d);
-        polar_geometry(d, channels, p.shape, p.g, p.mt);
+        direct_polar_geometry(d, channels, p);
         const int64_t blocks = (int64_t)((p.g.cols + pblk::kWaves - 1) / pblk::kWaves) * p.g.nrg;
-        polar_splits(p, W, target > 0 ? target : std::max<int64_t>(512 * rounds, blocks), max_partial);
+        const int per_cu = polar_per_cu(p.mt);
+        polar_splits(p, W, target > 0 ? target : std::max<int64_t>(256 * per_cu * rounds, blocks), max_partial);
         const double pts = (double)std::min<int64_t>(p.per, std::max<int64_t>(W, 1));
-        const double cycles = 2.0 * (3000.0 + std::ceil(pts / pblk::kChunk) * 700.0 +
-                                     std::ceil(pts / 4.0) * (128.0 * p.mt + 4.0 * p.mt + 40.0));
+        const double step = p.mt > 0 ? 132.0 * p.mt : 44.0 * (1 - p.mt);
+        const double cycles = per_cu * (3000.0 + std::ceil(pts / pblk::kChunk) * 700.0 +
+                                        std::ceil(pts / 4.0) * (step + 40.0));
         const double bytes = (double)polar_split_bytes(p.g, p.mt) * p.nsplit;
-        const double cost = std::ceil((double)(blocks * p.nsplit) / 512.0) * cycles +
+        const double cost = std::ceil((double)(blocks * p.nsplit) / (256.0 * per_cu)) * cycles +
                             (p.nsplit > 1 ? 8000.0 + 2.0 * bytes / 1700.0 : 0.0);
         if (best_cost < 0.0 || cost < 0.98 * best_cost) {
             best_cost = cost;
@@ -247,7 +278,7 @@ PolarPlan plan_direct_polar(const Detector &d, int64_t W, int channels, bool her
     PolarPlan p{};
     p.channels = channels;
     p.shape = ts.shape;
-    polar_geometry(d, channels, ts.shape, p.g, p.mt);
+    direct_polar_geometry(d, channels, p);
     polar_splits(p, W, ts.target, max_partial);
     return p;
 }
@@ -265,10 +296,12 @@ static void launch_polar_tiles(const Loader &ld, int64_t W, const PolarPlan &p, 
     // at most 16 row blocks: 2 CH tiles
 #define NUMAG_LAUNCH_POLAR(MT)   \
     case MT:                     \
-        if constexpr (MT <= 2 * CH) \
+        if constexpr (MT <= 2 * CH && (MT > 0 || CH <= 2 - 2 * MT)) \
             hipLaunchKernelGGL((direct_polar_kernel<MT, CH, NW, Loader>), grid, block, 0, s, ld, W, p.per, p.g, store, out); \
         break
     switch (p.mt) {
+        NUMAG_LAUNCH_POLAR(-1);
+        NUMAG_LAUNCH_POLAR(0);
         NUMAG_LAUNCH_POLAR(1);
         NUMAG_LAUNCH_POLAR(2);
         NUMAG_LAUNCH_POLAR(3);
@@ -287,9 +320,14 @@ static int combine_polar(const PolarPlan &p, const PointSource &src, int64_t W, 
 {
     NUMAG_HIP_CHECK(hipGetLastError());
     if (p.nsplit <= 1) return NUMAG_OK;
-    const int64_t n = (int64_t)p.g.nrg * p.g.cols * p.mt * 128;
-    hipLaunchKernelGGL(polar_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, partial, p.g, p.mt,
-                       p.channels, p.nsplit, src, W, accumulate, amp);
+    const int n = p.mt > 0 ? 2 * p.mt : 1 - p.mt;  // tile halves, or tiles of 4 x 16
+    const dim3 grid((unsigned)(((int64_t)p.g.nrg * p.g.cols * n * 64 + 255) / 256));
+    if (p.mt > 0)
+        hipLaunchKernelGGL((polar_combine_kernel<false>), grid, dim3(256), 0, s, partial, p.g, n, p.channels, p.nsplit,
+                           src, W, accumulate, amp);
+    else
+        hipLaunchKernelGGL((polar_combine_kernel<true>), grid, dim3(256), 0, s, partial, p.g, n, p.channels, p.nsplit,
+                           src, W, accumulate, amp);
     NUMAG_HIP_CHECK(hipGetLastError());
     return NUMAG_OK;
 }

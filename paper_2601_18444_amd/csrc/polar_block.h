@@ -37,15 +37,48 @@ constexpr int kChunk = 32;    // points per chunk of a wave
 constexpr int kRows = 32;     // q rows per block
 constexpr int kMaxNA = 16;    // row blocks per wave
 
-// Row blocks a wave of MT tiles holds.
+// Accumulators of a wave: MT tiles of 16 x 16 (eight slots, that is row blocks and channels,
+// each), or with MT <= 0 1 - MT tiles of 4 x 16 (two slots each), for detectors of so few rows
+// that the larger one would hold zeros: 16 x 16 takes 69 cycles of the SIMD's FP64 pipe, 4 x 16
+// 20.  (50,000 points, 8 x 181, one channel: 268 -> 169 us; four: 244 -> 210.)
+template <int MT>
+struct Tiles {
+    using T = v4d;
+    static constexpr int N = MT, kSlots = 8;
+};
+template <>
+struct Tiles<0> {
+    using T = double;
+    static constexpr int N = 1, kSlots = 2;
+};
+template <>
+struct Tiles<-1> {
+    using T = double;
+    static constexpr int N = 2, kSlots = 2;
+};
+__device__ __forceinline__ v4d mfma(double a, double b, v4d c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ double mfma(double a, double b, double c)
+{
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+// Row blocks a wave holds.
 template <int MT, int CH>
-constexpr int max_na() { return 8 * MT / CH < kMaxNA ? 8 * MT / CH : kMaxNA; }
+constexpr int max_na()
+{
+    constexpr int n = Tiles<MT>::kSlots * Tiles<MT>::N / CH;
+    return n < kMaxNA ? n : kMaxNA;
+}
 
 // NW weights per point: CH, or 2 CH for pairs of points at u and -u (accumulate below).
 template <int MT, int CH, int NW = CH>
 struct WaveSmem {
     double2 off[kChunk][17];
-    double2 ctr[kChunk][max_na<MT, CH>() + 1];
+    static constexpr int kCtr = max_na<MT, CH>() == 1 ? 1 : max_na<MT, CH>() + 1;
+    double2 ctr[kChunk][kCtr];
     double w[kChunk][NW + 1];
 };
 
@@ -137,19 +170,24 @@ __device__ __forceinline__ void generate(WaveSmem<MT, CH, NW> &sm, int a0, doubl
 // so RR and II, which make up the real parts, take the first, RI and IR the second.
 template <int MT, int CH, int NW, class Loader>
 __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64_t jend, double sth, double cth,
-                                           double dq, int a0, WaveSmem<MT, CH, NW> &sm, v4d (&accC)[MT],
-                                           v4d (&accS)[MT])
+                                           double dq, int a0, WaveSmem<MT, CH, NW> &sm,
+                                           typename Tiles<MT>::T (&accC)[Tiles<MT>::N],
+                                           typename Tiles<MT>::T (&accS)[Tiles<MT>::N])
 {
     const int lane = threadIdx.x & 63, gp = lane & 31;
     const int r16 = lane & 15, kq = lane >> 4;
     constexpr bool kPairs = NW != CH;
     static_assert(NW == CH || NW == 2 * CH, "one weight per channel, or two of a pair");
-    // this lane's matrix row: slot 8 t + 4 (r16 / 8) + r16 % 4, part (r16 / 4) % 2
-    const int part = (r16 >> 2) & 1;
-    int ea[MT], wc[MT];
+    constexpr int N = Tiles<MT>::N;
+    // this lane's matrix row: slot 8 t + 4 (r16 / 8) + r16 % 4, part (r16 / 4) % 2 of 16 rows;
+    // slot 2 t + r16 % 2, part (r16 / 2) % 2 of four
+    const int part = (r16 >> (MT > 0 ? 2 : 1)) & 1;
+    // weight of tile t: the same in every tile unless the slots of a tile are no multiple of CH
+    constexpr bool kEach = CH == 3 || (MT <= 0 && CH > 2);
+    int ea[N], wc[N];
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        const int s = 8 * t + 4 * (r16 >> 3) + (r16 & 3);
+    for (int t = 0; t < N; ++t) {
+        const int s = MT > 0 ? 8 * t + 4 * (r16 >> 3) + (r16 & 3) : 2 * t + (r16 & 1);
         ea[t] = min(s / CH, max_na<MT, CH>() - 1);
         wc[t] = s % CH;
     }
@@ -176,28 +214,28 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         const double *wp = &sm.w[kq][0];
         auto step = [&](int s) {
             const double2 z = op[s * 4 * 17];
-            const double *c = (const double *)(cp + s * 4 * (max_na<MT, CH>() + 1)) + part;
+            const double *c = (const double *)(cp + s * 4 * WaveSmem<MT, CH, NW>::kCtr) + part;
             const double *w = wp + s * 4 * (NW + 1);
-            double a[MT], b[kPairs ? MT : 1];
+            double a[N], b[kPairs ? N : 1];
             if (kPairs) {
 #pragma unroll
-                for (int t = 0; t < MT; ++t) {
+                for (int t = 0; t < N; ++t) {
                     const double y = c[2 * ea[t]];
-                    a[t] = y * w[2 * wc[CH == 3 ? t : 0] + part];
-                    b[t] = y * w[2 * wc[CH == 3 ? t : 0] + 1 - part];
+                    a[t] = y * w[2 * wc[kEach ? t : 0] + part];
+                    b[t] = y * w[2 * wc[kEach ? t : 0] + 1 - part];
                 }
-            } else if (CH == 3) {
+            } else if (kEach) {
 #pragma unroll
-                for (int t = 0; t < MT; ++t) a[t] = c[2 * ea[t]] * w[wc[t]];
+                for (int t = 0; t < N; ++t) a[t] = c[2 * ea[t]] * w[wc[t]];
             } else {
                 const double w0 = w[wc[0]];
 #pragma unroll
-                for (int t = 0; t < MT; ++t) a[t] = c[2 * ea[t]] * w0;
+                for (int t = 0; t < N; ++t) a[t] = c[2 * ea[t]] * w0;
             }
 #pragma unroll
-            for (int t = 0; t < MT; ++t) {
-                accC[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], z.x, accC[t], 0, 0, 0);
-                accS[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(kPairs ? b[t] : a[t], z.y, accS[t], 0, 0, 0);
+            for (int t = 0; t < N; ++t) {
+                accC[t] = mfma(a[t], z.x, accC[t]);
+                accS[t] = mfma(kPairs ? b[t] : a[t], z.y, accS[t]);
             }
         };
         int s = 0;
@@ -210,6 +248,14 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         for (; s < steps; ++s) step(s);
         wave_fence();
     }
+}
+
+// The sums of tile t of 4 x 16 in this lane: slot 2 t + (lane / 16) % 2, offset lane % 16, the
+// first row (lane < 32, which hold RR and RI) or the second (IR and II).
+__device__ __forceinline__ double2 few_rows(double c, double s)
+{
+    const double oc = other_half(c), os = other_half(s);
+    return (threadIdx.x & 32) == 0 ? make_double2(c - os, s + oc) : make_double2(oc + s, c - os);
 }
 
 // Rows of block a, offset b: 32 a + 16 + b (k = 0) and 32 a + 15 - b (k = 1).

@@ -135,3 +135,32 @@ def test_points_straight_from_the_sample(kind, n0, n1, W, chan):
     b, _ = numag.amplitudes(off, grid, rot=R)
     size = sum(np.abs(x).sum() for x in w.values() if x is not None)
     assert (a - b).abs().max().item() <= 2.0 ** -52 * (8 * 2 * 1.3 * 9 * 2 + 2 * W + 256) * size
+
+
+@pytest.mark.parametrize("n0", [1, 16, 17, 32, 33, 63, 64, 65, 96, 127, 128, 129])
+@pytest.mark.parametrize("chan", [0, 1, 2])
+def test_few_polar_rows(orc, n0, chan):
+    """Detectors whose slots (blocks of 32 q rows times channels) fill one or two tiles of
+    four rows, or just no longer: one point range and several, columns in pairs and not,
+    several row groups.  To the tolerance above comes the rounding of the rotated moments,
+    three products and two sums of |R| |m| on either side, which counts where they cancel."""
+    few = 1 if n0 <= 32 else 0
+    qmax, R = 1.3, synth.sample_rotation(33.0, 71.0)
+    for W, shape in [(1, None), (5, (few, 0)), (33, (0, 5)), (130, (few, 40)), (700, None)]:
+        for n1, path in ((4, numag.PATH_DIRECT), (9, numag.PATH_DIRECT), (10, numag.PATH_DIRECT_HERMITIAN)):
+            rng = np.random.default_rng(1000 * n0 + 10 * n1 + W + chan)
+            pos, nuc, mag = rng.uniform(-9, 9, (W, 3)), rng.standard_normal(W), rng.standard_normal((W, 3))
+            grid = numag.qgrid(1, n0, n1, qmax)
+            if shape is not None:
+                numag.tune_set(numag.TUNE_DIRECT, grid, W, shape, path=path)
+            s = numag.Sample(pos=pos, nuc=nuc if chan != 2 else None, mag=mag if chan != 1 else None, device=DEV)
+            amp, _ = numag.amplitudes(s, grid, rot=R, path=path)
+            qy, qz, _ = orc.pixels(1, n0, n1, qmax)
+            on, om = (nuc if chan != 2 else np.zeros(W)), (mag if chan != 1 else np.zeros((W, 3)))
+            ref = orc.amplitudes(pos, on, om, qy, qz, R=R)
+            w = np.concatenate([on[:, None], om @ R.T], axis=1)
+            m = np.concatenate([np.zeros((W, 1)), np.abs(om) @ np.abs(R).T], axis=1)
+            phase = 2 * qmax * np.abs(pos).sum(1).max()
+            tol = 2.0 ** -52 * ((4 * phase + W + 128) * np.abs(w).sum(0) + 3 * m.sum(0))
+            err = np.abs(amp_to_complex(amp[0]) - ref).max(0)
+            assert np.all(err <= tol), (W, n1, err, tol)
