@@ -500,7 +500,9 @@ static CartPlan cart_default_plan(const Detector &d, int64_t W, int channels, si
 
 double cart_default_cost(const Detector &d, int64_t W, int channels)
 {
-    return cart_cost(cart_default_plan(d, W, channels, 0), W);
+    const CartPlan p = cart_default_plan(d, W, channels, 0);
+    // (the combination adds the splits one after another, which counts for small detectors)
+    return cart_cost(p, W) + (p.nsplit > 1 ? 140.0 * p.nsplit : 0.0);
 }
 
 TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
