@@ -405,7 +405,8 @@ int numag_angular_spectrum(const numag_qgrid *grid, const double *f, int32_t n_f
  * class floor(2 log2 W), GPU architecture); a kernel without an entry uses the
  * library default.  With NUMAG_AUTOTUNE_CACHE naming a file, the table is read
  * from it on the first lookup and rewritten after every numag_autotune (one
- * text line per entry).
+ * text line per entry; a file that an earlier version of the library wrote is
+ * not read, since its labels stood for other workgroups).
  *   kernel    NUMAG_TUNE_DIRECT (direct sums; the detector kind selects the
  *             Cartesian or the polar kernel), NUMAG_TUNE_ADJOINT (the gradient's
  *             adjoint sums), NUMAG_TUNE_OBJECTS (the persistent object kernel of

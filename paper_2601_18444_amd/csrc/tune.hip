@@ -70,6 +70,12 @@ std::string cache_path()
     return e != nullptr ? std::string(e) : std::string();
 }
 
+// First line of the files this version writes.  Files that begin with an earlier version's
+// are not read: its labels and targets stood for other workgroups (polar shape 4: 256 rows
+// per workgroup, now 512 per wave).
+const char *const kHeader = "# numag launch shapes, version 2:";
+const char *const kOldHeader = "# numag launch shapes: ";
+
 // One entry per line: arch kernel kind n0 n1 wclass shape target ms default_ms
 void load_locked()
 {
@@ -81,6 +87,7 @@ void load_locked()
     if (f == nullptr) return;
     char line[512];
     while (fgets(line, sizeof line, f) != nullptr) {
+        if (strncmp(line, kOldHeader, strlen(kOldHeader)) == 0) break;
         if (line[0] == '#') continue;
         char arch[64], kname[32];
         int kind, n0, n1, wc, shape, target;
@@ -107,7 +114,7 @@ int save_locked()
         set_error("numag_autotune: cannot write " + tmp);
         return NUMAG_E_INVALID;
     }
-    fprintf(f, "# numag launch shapes: arch kernel kind n0 n1 wclass shape target ms default_ms\n");
+    fprintf(f, "%s arch kernel kind n0 n1 wclass shape target ms default_ms\n", kHeader);
     for (const auto &kv : g_table) {
         const Key &k = kv.first;
         const Entry &e = kv.second;

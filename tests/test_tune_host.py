@@ -80,3 +80,18 @@ def test_cache_file_is_read_on_first_lookup(tmp_path):
     out = subprocess.run([sys.executable, "-c", code, ROOT], env=env, capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stderr
     assert out.stdout.strip().endswith("(4, 1024), True)")
+
+
+@pytest.mark.parametrize("header,read", [("# numag launch shapes: arch kernel kind n0 n1 wclass shape target ms default_ms",
+                                          False),
+                                         ("# numag launch shapes, version 2: arch kernel kind", True)])
+def test_cache_file_of_an_earlier_version_is_not_read(tmp_path, header, read):
+    """The labels and targets of files without a version stood for other workgroups."""
+    path = tmp_path / "shapes.txt"
+    path.write_text(header + "\ngfx950 direct 1 1000 1000 42 4 1024 1.0 2.0\n")
+    code = ("import sys; sys.path.insert(0, sys.argv[1]); from paper_2601_18444_amd import numag; "
+            "print(numag.tune_get(numag.TUNE_DIRECT, numag.qgrid(1, 1000, 1000, 1.5), 2625870)[2])")
+    env = dict(os.environ, NUMAG_AUTOTUNE_CACHE=str(path))
+    out = subprocess.run([sys.executable, "-c", code, ROOT], env=env, capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.strip().endswith(str(read))
