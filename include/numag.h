@@ -419,16 +419,19 @@ int numag_angular_spectrum(const numag_qgrid *grid, const double *f, int32_t n_f
  *   target    workgroups a launch aims for (objects: work items); 0 = default.
  *   path      NUMAG_PATH_DIRECT or NUMAG_PATH_DIRECT_HERMITIAN (which part of
  *             the detector is evaluated).
- * numag_tune_get writes the default and the shape in use (either pointer may be
- * NULL) and returns 1 if the table holds an entry in use, 0 if the default is
+ * numag_tune_get writes the default (for four channels and a single object; it is
+ * the same on both paths) and the shape in use (either pointer may be NULL) and
+ * returns 1 if the table holds an entry in use, 0 if the default is
  * used, or a negative status.  numag_tune_set stores a shape (NULL removes the
  * entry; NUMAG_E_INVALID for a shape the kernel cannot take on this detector).
  * numag_autotune times the candidate shapes of `kernel` on the caller's sample
  * and detector (the direct and adjoint kernels on the first max_points points
  * as one object when max_points > 0; the object kernel on the first 64 of the
- * rotations, all objects), keeps the fastest in the table (the default unless
- * another is more than 1 % faster), writes it to *chosen_out (may be NULL) and
- * saves the cache file if one is named.  It allocates its own trial buffers,
+ * rotations, all objects), keeps the fastest in the table, writes it to
+ * *chosen_out (may be NULL) and saves the cache file if one is named.  The first
+ * candidate is the launch without an entry, which is planned for the sample's
+ * channels and objects; unless a shape is more than 1 % faster the table then says
+ * that the library's own plan is to be taken, and *chosen_out is the default.  It allocates its own trial buffers,
  * waits for the stream and cannot run under graph capture; call it when no
  * other call of this library is in flight (workspace sizes follow the table:
  * query them again after tuning).

@@ -370,7 +370,7 @@ double time_runs(F &&f, hipStream_t st, int reps)
     return best;
 }
 
-// Candidate shapes of a kernel on the evaluated detector d.
+// Candidate shapes of a kernel on the whole detector d, besides the untuned plan.
 std::vector<TuneShape> tune_candidates(int kernel, const Detector &d, int64_t W)
 {
     std::vector<TuneShape> c;
@@ -384,20 +384,16 @@ std::vector<TuneShape> tune_candidates(int kernel, const Detector &d, int64_t W)
     } else if (kernel == kTuneObjects && d.kind == NUMAG_GRID_POLAR) {
         for (int t : {2048, 4096, 8192, 16384}) c.push_back(TuneShape{def.shape, t});
     } else if (kernel == kTuneDirect || kernel == kTuneObjects) {
-        if (kernel == kTuneDirect) {
-            for (int l : {8, 64, 16, 32})
+        for (int l : {8, 64, 16, 32}) {
+            if (kernel == kTuneDirect)
                 for (int t : {256, 512, 768}) c.push_back(TuneShape{l, t});
-        } else {
-            for (int t : {512, 1024, 2048}) c.push_back(TuneShape{def.shape, t});
+            else
+                for (int t : {512, 1024, 2048}) c.push_back(TuneShape{l, t});
         }
     } else {
         for (int t : {256, 512, 1024, 2048}) c.push_back(TuneShape{0, t});
     }
-    // the default first (it is kept unless another shape is clearly faster)
-    std::vector<TuneShape> out{def};
-    for (const TuneShape &s : c)
-        if (s.shape != def.shape || s.target != def.target) out.push_back(s);
-    return out;
+    return c;
 }
 
 }  // namespace
@@ -810,12 +806,13 @@ int numag_tune_get(int32_t kernel, const numag_qgrid *grid, int32_t path, int64_
     if (path != NUMAG_PATH_DIRECT && path != NUMAG_PATH_DIRECT_HERMITIAN)
         return invalid("numag_tune_get: path must be NUMAG_PATH_DIRECT or NUMAG_PATH_DIRECT_HERMITIAN");
     if (n_points < 0) return invalid("numag_tune_get: n_points < 0");
-    const Detector d = evaluated_detector(make_detector(*grid), path);
-    const TuneShape def = default_tune_shape(kernel, d, n_points), cur = current_tune_shape(kernel, d, n_points);
+    const Detector whole = make_detector(*grid), d = evaluated_detector(whole, path);
+    const TuneShape def = default_tune_shape(kernel, whole, n_points);
+    const TuneShape cur = current_tune_shape(kernel, whole, d, n_points);
     if (default_out != nullptr) *default_out = numag_tune_shape{def.shape, def.target};
     if (current_out != nullptr) *current_out = numag_tune_shape{cur.shape, cur.target};
-    TuneShape t{};
-    return tuned_shape(kernel, d, n_points, &t) && valid_tune_shape(kernel, d, t) ? 1 : 0;
+    TuneEntry e{};
+    return tune_entry(kernel, d, n_points, &e) && (e.untuned || valid_tune_shape(kernel, d, e.shape)) ? 1 : 0;
 }
 
 int numag_tune_set(int32_t kernel, const numag_qgrid *grid, int32_t path, int64_t n_points,
@@ -835,7 +832,7 @@ int numag_tune_set(int32_t kernel, const numag_qgrid *grid, int32_t path, int64_
     }
     const TuneShape s{shape->shape, shape->target};
     if (!valid_tune_shape(kernel, d, s)) return invalid("numag_tune_set: shape not valid for this kernel and detector");
-    tune_store(kernel, d, n_points, s, 0.0, 0.0);
+    tune_store(kernel, d, n_points, TuneEntry{s, 0.0, 0.0, false});
     return NUMAG_OK;
 }
 
@@ -880,7 +877,10 @@ int numag_autotune(const numag_sample *sample, int64_t n_rot, const double *rot,
         if (max_points > 0 && max_points < W && ts.regular == nullptr) ts.n_points = max_points;
     }
     const int64_t n_rot_t = kernel == kTuneObjects ? std::min<int64_t>(n_rot, 64) : 1;
-    const std::vector<TuneShape> cands = tune_candidates(kernel, d, W);
+    // the first candidate is the plan without an entry, which is kept unless a shape is clearly
+    // faster: it is chosen for the sample's channels and objects, a shape for any
+    std::vector<TuneEntry> cands{TuneEntry{default_tune_shape(kernel, dfull, W), 0.0, 0.0, true}};
+    for (const TuneShape &s : tune_candidates(kernel, dfull, W)) cands.push_back(TuneEntry{s, 0.0, 0.0, false});
     // buffers: outputs, and a workspace large enough for every candidate
     DeviceBuffers mem;
     double *amp = (double *)mem.get((size_t)P * 8 * sizeof(double));
@@ -908,15 +908,15 @@ int numag_autotune(const numag_sample *sample, int64_t n_rot, const double *rot,
     // the result is stored under the sample's W.  An entry already held under Wt
     // is put back afterwards (or if tuning fails).
     const int64_t Wt = ts.n_points;
-    TuneShape prev{};
-    const bool had_prev = tuned_shape(kernel, d, Wt, &prev);
+    TuneEntry prev{};
+    const bool had_prev = tune_entry(kernel, d, Wt, &prev);
     auto restore = [&]() {
-        if (had_prev) tune_store(kernel, d, Wt, prev, 0.0, 0.0);
+        if (had_prev) tune_store(kernel, d, Wt, prev);
         else tune_erase(kernel, d, Wt);
     };
     size_t ws_need = 0;
-    for (const TuneShape &c : cands) {
-        tune_store(kernel, d, Wt, c, 0.0, 0.0);
+    for (const TuneEntry &c : cands) {
+        tune_store(kernel, d, Wt, c);
         size_t need = 0;
         if (kernel == kTuneObjects) {
             need = make_plan(sample, n_rot_t, nullptr, dfull, path, NUMAG_MODE_DILUTE, 1)->ws_bytes;
@@ -942,10 +942,10 @@ int numag_autotune(const numag_sample *sample, int64_t n_rot, const double *rot,
         }
     }
     double best_ms = -1.0, default_ms = -1.0;
-    TuneShape best = cands[0];
+    TuneEntry best = cands[0];
     for (size_t i = 0; i < cands.size(); ++i) {
-        const TuneShape &c = cands[i];
-        tune_store(kernel, d, Wt, c, 0.0, 0.0);
+        const TuneEntry &c = cands[i];
+        tune_store(kernel, d, Wt, c);
         std::unique_ptr<ObjPlan> pl;
         if (kernel == kTuneObjects) {
             pl = make_plan(sample, n_rot_t, rot, dfull, path, NUMAG_MODE_DILUTE, 1);
@@ -1000,14 +1000,16 @@ int numag_autotune(const numag_sample *sample, int64_t n_rot, const double *rot,
             best = c;
         }
     }
-    // keep the default unless another shape is faster by more than 1 %
+    // keep the untuned plan unless a shape is faster by more than 1 %
     if (best_ms > 0.99 * default_ms) {
         best = cands[0];
         best_ms = default_ms;
     }
     if (Wt != W) restore();
-    tune_store(kernel, d, W, best, best_ms, default_ms);
-    if (chosen_out != nullptr) *chosen_out = numag_tune_shape{best.shape, best.target};
+    best.ms = best_ms;
+    best.default_ms = default_ms;
+    tune_store(kernel, d, W, best);
+    if (chosen_out != nullptr) *chosen_out = numag_tune_shape{best.shape.shape, best.shape.target};
     return tune_save();
 }
 

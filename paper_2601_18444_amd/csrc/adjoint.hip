@@ -557,7 +557,7 @@ static GradPlan grad_plan(const Detector &d, int64_t W, bool hermitian, bool use
     };
     TuneShape ts{};
     int64_t target = env_target() > 0 ? 2 * (int64_t)env_target() : 0;
-    if (use_table && tuned_shape(kTuneAdjoint, key, W, &ts) && valid_tune_shape(kTuneAdjoint, key, ts) && ts.target > 0)
+    if (use_table && tuned_shape(kTuneAdjoint, key, W, &ts) && ts.target > 0)
         target = ts.target;
     if (target > 0) {
         set((target + p.pblocks - 1) / p.pblocks);

@@ -536,10 +536,10 @@ TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W)
     }
 }
 
-TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W)
+TuneShape current_tune_shape(int kernel, const Detector &d, const Detector &key, int64_t W)
 {
     TuneShape s{};
-    if (tuned_shape(kernel, d, W, &s) && valid_tune_shape(kernel, d, s)) {
+    if (tuned_shape(kernel, key, W, &s)) {
         if (s.target == 0) s.target = default_tune_shape(kernel, d, W).target;
         return s;
     }
@@ -551,9 +551,8 @@ CartPlan plan_direct_cartesian(const Detector &d, int64_t W, int channels, bool 
     Detector key = d;
     if (hermitian) key.n0 = (d.n0 + 1) / 2;
     TuneShape ts{};
-    if (!tuned_shape(kTuneDirect, key, W, &ts) || !valid_tune_shape(kTuneDirect, key, ts))
-        return cart_default_plan(d, W, channels, max_partial);
-    if (ts.target == 0) ts.target = default_tune_shape(kTuneDirect, key, W).target;
+    if (!tuned_shape(kTuneDirect, key, W, &ts)) return cart_default_plan(d, W, channels, max_partial);
+    if (ts.target == 0) ts.target = default_tune_shape(kTuneDirect, d, W).target;
     return cheapest_plan(d, W, channels, max_partial, {ts.shape}, ts.target);
 }
 

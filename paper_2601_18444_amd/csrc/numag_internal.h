@@ -92,17 +92,29 @@ struct TuneShape {
     int shape;   // Cartesian: column blocks (cart_nz); polar: row blocks per wave; adjoint: 0
     int target;  // workgroups (objects: work items) a launch aims for
 };
+// An entry: a launch shape, or (untuned) the autotuner's finding that the library's own plan,
+// which also knows the sample's channels and objects, is the fastest; `shape` then only names
+// the default.
+struct TuneEntry {
+    TuneShape shape;
+    double ms, default_ms;  // measured by numag_autotune (0 when set directly or unknown)
+    bool untuned;
+};
 int tune_wclass(int64_t W);
+bool tune_entry(int kernel, const Detector &d, int64_t W, TuneEntry *out);
+// The shape a plan has to take: false without a valid one in the table.
 bool tuned_shape(int kernel, const Detector &d, int64_t W, TuneShape *out);
-void tune_store(int kernel, const Detector &d, int64_t W, const TuneShape &s, double ms, double default_ms);
+void tune_store(int kernel, const Detector &d, int64_t W, const TuneEntry &e);
 void tune_erase(int kernel, const Detector &d, int64_t W);
 int tune_save();
 void tune_clear();
 bool valid_tune_shape(int kernel, const Detector &d, const TuneShape &s);
-// The library's untuned shape for a kernel on detector d (evaluated part) and W points.
+// The library's untuned shape for a kernel on the whole detector d and W points (four
+// channels; the objects are not known).
 TuneShape default_tune_shape(int kernel, const Detector &d, int64_t W);
-// The shape in use: the tuned one if the table holds it, else the default.
-TuneShape current_tune_shape(int kernel, const Detector &d, int64_t W);
+// The shape in use: the tuned one if the table holds it under `key` (the evaluated part), else
+// the default.
+TuneShape current_tune_shape(int kernel, const Detector &d, const Detector &key, int64_t W);
 // Plan of a Cartesian sum on the whole detector d.  The launch shape is looked up
 // under the part of the detector that the caller's path stands for (hermitian: the
 // first ceil(n0 / 2) rows); either way every pixel is written, the mirrored ones as

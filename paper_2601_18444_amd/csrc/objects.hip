@@ -603,9 +603,9 @@ Tables make_tables(const Detector &d, bool hermitian, const std::vector<int64_t>
     Tables T;
     ObjectsPlan &p = T.p;
     const Detector key = objects_detector(d, hermitian);
-    const TuneShape ts = current_tune_shape(kTuneObjects, key, W);
+    const TuneShape ts = current_tune_shape(kTuneObjects, d, key, W);
     TuneShape entry{};
-    const bool tuned = tuned_shape(kTuneObjects, key, W, &entry) && valid_tune_shape(kTuneObjects, key, entry);
+    const bool tuned = tuned_shape(kTuneObjects, key, W, &entry);
     if (d.kind == NUMAG_GRID_POLAR) {
         polar_geometry(d, 4, ts.shape, p.pg, p.mt);
         p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;

@@ -272,7 +272,7 @@ PolarPlan plan_direct_polar(const Detector &d, int64_t W, int channels, bool her
     Detector key = d;
     if (hermitian) key.n1 = d.n1 / 2;
     TuneShape ts{};
-    if (!tuned_shape(kTuneDirect, key, W, &ts) || !valid_tune_shape(kTuneDirect, key, ts))
+    if (!tuned_shape(kTuneDirect, key, W, &ts))
         return polar_default_plan(d, W, channels, max_partial, env_target());
     if (ts.target == 0) ts.target = default_polar_tune(d, W).target;
     PolarPlan p{};

@@ -40,13 +40,8 @@ struct Key {
     }
 };
 
-struct Entry {
-    TuneShape shape;
-    double ms, default_ms;  // measured by numag_autotune (0 when set directly or unknown)
-};
-
 std::mutex g_mu;
-std::map<Key, Entry> g_table;
+std::map<Key, TuneEntry> g_table;
 bool g_loaded = false;
 
 const char *kKernelNames[kTuneKernelCount] = {"direct", "adjoint", "objects"};
@@ -76,7 +71,7 @@ std::string cache_path()
 const char *const kHeader = "# numag launch shapes, version 2:";
 const char *const kOldHeader = "# numag launch shapes: ";
 
-// One entry per line: arch kernel kind n0 n1 wclass shape target ms default_ms
+// One entry per line: arch kernel kind n0 n1 wclass shape target ms default_ms [untuned]
 void load_locked()
 {
     if (g_loaded) return;
@@ -90,16 +85,16 @@ void load_locked()
         if (strncmp(line, kOldHeader, strlen(kOldHeader)) == 0) break;
         if (line[0] == '#') continue;
         char arch[64], kname[32];
-        int kind, n0, n1, wc, shape, target;
+        int kind, n0, n1, wc, shape, target, untuned = 0;
         double ms, dms;
-        if (sscanf(line, "%63s %31s %d %d %d %d %d %d %lf %lf", arch, kname, &kind, &n0, &n1, &wc, &shape, &target,
-                   &ms, &dms) != 10)
+        if (sscanf(line, "%63s %31s %d %d %d %d %d %d %lf %lf %d", arch, kname, &kind, &n0, &n1, &wc, &shape, &target,
+                   &ms, &dms, &untuned) < 10)
             continue;
         int kernel = -1;
         for (int k = 0; k < kTuneKernelCount; ++k)
             if (strcmp(kname, kKernelNames[k]) == 0) kernel = k;
         if (kernel < 0) continue;
-        g_table[Key{arch, kernel, kind, n0, n1, wc}] = Entry{TuneShape{shape, target}, ms, dms};
+        g_table[Key{arch, kernel, kind, n0, n1, wc}] = TuneEntry{TuneShape{shape, target}, ms, dms, untuned != 0};
     }
     fclose(f);
 }
@@ -114,12 +109,12 @@ int save_locked()
         set_error("numag_autotune: cannot write " + tmp);
         return NUMAG_E_INVALID;
     }
-    fprintf(f, "%s arch kernel kind n0 n1 wclass shape target ms default_ms\n", kHeader);
+    fprintf(f, "%s arch kernel kind n0 n1 wclass shape target ms default_ms untuned\n", kHeader);
     for (const auto &kv : g_table) {
         const Key &k = kv.first;
-        const Entry &e = kv.second;
-        fprintf(f, "%s %s %d %d %d %d %d %d %.6f %.6f\n", k.arch.c_str(), kKernelNames[k.kernel], k.kind, k.n0, k.n1,
-                k.wclass, e.shape.shape, e.shape.target, e.ms, e.default_ms);
+        const TuneEntry &e = kv.second;
+        fprintf(f, "%s %s %d %d %d %d %d %d %.6f %.6f %d\n", k.arch.c_str(), kKernelNames[k.kernel], k.kind, k.n0, k.n1,
+                k.wclass, e.shape.shape, e.shape.target, e.ms, e.default_ms, e.untuned ? 1 : 0);
     }
     fclose(f);
     if (rename(tmp.c_str(), path.c_str()) != 0) {
@@ -142,21 +137,29 @@ int tune_wclass(int64_t W)
     return (int)std::floor(2.0 * std::log2((double)W));  // half-octaves
 }
 
-bool tuned_shape(int kernel, const Detector &d, int64_t W, TuneShape *out)
+bool tune_entry(int kernel, const Detector &d, int64_t W, TuneEntry *out)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     load_locked();
     const auto it = g_table.find(make_key(kernel, d, W));
     if (it == g_table.end()) return false;
-    *out = it->second.shape;
+    *out = it->second;
     return true;
 }
 
-void tune_store(int kernel, const Detector &d, int64_t W, const TuneShape &s, double ms, double default_ms)
+bool tuned_shape(int kernel, const Detector &d, int64_t W, TuneShape *out)
+{
+    TuneEntry e{};
+    if (!tune_entry(kernel, d, W, &e) || e.untuned || !valid_tune_shape(kernel, d, e.shape)) return false;
+    *out = e.shape;
+    return true;
+}
+
+void tune_store(int kernel, const Detector &d, int64_t W, const TuneEntry &e)
 {
     std::lock_guard<std::mutex> lk(g_mu);
     load_locked();
-    g_table[make_key(kernel, d, W)] = Entry{s, ms, default_ms};
+    g_table[make_key(kernel, d, W)] = e;
 }
 
 void tune_erase(int kernel, const Detector &d, int64_t W)

@@ -233,3 +233,39 @@ def test_random_pinned_shapes_size_their_workspaces(orc, case):
             sl = slice(off[k], off[k + 1])
             Fs = [orc.amplitudes(pos[sl], nuc[sl], mag[sl], qy, qz, R=Rr) for Rr in R]
             assert max_norm_err(spec[k], orc.spectral(np.stack(Fs)) / len(R)) <= 1e-9, (path, k)
+
+
+def _shortest_ms(f, n=10):
+    best = float("inf")
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("per_object,kind,n0,n1", [(4000, 0, 200, 100), (300, 1, 40, 64)])
+def test_tuned_objects_are_no_slower_than_the_untuned_plan(per_object, kind, n0, n1):
+    """The untuned plan weighs how the objects' items fill the chip; a tuned call takes at most
+    1 % longer by the tuner's own clock, here within a factor that covers a call's noise."""
+    K = 4
+    rng = np.random.default_rng(97)
+    off = (np.arange(K + 1) * per_object).astype(np.int64)
+    W = int(off[-1])
+    s = numag.Sample(pos=rng.uniform(-7, 7, (W, 3)), nuc=rng.standard_normal(W), mag=rng.standard_normal((W, 3)),
+                     obj_offsets=off, device=DEV)
+    grid = numag.qgrid(kind, n0, n1, 1.0)
+
+    def planned():
+        plan = numag.Plan(s, grid, mode=numag.MODE_DILUTE, spec_per_object=True)
+        plan.upload()
+        spec = torch.empty((K, n0 * n1, 16), dtype=torch.float64, device=DEV)
+        return _shortest_ms(lambda: plan(spec_out=spec))
+
+    before = planned()
+    numag.autotune(s, grid, numag.TUNE_OBJECTS)
+    after = planned()
+    assert after <= 1.5 * before, (before, after)

@@ -95,3 +95,26 @@ def test_cache_file_of_an_earlier_version_is_not_read(tmp_path, header, read):
     out = subprocess.run([sys.executable, "-c", code, ROOT], env=env, capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stderr
     assert out.stdout.strip().endswith(str(read))
+
+
+def test_default_is_that_of_the_launch_on_both_paths():
+    """Both direct paths launch the same kernels on the whole detector."""
+    for kernel in (numag.TUNE_DIRECT, numag.TUNE_ADJOINT, numag.TUNE_OBJECTS):
+        for kind, n0, n1 in [(0, 256, 256), (0, 201, 333), (0, 48, 81), (0, 20, 500), (1, 256, 360), (1, 40, 128)]:
+            for W in (500, 20000, 262144):
+                grid = numag.qgrid(kind, n0, n1, 1.0)
+                direct, half = (numag.tune_get(kernel, grid, W, path=p)[0]
+                                for p in (numag.PATH_DIRECT, numag.PATH_DIRECT_HERMITIAN))
+                assert direct == half, (kernel, kind, n0, n1, W)
+
+
+def test_entry_for_the_untuned_plan_is_read(tmp_path):
+    """An entry that names the library's own plan counts as tuned and reports the default."""
+    path = tmp_path / "shapes.txt"
+    path.write_text("# numag launch shapes, version 2:\ngfx950 direct 1 1000 1000 42 2 77 1.0 1.0 1\n")
+    code = ("import sys; sys.path.insert(0, sys.argv[1]); from paper_2601_18444_amd import numag; "
+            "d, c, t = numag.tune_get(numag.TUNE_DIRECT, numag.qgrid(1, 1000, 1000, 1.5), 2625870); print(t and d == c)")
+    env = dict(os.environ, NUMAG_AUTOTUNE_CACHE=str(path))
+    out = subprocess.run([sys.executable, "-c", code, ROOT], env=env, capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stderr
+    assert out.stdout.strip().endswith("True")
