@@ -31,7 +31,8 @@ __device__ __forceinline__ void wave_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-// sin x and cos x in FP64 for the sum kernels' generation phases.
+// sin x and cos x in FP64 for single angles and phases (the separable tables, column angles,
+// object phases; the sum kernels' tables take phasor_fast below).
 // Cody-Waite reduction (Cody & Waite, Software Manual for the Elementary
 // Functions, 1980): x = k pi/2 + r with pi/2 split into P1 + P2 + P3, P1 and P2
 // holding 33 significant bits each, so k P1 and k P2 are exact for |k| < 2^20,
