@@ -210,10 +210,10 @@ int numag_amplitudes(const numag_sample *sample, int64_t n_rot, const double *ro
  *   Scratch: the point records and split partial sums live in one static device
  *   array of NUMAG_NOALLOC_SCRATCH_BYTES that the library holds on every device
  *   it runs on until the process ends; its device address is looked up on the
- *   first call on a device.  Points go through in chunks, so any W fits; the
- *   partial sums of the evaluated pixels (64 bytes each: the whole detector, or
- *   the half that the Hermitian path sums) must fit in half of the array, at
- *   most 1,048,576 evaluated pixels, else NUMAG_E_UNSUPPORTED with a message.
+ *   first call on a device.  Points go through in chunks, so any W fits.  The
+ *   call takes detectors of at most 1,048,576 evaluated pixels (the whole
+ *   detector, or the half that the Hermitian path stands for; 64 bytes each are
+ *   half of the array), else NUMAG_E_UNSUPPORTED with a message.
  *   Calls on one device share the array: calls that may overlap in time on one
  *   device (streams not ordered with each other, or other host threads) race
  *   and give wrong results; calls ordered on one stream are safe.  Nothing in

@@ -23,7 +23,11 @@ namespace numag {
 namespace {
 
 constexpr size_t kCap = NUMAG_NOALLOC_SCRATCH_BYTES;
-constexpr size_t kPixelBytes = 8 * sizeof(double);  // one pixel of partial sums
+// The call takes detectors of which one set of sums fits half of the array.  (Sums that are not
+// split over points need no scratch, so this is the call's stated limit, not a need of the
+// kernels.)
+constexpr size_t kPixelBytes = 8 * sizeof(double);
+constexpr size_t kMaxPixels = kCap / 2 / kPixelBytes;
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -68,8 +72,8 @@ int stream_device(hipStream_t st, int *dev)
     return NUMAG_OK;
 }
 
-// Pixels whose partial sums one launch writes: the whole detector, or the half
-// that the Hermitian path evaluates.
+// The part of the detector that counts against that limit: the whole of it, or the half that
+// the Hermitian path stands for.
 Detector evaluated(const Detector &d, bool hermitian)
 {
     Detector dh = d;
@@ -142,12 +146,12 @@ extern "C" int numag_amplitudes_noalloc(const numag_sample *sample, int64_t n_ro
     const Detector d = make_detector(*grid);
     const bool hermitian = path == NUMAG_PATH_DIRECT_HERMITIAN;
     const Detector dh = evaluated(d, hermitian);
-    const size_t need = (size_t)dh.n0 * (size_t)dh.n1 * kPixelBytes;
-    if (need > kCap / 2) {
-        set_error("numag_amplitudes_noalloc: the detector's partial sums need " + std::to_string(need) +
-                  " bytes, more than half of the " + std::to_string(kCap) +
-                  "-byte static scratch (at most " + std::to_string(kCap / 2 / kPixelBytes) +
-                  " evaluated pixels); use numag_amplitudes with a workspace");
+    const size_t pixels = (size_t)dh.n0 * (size_t)dh.n1;
+    if (pixels > kMaxPixels) {
+        set_error("numag_amplitudes_noalloc: takes detectors of at most " + std::to_string(kMaxPixels) +
+                  " evaluated pixels (64 bytes each in half of the " + std::to_string(kCap) +
+                  "-byte static scratch), not " + std::to_string(pixels) +
+                  "; use numag_amplitudes with a workspace");
         return NUMAG_E_UNSUPPORTED;
     }
     hipStream_t st = (hipStream_t)stream;
