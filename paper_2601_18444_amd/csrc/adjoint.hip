@@ -324,6 +324,11 @@ __device__ __forceinline__ double lane_value(double v, int k)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// MT tiles of 16 coefficient rows, two row blocks each; MT = 0: one block of rows, whose eight
+// coefficient rows are two tiles of 4 x 16 (a third of the cycles of a tile of 16 that they
+// would half fill, and registers and LDS for twice the waves).  20,000 points, adjoint sums with
+// their residuals, tiles of 16 and now: 16 x 361 212 -> 133 us (134 by walking the rows), 32 x 181
+// 113 -> 80 (122), 8 x 180 70 -> 57 (101).
 template <int MT>
 struct PolWaveTables {
     double2 off[32][17];
@@ -331,12 +336,14 @@ struct PolWaveTables {
 };
 
 template <int MT>
-__global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
+__global__ __launch_bounds__(kPolThreads, MT == 0 ? 4 : 2) void adjoint_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
                                                                        PolGeom g, int cols_per_split,
                                                                        const double2 *__restrict__ coef,
                                                                        double *__restrict__ gpart)
 {
-    constexpr int kStage = 4 * MT * 64;
+    constexpr bool kOne = MT == 0;
+    constexpr int NT = kOne ? 2 : MT;
+    constexpr int kStage = 4 * (kOne ? 1 : MT) * 64;
     __shared__ PolWaveTables<MT> s_t[kPolWaves];
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
     const int pt = lane & 15, kq = lane >> 4;
@@ -350,12 +357,14 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
 #pragma unroll
     for (int u = 0; u < kPolNP; ++u) G[u] = 0.0;
 
-    const double2 *src = coef + (int64_t)c0 * g.nrg * kStage + lane;
-    const double2 *last = coef + ((int64_t)c1 * g.nrg - 1) * kStage + lane;
-    double2 co[4][MT];  // coefficients of a block, loaded one block ahead of their use
+    // (kOne: tile t holds part t of the four channels, coef_index)
+    const int at = kOne ? 16 * kq + (pt & 3) : lane;
+    const double2 *src = coef + (int64_t)c0 * g.nrg * kStage + at;
+    const double2 *last = coef + ((int64_t)c1 * g.nrg - 1) * kStage + at;
+    double2 co[4][NT];  // coefficients of a block, loaded one block ahead of their use
     auto load = [&](const double2 *from) {
 #pragma unroll
-        for (int k = 0; k < 4 * MT; ++k) co[k / MT][k % MT] = from[64 * k];
+        for (int k = 0; k < 4 * NT; ++k) co[k / NT][k % NT] = from[kOne ? 64 * (k / NT) + 4 * (k % NT) : 64 * k];
     };
     if (c0 < c1) load(src);
     double2 dir = make_double2(0.0, 0.0);  // (sin, cos) of the angles of 64 columns, one per lane
@@ -375,43 +384,43 @@ __global__ __launch_bounds__(kPolThreads, 2) void adjoint_polar_kernel(const Poi
         }
 #pragma unroll 1
         for (int rg = 0; rg < g.nrg; ++rg) {
-            if (half != 0) pblk::centres<2 * MT>(tab.ctr[gp], first, step);
+            if (half != 0) pblk::centres<kOne ? 1 : 2 * MT>(tab.ctr[gp], first, step);
             if (g.nrg > 1) first = cmul(first, adv);
             wave_fence();
             __builtin_amdgcn_s_setprio(0);
-            cblk::v4d acc[MT][kPolNP];
-#pragma unroll
-            for (int t = 0; t < MT; ++t)
-#pragma unroll
-                for (int u = 0; u < kPolNP; ++u) acc[t][u] = cblk::v4d{0.0, 0.0, 0.0, 0.0};
+            typename pblk::Tiles<MT>::T acc[NT][kPolNP] = {};
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 double2 z[kPolNP];
 #pragma unroll
                 for (int u = 0; u < kPolNP; ++u) z[u] = tab.off[16 * u + pt][4 * s + kq];
 #pragma unroll
-                for (int t = 0; t < MT; ++t) {
+                for (int t = 0; t < NT; ++t) {
                     const double2 a = co[s][t];
 #pragma unroll
-                    for (int u = 0; u < kPolNP; ++u)
-                        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, z[u].x, acc[t][u], 0, 0, 0);
+                    for (int u = 0; u < kPolNP; ++u) acc[t][u] = pblk::mfma(a.x, z[u].x, acc[t][u]);
 #pragma unroll
-                    for (int u = 0; u < kPolNP; ++u)
-                        acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, z[u].y, acc[t][u], 0, 0, 0);
+                    for (int u = 0; u < kPolNP; ++u) acc[t][u] = pblk::mfma(a.y, z[u].y, acc[t][u]);
                 }
             }
             src += kStage;
             load(src < last ? src : last);  // (the last block again at the end, unused)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < kPolNP; ++u)
+            for (int u = 0; u < kPolNP; ++u) {
+                if constexpr (kOne) {
+                    const double2 y = tab.ctr[16 * u + pt][0];
+                    G[u] = fma(y.x, acc[0][u], fma(y.y, acc[1][u], G[u]));
+                } else {
 #pragma unroll
-                for (int t = 0; t < MT; ++t)
+                    for (int t = 0; t < MT; ++t)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const double2 y = tab.ctr[16 * u + pt][2 * t + h];
-                        G[u] = fma(y.x, acc[t][u][2 * h], fma(y.y, acc[t][u][2 * h + 1], G[u]));
-                    }
+                        for (int h = 0; h < 2; ++h) {
+                            const double2 y = tab.ctr[16 * u + pt][2 * t + h];
+                            G[u] = fma(y.x, acc[t][u][2 * h], fma(y.y, acc[t][u][2 * h + 1], G[u]));
+                        }
+                }
+            }
             wave_fence();
         }
     }
@@ -502,7 +511,8 @@ struct GradPlan {
 };
 
 // Ranges the detector is split into, so that point blocks x ranges fill the chip (one
-// workgroup per CU at a time): of the counts up to four rounds of 256 workgroups, the one
+// workgroup per CU at a time; two on a polar detector of one row block): of the counts up to
+// four rounds of these workgroups, the one
 // with the fewest coefficient blocks on the busiest CU; a split costs the point's
 // phasors and partial gradients, about one block's time.  A table entry's target sets
 // the workgroups instead.
@@ -565,11 +575,12 @@ static GradPlan grad_plan(const Detector &d, int64_t W, bool hermitian, bool use
     }
     int64_t best = 1;
     double best_cost = -1.0;
+    const int64_t fit = !cart && p.pg.na == 1 ? 512 : 256;
     for (int r = 0; r <= 8; ++r) {  // half rounds
-        const int64_t want = std::max<int64_t>(1, 128 * r / p.pblocks);
+        const int64_t want = std::max<int64_t>(1, fit / 2 * r / p.pblocks);
         set(want);
         const double per = cart ? (double)p.sp.per_r * p.sp.per_v + 0.2 * p.sp.per_r : (double)p.cols_per * p.pg.nrg;
-        const double rounds = std::ceil((double)(p.pblocks * p.nsplit) / 256.0);
+        const double rounds = std::ceil((double)(p.pblocks * p.nsplit) / (double)fit);
         const double cost = rounds * (per + 0.5) + 2e-6 * (double)p.nsplit * (double)W;
         if (best_cost < 0.0 || cost < 0.99 * best_cost) {
             best_cost = cost;
@@ -655,7 +666,8 @@ int launch_grad(const PointRec *pts, int64_t W, const Detector &d, const numag_c
                 NUMAG_LAUNCH_ADJ_C(8);
             }
         } else {
-            switch (p.mt) {
+            switch (p.pg.na == 1 ? 0 : p.mt) {
+                NUMAG_LAUNCH_ADJ_P(0);
                 NUMAG_LAUNCH_ADJ_P(1);
                 NUMAG_LAUNCH_ADJ_P(2);
                 NUMAG_LAUNCH_ADJ_P(3);

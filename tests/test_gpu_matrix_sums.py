@@ -164,3 +164,32 @@ def test_few_polar_rows(orc, n0, chan):
             tol = 2.0 ** -52 * ((4 * phase + W + 128) * np.abs(w).sum(0) + 3 * m.sum(0))
             err = np.abs(amp_to_complex(amp[0]) - ref).max(0)
             assert np.all(err <= tol), (W, n1, err, tol)
+
+
+@pytest.mark.parametrize("n0", [1, 2, 15, 16, 17, 31, 32, 33, 64, 65])
+@pytest.mark.parametrize("n1", [1, 2, 9, 12])
+def test_gradient_of_few_polar_rows(orc, n0, n1):
+    """One block of 32 q rows (tiles of four coefficient rows) and just more, columns in pairs
+    and not, point counts around the 32 of a wave, several ranges of columns.  With S the sum
+    of the weights' moduli, |F| <= S and I <= (1 + b^2) S^2; the gradient is a sum over pixels
+    of 4 w (I - T) F times phasors, each factor within 2^-52 (4 phase + W + P + 128) of such a
+    bound; four factors count."""
+    qmax, bH, R = 1.3, 0.7, synth.sample_rotation(33.0, 71.0)
+    grid, P = numag.qgrid(1, n0, n1, qmax), n0 * n1
+    qy, qz, qhat = orc.pixels(1, n0, n1, qmax)
+    for W, target in [(1, 0), (31, 3), (33, 0), (300, 40)]:
+        rng = np.random.default_rng(1000 * n0 + 10 * n1 + W)
+        pos, nuc, mag = rng.uniform(-9, 9, (W, 3)), rng.standard_normal(W), rng.standard_normal((W, 3))
+        T, w = rng.uniform(0.0, 1.0, P), rng.uniform(0.5, 1.5, P)
+        L, dn, dm = orc.loss_grad(pos, nuc, mag, qy, qz, qhat, T, w, bH=bH, R=R)
+        s = numag.Sample(pos=pos, nuc=nuc, mag=mag, device=DEV)
+        if target:
+            numag.tune_set(numag.TUNE_ADJOINT, grid, W, (0, target))
+        loss, gn, gm = numag.grad(s, grid, numag.consts(bH=bH), weight=torch.as_tensor(w, device=DEV),
+                                  target=torch.as_tensor(T, device=DEV), rot=R)
+        S = np.abs(nuc).sum() + np.abs(mag).sum()
+        phase = 2 * qmax * np.abs(pos).sum(1).max()
+        tol = 4 * 2.0 ** -52 * (4 * phase + W + P + 128) * (4 * w * ((1 + bH ** 2) * S ** 2 + T) * S).sum()
+        assert np.abs(gn.cpu().numpy() - dn).max() <= tol and np.abs(gm.cpu().numpy() - dm).max() <= tol
+        assert np.abs(dn).max() > 1e4 * tol  # the bound says something
+        assert abs(loss.item() - L) <= 1e-9 * abs(L)
