@@ -131,12 +131,19 @@ def kernel_timer_read(kernel: int):
     return ms.value, n.value
 
 
+def _stream_of_object(index: int) -> int:
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# (Raw: a torch.cuda.Stream object per call takes 2.9 us, this 0.3, of the 3 to 10 us a small
+# call has.  The name is not part of torch's documented interface, hence the fallback.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_of_object)
+
+
 def _stream(device=None) -> int:
-    """Handle of the current stream of `device` (default: the current device).  (Raw: a
-    torch.cuda.Stream object per call takes 2.9 us, this 0.3, of the 3 to 10 us a small call
-    has.)"""
+    """Handle of the current stream of `device` (default: the current device)."""
     index = None if device is None else device.index
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+    return _raw_stream(torch.cuda.current_device() if index is None else index)
 
 
 def _dev(x, device, shape=None):

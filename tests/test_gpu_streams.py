@@ -49,3 +49,16 @@ def test_direct_sums_and_gradients_on_two_streams():
             assert torch.equal(amps[i], ref_amp[i]), f"sums of sample {i}, round {rep}"
             for a, b in zip(grads[i], ref_grad[i]):
                 assert torch.equal(a, b), f"gradient of sample {i}, round {rep}"
+
+
+def test_stream_handles_agree_with_stream_objects(monkeypatch):
+    """The raw handle and the one from a stream object, which serves where torch has no raw
+    form, name the same stream, also inside a stream context."""
+    side = torch.cuda.Stream()
+    for ctx in (torch.cuda.stream(torch.cuda.default_stream()), torch.cuda.stream(side)):
+        with ctx:
+            raw = numag._stream()
+            with monkeypatch.context() as m:
+                m.setattr(numag, "_raw_stream", numag._stream_of_object)
+                assert numag._stream() == raw == torch.cuda.current_stream().cuda_stream
+                assert numag._stream(torch.device("cuda:0")) == raw
