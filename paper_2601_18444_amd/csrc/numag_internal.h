@@ -175,7 +175,7 @@ int launch_fill(double *out, int64_t n, double value, hipStream_t s);
 struct ObjectsPlan {
     CartGeom cg;     // Cartesian detector
     PolGeom pg;      // polar detector
-    int mt;          // matrix tiles per wave
+    int mt;          // matrix tiles per wave; -1 (polar): two of 4 rows
     int64_t n_blocks;  // pixel blocks (items per slot)
     int64_t strips;  // accumulator strips of a slot (sixteen pixels each)
     int n_slots;     // accumulator slots (object set x rotation range)

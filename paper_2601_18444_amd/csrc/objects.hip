@@ -11,9 +11,9 @@
 // of its range with the matrix building blocks of the direct sums, then F F^H (and,
 // in split mode, exp(-i q.R r^k) F for the coherent total) goes into the slot's FP64
 // accumulators, which no other item touches.  Items are sorted by cost and handed out by
-// a persistent kernel through an atomic counter (small polar ones in order) -- to workgroups of 8 waves on a
-// Cartesian detector (cartesian_block.h), to single waves on a polar one
-// (polar_block.h); slots are reduced in a fixed order, so results are reproducible
+// a persistent kernel through an atomic counter (small polar ones in order) -- to
+// workgroups of 8 waves on a Cartesian detector (cartesian_block.h), to single waves on a
+// polar one (polar_block.h); slots are reduced in a fixed order, so results are reproducible
 // bit for bit.
 //
 // Rotations are applied on the fly (X = R x, w' = (n, R m)) while a chunk's
@@ -32,6 +32,11 @@
 // and now: 16 particles (96,000 points) x 24 rotations, 128 x 128: 14.2 -> 5.70 ms (4.04 of
 // it multiply-adds at 74.7 TFLOP/s); 96 objects (240,000 points) split, 256 x 256: 6.19 -> 2.50 ms
 // (1.68; the largest object's items run alone at the end).
+//
+// The eight tiles of accumulators and an object's epilogue (F F^H, object phases) do not fit
+// 256 registers: the compiler spills 98 in objects_kernel<8> and 94 in objects_polar_kernel<8>
+// (fewer with fewer tiles, none up to three), outside the matrix loop, so that they cost once
+// per object and rotation and count on small objects.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -241,9 +246,13 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
     }
 }
 
-// A work item belongs to one wave: (slot, theta column and row group).
+// A work item belongs to one wave: (slot, theta column and row group).  MT = kFewRows: detectors
+// of one row block, whose four channels are two tiles of 4 x 16 (they half fill a tile of 16
+// rows, which takes twice as long: 20 objects of 2,000 points, ten rotations, 16 x 361 pixels
+// 3.67 ms -> 2.89; 2.64 by walking the rows).
+constexpr int kFewRows = -1;
 template <int MT>
-__global__ __launch_bounds__(pblk::kThreads, MT == 1 ? 3 : 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
+__global__ __launch_bounds__(pblk::kThreads, MT <= 1 ? 3 : 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
 {
     __shared__ pblk::WaveSmem<MT, 4> sm[pblk::kWaves];
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
@@ -270,8 +279,8 @@ __global__ __launch_bounds__(pblk::kThreads, MT == 1 ? 3 : 2) void objects_polar
         for (int r = r0; r < r1; ++r) {
             ld.R = uniform_rot(a.rot + 9 * (int64_t)r);
             for (int k = k0; k < k1; ++k) {
-                cblk::v4d accC[MT], accS[MT];
-                cblk::zero<MT>(accC, accS);
+                constexpr int N = pblk::Tiles<MT>::N;
+                typename pblk::Tiles<MT>::T accC[N] = {}, accS[N] = {};
                 pblk::accumulate<MT, 4, 4>(ld, a.off[k], a.off[k + 1], sth, cth, g.dq, rg * g.na, sm[wave], accC, accS);
                 const bool first = r == r0 && k == k0;
                 double uk = 0.0;
@@ -297,8 +306,17 @@ __global__ __launch_bounds__(pblk::kThreads, MT == 1 ? 3 : 2) void objects_polar
                         if (lower) add_amplitude(u, first, vm, y, make_double2(z.x, -z.y));
                     }
                 };
-                cblk::finish_whole<MT>(accC, accS,
-                                       [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); });
+                if constexpr (MT > 0) {
+                    cblk::finish_whole<MT>(accC, accS,
+                                           [&](int t, int h, double2 vp, double2 vm) { add(2 * t + h, vp, vm); });
+                } else {
+                    // tile t: channel 2 t + l / 16 % 2, the upper rows in the first half of the lanes
+                    const double2 v0 = pblk::few_rows(accC[0], accS[0]), v1 = pblk::few_rows(accC[1], accS[1]);
+                    const bool low = lane < 32;
+                    const double2 send = low ? v1 : v0;
+                    const double2 o = make_double2(pblk::other_half(send.x), pblk::other_half(send.y));
+                    add(0, low ? v0 : o, low ? o : v1);
+                }
             }
         }
     }
@@ -608,6 +626,7 @@ Tables make_tables(const Detector &d, bool hermitian, const std::vector<int64_t>
     const bool tuned = tuned_shape(kTuneObjects, key, W, &entry);
     if (d.kind == NUMAG_GRID_POLAR) {
         polar_geometry(d, 4, ts.shape, p.pg, p.mt);
+        if (p.pg.na == 1) p.mt = kFewRows;
         p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;
         p.strips = slot_strips(p.pg, p.mt);
     } else {
@@ -754,7 +773,7 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     const bool pol = pl.d.kind == NUMAG_GRID_POLAR;
     // persistent grid: as many workgroups as fit the chip at once (two of 4 waves, three of one
     // tile, or one of 8 waves, per CU; the third: 73 -> 62 us and 101 -> 86 in the cases below)
-    const int64_t fit = (!pol ? 1 : p.mt == 1 ? 3 : 2) * (int64_t)device_cus();
+    const int64_t fit = (!pol ? 1 : p.mt <= 1 ? 3 : 2) * (int64_t)device_cus();
     const int64_t want = pol ? (p.n_items + pblk::kWaves - 1) / pblk::kWaves : p.n_items;
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(want, fit)));
     // The counter takes an atomic every 12 ns, 25 us for a turn of the chip's waves: small items
@@ -764,7 +783,7 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     // tile, all by the counter and now: 8 x 40 pixels 260 -> 62 us, 16 x 64 397 -> 86; of four
     // tiles, 200 x 120: 730 by the counter, 790 in order).
     const int64_t waves = (int64_t)grid.x * pblk::kWaves;
-    const bool small = (double)pl.W * (double)pl.n_rot * p.mt < 160.0 * (double)p.n_slots;
+    const bool small = (double)pl.W * (double)pl.n_rot * std::max(p.mt, 1) < 160.0 * (double)p.n_slots;
     args.rounds = small ? (int)(p.n_items / waves + 1) : 0;
     {
         TimedLaunch timed(NUMAG_KERNEL_OBJECTS, st);
@@ -774,6 +793,9 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
         else hipLaunchKernelGGL((objects_kernel<MT>), grid, dim3(cblk::kThreads), 0, st, args, p.cg);              \
         break
         switch (p.mt) {
+            case kFewRows:
+                hipLaunchKernelGGL((objects_polar_kernel<kFewRows>), grid, dim3(pblk::kThreads), 0, st, args, p.pg);
+                break;
             NUMAG_LAUNCH_OBJ(1);
             NUMAG_LAUNCH_OBJ(2);
             NUMAG_LAUNCH_OBJ(3);

@@ -436,3 +436,44 @@ def test_very_many_small_objects(orc, kind, n0, n1, path):
     amp1, tot = numag.amplitudes(_sample(cfg), grid, path=path, mode=numag.MODE_SPLIT)
     assert max_norm_err(tot[0].cpu().numpy(), spec.sum(axis=0)) <= 1e-12
     assert max_norm_err(amp1.cpu().numpy(), amp.cpu().numpy()) <= 1e-12
+
+
+@pytest.mark.parametrize("nq", [1, 15, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("nt", [1, 2, 9, 12])
+def test_objects_of_few_polar_rows(orc, nq, nt):
+    """One block of 32 q rows (tiles of four rows) and just more, columns in pairs and not;
+    dilute spectra of several objects and rotations, and the split total.  With S the sum of
+    an object's weights' moduli a sum is off by at most e = 2^-52 (4 phase + W + 128) S, to
+    which the rotated moments' three products and two sums add 3 S, and an entry of F F^H by
+    2 S e and its own two roundings.  The object's phase adds its own to the total."""
+    cfg = _objects(71, [1, 33, 0, 150], spread=9.0)
+    pos, nuc, mag, off = cfg["pos"], cfg["nuc"], cfg["mag"], cfg["obj_offsets"]
+    qmax = 1.2
+    grid = numag.qgrid(1, nq, nt, qmax)
+    qy, qz, _ = orc.pixels(1, nq, nt, qmax)
+    rots = synth.uniform_rotations(3, np.random.default_rng(72))
+    _, spec = numag.amplitudes(_sample(cfg), grid, rot=rots, mode=numag.MODE_DILUTE, spec_per_object=True)
+    total, both = numag.amplitudes(_sample(cfg), grid, rot=rots[:1], mode=numag.MODE_SPLIT)
+    spec, both = spec.cpu().numpy(), both[0].cpu().numpy()
+    sums = np.zeros_like(both)
+    A, tol_a, tol_s = np.zeros((qy.size, 4), dtype=complex), 0.0, 0.0
+    for k in range(len(off) - 1):
+        sl = slice(off[k], off[k + 1])
+        W = off[k + 1] - off[k]
+        if W == 0:
+            assert np.count_nonzero(spec[k]) == 0
+            continue
+        S = np.abs(nuc[sl]).sum() + np.abs(mag[sl]).sum()
+        phase = 2 * qmax * np.abs(pos[sl]).sum(1).max()
+        e = 2.0 ** -52 * (4 * phase + W + 128 + 3) * S
+        Fs = [orc.amplitudes(pos[sl], nuc[sl], mag[sl], qy, qz, R=R) for R in rots]
+        tol = 2 * S * e + 2.0 ** -51 * S * S
+        assert np.abs(spec[k] - orc.spectral(np.stack(Fs)) / len(rots)).max() <= tol, k
+        X = rots[0] @ cfg["obj_pos"][k]
+        phi = qy * X[1] + qz * X[2]
+        A += np.exp(-1j * phi)[:, None] * Fs[0]
+        sums += orc.spectral(Fs[0][None])
+        tol_a += e + 2.0 ** -52 * (4 * np.abs(phi).max() + 16 * qmax * np.abs(X).sum() + 16) * S
+        tol_s += tol
+    assert np.abs(amp_to_complex(total[0]) - A).max() <= tol_a
+    assert np.abs(both - sums).max() <= tol_s
