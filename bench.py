@@ -41,14 +41,15 @@ FLOPS_PER_TERM = 8
 PROFILES = os.path.join(ROOT, "profiles")
 # kernel -> (library timer id, sources that define it, file holding its HBM counters)
 KERNELS = {
-    "direct_cartesian_kernel": (0, ["cartesian_block.h", "direct.hip", "phasor.h", "types.h"],
+    "direct_cartesian_kernel": (0, ["cartesian_block.h", "direct.hip", "nonfinite.h", "phasor.h", "types.h"],
                                 "direct_cartesian_kernel_vortex64_256x256_pmc.md"),
-    "adjoint_cartesian_kernel": (1, ["adjoint.hip", "cartesian_block.h", "phasor.h", "types.h"],
+    "adjoint_cartesian_kernel": (1, ["adjoint.hip", "cartesian_block.h", "nonfinite.h", "phasor.h",
+                                     "polar_block.h", "types.h"],
                                  "adjoint_cartesian_kernel_vortex64_256x256_pmc.md"),
 }
 # kernels measured outside the step (their counter summaries, same format)
 SIDE_KERNELS = {
-    "direct_polar_kernel": (0, ["cartesian_block.h", "polar_block.h", "polar.hip", "phasor.h", "types.h"],
+    "direct_polar_kernel": (0, ["cartesian_block.h", "nonfinite.h", "polar_block.h", "polar.hip", "phasor.h", "types.h"],
                             "direct_polar_kernel_vortex64_polar256x256.md"),
 }
 
@@ -511,8 +512,9 @@ def sources_sha256(names):
 
 def traffic_per_launch(kernel, shape=None):
     """HBM bytes per launch of `kernel` from its committed counter summary, or None
-    when there is none, the kernel's sources changed since it was taken, or (with
-    `shape`) the summary was taken under another launch shape."""
+    when there is none, the kernel's sources changed since it was taken, or the summary
+    was taken under another launch shape than `shape` (the number of point splits, and
+    with it the bytes, follows the shape)."""
     _, srcs, name = {**KERNELS, **SIDE_KERNELS}[kernel]
     path = os.path.join(PROFILES, name)
     if not os.path.exists(path):
@@ -524,8 +526,8 @@ def traffic_per_launch(kernel, shape=None):
             vals[m.group(1)] = m.group(2)
     if vals.get("sources_sha256") != sources_sha256(srcs):
         return None
-    if shape is not None and vals.get("launch_shape") is not None and \
-            [int(v) for v in vals["launch_shape"].split()] != list(shape):
+    if vals.get("launch_shape") is not None and \
+            (shape is None or [int(v) for v in vals["launch_shape"].split()] != list(shape)):
         return None
     try:
         return int(float(vals["fetch_bytes_per_launch"]) + float(vals["write_bytes_per_launch"]))
@@ -812,7 +814,7 @@ def main():
             "workload": "vortex grid 64^3 at 1 nm (262144 points), 256x256 detector |q|<=2 nm^-1: "
                         "direct sums + 13 cross sections + azimuthal average + correlation"
                         + (" + separable FP64-MFMA sums" if have_sep else "") + " + loss gradient (adjoint)",
-            "points": W, "pixels": P, "evaluated_terms_per_step": 2 * terms,
+            "points": W, "pixels": P, "counted_terms_per_step": 2 * terms,
             "launch_shapes": "autotuned" if TUNE else ("from NUMAG_AUTOTUNE_CACHE" if os.environ.get(
                 "NUMAG_AUTOTUNE_CACHE") else "library defaults"),
         },
