@@ -111,7 +111,6 @@ struct ObjArgs {
     const int4 *slots;       // (object lo, object hi, rotation lo, rotation hi)
     int n_items;
     int *counter;
-    int rounds;              // turns that every wave takes without the counter (polar)
     double *spec;            // [n_slots][strips][4][64]
     double *amp;             // [n_slots][strips][2][64] or null (split mode)
 };
@@ -249,20 +248,27 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
 // A work item belongs to one wave: (slot, theta column and row group).  MT = kFewRows: detectors
 // of one row block, whose four channels are two tiles of 4 x 16 (they half fill a tile of 16
 // rows, which takes twice as long: 20 objects of 2,000 points, ten rotations, 16 x 361 pixels
-// 3.67 ms -> 2.89; 2.64 by walking the rows).
+// 3.67 ms -> 2.9; 2.64 by walking the rows).
+//
+// Items by the counter, or (TURNS) in order.  (Forms of their own: with both in one kernel the
+// sums take 4 % longer, 64 particles x 50 rotations on 128 x 128 305 ms against 293.)
 constexpr int kFewRows = -1;
-template <int MT>
+template <int MT, bool TURNS>
 __global__ __launch_bounds__(pblk::kThreads, MT <= 1 ? 3 : 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
 {
     __shared__ pblk::WaveSmem<MT, 4> sm[pblk::kWaves];
     if (*a.tag_ptr != a.tag) return;  // the workspace does not hold this plan's tables
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
     const int64_t strips = slot_strips(g, MT), per_col = column_strips(g, MT);
-    const int waves = (int)gridDim.x * pblk::kWaves;
-    for (int turn = 0;; ++turn) {
-        int it = turn * waves + (int)blockIdx.x * pblk::kWaves + wave;
-        if (turn >= a.rounds) {
-            if (lane == 0) it = atomicAdd(a.counter, 1) + a.rounds * waves;
+    int next = (int)blockIdx.x * pblk::kWaves + wave;
+    for (;;) {
+        int it;
+        if constexpr (TURNS) {
+            it = next;
+            next += (int)gridDim.x * pblk::kWaves;
+        } else {
+            it = 0;
+            if (lane == 0) it = atomicAdd(a.counter, 1);
             it = __builtin_amdgcn_readfirstlane(it);
         }
         if (it >= a.n_items) break;
@@ -782,19 +788,25 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
     // of 25 us, 160 points, rotations and tiles (500 objects of 40 points, two rotations, one
     // tile, all by the counter and now: 8 x 40 pixels 260 -> 62 us, 16 x 64 397 -> 86; of four
     // tiles, 200 x 120: 730 by the counter, 790 in order).
-    const int64_t waves = (int64_t)grid.x * pblk::kWaves;
     const bool small = (double)pl.W * (double)pl.n_rot * std::max(p.mt, 1) < 160.0 * (double)p.n_slots;
-    args.rounds = small ? (int)(p.n_items / waves + 1) : 0;
     {
         TimedLaunch timed(NUMAG_KERNEL_OBJECTS, st);
+#define NUMAG_LAUNCH_OBJ_P(MT)                                                                                  \
+    if (small)                                                                                                  \
+        hipLaunchKernelGGL((objects_polar_kernel<MT, true>), grid, dim3(pblk::kThreads), 0, st, args, p.pg);       \
+    else                                                                                                        \
+        hipLaunchKernelGGL((objects_polar_kernel<MT, false>), grid, dim3(pblk::kThreads), 0, st, args, p.pg)
 #define NUMAG_LAUNCH_OBJ(MT)                                                                                    \
     case MT:                                                                                                    \
-        if (pol) hipLaunchKernelGGL((objects_polar_kernel<MT>), grid, dim3(pblk::kThreads), 0, st, args, p.pg);     \
-        else hipLaunchKernelGGL((objects_kernel<MT>), grid, dim3(cblk::kThreads), 0, st, args, p.cg);              \
+        if (!pol) {                                                                                             \
+            hipLaunchKernelGGL((objects_kernel<MT>), grid, dim3(cblk::kThreads), 0, st, args, p.cg);               \
+            break;                                                                                              \
+        }                                                                                                       \
+        NUMAG_LAUNCH_OBJ_P(MT);                                                                                 \
         break
         switch (p.mt) {
             case kFewRows:
-                hipLaunchKernelGGL((objects_polar_kernel<kFewRows>), grid, dim3(pblk::kThreads), 0, st, args, p.pg);
+                NUMAG_LAUNCH_OBJ_P(kFewRows);
                 break;
             NUMAG_LAUNCH_OBJ(1);
             NUMAG_LAUNCH_OBJ(2);
@@ -806,6 +818,7 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
             NUMAG_LAUNCH_OBJ(8);
         }
 #undef NUMAG_LAUNCH_OBJ
+#undef NUMAG_LAUNCH_OBJ_P
     }
     NUMAG_HIP_CHECK(hipGetLastError());
     const int *d_off = (const int *)(base + c.o_slot_off);
