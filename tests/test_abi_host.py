@@ -358,7 +358,8 @@ def test_object_accumulators_follow_the_detector(kind, n0, n1):
     amplitude for each independent pixel, rounded up to blocks of 16 along one axis (and 16
     pixels more on a Cartesian detector), not to the tiles of the matrix instructions."""
     K, per = 3000, 20
-    s = _cpu_sample(W=K * per, K=K, offsets=np.arange(K + 1, dtype=np.int64) * per)
+    offsets = np.arange(K + 1, dtype=np.int64) * per  # (the sample holds its address only)
+    s = _cpu_sample(W=K * per, K=K, offsets=offsets)
     grid = numag.qgrid(kind, n0, n1, 1.0)
     nws = numag._lib.numag_workspace_size(ctypes.byref(s), 1, ctypes.byref(grid), numag.PATH_DIRECT_HERMITIAN,
                                           numag.MODE_DILUTE)
