@@ -114,8 +114,8 @@ __global__ __launch_bounds__(kResThreads) void residual_kernel(Detector d, numag
             block = r / ne;  // col * nrg + rg
             const int rg = (int)(block % pg.nrg), col = (int)(block / pg.nrg);
             const int a = rg * pg.na + e;
-            if (e < pg.na) {
-                const int rp = pblk::kRows * a + 16 + b16, rm = pblk::kRows * a + 15 - b16;
+            if (e < pg.na && b16 < pg.mid) {
+                const int rp = pblk::kRows * a + pg.mid + b16, rm = pblk::kRows * a + pg.mid - 1 - b16;
                 if (rp < pg.n0) px[0] = (int64_t)rp * pg.n_out + col;
                 if (rm < pg.n0) px[1] = (int64_t)rm * pg.n_out + col;
                 if (pg.nh > 0) {
@@ -325,23 +325,24 @@ __device__ __forceinline__ double lane_value(double v, int k)
 }
 
 // MT tiles of 16 coefficient rows, two row blocks each; MT = 0: one block of rows, whose eight
-// coefficient rows are two tiles of 4 x 16 (a third of the cycles of a tile of 16 that they
+// coefficient rows are two tiles of 4 x 16, MT = -2 of up to 16 rows, with half the offsets (a third of the cycles of a tile of 16 that they
 // would half fill, and registers and LDS for twice the waves).  20,000 points, adjoint sums with
-// their residuals, tiles of 16 and now: 16 x 361 212 -> 133 us (134 by walking the rows), 32 x 181
-// 113 -> 80 (122), 8 x 180 70 -> 57 (101).
+// their residuals, tiles of 16 and now: 16 x 361 212 -> 92 us (134 by walking the rows; 133 with 16
+// offsets), 32 x 181 113 -> 77 (121); 100,000 points 16 x 361 356 (344; 564 with 16 offsets).
 template <int MT>
 struct PolWaveTables {
-    double2 off[32][17];
-    double2 ctr[32][2 * MT + 1];
+    double2 off[32][pblk::Tiles<MT>::kOffsets + 1];
+    double2 ctr[32][MT <= 0 ? 1 : 2 * MT + 1];
 };
 
 template <int MT>
-__global__ __launch_bounds__(kPolThreads, MT == 0 ? 4 : 2) void adjoint_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
+__global__ __launch_bounds__(kPolThreads, MT <= 0 ? 4 : 2) void adjoint_polar_kernel(const PointRec *__restrict__ pts, int64_t W,
                                                                        PolGeom g, int cols_per_split,
                                                                        const double2 *__restrict__ coef,
                                                                        double *__restrict__ gpart)
 {
-    constexpr bool kOne = MT == 0;
+    constexpr bool kOne = MT <= 0;
+    constexpr int kOff = pblk::Tiles<MT>::kOffsets, kSteps = kOff / 4;
     constexpr int NT = kOne ? 2 : MT;
     constexpr int kStage = 4 * (kOne ? 1 : MT) * 64;
     __shared__ PolWaveTables<MT> s_t[kPolWaves];
@@ -361,12 +362,13 @@ __global__ __launch_bounds__(kPolThreads, MT == 0 ? 4 : 2) void adjoint_polar_ke
     const int at = kOne ? 16 * kq + (pt & 3) : lane;
     const double2 *src = coef + (int64_t)c0 * g.nrg * kStage + at;
     const double2 *last = coef + ((int64_t)c1 * g.nrg - 1) * kStage + at;
-    double2 co[4][NT];  // coefficients of a block, loaded one block ahead of their use
+    double2 co[kSteps][NT];  // coefficients of a block, loaded one block ahead of their use (kOne: with the
+                             // tables, since they would spill)
     auto load = [&](const double2 *from) {
 #pragma unroll
-        for (int k = 0; k < 4 * NT; ++k) co[k / NT][k % NT] = from[kOne ? 64 * (k / NT) + 4 * (k % NT) : 64 * k];
+        for (int k = 0; k < kSteps * NT; ++k) co[k / NT][k % NT] = from[kOne ? 64 * (k / NT) + 4 * (k % NT) : 64 * k];
     };
-    if (c0 < c1) load(src);
+    if (!kOne && c0 < c1) load(src);
     double2 dir = make_double2(0.0, 0.0);  // (sin, cos) of the angles of 64 columns, one per lane
 #pragma unroll 1
     for (int col = c0; col < c1; ++col) {
@@ -376,7 +378,7 @@ __global__ __launch_bounds__(kPolThreads, MT == 0 ? 4 : 2) void adjoint_polar_ke
         const double u0 = Y * sth + Z * cth;
         __builtin_amdgcn_s_setprio(2);  // as in polar_block.h: tables before products
         double2 first, step;  // centre of the group's first block, centre step (second half)
-        pblk::offsets(tab.off, g.dq, u0, first, step);
+        pblk::offsets<kOff>(tab.off, g.dq, u0, first, step);
         double2 adv = make_double2(1.0, 0.0);  // from one row group to the next
         if (g.nrg > 1) {
             const double q = (double)(pblk::kRows * g.na) * g.dq;
@@ -386,11 +388,12 @@ __global__ __launch_bounds__(kPolThreads, MT == 0 ? 4 : 2) void adjoint_polar_ke
         for (int rg = 0; rg < g.nrg; ++rg) {
             if (half != 0) pblk::centres<kOne ? 1 : 2 * MT>(tab.ctr[gp], first, step);
             if (g.nrg > 1) first = cmul(first, adv);
+            if (kOne) load(src);
             wave_fence();
             __builtin_amdgcn_s_setprio(0);
             typename pblk::Tiles<MT>::T acc[NT][kPolNP] = {};
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < kSteps; ++s) {
                 double2 z[kPolNP];
 #pragma unroll
                 for (int u = 0; u < kPolNP; ++u) z[u] = tab.off[16 * u + pt][4 * s + kq];
@@ -404,7 +407,7 @@ __global__ __launch_bounds__(kPolThreads, MT == 0 ? 4 : 2) void adjoint_polar_ke
                 }
             }
             src += kStage;
-            load(src < last ? src : last);  // (the last block again at the end, unused)
+            if (!kOne) load(src < last ? src : last);  // (the last block again at the end, unused)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < kPolNP; ++u) {
@@ -533,6 +536,7 @@ static GradPlan grad_plan(const Detector &d, int64_t W, bool hermitian, bool use
         p.pg.nh = d.n_theta % 2 == 0 ? d.n_theta / 2 : 0;
         p.pg.cols = p.pg.nh > 0 ? p.pg.nh : d.n_theta;
         p.pg.dq = d.step0;
+        p.pg.mid = d.n0 <= 16 ? 8 : pblk::kRows / 2;
         const int blocks = (d.n0 + pblk::kRows - 1) / pblk::kRows;
         p.pg.nrg = (blocks + kPolNA - 1) / kPolNA;
         p.pg.na = (blocks + p.pg.nrg - 1) / p.pg.nrg;
@@ -666,7 +670,8 @@ int launch_grad(const PointRec *pts, int64_t W, const Detector &d, const numag_c
                 NUMAG_LAUNCH_ADJ_C(8);
             }
         } else {
-            switch (p.pg.na == 1 ? 0 : p.mt) {
+            switch (p.pg.mid == 8 ? -2 : p.pg.na == 1 ? 0 : p.mt) {
+                NUMAG_LAUNCH_ADJ_P(-2);
                 NUMAG_LAUNCH_ADJ_P(0);
                 NUMAG_LAUNCH_ADJ_P(1);
                 NUMAG_LAUNCH_ADJ_P(2);

@@ -11,8 +11,9 @@
 // exp(+i q.r), with real weights wq_p f_p; the real-space grid plays the role of
 // the detector.
 //  - Cartesian detector and Cartesian real-space grid: the pixels are a regular grid, and
-//    the sum factors (separable.hip), four data sets a pass; but for thin grids (factored()).  220 x 190 pixels to 180 x 170
-//    points, 4 sets: 36 us, against 306 as a direct sum.
+//    the sum factors (separable.hip), four data sets a pass, but for thin and very large
+//    grids (factored()).  220 x 190 pixels to 180 x 170 points, 4 sets: 36 us, against 306
+//    as a direct sum.
 //  - Polar real-space grid, and a detector that has the pixel at -q for every one at q (a
 //    Cartesian one, a polar one with an even number of columns): the polar sums with the
 //    two pixels as one point of two weights (polar_block.h), half the points, four data
@@ -23,7 +24,6 @@
 //    in channels 1-3, four in all four.
 #include <algorithm>
 
-#include "nonfinite.h"
 #include "nonfinite.h"
 #include "numag_internal.h"
 #include "phasor.h"

@@ -144,7 +144,7 @@ int launch_sample_cartesian(const double *pos, const double *nuc, const double *
 constexpr int kPolarShapeCount = 5;
 struct PolarPlan {
     PolGeom g;
-    int mt;          // 16-row matrix tiles per wave; 0, -1: one, two of 4 rows
+    int mt;          // 16-row matrix tiles per wave; 0, -1: one, two of 4 rows; -2, -3: of 8 offsets
     int shape;       // launch shape: 1, 0, 2, 3, 4 for 1, 2, 4, 8 or 16 row blocks of 32 per wave
     int channels;    // channels summed: 4 (N, M), 3 (M only) or 1 (N only); the rest are written as 0
     int nsplit;      // point ranges summed by different workgroups
@@ -175,7 +175,7 @@ int launch_fill(double *out, int64_t n, double value, hipStream_t s);
 struct ObjectsPlan {
     CartGeom cg;     // Cartesian detector
     PolGeom pg;      // polar detector
-    int mt;          // matrix tiles per wave; -1 (polar): two of 4 rows
+    int mt;          // matrix tiles per wave; -1, -3 (polar): two of 4 rows
     int64_t n_blocks;  // pixel blocks (items per slot)
     int64_t strips;  // accumulator strips of a slot (sixteen pixels each)
     int n_slots;     // accumulator slots (object set x rotation range)

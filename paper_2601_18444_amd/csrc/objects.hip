@@ -245,14 +245,14 @@ __global__ __launch_bounds__(cblk::kThreads, 2) void objects_kernel(ObjArgs a, C
     }
 }
 
-// A work item belongs to one wave: (slot, theta column and row group).  MT = kFewRows: detectors
+// A work item belongs to one wave: (slot, theta column and row group).  MT < 0: detectors
 // of one row block, whose four channels are two tiles of 4 x 16 (they half fill a tile of 16
 // rows, which takes twice as long: 20 objects of 2,000 points, ten rotations, 16 x 361 pixels
-// 3.67 ms -> 2.9; 2.64 by walking the rows).
+// 3.67 -> 1.98 ms, 2.9 with 16 offsets, 2.64 by walking the rows; 32 x 181 1.79 -> 1.45, 1.62).
 //
 // Items by the counter, or (TURNS) in order.  (Forms of their own: with both in one kernel the
 // sums take 4 % longer, 64 particles x 50 rotations on 128 x 128 305 ms against 293.)
-constexpr int kFewRows = -1;
+constexpr int kFewRows = -1, kFewestRows = -3;  // (-3: detectors of up to 16 rows, a single strip)
 template <int MT, bool TURNS>
 __global__ __launch_bounds__(pblk::kThreads, MT <= 1 ? 3 : 2) void objects_polar_kernel(ObjArgs a, PolGeom g)
 {
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(pblk::kThreads, MT <= 1 ? 3 : 2) void objects_polar
                 if (a.amp != nullptr) {
                     const double2 X = object_yz(a, ld.R.m, k);
                     uk = X.x * sth + X.y * cth;
-                    z = twiddle(((double)(lane & 15) + 0.5) * g.dq * uk);
+                    z = twiddle(((double)(lane & (pblk::Tiles<MT>::kOffsets - 1)) + 0.5) * g.dq * uk);
                 }
                 auto add = [&](int i, double2 vp, double2 vm) {
                     // rows 32 a + 15 - b, 32 a + 16 + b
@@ -321,7 +321,17 @@ __global__ __launch_bounds__(pblk::kThreads, MT <= 1 ? 3 : 2) void objects_polar
                     const bool low = lane < 32;
                     const double2 send = low ? v1 : v0;
                     const double2 o = make_double2(pblk::other_half(send.x), pblk::other_half(send.y));
-                    add(0, low ? v0 : o, low ? o : v1);
+                    const double2 vp = low ? v0 : o, vm = low ? o : v1;
+                    if constexpr (MT == kFewestRows) {  // both in the strip, strip_row
+                        const bool upper = (lane & 8) != 0;
+                        const double2 v = upper ? vp : vm;
+                        add_spectral(a.spec + strip0 * 256 + lane, first, v);
+                        if (a.amp != nullptr)
+                            add_amplitude(a.amp + strip0 * 128 + lane, first, v, twiddle(7.5 * g.dq * uk),
+                                          make_double2(z.x, upper ? z.y : -z.y));
+                    } else {
+                        add(0, vp, vm);
+                    }
                 }
             }
         }
@@ -353,6 +363,7 @@ __device__ __forceinline__ void strip_pixel(const CartGeom &g, int mt, int line,
 }
 __device__ __forceinline__ int strip_row(const PolGeom &g, int mt, int at, int b)
 {
+    if (g.mid == 8) return b < 8 ? 7 - b : b;
     const int per = block_values(g.na, mt), rg = g.nrg == 1 ? 0 : (at >> 1) / per;
     return pblk::slot_row(g, rg, (at >> 1) - rg * per, b, at & 1 ? 0 : 1);
 }
@@ -633,6 +644,10 @@ Tables make_tables(const Detector &d, bool hermitian, const std::vector<int64_t>
     if (d.kind == NUMAG_GRID_POLAR) {
         polar_geometry(d, 4, ts.shape, p.pg, p.mt);
         if (p.pg.na == 1) p.mt = kFewRows;
+        if (d.n0 <= 16) {
+            p.mt = kFewestRows;
+            p.pg.mid = 8;
+        }
         p.n_blocks = (int64_t)p.pg.cols * p.pg.nrg;
         p.strips = slot_strips(p.pg, p.mt);
     } else {
@@ -805,6 +820,9 @@ int launch_objects_plan(const ObjPlan &pl, const numag_sample &s, double *spec_o
         NUMAG_LAUNCH_OBJ_P(MT);                                                                                 \
         break
         switch (p.mt) {
+            case kFewestRows:
+                NUMAG_LAUNCH_OBJ_P(kFewestRows);
+                break;
             case kFewRows:
                 NUMAG_LAUNCH_OBJ_P(kFewRows);
                 break;

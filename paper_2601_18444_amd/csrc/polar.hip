@@ -111,9 +111,9 @@ __global__ __launch_bounds__(pblk::kThreads, polar_per_cu(MT)) void direct_polar
     unsigned bad = 0;  // NaN sums of this lane, two bits per tile half (or tile)
     // `which` (1, 2) of slot's sums vp, vm, put away unless NaN
     auto put = [&](int i, int slot, double2 vp, double2 vm, int which) {
-        const int nan = which & (NW == CH ? pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0);
+        const int nan = which & (NW == CH ? pblk::which_nan(g, CH, rg, slot, pblk::lane_offset(g), vp, vm) : 0);
         bad |= (unsigned)nan << (2 * i);
-        pblk::put_slot(out, g, CH, rg, col, slot, lane & 15, vp, vm, store == 2, which & ~nan);
+        pblk::put_slot(out, g, CH, rg, col, slot, pblk::lane_offset(g), vp, vm, store == 2, which & ~nan);
     };
     if constexpr (MT > 0) {
         cblk::finish_whole<MT>(accC, accS, [&](int t, int h, double2 vp, double2 vm) {
@@ -142,8 +142,8 @@ __global__ __launch_bounds__(pblk::kThreads, polar_per_cu(MT)) void direct_polar
         const int slot = MT > 0 ? 4 * i + (lane >> 4) : 2 * i + (lane >> 4 & 1);
         bad &= ~(3u << (2 * i));
         double2 vp = make_double2(__builtin_nan(""), __builtin_nan("")), vm = vp;
-        pblk::repair(g, ld.source(), jbeg, jend, CH, rg, slot, lane & 15, sth, cth, which, vp, vm);
-        pblk::put_slot(out, g, CH, rg, col, slot, lane & 15, vp, vm, store == 2, which);
+        pblk::repair(g, ld.source(), jbeg, jend, CH, rg, slot, pblk::lane_offset(g), sth, cth, which, vp, vm);
+        pblk::put_slot(out, g, CH, rg, col, slot, pblk::lane_offset(g), vp, vm, store == 2, which);
     }
 }
 
@@ -172,13 +172,13 @@ __global__ __launch_bounds__(256) void polar_combine_kernel(const double *__rest
     const int rg = (int)(rc / g.cols), col = (int)(rc % g.cols);
     const int slot = FEW ? 2 * i + (lane >> 4 & 1) : 4 * i + (lane >> 4), which = FEW ? 1 + (lane >> 5) : 3;
     double2 vp = make_double2(v[0], v[1]), vm = make_double2(v[V - 2], v[V - 1]);
-    const int nan = W > 0 ? which & pblk::which_nan(g, CH, rg, slot, lane & 15, vp, vm) : 0;
+    const int nan = W > 0 ? which & pblk::which_nan(g, CH, rg, slot, pblk::lane_offset(g), vp, vm) : 0;
     if (__builtin_expect(nan != 0, 0)) {
         double sth, cth;
         sincos_cw((2.0 * 3.141592653589793 * (double)col) / (double)g.n_out, &sth, &cth);
-        pblk::repair(g, src, 0, W, CH, rg, slot, lane & 15, sth, cth, nan, vp, vm);
+        pblk::repair(g, src, 0, W, CH, rg, slot, pblk::lane_offset(g), sth, cth, nan, vp, vm);
     }
-    pblk::put_slot(amp, g, CH, rg, col, slot, lane & 15, vp, vm, accumulate != 0, which);
+    pblk::put_slot(amp, g, CH, rg, col, slot, pblk::lane_offset(g), vp, vm, accumulate != 0, which);
 }
 
 // ---------------------------------------------------------------------------
@@ -202,6 +202,7 @@ void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int 
     const int cap = std::min(shape_blocks(shape), std::min(pblk::kMaxNA, 8 * cblk::kMaxMT / channels));
     g.nrg = (blocks + cap - 1) / cap;
     g.na = (blocks + g.nrg - 1) / g.nrg;
+    g.mid = pblk::kRows / 2;
     g.dq = d.step0;
     mt = (g.na * channels + 7) / 8;
 }
@@ -210,12 +211,17 @@ void polar_geometry(const Detector &d, int channels, int shape, PolGeom &g, int 
 static void direct_polar_geometry(const Detector &d, int channels, PolarPlan &p)
 {
     polar_geometry(d, channels, p.shape, p.g, p.mt);
-    if (p.g.na * channels <= 4) p.mt = p.g.na * channels <= 2 ? 0 : -1;
+    if (p.g.na * channels > 4) return;
+    p.mt = p.g.na * channels <= 2 ? 0 : -1;
+    if (d.n0 <= 16) {  // offsets of one half block
+        p.mt -= 2;
+        p.g.mid = 8;
+    }
 }
 
 static size_t polar_split_bytes(const PolGeom &g, int mt)
 {
-    return (size_t)g.nrg * g.cols * (mt > 0 ? mt * 512 : (1 - mt) * 128) * sizeof(double);
+    return (size_t)g.nrg * g.cols * (mt > 0 ? mt * 512 : pblk::few_tiles(mt) * 128) * sizeof(double);
 }
 
 static void polar_splits(PolarPlan &p, int64_t W, int64_t target, size_t max_partial)
@@ -247,7 +253,7 @@ static PolarPlan polar_default_plan(const Detector &d, int64_t W, int channels, 
         const int per_cu = polar_per_cu(p.mt);
         polar_splits(p, W, target > 0 ? target : std::max<int64_t>(256 * per_cu * rounds, blocks), max_partial);
         const double pts = (double)std::min<int64_t>(p.per, std::max<int64_t>(W, 1));
-        const double step = p.mt > 0 ? 132.0 * p.mt : 44.0 * (1 - p.mt);
+        const double step = p.mt > 0 ? 132.0 * p.mt : (p.g.mid == 8 ? 22.0 : 44.0) * pblk::few_tiles(p.mt);
         const double cycles = per_cu * (3000.0 + std::ceil(pts / pblk::kChunk) * 700.0 +
                                         std::ceil(pts / 4.0) * (step + 40.0));
         const double bytes = (double)polar_split_bytes(p.g, p.mt) * p.nsplit;
@@ -296,10 +302,12 @@ static void launch_polar_tiles(const Loader &ld, int64_t W, const PolarPlan &p, 
     // at most 16 row blocks: 2 CH tiles
 #define NUMAG_LAUNCH_POLAR(MT)   \
     case MT:                     \
-        if constexpr (MT <= 2 * CH && (MT > 0 || CH <= 2 - 2 * MT)) \
+        if constexpr (MT <= 2 * CH && (MT > 0 || CH <= 2 * pblk::few_tiles(MT))) \
             hipLaunchKernelGGL((direct_polar_kernel<MT, CH, NW, Loader>), grid, block, 0, s, ld, W, p.per, p.g, store, out); \
         break
     switch (p.mt) {
+        NUMAG_LAUNCH_POLAR(-3);
+        NUMAG_LAUNCH_POLAR(-2);
         NUMAG_LAUNCH_POLAR(-1);
         NUMAG_LAUNCH_POLAR(0);
         NUMAG_LAUNCH_POLAR(1);
@@ -320,7 +328,7 @@ static int combine_polar(const PolarPlan &p, const PointSource &src, int64_t W, 
 {
     NUMAG_HIP_CHECK(hipGetLastError());
     if (p.nsplit <= 1) return NUMAG_OK;
-    const int n = p.mt > 0 ? 2 * p.mt : 1 - p.mt;  // tile halves, or tiles of 4 x 16
+    const int n = p.mt > 0 ? 2 * p.mt : pblk::few_tiles(p.mt);  // tile halves, or tiles of 4 x 16
     const dim3 grid((unsigned)(((int64_t)p.g.nrg * p.g.cols * n * 64 + 255) / 256));
     if (p.mt > 0)
         hipLaunchKernelGGL((polar_combine_kernel<false>), grid, dim3(256), 0, s, partial, p.g, n, p.channels, p.nsplit,

@@ -41,21 +41,37 @@ constexpr int kMaxNA = 16;    // row blocks per wave
 // each), or with MT <= 0 1 - MT tiles of 4 x 16 (two slots each), for detectors of so few rows
 // that the larger one would hold zeros: 16 x 16 takes 69 cycles of the SIMD's FP64 pipe, 4 x 16
 // 20.  (50,000 points, 8 x 181, one channel: 268 -> 169 us; four: 244 -> 210.)
+// MT = -2 and -3 are the one and two tiles of a detector of up to 16 rows, a block of 8 offsets:
+// the four products of 4 x 4 x 4 of an instruction take these for eight points instead of 16
+// offsets for four, half of the products and tables (100,000 points, 16 x 361, four channels:
+// 741 -> 509 us, 611 by walking the rows).
 template <int MT>
 struct Tiles {
     using T = v4d;
-    static constexpr int N = MT, kSlots = 8;
+    static constexpr int N = MT, kSlots = 8, kOffsets = 16;
 };
 template <>
 struct Tiles<0> {
     using T = double;
-    static constexpr int N = 1, kSlots = 2;
+    static constexpr int N = 1, kSlots = 2, kOffsets = 16;
 };
 template <>
 struct Tiles<-1> {
     using T = double;
-    static constexpr int N = 2, kSlots = 2;
+    static constexpr int N = 2, kSlots = 2, kOffsets = 16;
 };
+template <>
+struct Tiles<-2> {
+    using T = double;
+    static constexpr int N = 1, kSlots = 2, kOffsets = 8;
+};
+template <>
+struct Tiles<-3> {
+    using T = double;
+    static constexpr int N = 2, kSlots = 2, kOffsets = 8;
+};
+// Tiles of 4 x 16 of a wave.
+__host__ __device__ constexpr int few_tiles(int mt) { return mt == 0 || mt == -2 ? 1 : 2; }
 __device__ __forceinline__ v4d mfma(double a, double b, v4d c)
 {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -69,14 +85,14 @@ __device__ __forceinline__ double mfma(double a, double b, double c)
 template <int MT, int CH>
 constexpr int max_na()
 {
-    constexpr int n = Tiles<MT>::kSlots * Tiles<MT>::N / CH;
+    constexpr int n = Tiles<MT>::kOffsets == 8 ? 1 : Tiles<MT>::kSlots * Tiles<MT>::N / CH;
     return n < kMaxNA ? n : kMaxNA;
 }
 
 // NW weights per point: CH, or 2 CH for pairs of points at u and -u (accumulate below).
 template <int MT, int CH, int NW = CH>
 struct WaveSmem {
-    double2 off[kChunk][17];
+    double2 off[kChunk][Tiles<MT>::kOffsets + 1];
     static constexpr int kCtr = max_na<MT, CH>() == 1 ? 1 : max_na<MT, CH>() + 1;
     double2 ctr[kChunk][kCtr];
     double w[kChunk][NW + 1];
@@ -96,23 +112,25 @@ __device__ __forceinline__ double2 next_term(double k2, double2 x, double2 befor
     return make_double2(fma(k2, x.x, -before.x), fma(k2, x.y, -before.y));
 }
 
-// Offset phasors of point gp = lane % 32 at u, written to off[gp]; returns, in the second
-// half of the lanes, the centre of block 0 (exp(-i 15.5 dq u)) and the centre step.
-__device__ __forceinline__ void offsets(double2 (*off)[17], double dq, double u, double2 &centre, double2 &step)
+// Offset phasors of point gp = lane % 32 at u, M = 16 or 8 of them, written to off[gp]; returns,
+// in the second half of the lanes, the centre of block 0 (exp(-i (M - 1/2) dq u)) and the
+// centre step.
+template <int M>
+__device__ __forceinline__ void offsets(double2 (*off)[M + 1], double dq, double u, double2 &centre, double2 &step)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
-    double2 x = phasor(half_turns((half == 0 ? 0.5 : 15.5) * dq), u, fabs(u) < phasor_range(16.0 * dq));
+    double2 x = phasor(half_turns((half == 0 ? 0.5 : M - 0.5) * dq), u, fabs(u) < phasor_range(M * dq));
     centre = x;
     double2 st = cmul(x, x);  // dq u in the first half
     const double2 so = make_double2(other_half(st.x), other_half(st.y));
     if (half != 0) st = make_double2(so.x, -so.y);  // the second half walks down
     const double k2 = st.x + st.x;
-    const int at = half == 0 ? 0 : 15, by = half == 0 ? 1 : -1;
+    const int at = half == 0 ? 0 : M - 1, by = half == 0 ? 1 : -1;
     double2 y = cmul(x, st);
     off[gp][at] = x;
     off[gp][at + by] = y;
 #pragma unroll
-    for (int k = 2; k < 8; ++k) {
+    for (int k = 2; k < M / 2; ++k) {
         const double2 z = next_term(k2, y, x);
         off[gp][at + by * k] = z;
         x = y;
@@ -147,7 +165,7 @@ __device__ __forceinline__ void generate(WaveSmem<MT, CH, NW> &sm, int a0, doubl
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, gp = lane & 31;
     double2 centre, step, first = make_double2(1.0, 0.0);
-    offsets(sm.off, dq, u, centre, step);
+    offsets<Tiles<MT>::kOffsets>(sm.off, dq, u, centre, step);
     if (a0 != 0) {  // wave-uniform
         const double q = (double)(kRows * a0) * dq;
         first = phasor(half_turns(q), u, fabs(u) < phasor_range(q));
@@ -178,7 +196,9 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     const int r16 = lane & 15, kq = lane >> 4;
     constexpr bool kPairs = NW != CH;
     static_assert(NW == CH || NW == 2 * CH, "one weight per channel, or two of a pair");
-    constexpr int N = Tiles<MT>::N;
+    constexpr int N = Tiles<MT>::N, kOff = Tiles<MT>::kOffsets;
+    constexpr int kPoints = 64 / kOff;  // points of a matrix step
+    const int pt = kOff == 8 ? kq + 4 * (r16 >> 3) : kq;
     // this lane's matrix row: slot 8 t + 4 (r16 / 8) + r16 % 4, part (r16 / 4) % 2 of 16 rows;
     // slot 2 t + r16 % 2, part (r16 / 2) % 2 of four
     const int part = (r16 >> (MT > 0 ? 2 : 1)) & 1;
@@ -209,13 +229,13 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         wave_fence();
         __builtin_amdgcn_s_setprio(0);
         raw = fetch(j0 + kChunk);
-        const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + 3) >> 2));
-        const double2 *op = &sm.off[kq][r16], *cp = &sm.ctr[kq][0];
-        const double *wp = &sm.w[kq][0];
+        const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + kPoints - 1) / kPoints));
+        const double2 *op = &sm.off[pt][r16 % kOff], *cp = &sm.ctr[pt][0];
+        const double *wp = &sm.w[pt][0];
         auto step = [&](int s) {
-            const double2 z = op[s * 4 * 17];
-            const double *c = (const double *)(cp + s * 4 * WaveSmem<MT, CH, NW>::kCtr) + part;
-            const double *w = wp + s * 4 * (NW + 1);
+            const double2 z = op[s * kPoints * (kOff + 1)];
+            const double *c = (const double *)(cp + s * kPoints * WaveSmem<MT, CH, NW>::kCtr) + part;
+            const double *w = wp + s * kPoints * (NW + 1);
             double a[N], b[kPairs ? N : 1];
             if (kPairs) {
 #pragma unroll
@@ -248,6 +268,13 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         for (; s < steps; ++s) step(s);
         wave_fence();
     }
+    if constexpr (kOff == 8) {  // the two sets of points
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            accC[t] += __shfl_xor(accC[t], 8);
+            accS[t] += __shfl_xor(accS[t], 8);
+        }
+    }
 }
 
 // The sums of tile t of 4 x 16 in this lane: slot 2 t + (lane / 16) % 2, offset lane % 16, the
@@ -258,11 +285,20 @@ __device__ __forceinline__ double2 few_rows(double c, double s)
     return (threadIdx.x & 32) == 0 ? make_double2(c - os, s + oc) : make_double2(oc + s, c - os);
 }
 
-// Rows of block a, offset b: 32 a + 16 + b (k = 0) and 32 a + 15 - b (k = 1).
+// Offset of a lane's sums; of 8 offsets the second half of the lanes of 16 repeat the first,
+// and have no row.
+__device__ __forceinline__ int lane_offset(const PolGeom &g)
+{
+    const int b = threadIdx.x & 15;
+    return b < g.mid ? b : (1 << 29);
+}
+
+// Rows of block a, offset b: 32 a + mid + b (k = 0) and 32 a + mid - 1 - b (k = 1).  Negative or
+// beyond the detector: none.
 __device__ __forceinline__ int slot_row(const PolGeom &g, int rg, int e, int b, int k)
 {
     const int a = kRows * (rg * g.na + e);
-    return k == 0 ? a + 16 + b : a + 15 - b;
+    return k == 0 ? a + g.mid + b : a + g.mid - 1 - b;
 }
 
 // Writes (add: adds) the two rows of slot s, offset b, at the mirrored column too (nh > 0:
@@ -276,7 +312,7 @@ __device__ __forceinline__ void put_slot(double *__restrict__ amp, const PolGeom
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int row = slot_row(g, rg, e, b, k);
-        if (row >= g.n0 || !(which >> k & 1)) continue;
+        if ((unsigned)row >= (unsigned)g.n0 || !(which >> k & 1)) continue;
         const double2 v = k == 0 ? vp : vm;
         const int64_t p = (int64_t)row * g.n_out + col;
         auto put = [&](int ch, double2 x) {
@@ -297,8 +333,8 @@ __device__ __forceinline__ int which_nan(const PolGeom &g, int CH, int rg, int s
 {
     const int e = s / CH;
     if (e >= g.na) return 0;
-    return (is_nan(vp) && slot_row(g, rg, e, b, 0) < g.n0 ? 1 : 0) |
-           (is_nan(vm) && slot_row(g, rg, e, b, 1) < g.n0 ? 2 : 0);
+    return (is_nan(vp) && (unsigned)slot_row(g, rg, e, b, 0) < (unsigned)g.n0 ? 1 : 0) |
+           (is_nan(vm) && (unsigned)slot_row(g, rg, e, b, 1) < (unsigned)g.n0 ? 2 : 0);
 }
 
 // A slot's sums vp, vm over the points [j0, j1) of src (nonfinite.h), which of them (1, 2)

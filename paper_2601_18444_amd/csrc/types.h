@@ -44,6 +44,8 @@ struct PolGeom {
     int n0, n_out;          // q rows, theta columns of the detector
     int cols, nh;
     int na, nrg;            // row blocks (of 32 rows) per wave, row groups
+    int mid;                // rows mid + b and mid - 1 - b of a block share offset b: 16; 8 in the block of a
+                            // detector of up to 16 rows
     double dq;
 };
 
