@@ -100,6 +100,7 @@ __global__ __launch_bounds__(pblk::kThreads, polar_per_cu(MT)) void direct_polar
     const int lane = threadIdx.x & 63, wave = cblk::wave_id();
     const int col = blockIdx.x * pblk::kWaves + wave, rg = blockIdx.y;
     if (col >= g.cols) return;  // no workgroup barriers below
+    g.mid = pblk::Tiles<MT>::kOffsets;  // (a constant)
     const int64_t jbeg = (int64_t)blockIdx.z * per;
     const int64_t jend = min(W, jbeg + per);
     double sth, cth;
@@ -155,6 +156,7 @@ __global__ __launch_bounds__(256) void polar_combine_kernel(const double *__rest
                                                             double *__restrict__ amp)
 {
     constexpr int V = FEW ? 2 : 4;
+    if (!FEW) g.mid = pblk::kRows / 2;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int lane = (int)(idx & 63);
     const int64_t block = idx >> 6;
@@ -302,7 +304,7 @@ static void launch_polar_tiles(const Loader &ld, int64_t W, const PolarPlan &p, 
     // at most 16 row blocks: 2 CH tiles
 #define NUMAG_LAUNCH_POLAR(MT)   \
     case MT:                     \
-        if constexpr (MT <= 2 * CH && (MT > 0 || CH <= 2 * pblk::few_tiles(MT))) \
+        if constexpr (MT <= 2 * CH && (MT > 0 || CH <= 2 * pblk::few_tiles(MT)) && (MT != -3 || CH > 2)) \
             hipLaunchKernelGGL((direct_polar_kernel<MT, CH, NW, Loader>), grid, block, 0, s, ld, W, p.per, p.g, store, out); \
         break
     switch (p.mt) {

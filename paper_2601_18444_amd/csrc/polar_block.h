@@ -197,7 +197,7 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
     constexpr bool kPairs = NW != CH;
     static_assert(NW == CH || NW == 2 * CH, "one weight per channel, or two of a pair");
     constexpr int N = Tiles<MT>::N, kOff = Tiles<MT>::kOffsets;
-    constexpr int kPoints = 64 / kOff;  // points of a matrix step
+    constexpr int kLog = kOff == 8 ? 3 : 2, kPoints = 1 << kLog;  // points of a matrix step
     const int pt = kOff == 8 ? kq + 4 * (r16 >> 3) : kq;
     // this lane's matrix row: slot 8 t + 4 (r16 / 8) + r16 % 4, part (r16 / 4) % 2 of 16 rows;
     // slot 2 t + r16 % 2, part (r16 / 2) % 2 of four
@@ -229,8 +229,8 @@ __device__ __forceinline__ void accumulate(const Loader &ld, int64_t jbeg, int64
         wave_fence();
         __builtin_amdgcn_s_setprio(0);
         raw = fetch(j0 + kChunk);
-        const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + kPoints - 1) / kPoints));
-        const double2 *op = &sm.off[pt][r16 % kOff], *cp = &sm.ctr[pt][0];
+        const int steps = __builtin_amdgcn_readfirstlane((int)((min((int64_t)kChunk, jend - j0) + kPoints - 1) >> kLog));
+        const double2 *op = &sm.off[pt][r16 & (kOff - 1)], *cp = &sm.ctr[pt][0];
         const double *wp = &sm.w[pt][0];
         auto step = [&](int s) {
             const double2 z = op[s * kPoints * (kOff + 1)];
