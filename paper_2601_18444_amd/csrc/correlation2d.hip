@@ -190,7 +190,7 @@ static numag_regular pixel_grid(const Detector &d)
 // 32 x 32 18 and 22, 100 x 100 to 30 x 30 22 and 45 to 53.  A thin pair of grids (10^5 x 10 to
 // 10 x 10^5) would need 320 GB where the direct sums' records take 128 MB, which bounds it,
 // and a launch takes 2^31 threads.
-static bool factored(const Detector &d, const Detector &rd)
+static bool factored_is_cheaper(const Detector &d, const Detector &rd)
 {
     const int64_t P = (int64_t)d.n0 * d.n1, R = (int64_t)rd.n0 * rd.n1;
     const double na = (rd.n0 + 1) / 2, nb = (rd.n1 + 1) / 2, ny = d.n0, nz = d.n1;
@@ -200,6 +200,24 @@ static bool factored(const Detector &d, const Detector &rd)
     const double flops = 16.0 * ny * nb * nz + 32.0 * na * nb * ny;
     const double f = 46000.0 + 113.0 * ny + 72.0 * nz + flops / 15000.0;
     return f <= 38000.0 + 0.1 * (double)P + cart_default_cost(rd, P, 4);
+}
+
+// The same for the thread's last sizes: a call asks several times (its workspace's size, its
+// layout, its launch), and the estimate of the direct sums compares 32 plans, 0.4 us (calls of 40
+// us are bound by the host).
+static bool factored(const Detector &d, const Detector &rd)
+{
+    struct Last {
+        int n[4];
+        bool factored;
+    };
+    static thread_local Last last{{-1, -1, -1, -1}, false};
+    const int n[4] = {d.n0, d.n1, rd.n0, rd.n1};
+    if (!std::equal(n, n + 4, last.n)) {
+        last.factored = factored_is_cheaper(d, rd);
+        std::copy(n, n + 4, last.n);
+    }
+    return last.factored;
 }
 
 static Route corr2d_route(const Detector &d, const Detector &rd)
